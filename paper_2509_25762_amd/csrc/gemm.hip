@@ -22,6 +22,8 @@
 // made beforehand for the pass's rows, and store 16 bytes at a time.
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "oppo_internal.h"
 
 namespace oppo {
@@ -95,6 +97,73 @@ __device__ __forceinline__ uint32_t gemm_pack_bf16(float a, float b) {
   return *(uint32_t*)&p;
 }
 
+// Which tile the workgroup with number `block` takes.  Workgroups are dealt round-robin to the
+// chip's 8 XCDs, each with a level-2 cache of its own.  The tiles are laid out as blocks of 8 row
+// tiles x 4 column tiles, one after the other (those at the edges are smaller); a round of 256
+// workgroups takes the next 256 of that list, each XCD 32 consecutive ones: they stream through
+// k together, so every slice of a block's row tiles and column tiles is fetched into that cache
+// once and serves 4 resp. 8 workgroups.  The list has no gaps, so a pass of up to 256 tiles is
+// one round whatever its number of row tiles, and the tiles of a last, smaller round are dealt
+// evenly to the XCDs (all on a few of them would share those caches' bandwidth: measured 15 %
+// slower at 96 tiles).
+struct TileOrder {
+  int m_tiles, n_tiles;
+  __device__ __forceinline__ TileOrder(const ProjParams& P, int bm, int bn)
+      : m_tiles((P.rows + bm - 1) / bm), n_tiles((P.n_out + bn - 1) / bn) {}
+  __device__ __forceinline__ bool at(int block, int* tile_m, int* tile_n) const {
+    const int first = block & ~255, left = m_tiles * n_tiles - first;
+    const int share = left >= 256 ? 32 : (left + 7) / 8;   // an XCD's tiles of this round
+    const int mine = (block / 8) % 32, in_round = (block % 8) * share + mine;
+    if (mine >= share || in_round >= left) return false;
+    const int pos = first + in_round;
+    const int strip = pos / (4 * m_tiles), in_strip = pos % (4 * m_tiles);    // strips of 4 column tiles
+    const int width = min(4, n_tiles - 4 * strip);
+    const int mg = in_strip / (8 * width), in_group = in_strip % (8 * width);
+    const int height = min(8, m_tiles - 8 * mg);
+    *tile_m = 8 * mg + in_group % height;
+    *tile_n = 4 * strip + in_group / height;
+    return true;
+  }
+};
+
+// Elements 8 g .. of the first half of a head's row (a0, a1) and their partners D / 2 further on
+// (b0, b1): rotated (query and key heads), rounded, and stored to q_out or to the row's cache slot.
+template <int D>
+__device__ __forceinline__ void store_piece(const ProjParams& P, int64_t row, int head, int g, f32x4 a0, f32x4 a1, f32x4 b0,
+                                            f32x4 b1) {
+  constexpr int HALF = D / 2;
+  const float av[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+  const float bv[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
+  uint16_t* dst;
+  u32x4 ra, rb;
+  if (head >= P.Hq + P.Hkv) {   // a value head: as it is
+    dst = P.cache_v + (P.dst[row] * P.Hkv + (head - P.Hq - P.Hkv)) * D;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      ra[w] = gemm_pack_bf16(av[2 * w], av[2 * w + 1]);
+      rb[w] = gemm_pack_bf16(bv[2 * w], bv[2 * w + 1]);
+    }
+  } else {
+    dst = head < P.Hq ? P.q_out + (row * P.Hq + head) * D : P.cache_k + (P.dst[row] * P.Hkv + (head - P.Hq)) * D;
+    const float2* cs = P.cs + row * HALF + g * 8;
+    float ca[8], sa[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float2 v = cs[e];
+      ca[e] = v.x;
+      sa[e] = v.y;
+    }
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+      const int e = 2 * w;
+      ra[w] = gemm_pack_bf16(av[e] * ca[e] - bv[e] * sa[e], av[e + 1] * ca[e + 1] - bv[e + 1] * sa[e + 1]);
+      rb[w] = gemm_pack_bf16(bv[e] * ca[e] + av[e] * sa[e], bv[e + 1] * ca[e + 1] + av[e + 1] * sa[e + 1]);
+    }
+  }
+  *(u32x4*)(dst + g * 8) = ra;
+  *(u32x4*)(dst + HALF + g * 8) = rb;
+}
+
 template <int D, int BM>
 __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   constexpr int BN = kGemmBN, BK = kGemmBK;
@@ -118,16 +187,9 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, hi = lane >> 5;
   const int wm = wave / WC, wn = wave % WC;    // the wave's (32 MI) x (32 NJ) part of the tile
-  // Workgroups are dealt round-robin to the chip's 8 XCDs, each with a level-2 cache of its own.
-  // The 32 workgroups an XCD runs at a time take one block of 8 x 4 tiles: they stream through k
-  // together, so every slice of the block's 8 row tiles and 4 column tiles is fetched into that
-  // cache once and serves 4 resp. 8 workgroups.
-  const int m_tiles = (P.rows + BM - 1) / BM, n_tiles = (P.n_out + BN - 1) / BN;
-  const int gm_count = (m_tiles + 7) / 8;
-  const int xcd = blockIdx.x % 8, slot = blockIdx.x / 8;
-  const int group = (slot / 32) * 8 + xcd, within = slot % 32;
-  const int tile_m = (group % gm_count) * 8 + within % 8, tile_n = (group / gm_count) * 4 + within / 8;
-  if (tile_m >= m_tiles || tile_n >= n_tiles) return;
+  const TileOrder order(P, BM, BN);
+  int tile_m, tile_n;
+  if (!order.at((int)blockIdx.x, &tile_m, &tile_n)) return;
   const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
 
   // ---- loads: a wave-wide copy moves 8 rows (8 x 128 B); wave w moves rows 8 (w + 8 i) .. of
@@ -275,38 +337,279 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
       const float* src = ct + m * BN + hl * D + g * 8;
       const f32x4 a0 = *(const f32x4*)(src), a1 = *(const f32x4*)(src + 4);
       const f32x4 b0 = *(const f32x4*)(src + HALF), b1 = *(const f32x4*)(src + HALF + 4);
-      const float av[8] = {a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
-      const float bv[8] = {b0[0], b0[1], b0[2], b0[3], b1[0], b1[1], b1[2], b1[3]};
-      uint16_t* dst;
+      store_piece<D>(P, row, head, g, a0, a1, b0, b1);
+    }
+    __syncthreads();
+  }
+}
+
+// The kernel for tiles of 256 rows: the same operand tiles, another k loop and another epilogue.
+// Bound by the matrix cores; what the loop above loses on this tile is the time in which both
+// waves of a SIMD read fragments or request copies (a wave that issues a copy issues no MFMA).
+// Here the two take turns: the waves form two groups, one wave of each SIMD in either, and run
+// the same sequence of phases one barrier apart, so that one group's MFMAs always run beside the
+// other group's memory instructions.  A wave computes 128 x 64, as four quadrants of 64 x 32 (two
+// halves of the x tile by two of the w tile), and a phase is
+//     read the fragments the quadrant still needs; request one half tile (two copies per wave);
+//     barrier; the quadrant's 8 MFMAs (32x32x16); barrier
+// with, for k tile t,   phase   reads              quadrant   requests
+//                         0     x0                 x0 w0      x1 of tile t + 1
+//                         1     w1                 x0 w1      w0 of tile t + 2
+//                         2     x1                 x1 w1      x0 of tile t + 2
+//                         3     w0 of tile t + 1   x1 w0      w1 of tile t + 2
+// (8, 4, 8 and 4 fragments: the LDS delivers one group's eight, 32 KiB, in about the time of the
+// other group's MFMAs.)  A half tile is read in one phase only and overwritten two phases later
+// at the earliest: the later group waits for its reads behind the barrier that follows them, and
+// the requesting group has passed the barrier after that.  A half tile has five phases to arrive:
+// a wave waits for its own copies in the phase before the one that reads them, with the five
+// requests made since still in flight, and the barrier that follows makes the half tile complete
+// for every wave of either group.
+// The product is computed transposed (w rows as the A operand), so a lane owns one row of y, and
+// the w rows are dealt to LDS rows such that it holds 16 consecutive columns of a head and, in
+// the accumulators of the other w half, their rotation partners D/2 further on: rotation and
+// stores (32 bytes per row and lane) need neither LDS nor barriers, and workgroups stay for
+// several tiles, requesting the next tile's first operands before they store the current one.
+template <int D>
+__global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P) {
+  constexpr int BM = 256, BN = kGemmBN, BK = kGemmBK;
+  constexpr int ROWB = BK * 2, NGR = ROWB / 16, RPL = 1024 / ROWB;
+  constexpr int HALF_TILE = 128 * ROWB;        // 16 KiB
+  constexpr int TILE = 2 * HALF_TILE;          // an x or w tile
+  constexpr int B_AREA = 2 * TILE;             // [x: 2 stages][w: 2 stages]: offsets within either area fit 16 bits
+  __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * TILE];
+
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int l32 = lane & 31, hi = lane >> 5;
+  const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
+  const int wm = (int)(wave_u >> 2), wn = (int)(wave_u & 3);   // wm is also the wave's group
+  const TileOrder order(P, BM, BN);
+  int tile_m, tile_n;
+  int block = (int)blockIdx.x;
+  if (!order.at(block, &tile_m, &tile_n)) return;
+
+  // copies: copies 2 h, 2 h + 1 of a wave belong to half h of the tile, 8 LDS rows each, swizzled
+  // as in qkv_proj_kernel.  LDS row 128 j + 32 wn + l of w holds the column that MFMA row l of
+  // wave column wn and half j stands for: MFMA row 8 a + 4 h + b is column 16 h + 4 a + b of its
+  // 32 (register i of lane half h is then column 16 h + i), the halves j are D/2 columns apart.
+  // (Lane-dependent values that only matter between tiles are recomputed there from a copy of the
+  // lane number that the optimiser cannot see through, instead of living in registers meanwhile.)
+  auto lane_now = [&]() __attribute__((always_inline)) -> int {
+    int x = lane;
+    asm volatile("" : "+v"(x));
+    return x;
+  };
+  uint32_t offa[4], offb[4];
+  const uint16_t *xa, *wb;
+  auto open_tile = [&]() __attribute__((always_inline)) {
+    const int ln = lane_now(), lrow = ln / NGR, pg = ln % NGR;
+    const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int r = RPL * ((int)wave_u + 8 * i) + lrow;
+      const int col = 16 * ((r >> 2) & 1) + 4 * ((r >> 3) & 3) + (r & 3), wc = (r >> 5) & 3, j = r >> 7;
+      const int n = D == 128 ? (wc >> 1) * 128 + j * 64 + (wc & 1) * 32 + col : wc * 64 + j * 32 + col;
+      // rows past the end of x / w repeat the last valid row (their products are never stored)
+      const int ra = min(r, P.rows - 1 - tile_m * BM), rb = min(n, P.n_out - 1 - tile_n * BN);
+      offa[i] = ((uint32_t)ra * (uint32_t)P.hidden + (uint32_t)((pg ^ ((r >> 1) % NGR)) * 8)) * 2u;
+      offb[i] = ((uint32_t)rb * (uint32_t)P.hidden + (uint32_t)((pg ^ ((r >> 1) % NGR)) * 8)) * 2u;
+    }
+    xa = P.x + m0 * P.hidden;
+    wb = P.w + n0 * P.hidden;
+  };
+  const uint32_t smem0 = (uint32_t)(uintptr_t)((const __attribute__((address_space(3))) unsigned char*)smem);
+  const uint32_t copy0 = smem0 + wave_u * 1024u;
+  auto issue_x = [&](int kt, int stage, int h) __attribute__((always_inline)) {
+    const uint32_t dst = copy0 + (uint32_t)(stage * TILE + h * HALF_TILE);
+    gemm_async_copy16(xa + (int64_t)kt * BK, offa[2 * h], dst);
+    gemm_async_copy16(xa + (int64_t)kt * BK, offa[2 * h + 1], dst + 8192u);
+  };
+  auto issue_w = [&](int kt, int stage, int h) __attribute__((always_inline)) {
+    const uint32_t dst = copy0 + (uint32_t)(B_AREA + stage * TILE + h * HALF_TILE);
+    gemm_async_copy16(wb + (int64_t)kt * BK, offb[2 * h], dst);
+    gemm_async_copy16(wb + (int64_t)kt * BK, offb[2 * h + 1], dst + 8192u);
+  };
+  const int KT = P.hidden / BK;
+  auto issue_first = [&]() __attribute__((always_inline)) {   // what the phases before a tile's first would have requested
+    issue_w(0, 0, 0);
+    issue_x(0, 0, 0);
+    issue_w(0, 0, 1);
+    issue_x(0, 0, 1);
+    if (KT > 1) {
+      issue_w(1, 1, 0);
+      issue_x(1, 1, 0);
+      issue_w(1, 1, 1);
+    }
+  };
+  // nothing moves across a barrier, MFMAs included
+  auto barrier = [&]() __attribute__((always_inline)) {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // This wave's copies have landed, except for the five half tiles (ten copies) requested last, if
+  // so many were requested since.  Not needed in a tile's first k step, whose halves and the next
+  // step's were waited for before it: there the previous tile's stores may still be on their way.
+  // (The second k step's first wait is for everything, so that the counted ones have nothing but
+  // copies to count.)
+  auto landed = [&](int t, bool five_behind) __attribute__((always_inline)) {
+    if (t == 0) return;
+    if (five_behind) __builtin_amdgcn_s_waitcnt(0x0F7A);   // vmcnt(10)
+    else __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+  };
+
+  // fragments: rows 32 * block + l32 of the wave's part of a half tile, elements 16 kk + 8 hi ..
+  typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
+  lds_cptr pa[4], pb[4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const uint32_t g = (((uint32_t)(kk * 2 + hi)) ^ (uint32_t)((l32 >> 1) % NGR)) * 16u;
+    uint32_t a = smem0 + (uint32_t)((wm * 64 + l32) * ROWB) + g;
+    uint32_t b = smem0 + (uint32_t)(B_AREA + (wn * 32 + l32) * ROWB) + g;
+    asm volatile("" : "+v"(a), "+v"(b));   // (one register each: stage, half and block are immediate offsets)
+    pa[kk] = (lds_cptr)(uintptr_t)a;
+    pb[kk] = (lds_cptr)(uintptr_t)b;
+  }
+  // x fragments [block][kk] of the half at hand; w fragments [set][kk]: tile t has its w0 in set t & 1, its w1 in the other
+  bf16x8 a[2][4], b[2][4];
+  auto read_x = [&](int stage, int h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        a[i][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pa[kk] + stage * TILE + h * HALF_TILE + i * 32 * ROWB);
+  };
+  auto read_w = [&](int set, int stage, int h) __attribute__((always_inline)) {
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+      b[set][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pb[kk] + stage * TILE + h * HALF_TILE);
+  };
+  auto reads_done = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
+  f32x16 acc[2][2][2];   // [x half][block][w half]
+  auto quadrant = [&](int h, int j, int set) __attribute__((always_inline)) {
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+        acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][kk], a[i][kk], acc[h][i][j], 0, 0, 0);
+    __builtin_amdgcn_s_setprio(0);
+  };
+  auto k_tile = [&](int t, auto ST) __attribute__((always_inline)) {
+    constexpr int st = decltype(ST)::value;   // t & 1
+    const bool one = t + 1 < KT, two = t + 2 < KT;
+    read_x(st, 0);
+    if (one) issue_x(t + 1, st ^ 1, 1);
+    landed(t, one && t > 1);   // w1 of tile t
+    barrier();
+    quadrant(0, 0, st);
+    barrier();
+    read_w(st ^ 1, st, 1);
+    if (two) issue_w(t + 2, st, 0);
+    landed(t, two);   // x1 of tile t
+    barrier();
+    quadrant(0, 1, st ^ 1);
+    barrier();
+    read_x(st, 1);
+    if (two) issue_x(t + 2, st, 0);
+    landed(t, two);   // w0 of tile t + 1
+    barrier();
+    quadrant(1, 1, st ^ 1);
+    barrier();
+    if (one) read_w(st ^ 1, st ^ 1, 0);
+    if (two) issue_w(t + 2, st, 1);
+    landed(t, two);   // x0 of tile t + 1
+    barrier();
+    reads_done();     // (the quadrant does not use them)
+    quadrant(1, 0, st);
+    barrier();
+  };
+
+  constexpr int HALF = D / 2;
+  const int heads = P.Hq + 2 * P.Hkv;
+  open_tile();
+  issue_first();
+  __builtin_amdgcn_s_waitcnt(0x0F70);
+  for (;;) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[h][i][j][r] = 0.f;
+    barrier();
+    read_w(0, 0, 0);
+    reads_done();
+    if (wm == 1) barrier();   // the second group runs one barrier behind the first ...
+    for (int t = 0; t < KT; t += 2) {
+      k_tile(t, std::integral_constant<int, 0>{});
+      if (t + 1 < KT) k_tile(t + 1, std::integral_constant<int, 1>{});
+    }
+    if (wm == 0) barrier();   // ... and both have passed the same number of them here
+    // (every fragment read has fed an MFMA in front of a barrier: the LDS is free)
+
+    // ---- the next tile's operands, and this tile's rows: cache slots and rotation angles
+    const int ln = lane_now();
+    const int row_first = tile_m * BM + wm * 64 + (ln & 31);
+    const int head = tile_n * (BN / D) + (D == 128 ? wn >> 1 : wn);      // one head per wave
+    const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 16 * (ln >> 5);      // the lane's first column of the head
+    block += (int)gridDim.x;
+    const bool more = order.at(block, &tile_m, &tile_n);
+    if (more) {
+      open_tile();
+      issue_first();
+    }
+    const bool turned = head < P.Hq + P.Hkv;   // queries and keys
+    auto row_of = [&](int q) __attribute__((always_inline)) -> int { return row_first + (q >> 1) * 128 + (q & 1) * 32; };
+    uint16_t* out[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int64_t row = min(row_of(q), P.rows - 1);
+      if (head < P.Hq) out[q] = P.q_out + (row * P.Hq + head) * D + e0;
+      else if (turned) out[q] = P.cache_k + (P.dst[row] * P.Hkv + (head - P.Hq)) * D + e0;
+      else out[q] = P.cache_v + (P.dst[row] * P.Hkv + (head - P.Hq - P.Hkv)) * D + e0;
+    }
+    // step s: 8 of the 16 columns (and their partners) of row block s / 2; the angles one step ahead
+    float2 cs[2][8];
+    auto load_cs = [&](int st, float2* c) __attribute__((always_inline)) {
+      const float2* src = P.cs + (int64_t)min(row_of(st >> 1), P.rows - 1) * HALF + e0 + (st & 1) * 8;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) c[e] = src[e];
+    };
+    if (turned) load_cs(0, cs[0]);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), before the first store: see `landed`
+#pragma unroll
+    for (int st = 0; st < 8; ++st) {
+      const f32x16& u = acc[st >> 2][(st >> 1) & 1][0];
+      const f32x16& v = acc[st >> 2][(st >> 1) & 1][1];
+      const int f = (st & 1) * 8;
       u32x4 ra, rb;
-      if (head >= P.Hq + P.Hkv) {   // a value head: as it is
-        dst = P.cache_v + (P.dst[row] * P.Hkv + (head - P.Hq - P.Hkv)) * D;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-          ra[w] = gemm_pack_bf16(av[2 * w], av[2 * w + 1]);
-          rb[w] = gemm_pack_bf16(bv[2 * w], bv[2 * w + 1]);
-        }
-      } else {
-        dst = head < P.Hq ? P.q_out + (row * P.Hq + head) * D : P.cache_k + (P.dst[row] * P.Hkv + (head - P.Hq)) * D;
-        const float2* cs = P.cs + row * HALF + g * 8;
-        float ca[8], sa[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          const float2 v = cs[e];
-          ca[e] = v.x;
-          sa[e] = v.y;
-        }
+      if (turned) {
+        if (st < 7) load_cs(st + 1, cs[(st + 1) & 1]);
+        const float2* c = cs[st & 1];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
           const int e = 2 * w;
-          ra[w] = gemm_pack_bf16(av[e] * ca[e] - bv[e] * sa[e], av[e + 1] * ca[e + 1] - bv[e + 1] * sa[e + 1]);
-          rb[w] = gemm_pack_bf16(bv[e] * ca[e] + av[e] * sa[e], bv[e + 1] * ca[e + 1] + av[e + 1] * sa[e + 1]);
+          ra[w] = gemm_pack_bf16(u[f + e] * c[e].x - v[f + e] * c[e].y, u[f + e + 1] * c[e + 1].x - v[f + e + 1] * c[e + 1].y);
+          rb[w] = gemm_pack_bf16(v[f + e] * c[e].x + u[f + e] * c[e].y, v[f + e + 1] * c[e + 1].x + u[f + e + 1] * c[e + 1].y);
+        }
+      } else {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          ra[w] = gemm_pack_bf16(u[f + 2 * w], u[f + 2 * w + 1]);
+          rb[w] = gemm_pack_bf16(v[f + 2 * w], v[f + 2 * w + 1]);
         }
       }
-      *(u32x4*)(dst + g * 8) = ra;
-      *(u32x4*)(dst + HALF + g * 8) = rb;
+      if (row_of(st >> 1) < P.rows && head < heads) {
+        *(u32x4*)(out[st >> 1] + f) = ra;
+        *(u32x4*)(out[st >> 1] + f + HALF) = rb;
+      }
+      __builtin_amdgcn_sched_barrier(0);   // (one step's values at a time in the registers)
     }
-    __syncthreads();
+    if (!more) break;
   }
 }
 
@@ -358,16 +661,15 @@ int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t 
   auto rounds_at = [&](int bm) { return (((int64_t)(rows + bm - 1) / bm) * n_tiles + kProjCUs - 1) / kProjCUs; };
   const double cost256 = 1.8 * (double)rounds_at(256), cost128 = 1.0 * (double)rounds_at(128), cost64 = 0.67 * (double)rounds_at(64);
   const int bm = (cost256 <= cost128 && cost256 <= cost64) ? 256 : cost128 <= cost64 ? 128 : 64;
-  // blocks of 8 x 4 tiles, one block per XCD at a time (see the kernel); a launch has whole rounds of 8 blocks
-  const int m_tiles = (rows + bm - 1) / bm;
-  const int groups = ((m_tiles + 7) / 8) * ((n_tiles + 3) / 4);
-  dim3 grid((unsigned)(((groups + 7) / 8) * 8 * 32));
+  // (the 256-row kernel's workgroups stay for as many tiles as there are rounds)
+  const int64_t rounds = rounds_at(bm);
+  dim3 grid((unsigned)(bm == 256 ? kProjCUs : rounds * kProjCUs));
   if (ls.D == 128) {
-    if (bm == 256) hipLaunchKernelGGL((qkv_proj_kernel<128, 256>), grid, dim3(512), 0, st, P);
+    if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<128>), grid, dim3(512), 0, st, P);
     else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<128, 128>), grid, dim3(512), 0, st, P);
     else hipLaunchKernelGGL((qkv_proj_kernel<128, 64>), grid, dim3(512), 0, st, P);
   } else {
-    if (bm == 256) hipLaunchKernelGGL((qkv_proj_kernel<64, 256>), grid, dim3(512), 0, st, P);
+    if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<64>), grid, dim3(512), 0, st, P);
     else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<64, 128>), grid, dim3(512), 0, st, P);
     else hipLaunchKernelGGL((qkv_proj_kernel<64, 64>), grid, dim3(512), 0, st, P);
   }
