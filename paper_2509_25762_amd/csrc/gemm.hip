@@ -9,12 +9,11 @@
 // rounded once to bf16 and written to q_out / to the sequence's cache slab; value heads go
 // to the cache as they are.  The projection's output never exists in memory.
 //
-// Workgroup = 256 x 256 tile of y, 8 waves in a 4 x 2 arrangement of 64 x 128 (2 x 4 blocks of
-// v_mfma_f32_32x32x16_bf16: six fragment reads feed eight MFMAs).  Passes too thin to give every
-// compute unit such a tile take tiles of 128 or 64 rows instead (2 x 4 waves of 64 x 64 or 32 x 64).
-// k advances in tiles of 64
-// through two LDS stages per operand (128 KiB in all, one workgroup per compute unit, two
-// waves per SIMD); tiles travel global -> LDS directly, the
+// Workgroup = 256 columns of y by 256, 192, 128 or 64 rows, 8 waves (two per SIMD), blocks of
+// v_mfma_f32_32x32x16_bf16.  Tall tiles have a kernel of their own (qkv_proj_phased_kernel, below);
+// passes too thin to give every compute unit such a tile take qkv_proj_kernel with 128 or 64 rows:
+// k advances in tiles of 64 through a ring of LDS stages, one workgroup per compute unit; tiles
+// travel global -> LDS directly, the
 // XOR swizzle of the LDS rows applied by choosing which 16-byte granule each lane fetches, so
 // the fragment reads (ds_read_b128, one row per lane) spread over the banks.  The epilogue
 // parks the fp32 tile in the same LDS, 64 rows at a time, from where threads take 8-column pieces of a row and
@@ -173,13 +172,13 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   constexpr int TILE_A = BM * ROWB;       // bytes of an x tile (32, 16 or 8 KiB)
   constexpr int TILE_B = BN * ROWB;       // bytes of a w tile (32 KiB)
   constexpr int STAGE = TILE_A + TILE_B;
-  constexpr int WR = BM == 256 ? 4 : 2, WC = 8 / WR;   // waves down and across the tile
-  constexpr int MI = BM / WR / 32, NJ = BN / WC / 32;  // 32 x 32 blocks of a wave: 2 x 4, 2 x 2 or 1 x 2
-  constexpr int CA = BM / RPL / 8, CB = BN / RPL / 8;  // copies per wave and tile: x (4, 2 or 1), w (4)
-  static_assert(BN == 256 && BK == 64 && (BM == 256 || BM == 128 || BM == 64), "8 waves, k tiles of 64");
-  // stages of the tile ring: two tiles of 256 rows fill the LDS; the smaller tiles run on passes
-  // whose k loop is bound by the tiles' latency, and keep two tiles in flight instead of one
-  constexpr int NST = BM == 256 ? 2 : 3;   // (four stages of the 64-row tile: measured, no faster)
+  constexpr int WR = 2, WC = 4;                        // waves down and across the tile
+  constexpr int MI = BM / WR / 32, NJ = BN / WC / 32;  // 32 x 32 blocks of a wave: 2 x 2 or 1 x 2
+  constexpr int CA = BM / RPL / 8, CB = BN / RPL / 8;  // copies per wave and tile: x (2 or 1), w (4)
+  static_assert(BN == 256 && BK == 64 && (BM == 128 || BM == 64), "8 waves, k tiles of 64");
+  // stages of the tile ring: these tiles run on passes whose k loop is bound by the tiles' latency,
+  // and keep two tiles in flight
+  constexpr int NST = 3;   // (four stages of the 64-row tile: measured, no faster)
   static_assert(NST * STAGE >= 64 * BN * 4 && NST * STAGE <= 160 * 1024, "ring and the epilogue's 64 x 256 fp32 strip fit the LDS");
   // [stage][x tile | w tile]; the epilogue reuses it as a 64 x 256 fp32 strip at a time
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
@@ -269,22 +268,10 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][i], b[c][j], acc[i][j], 0, 0, 0);
     }
   };
-  if constexpr (NST == 2) {
-    issue(0, 0);
-    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
-    barrier();
-    for (int kt = 0; kt < KT; ++kt) {
-      const int st = kt & 1;
-      if (kt + 1 < KT) issue(kt + 1, st ^ 1);
-      compute(st);
-      __builtin_amdgcn_s_waitcnt(0x0F70);   // this wave's share of the next tile is in LDS
-      barrier();
-    }
-  } else {
-    // tile t lives in stage t % NST; tiles kt + 1 .. kt + NST - 2 stay in flight while tile kt is
-    // waited for, and tile kt + NST - 1 is requested into the stage of tile kt - 1 once every wave
+  {
+    // tile t lives in stage t % NST; tile kt + 1 stays in flight while tile kt is
+    // waited for, and tile kt + 2 is requested into the stage of tile kt - 1 once every wave
     // has passed the barrier behind that tile's MFMAs
-    static_assert(NST == 3 || NST == 4, "the waits below are written for one or two later tiles in flight");
     constexpr int CPT = CA + CB;   // copies per wave and tile
 #pragma unroll
     for (int t = 0; t < NST - 1; ++t)
@@ -292,9 +279,7 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
     int st = 0, st_in = NST - 1;
     for (int kt = 0; kt < KT; ++kt) {
       // this wave's copies of tile kt have landed: only those of the later tiles may be outstanding
-      if (NST == 4 && kt + 2 < KT)
-        __builtin_amdgcn_s_waitcnt(0x0F70 | (2 * CPT));   // vmcnt(2 CPT)
-      else if (kt + 1 < KT)
+      if (kt + 1 < KT)
         __builtin_amdgcn_s_waitcnt(0x0F70 | CPT);         // vmcnt(CPT)
       else
         __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
@@ -343,7 +328,7 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   }
 }
 
-// The kernel for tiles of 256 rows: the same operand tiles, another k loop and another epilogue.
+// The kernel for tiles of 256 and 192 rows: the same operand tiles, another k loop and another epilogue.
 // Bound by the matrix cores; what the loop above loses on this tile is the time in which both
 // waves of a SIMD read fragments or request copies (a wave that issues a copy issues no MFMA).
 // Here the two take turns: the waves form two groups, one wave of each SIMD in either, and run
@@ -369,9 +354,12 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
 // the accumulators of the other w half, their rotation partners D/2 further on: rotation and
 // stores (32 bytes per row and lane) need neither LDS nor barriers, and workgroups stay for
 // several tiles, requesting the next tile's first operands before they store the current one.
-template <int D>
+// Tiles of 192 rows are the same with a second x half of 64 rows (M1 = 1 block of 32 rows per wave
+// instead of 2); its LDS rows stay where the 128-row half has each wave row's first block.
+template <int D, int BM>
 __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P) {
-  constexpr int BM = 256, BN = kGemmBN, BK = kGemmBK;
+  static_assert(BM == 256 || BM == 192, "x halves of 128 and 128 or 64 rows");
+  constexpr int M1 = (BM - 128) / 64, BN = kGemmBN, BK = kGemmBK;
   constexpr int ROWB = BK * 2, NGR = ROWB / 16, RPL = 1024 / ROWB;
   constexpr int HALF_TILE = 128 * ROWB;        // 16 KiB
   constexpr int TILE = 2 * HALF_TILE;          // an x or w tile
@@ -388,7 +376,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
   if (!order.at(block, &tile_m, &tile_n)) return;
 
   // copies: copies 2 h, 2 h + 1 of a wave belong to half h of the tile, 8 LDS rows each, swizzled
-  // as in qkv_proj_kernel.  LDS row 128 j + 32 wn + l of w holds the column that MFMA row l of
+  // as in qkv_proj_kernel (a second x half of 64 rows takes one copy per wave).  LDS row 128 j + 32 wn + l of w holds the column that MFMA row l of
   // wave column wn and half j stands for: MFMA row 8 a + 4 h + b is column 16 h + 4 a + b of its
   // 32 (register i of lane half h is then column 16 h + i), the halves j are D/2 columns apart.
   // (Lane-dependent values that only matter between tiles are recomputed there from a copy of the
@@ -409,7 +397,8 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
       const int col = 16 * ((r >> 2) & 1) + 4 * ((r >> 3) & 3) + (r & 3), wc = (r >> 5) & 3, j = r >> 7;
       const int n = D == 128 ? (wc >> 1) * 128 + j * 64 + (wc & 1) * 32 + col : wc * 64 + j * 32 + col;
       // rows past the end of x / w repeat the last valid row (their products are never stored)
-      const int ra = min(r, P.rows - 1 - tile_m * BM), rb = min(n, P.n_out - 1 - tile_n * BN);
+      const int rx = i < 2 || M1 == 2 ? r : 128 + RPL * (int)wave_u + lrow;   // (32 rows per wave row: 128 + 32 wm + ..)
+      const int ra = min(rx, P.rows - 1 - tile_m * BM), rb = min(n, P.n_out - 1 - tile_n * BN);
       offa[i] = ((uint32_t)ra * (uint32_t)P.hidden + (uint32_t)((pg ^ ((r >> 1) % NGR)) * 8)) * 2u;
       offb[i] = ((uint32_t)rb * (uint32_t)P.hidden + (uint32_t)((pg ^ ((r >> 1) % NGR)) * 8)) * 2u;
     }
@@ -420,6 +409,10 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
   const uint32_t copy0 = smem0 + wave_u * 1024u;
   auto issue_x = [&](int kt, int stage, int h) __attribute__((always_inline)) {
     const uint32_t dst = copy0 + (uint32_t)(stage * TILE + h * HALF_TILE);
+    if (h == 1 && M1 == 1) {
+      gemm_async_copy16(xa + (int64_t)kt * BK, offa[2], dst + (wave_u >= 4 ? 4096u : 0u));   // LDS rows 0 .. 31 and 64 .. 95
+      return;
+    }
     gemm_async_copy16(xa + (int64_t)kt * BK, offa[2 * h], dst);
     gemm_async_copy16(xa + (int64_t)kt * BK, offa[2 * h + 1], dst + 8192u);
   };
@@ -448,14 +441,16 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  // This wave's copies have landed, except for the five half tiles (ten copies) requested last, if
+  // This wave's copies have landed, except for the five half tiles requested last (N copies), if
   // so many were requested since.  Not needed in a tile's first k step, whose halves and the next
   // step's were waited for before it: there the previous tile's stores may still be on their way.
   // (The second k step's first wait is for everything, so that the counted ones have nothing but
   // copies to count.)
-  auto landed = [&](int t, bool five_behind) __attribute__((always_inline)) {
+  constexpr std::integral_constant<int, 10 - (2 - M1)> kOneX1{};       // one second x half among the five
+  constexpr std::integral_constant<int, 10 - 2 * (2 - M1)> kTwoX1{};   // two
+  auto landed = [&](int t, bool five_behind, auto N) __attribute__((always_inline)) {
     if (t == 0) return;
-    if (five_behind) __builtin_amdgcn_s_waitcnt(0x0F7A);   // vmcnt(10)
+    if (five_behind) __builtin_amdgcn_s_waitcnt(0x0F70 | decltype(N)::value);   // vmcnt(N)
     else __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
   };
 
@@ -477,7 +472,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < (h == 0 ? 2 : M1); ++i)
         a[i][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pa[kk] + stage * TILE + h * HALF_TILE + i * 32 * ROWB);
   };
   auto read_w = [&](int set, int stage, int h) __attribute__((always_inline)) {
@@ -492,7 +487,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < (h == 0 ? 2 : M1); ++i)
         acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][kk], a[i][kk], acc[h][i][j], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
   };
@@ -501,25 +496,25 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     const bool one = t + 1 < KT, two = t + 2 < KT;
     read_x(st, 0);
     if (one) issue_x(t + 1, st ^ 1, 1);
-    landed(t, one && t > 1);   // w1 of tile t
+    landed(t, one && t > 1, kTwoX1);   // w1 of tile t
     barrier();
     quadrant(0, 0, st);
     barrier();
     read_w(st ^ 1, st, 1);
     if (two) issue_w(t + 2, st, 0);
-    landed(t, two);   // x1 of tile t
+    landed(t, two, kOneX1);   // x1 of tile t
     barrier();
     quadrant(0, 1, st ^ 1);
     barrier();
     read_x(st, 1);
     if (two) issue_x(t + 2, st, 0);
-    landed(t, two);   // w0 of tile t + 1
+    landed(t, two, kOneX1);   // w0 of tile t + 1
     barrier();
     quadrant(1, 1, st ^ 1);
     barrier();
     if (one) read_w(st ^ 1, st ^ 1, 0);
     if (two) issue_w(t + 2, st, 1);
-    landed(t, two);   // x0 of tile t + 1
+    landed(t, two, kOneX1);   // x0 of tile t + 1
     barrier();
     reads_done();     // (the quadrant does not use them)
     quadrant(1, 0, st);
@@ -553,7 +548,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 
     // ---- the next tile's operands, and this tile's rows: cache slots and rotation angles
     const int ln = lane_now();
-    const int row_first = tile_m * BM + wm * 64 + (ln & 31);
+    const int row_first = tile_m * BM + (ln & 31);
     const int head = tile_n * (BN / D) + (D == 128 ? wn >> 1 : wn);      // one head per wave
     const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 16 * (ln >> 5);      // the lane's first column of the head
     block += (int)gridDim.x;
@@ -563,10 +558,12 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
       issue_first();
     }
     const bool turned = head < P.Hq + P.Hkv;   // queries and keys
-    auto row_of = [&](int q) __attribute__((always_inline)) -> int { return row_first + (q >> 1) * 128 + (q & 1) * 32; };
-    uint16_t* out[4];
+    auto row_of = [&](int q) __attribute__((always_inline)) -> int {   // row of row block q of the wave
+      return row_first + (q < 2 ? wm * 64 + q * 32 : 128 + wm * 32 * M1 + (q - 2) * 32);
+    };
+    uint16_t* out[2 + M1];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 2 + M1; ++q) {
       const int64_t row = min(row_of(q), P.rows - 1);
       if (head < P.Hq) out[q] = P.q_out + (row * P.Hq + head) * D + e0;
       else if (turned) out[q] = P.cache_k + (P.dst[row] * P.Hkv + (head - P.Hq)) * D + e0;
@@ -582,13 +579,13 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     if (turned) load_cs(0, cs[0]);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), before the first store: see `landed`
 #pragma unroll
-    for (int st = 0; st < 8; ++st) {
+    for (int st = 0; st < 2 * (2 + M1); ++st) {
       const f32x16& u = acc[st >> 2][(st >> 1) & 1][0];
       const f32x16& v = acc[st >> 2][(st >> 1) & 1][1];
       const int f = (st & 1) * 8;
       u32x4 ra, rb;
       if (turned) {
-        if (st < 7) load_cs(st + 1, cs[(st + 1) & 1]);
+        if (st + 1 < 2 * (2 + M1)) load_cs(st + 1, cs[(st + 1) & 1]);
         const float2* c = cs[st & 1];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
@@ -617,6 +614,19 @@ size_t proj_workspace_bytes(int D, int64_t rows) {
   return (size_t)rows * (sizeof(int64_t) + (size_t)(D / 2) * sizeof(float2));
 }
 
+// The projection of P.rows rows with tiles of bm rows.  (The kernel of the tall tiles: workgroups stay for
+// as many tiles as there are rounds.)
+template <int D>
+static int launch_tiles(const ProjParams& P, int bm, int n_tiles, hipStream_t st) {
+  const int64_t tiles = (int64_t)((P.rows + bm - 1) / bm) * n_tiles;
+  const dim3 once((unsigned)kProjCUs), all((unsigned)((tiles + kProjCUs - 1) / kProjCUs * kProjCUs)), block(512);
+  if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 256>), once, block, 0, st, P);
+  else if (bm == 192) hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 192>), once, block, 0, st, P);
+  else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<D, 128>), all, block, 0, st, P);
+  else hipLaunchKernelGGL((qkv_proj_kernel<D, 64>), all, block, 0, st, P);
+  return (int)hipGetLastError();
+}
+
 int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t hidden, int32_t rows, void* q_out,
                     void* cache_k, void* cache_v, const QkvItem* items, int n_items, double theta_base, void* workspace,
                     void* stream) {
@@ -640,40 +650,52 @@ int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t 
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return (int)e;
   }
-  ProjParams P;
-  P.x = (const uint16_t*)x;
-  P.w = (const uint16_t*)w;
-  P.q_out = (uint16_t*)q_out;
-  P.cache_k = (uint16_t*)cache_k;
-  P.cache_v = (uint16_t*)cache_v;
-  P.dst = dst;
-  P.cs = cs;
-  P.rows = rows;
-  P.hidden = hidden;
-  P.n_out = (ls.Hq + 2 * ls.Hkv) * ls.D;
-  P.Hq = ls.Hq;
-  P.Hkv = ls.Hkv;
-  // Tile rows: one workgroup per compute unit at a time, so a launch takes ceil(tiles / 256) rounds of one
-  // tile's duration; per k tile that duration was measured as 1.8 / 1.0 / 0.67 us for tiles of 256 / 128 /
-  // 64 rows.  The cheapest estimate wins, the larger tile on a tie: thin passes spread over more compute
-  // units, mid-sized ones avoid a mostly empty last round.
-  const int n_tiles = (P.n_out + kGemmBN - 1) / kGemmBN;
-  auto rounds_at = [&](int bm) { return (((int64_t)(rows + bm - 1) / bm) * n_tiles + kProjCUs - 1) / kProjCUs; };
-  const double cost256 = 1.8 * (double)rounds_at(256), cost128 = 1.0 * (double)rounds_at(128), cost64 = 0.67 * (double)rounds_at(64);
-  const int bm = (cost256 <= cost128 && cost256 <= cost64) ? 256 : cost128 <= cost64 ? 128 : 64;
-  // (the 256-row kernel's workgroups stay for as many tiles as there are rounds)
-  const int64_t rounds = rounds_at(bm);
-  dim3 grid((unsigned)(bm == 256 ? kProjCUs : rounds * kProjCUs));
-  if (ls.D == 128) {
-    if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<128>), grid, dim3(512), 0, st, P);
-    else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<128, 128>), grid, dim3(512), 0, st, P);
-    else hipLaunchKernelGGL((qkv_proj_kernel<128, 64>), grid, dim3(512), 0, st, P);
-  } else {
-    if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<64>), grid, dim3(512), 0, st, P);
-    else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<64, 128>), grid, dim3(512), 0, st, P);
-    else hipLaunchKernelGGL((qkv_proj_kernel<64, 64>), grid, dim3(512), 0, st, P);
+  // Tile heights: one workgroup per compute unit at a time, so a launch takes ceil(tiles / 256) rounds of one
+  // tile's duration; per k tile that was measured as 1.6 / 1.3 / 1.0 / 0.67 us for tiles of 256 / 192 / 128 / 64
+  // rows, and a launch costs a few us besides.  The cheapest estimate wins: thin passes spread over more compute
+  // units, mid-sized ones avoid a mostly empty last round, and a pass whose last round of 256-row tiles would be
+  // mostly empty takes those rows that fill its rounds with them and the rest with the best height for the rest.
+  constexpr int kHeights[4] = {256, 192, 128, 64};
+  constexpr double kTileUs[4] = {1.6, 1.3, 1.0, 0.67};
+  constexpr double kLaunchUs = 4.0;
+  const int n_out = (ls.Hq + 2 * ls.Hkv) * ls.D;
+  const int n_tiles = (n_out + kGemmBN - 1) / kGemmBN;
+  auto rounds_of = [&](int bm, int n) { return ((int64_t)((n + bm - 1) / bm) * n_tiles + kProjCUs - 1) / kProjCUs; };
+  auto best_height = [&](int n, double* us) {
+    int best = 0;
+    for (int h = 0; h < 4; ++h) {
+      const double t = kLaunchUs + (double)rounds_of(kHeights[h], n) * kTileUs[h] * (hidden / kGemmBK);
+      if (h == 0 || t < *us) best = h, *us = t;
+    }
+    return kHeights[best];
+  };
+  double us = 0.0, us_rest = 0.0;
+  int bm = best_height(rows, &us), rows_first = rows, bm_rest = 0;
+  const int64_t full = (int64_t)((rows + 255) / 256) * n_tiles / kProjCUs;   // full rounds of 256-row tiles
+  const int64_t fit = full * kProjCUs / n_tiles * 256;                       // rows that fit into them
+  if (fit > 0 && fit < rows) {
+    const int rest = best_height(rows - (int)fit, &us_rest);
+    if (kLaunchUs + (double)full * kTileUs[0] * (hidden / kGemmBK) + us_rest < us) bm = 256, rows_first = (int)fit, bm_rest = rest;
   }
-  return (int)hipGetLastError();
+  for (int first = 0; first < rows; first = rows_first) {
+    ProjParams P;
+    P.rows = first == 0 ? rows_first : rows - rows_first;
+    P.x = (const uint16_t*)x + (int64_t)first * hidden;
+    P.w = (const uint16_t*)w;
+    P.q_out = (uint16_t*)q_out + (int64_t)first * ls.Hq * ls.D;
+    P.cache_k = (uint16_t*)cache_k;
+    P.cache_v = (uint16_t*)cache_v;
+    P.dst = dst + first;
+    P.cs = cs + (int64_t)first * (ls.D / 2);
+    P.hidden = hidden;
+    P.n_out = n_out;
+    P.Hq = ls.Hq;
+    P.Hkv = ls.Hkv;
+    const int e = ls.D == 128 ? launch_tiles<128>(P, first == 0 ? bm : bm_rest, n_tiles, st)
+                              : launch_tiles<64>(P, first == 0 ? bm : bm_rest, n_tiles, st);
+    if (e || first != 0) return e;
+  }
+  return 0;
 }
 
 }  // namespace oppo

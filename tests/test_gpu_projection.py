@@ -128,6 +128,33 @@ def test_larger_passes_take_the_larger_tiles(gpu, rows):
         assert (gv[b:b + n0] == 0xFFFF).all() and (gv[b + n1:int(slot_begin[i + 1])] == 0xFFFF).all()
 
 
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [
+    (6001, 8, 2, 128, 64),      # tiles of 192 rows, one k tile, a ragged last row tile
+    (6145, 16, 4, 64, 192),     # the same at head size 64, three k tiles, one row in the last row tile
+    (8155, 16, 4, 64, 128),     # tiles of 256 rows, two k tiles
+    (8064, 5, 1, 128, 192),     # a last column tile that is half empty, row tiles without a remainder
+    (10789, 8, 2, 128, 128),    # 258 tiles of 256 rows: two workgroups take a second one
+    (10789, 8, 2, 128, 1024),   # full rounds of 256-row tiles, the last 37 rows in a launch of their own
+])
+def test_tall_tiles_few_k_tiles_and_split_launches(gpu, rows, Hq, Hkv, D, hidden):
+    """Edges of the tall-tile kernel: k loops shorter than its request distance, both tile heights, several tiles
+    per workgroup, and passes cut into two launches; bounds as above."""
+    rng = np.random.default_rng(rows + hidden)
+    q_len = np.array([rows - 1000, 1, 0, 999], dtype=np.int32)
+    kv_before = np.array([3, 70000, 0, 9], dtype=np.int32)
+    xb, wb, cu, slot_begin, cache, gq, gk, gv = run_projection(gpu, rng, Hq, Hkv, D, hidden, kv_before, q_len, 10000.0)
+    q_ref, k_ref, v_ref = qkv_projection_rope(xb, wb, pass_positions(kv_before, q_len), Hq, Hkv, D, 10000.0)
+    mag = (np.abs(bf16_bits_to_f64(xb)) @ np.abs(bf16_bits_to_f64(wb)).T).reshape(rows, Hq + 2 * Hkv, D)
+    pair = np.tile(mag[..., :D // 2] + mag[..., D // 2:], 2)
+    assert (gq[0] == 0x7FC0).all() and (gq[-1] == 0x7FC0).all(), "rows outside the pass were written"
+    assert (np.abs(bf16_bits_to_f64(gq[1:-1]) - q_ref) <= bound_of(q_ref, pair[:, :Hq])).all(), "queries"
+    slots = np.concatenate([int(slot_begin[i]) + int(kv_before[i]) + np.arange(q_len[i]) for i in range(len(q_len))])
+    assert (np.abs(bf16_bits_to_f64(gk[slots]) - k_ref) <= bound_of(k_ref, pair[:, Hq:Hq + Hkv])).all(), "keys"
+    assert (np.abs(bf16_bits_to_f64(gv[slots]) - v_ref) <= bound_of(v_ref, mag[:, Hq + Hkv:])).all(), "values"
+    others = np.setdiff1d(np.arange(gk.shape[0]), slots)
+    assert (gk[others] == 0xFFFF).all() and (gv[others] == 0xFFFF).all(), "other cache slots were written"
+
+
 def test_values_are_the_rounded_fp32_sums_when_products_are_exact(gpu):
     """Small integers: every product and partial sum is exact in fp32, so value heads (no rotation) and
     the rows at position 0 (rotation by 0) must be bit-exact, whatever the order of accumulation."""
