@@ -46,8 +46,8 @@
 // The values' scale is folded into the final normalisation.
 // Head size 64: the contraction of S^T is one MFMA deep, O^T has two 32-row blocks; a tile of
 // either array is 4 KiB, so waves 0-3 move the keys and waves 4-7 the values.
-template <int D>
-__global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams P) {
+template <int D, int NI>
+__global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> P) {
   static_assert(D == 128 || D == 64, "head sizes 64 and 128");
   constexpr int NT = 512;
   constexpr int BN = kKeyTile;
@@ -82,7 +82,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams P) {
   const int q_scale = P.q_scale_byte;      // E8M0 code of 2^-k, the B operand's scale in S^T
 
   // the queue's piece descriptors, copied from the kernel-argument segment into LDS once
-  __shared__ __attribute__((aligned(16))) AttnItem spiece[kMaxAttnItems];
+  __shared__ __attribute__((aligned(16))) AttnItem spiece[NI];
   {
     const u32x4* src = (const u32x4*)(P.items + p_first);
     const int n16 = (p_last - p_first) * (int)(sizeof(AttnItem) / 16);

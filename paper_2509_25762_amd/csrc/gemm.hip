@@ -36,23 +36,26 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 constexpr int kGemmBN = 256, kGemmBK = 64;   // the tile's rows BM (256, 128 or 64) are chosen per launch
 constexpr int kProjCUs = 256;         // compute units of the chip: what a pass's tile count is weighed against
 constexpr int kMaxProjItems = 1000;   // 1000 * 24 B + header in the kernel arguments
+constexpr int kFewProjItems = 64;     // the short list: kernel arguments are written across the bus for every launch
 
 // Per-row data of a pass, made by proj_rows_kernel in the caller's workspace:
 //   dst[rows]            int64  cache row (token slot) the row's keys and values go to
 //   cs[rows][D/2]        float2 (cos, sin) of position * base^(-2t/D)
+template <int NI>
 struct ProjRowsParams {
   int64_t* dst;
   float2* cs;
   double log2_base;
   int32_t half;      // D / 2
   int32_t n_items;
-  QkvItem items[kMaxProjItems];
+  QkvItem items[NI];
 };
-static_assert(sizeof(ProjRowsParams) <= 32768, "kernel arguments are kept within 32 KiB");
+static_assert(sizeof(ProjRowsParams<kMaxProjItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
 // grid = (items, pieces of 8 tokens); 256 threads.  Angles in double precision (they reach
 // tens of thousands of radians for the fastest pair), kept as fp32.
-__global__ __launch_bounds__(256) void proj_rows_kernel(const ProjRowsParams P) {
+template <int NI>
+__global__ __launch_bounds__(256) void proj_rows_kernel(const ProjRowsParams<NI> P) {
   const QkvItem it = P.items[blockIdx.x];
   const int tok0 = blockIdx.y * 8;
   if (tok0 >= it.n_tok) return;
@@ -614,6 +617,23 @@ size_t proj_workspace_bytes(int D, int64_t rows) {
   return (size_t)rows * (sizeof(int64_t) + (size_t)(D / 2) * sizeof(float2));
 }
 
+template <int NI>
+static int launch_rows_list(int64_t* dst, float2* cs, double log2_base, int half, const QkvItem* items, int n, hipStream_t st) {
+  ProjRowsParams<NI> R;
+  R.dst = dst;
+  R.cs = cs;
+  R.log2_base = log2_base;
+  R.half = half;
+  R.n_items = n;
+  int mt = 0;
+  for (int i = 0; i < n; ++i) {
+    R.items[i] = items[i];
+    if (items[i].n_tok > mt) mt = items[i].n_tok;
+  }
+  hipLaunchKernelGGL(proj_rows_kernel<NI>, dim3((unsigned)n, (unsigned)((mt + 7) / 8)), dim3(256), 0, st, R);
+  return (int)hipGetLastError();
+}
+
 // The projection of P.rows rows with tiles of bm rows.  (The kernel of the tall tiles: workgroups stay for
 // as many tiles as there are rounds.)
 template <int D>
@@ -634,21 +654,10 @@ int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t 
   int64_t* dst = (int64_t*)workspace;
   float2* cs = (float2*)((unsigned char*)workspace + (size_t)rows * sizeof(int64_t));
   for (int base = 0; base < n_items; base += kMaxProjItems) {
-    ProjRowsParams R;
-    R.dst = dst;
-    R.cs = cs;
-    R.log2_base = log2(theta_base);
-    R.half = ls.D / 2;
     const int n = n_items - base < kMaxProjItems ? n_items - base : kMaxProjItems;
-    R.n_items = n;
-    int mt = 0;
-    for (int i = 0; i < n; ++i) {
-      R.items[i] = items[base + i];
-      if (items[base + i].n_tok > mt) mt = items[base + i].n_tok;
-    }
-    hipLaunchKernelGGL(proj_rows_kernel, dim3((unsigned)n, (unsigned)((mt + 7) / 8)), dim3(256), 0, st, R);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
+    const int e = n <= kFewProjItems ? launch_rows_list<kFewProjItems>(dst, cs, log2(theta_base), ls.D / 2, items + base, n, st)
+                                     : launch_rows_list<kMaxProjItems>(dst, cs, log2(theta_base), ls.D / 2, items + base, n, st);
+    if (e) return e;
   }
   // Tile heights: one workgroup per compute unit at a time, so a launch takes ceil(tiles / 256) rounds of one
   // tile's duration; per k tile that was measured as 1.6 / 1.3 / 1.0 / 0.67 us for tiles of 256 / 192 / 128 / 64

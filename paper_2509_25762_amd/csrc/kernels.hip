@@ -35,7 +35,13 @@ typedef __attribute__((ext_vector_type(2))) int i32x2;
 typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
-struct AttnParams {
+// Work lists travel in the kernel arguments, which the host writes anew for every launch, across
+// the bus: 31 KiB of them are most of a small call.  Each of these kernels therefore exists with
+// a short list as well, and the launcher takes the short one whenever the work fits it.
+constexpr int kFewAttnItems = 96;
+constexpr int kFewItems = 64;    // merge and append items
+
+struct AttnFields {
   const uint16_t* q;
   uint16_t* k;             // keys / values: the cache, or the packed sequences of a one-shot prefill
   uint16_t* v;
@@ -51,11 +57,16 @@ struct AttnParams {
   int32_t q_scale_byte;   // ... and the E8M0 code of 2^-k (127 - k), the query operand's scale in the MFMA
   int32_t n_queues;
   uint32_t g_magic;    // ceil(2^16 / G): r / G == (r * g_magic) >> 16 for the rows r < 256 of a packed tile
-  uint16_t first[kMaxQueues + 1];   // queue j runs pieces first[j] .. first[j+1]-1, in that order
-  AttnItem items[kMaxAttnItems];
 };
-static_assert(sizeof(AttnParams) <= 32768, "kernel arguments are kept within 32 KiB");
+template <int NI>
+struct AttnParams : AttnFields {
+  // queue j runs pieces first[j] .. first[j+1]-1, in that order (a short list has no more queues than pieces)
+  uint16_t first[(NI < kMaxQueues ? NI : kMaxQueues) + 1];
+  AttnItem items[NI];
+};
+static_assert(sizeof(AttnParams<kMaxAttnItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
+template <int NI>
 struct CombineParams {
   uint16_t* out;
   const float* part_o;
@@ -64,10 +75,11 @@ struct CombineParams {
   float c;
   float out_scale;     // 1, or the value tensor's scale of an 8-bit cache
   int32_t n_items;
-  CombineItem items[kMaxCombineItems];
+  CombineItem items[NI];
 };
-static_assert(sizeof(CombineParams) <= 32768, "kernel arguments are kept within 32 KiB");
+static_assert(sizeof(CombineParams<kMaxCombineItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
+template <int NI>
 struct AppendParams {
   uint16_t* cache_k;
   uint16_t* cache_v;
@@ -75,9 +87,9 @@ struct AppendParams {
   const uint16_t* v_new;
   int32_t row_granules;  // 16-byte granules per token row = Hkv*D/8
   int32_t n_items;
-  AppendItem items[kMaxAppendItems];
+  AppendItem items[NI];
 };
-static_assert(sizeof(AppendParams) <= 32768, "kernel arguments are kept within 32 KiB");
+static_assert(sizeof(AppendParams<kMaxAppendItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -163,8 +175,8 @@ __device__ __forceinline__ long bf16x8_to_fp8x8(bf16x8 x, float mult) {
 // takes them from k_new / v_new, and the piece that starts a query tile's key
 // range also copies the tile's token rows into the cache (nothing in this launch
 // reads those cache rows).
-template <int D, bool APPEND>
-__global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams P) {
+template <int D, bool APPEND, int NI>
+__global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   constexpr int NT = 512;            // threads
   constexpr int NG = D / 8;          // 16-byte granules per K/V row
   constexpr int KK = D / 16;         // k-steps of S^T = K Q^T
@@ -203,7 +215,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams P) {
   // The queue's piece descriptors are copied from the kernel-argument segment into
   // LDS once: a read of that segment costs microseconds, far too much to pay at
   // every piece boundary.
-  __shared__ __attribute__((aligned(16))) AttnItem spiece[kMaxAttnItems];
+  __shared__ __attribute__((aligned(16))) AttnItem spiece[NI];
   {
     const u32x4* src = (const u32x4*)(P.items + p_first);
     const int n16 = (p_last - p_first) * (int)(sizeof(AttnItem) / 16);
@@ -856,8 +868,8 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams P) {
 // out = sum_s w_s O_s / sum_s w_s l_s with w_s = exp2((m_s - max_s m_s) * c).
 // MAXS: upper bound on the pieces of any tile of the launch (4, 8 or MAXS); the per-piece
 // arrays live in registers, and fewer of them means more waves in flight to hide the loads.
-template <int D, int MAXS>
-__global__ __launch_bounds__(256) void combine_kernel(const CombineParams P) {
+template <int D, int MAXS, int NI>
+__global__ __launch_bounds__(256) void combine_kernel(const CombineParams<NI> P) {
   constexpr int TPR = D / 4;          // threads per row (float4 each)
   constexpr int RPB = 256 / TPR;      // rows per block
   const CombineItem it = P.items[blockIdx.x / P.Hkv];
@@ -922,7 +934,8 @@ __global__ __launch_bounds__(256) void combine_kernel(const CombineParams P) {
 // makes a sequence's chunk contiguous in both source and destination).
 // grid = (items, pieces of kAppendTok tokens, 2 = K/V); 16-byte copies.
 constexpr int kAppendTok = 16;
-__global__ __launch_bounds__(256) void kv_append_kernel(const AppendParams P) {
+template <int NI>
+__global__ __launch_bounds__(256) void kv_append_kernel(const AppendParams<NI> P) {
   const AppendItem it = P.items[blockIdx.x];
   const int tok0 = blockIdx.y * kAppendTok;
   if (tok0 >= it.n_tok) return;
@@ -941,6 +954,7 @@ __global__ __launch_bounds__(256) void kv_append_kernel(const AppendParams P) {
 // element; values go into blocks of 64 tokens, [block][kv-head][element][token % 64], and what is
 // left of the last block a run touches is filled with zero bytes.
 // grid = (items, 64-token blocks the longest run touches, kv-heads); 2 * D threads.
+template <int NI>
 struct Append8Params {
   uint8_t* cache_k;
   uint8_t* cache_v;
@@ -949,16 +963,16 @@ struct Append8Params {
   float k_inv, v_inv;    // fl32(1 / scale) of the two tensors
   int32_t Hkv;
   int32_t n_items;
-  AppendItem items[kMaxAppendItems];
+  AppendItem items[NI];
 };
-static_assert(sizeof(Append8Params) <= 32768, "kernel arguments are kept within 32 KiB");
+static_assert(sizeof(Append8Params<kMaxAppendItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
 __device__ __forceinline__ float code_range(uint32_t bf16_bits, float inv) {
   return __builtin_amdgcn_fmed3f(__uint_as_float(bf16_bits << 16) * inv, -448.0f, 448.0f);
 }
 
-template <int D>
-__global__ __launch_bounds__(2 * D) void kv_append_fp8_kernel(const Append8Params P) {
+template <int D, int NI>
+__global__ __launch_bounds__(2 * D) void kv_append_fp8_kernel(const Append8Params<NI> P) {
   constexpr int NT = 2 * D;       // one thread per (4 tokens, 8 elements) of a 64-token block
   constexpr int BLK = kKeyTile;   // tokens per value block
   constexpr int NG = D / 8;       // 16-byte granules of a bf16 row of one kv-head
@@ -1144,18 +1158,76 @@ int static_scratch(void** ptr) {
   return 0;
 }
 
+template <int NI>
+static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool append, const AttnItem* items, int n_items,
+                                 const uint16_t* first, int n_queues, hipStream_t st) {
+  if (n_items > NI || n_queues > n_items) return (int)hipErrorInvalidValue;
+  AttnParams<NI> P;
+  static_cast<AttnFields&>(P) = F;
+  for (int j = 0; j <= n_queues; ++j) P.first[j] = first[j];
+  for (int i = 0; i < n_items; ++i) P.items[i] = items[i];
+  const dim3 grid((unsigned)(n_queues * ls.Hkv)), block(512);
+  if (ls.fp8) {
+    // (the 8-bit cache is filled by its own append kernel)
+    if (append) return (int)hipErrorInvalidValue;
+    if (ls.D == 128) hipLaunchKernelGGL((attn_fwd_fp8_kernel<128, NI>), grid, block, 0, st, P);
+    else hipLaunchKernelGGL((attn_fwd_fp8_kernel<64, NI>), grid, block, 0, st, P);
+  } else if (ls.D == 128) {
+    if (append) hipLaunchKernelGGL((attn_fwd_kernel<128, true, NI>), grid, block, 0, st, P);
+    else hipLaunchKernelGGL((attn_fwd_kernel<128, false, NI>), grid, block, 0, st, P);
+  } else {
+    if (append) hipLaunchKernelGGL((attn_fwd_kernel<64, true, NI>), grid, block, 0, st, P);
+    else hipLaunchKernelGGL((attn_fwd_kernel<64, false, NI>), grid, block, 0, st, P);
+  }
+  return (int)hipGetLastError();
+}
+
 int launch_attention(const LayerShape& ls, const void* q, void* k, void* v, const void* k_new, const void* v_new,
                      void* out, float* part_o, float* part_ml, const AttnItem* items, int n_items,
                      const uint16_t* first, int n_queues, void* stream, bool timed) {
   hipStream_t st = (hipStream_t)stream;
   if (n_items <= 0 || n_queues <= 0) return 0;
   if (n_items > kMaxAttnItems || n_queues > kMaxQueues) return (int)hipErrorInvalidValue;
-  AttnParams P;
-  P.q = (const uint16_t*)q;
-  P.k = (uint16_t*)k;
-  P.v = (uint16_t*)v;
-  P.k_new = (const uint16_t*)k_new;
-  P.v_new = (const uint16_t*)v_new;
+  AttnFields F;
+  F.q = (const uint16_t*)q;
+  F.k = (uint16_t*)k;
+  F.v = (uint16_t*)v;
+  F.k_new = (const uint16_t*)k_new;
+  F.v_new = (const uint16_t*)v_new;
+  F.out = (uint16_t*)out;
+  F.part_o = part_o;
+  F.part_ml = part_ml;
+  F.Hq = ls.Hq;
+  F.Hkv = ls.Hkv;
+  F.G = ls.G;
+  F.TM = ls.TM;
+  F.c = ls.c;
+  F.out_scale = ls.out_scale;
+  F.q_mult = 1.0f;
+  F.q_scale_byte = 127;
+  if (ls.fp8) {
+    // k with 4 <= c * 2^k < 8: queries of magnitude 2^-8 .. 56 stay inside E4M3's normal range
+    int e = 0;
+    (void)frexpf(ls.c, &e);                  // c = f * 2^e, 0.5 <= f < 1
+    const int k = 3 - e;                     // c * 2^k = 8 f, in [4, 8)
+    if (k < -120 || k > 120) return (int)hipErrorInvalidValue;
+    F.q_mult = ldexpf(ls.c, k);
+    F.q_scale_byte = 127 - k;
+  }
+  F.n_queues = n_queues;
+  F.g_magic = (65536u + (uint32_t)ls.G - 1u) / (uint32_t)ls.G;
+  const int pair = timed ? prof_begin(0, st) : -1;
+  const int rc = n_items <= kFewAttnItems
+                     ? launch_attention_list<kFewAttnItems>(ls, F, k_new != nullptr, items, n_items, first, n_queues, st)
+                     : launch_attention_list<kMaxAttnItems>(ls, F, k_new != nullptr, items, n_items, first, n_queues, st);
+  prof_end(pair, st);
+  return rc;
+}
+
+template <int NI>
+static int launch_combine_list(const LayerShape& ls, void* out, const float* part_o, const float* part_ml,
+                               const CombineItem* items, int n, hipStream_t st) {
+  CombineParams<NI> P;
   P.out = (uint16_t*)out;
   P.part_o = part_o;
   P.part_ml = part_ml;
@@ -1163,39 +1235,23 @@ int launch_attention(const LayerShape& ls, const void* q, void* k, void* v, cons
   P.Hkv = ls.Hkv;
   P.G = ls.G;
   P.TM = ls.TM;
-  P.c = ls.c;
+  P.c = ls.fp8 ? 1.0f : ls.c;   // (the 8-bit kernel stores its references in log2 units)
   P.out_scale = ls.out_scale;
-  P.q_mult = 1.0f;
-  P.q_scale_byte = 127;
-  if (ls.fp8) {
-    // k with 4 <= c * 2^k < 8: queries of magnitude 2^-8 .. 56 stay inside E4M3's normal range
-    int e = 0;
-    (void)frexpf(ls.c, &e);                  // c = f * 2^e, 0.5 <= f < 1
-    const int k = 3 - e;                     // c * 2^k = 8 f, in [4, 8)
-    if (k < -120 || k > 120) return (int)hipErrorInvalidValue;
-    P.q_mult = ldexpf(ls.c, k);
-    P.q_scale_byte = 127 - k;
-  }
-  P.n_queues = n_queues;
-  P.g_magic = (65536u + (uint32_t)ls.G - 1u) / (uint32_t)ls.G;
-  for (int j = 0; j <= n_queues; ++j) P.first[j] = first[j];
-  for (int i = 0; i < n_items; ++i) P.items[i] = items[i];
-  dim3 grid((unsigned)(n_queues * ls.Hkv));
-  const bool append = k_new != nullptr;
-  const int pair = timed ? prof_begin(0, st) : -1;
-  if (ls.fp8) {
-    // (the 8-bit cache is filled by its own append kernel)
-    if (append) return (int)hipErrorInvalidValue;
-    if (ls.D == 128) hipLaunchKernelGGL(attn_fwd_fp8_kernel<128>, grid, dim3(512), 0, st, P);
-    else hipLaunchKernelGGL(attn_fwd_fp8_kernel<64>, grid, dim3(512), 0, st, P);
-  } else if (ls.D == 128) {
-    if (append) hipLaunchKernelGGL((attn_fwd_kernel<128, true>), grid, dim3(512), 0, st, P);
-    else hipLaunchKernelGGL((attn_fwd_kernel<128, false>), grid, dim3(512), 0, st, P);
+  P.n_items = n;
+  for (int i = 0; i < n; ++i) P.items[i] = items[i];
+  const int rpb = 256 / (ls.D / 4);
+  const dim3 grid((unsigned)(n * ls.Hkv), (unsigned)(kTileRows / rpb)), block(256);
+  int max_split = 0;
+  for (int i = 0; i < n; ++i) max_split = items[i].nsplit > max_split ? items[i].nsplit : max_split;
+  if (ls.D == 128) {
+    if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<128, 4, NI>), grid, block, 0, st, P);
+    else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<128, 8, NI>), grid, block, 0, st, P);
+    else hipLaunchKernelGGL((combine_kernel<128, kMaxSplit, NI>), grid, block, 0, st, P);
   } else {
-    if (append) hipLaunchKernelGGL((attn_fwd_kernel<64, true>), grid, dim3(512), 0, st, P);
-    else hipLaunchKernelGGL((attn_fwd_kernel<64, false>), grid, dim3(512), 0, st, P);
+    if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<64, 4, NI>), grid, block, 0, st, P);
+    else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<64, 8, NI>), grid, block, 0, st, P);
+    else hipLaunchKernelGGL((combine_kernel<64, kMaxSplit, NI>), grid, block, 0, st, P);
   }
-  prof_end(pair, st);
   return (int)hipGetLastError();
 }
 
@@ -1203,66 +1259,75 @@ int launch_combine(const LayerShape& ls, void* out, const float* part_o, const f
                    const CombineItem* items, int n_items, void* stream, bool timed) {
   hipStream_t st = (hipStream_t)stream;
   for (int base = 0; base < n_items; base += kMaxCombineItems) {
-    CombineParams P;
-    P.out = (uint16_t*)out;
-    P.part_o = part_o;
-    P.part_ml = part_ml;
-    P.Hq = ls.Hq;
-    P.Hkv = ls.Hkv;
-    P.G = ls.G;
-    P.TM = ls.TM;
-    P.c = ls.fp8 ? 1.0f : ls.c;   // (the 8-bit kernel stores its references in log2 units)
-    P.out_scale = ls.out_scale;
     const int n = n_items - base < kMaxCombineItems ? n_items - base : kMaxCombineItems;
-    P.n_items = n;
-    for (int i = 0; i < n; ++i) P.items[i] = items[base + i];
-    const int rpb = 256 / (ls.D / 4);
-    dim3 grid((unsigned)(n * ls.Hkv), (unsigned)(kTileRows / rpb)), block(256);
-    int max_split = 0;
-    for (int i = 0; i < n; ++i) max_split = items[base + i].nsplit > max_split ? items[base + i].nsplit : max_split;
     const int pair = timed ? prof_begin(1, st) : -1;
-    if (ls.D == 128) {
-      if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<128, 4>), grid, block, 0, st, P);
-      else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<128, 8>), grid, block, 0, st, P);
-      else hipLaunchKernelGGL((combine_kernel<128, kMaxSplit>), grid, block, 0, st, P);
-    } else {
-      if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<64, 4>), grid, block, 0, st, P);
-      else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<64, 8>), grid, block, 0, st, P);
-      else hipLaunchKernelGGL((combine_kernel<64, kMaxSplit>), grid, block, 0, st, P);
-    }
+    const int e = n <= kFewItems ? launch_combine_list<kFewItems>(ls, out, part_o, part_ml, items + base, n, st)
+                                 : launch_combine_list<kMaxCombineItems>(ls, out, part_o, part_ml, items + base, n, st);
     prof_end(pair, st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
+    if (e) return e;
   }
   return 0;
+}
+
+template <int NI>
+static int launch_append_list(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new, const void* v_new,
+                              const AppendItem* items, int n, hipStream_t st) {
+  AppendParams<NI> P;
+  P.cache_k = (uint16_t*)cache_k;
+  P.cache_v = (uint16_t*)cache_v;
+  P.k_new = (const uint16_t*)k_new;
+  P.v_new = (const uint16_t*)v_new;
+  P.row_granules = ls.Hkv * ls.D / 8;
+  P.n_items = n;
+  int mt = 0;
+  for (int i = 0; i < n; ++i) {
+    P.items[i] = items[i];
+    if (items[i].n_tok > mt) mt = items[i].n_tok;
+  }
+  const dim3 grid((unsigned)n, (unsigned)((mt + kAppendTok - 1) / kAppendTok), 2), block(256);
+  hipLaunchKernelGGL(kv_append_kernel<NI>, grid, block, 0, st, P);
+  return (int)hipGetLastError();
 }
 
 int launch_append(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new,
                   const void* v_new, const AppendItem* items, int n_items, int max_tok, void* stream) {
   hipStream_t st = (hipStream_t)stream;
+  (void)max_tok;
   for (int base = 0; base < n_items; base += kMaxAppendItems) {
-    AppendParams P;
-    P.cache_k = (uint16_t*)cache_k;
-    P.cache_v = (uint16_t*)cache_v;
-    P.k_new = (const uint16_t*)k_new;
-    P.v_new = (const uint16_t*)v_new;
-    P.row_granules = ls.Hkv * ls.D / 8;
     const int n = n_items - base < kMaxAppendItems ? n_items - base : kMaxAppendItems;
-    P.n_items = n;
-    int mt = 0;
-    for (int i = 0; i < n; ++i) {
-      P.items[i] = items[base + i];
-      if (items[base + i].n_tok > mt) mt = items[base + i].n_tok;
-    }
-    (void)max_tok;
-    dim3 grid((unsigned)n, (unsigned)((mt + kAppendTok - 1) / kAppendTok), 2), block(256);
     const int pair = prof_begin(2, st);
-    hipLaunchKernelGGL(kv_append_kernel, grid, block, 0, st, P);
+    const int e = n <= kFewItems ? launch_append_list<kFewItems>(ls, cache_k, cache_v, k_new, v_new, items + base, n, st)
+                                 : launch_append_list<kMaxAppendItems>(ls, cache_k, cache_v, k_new, v_new, items + base, n, st);
     prof_end(pair, st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
+    if (e) return e;
   }
   return 0;
+}
+
+template <int NI>
+static int launch_append_fp8_list(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new, const void* v_new,
+                                  float k_inv, float v_inv, const AppendItem* items, int n, hipStream_t st) {
+  Append8Params<NI> P;
+  P.cache_k = (uint8_t*)cache_k;
+  P.cache_v = (uint8_t*)cache_v;
+  P.k_new = (const uint16_t*)k_new;
+  P.v_new = (const uint16_t*)v_new;
+  P.k_inv = k_inv;
+  P.v_inv = v_inv;
+  P.Hkv = ls.Hkv;
+  P.n_items = n;
+  int64_t blocks = 0;   // 64-token blocks the longest run of this launch touches
+  for (int i = 0; i < n; ++i) {
+    const AppendItem& a = items[i];
+    P.items[i] = a;
+    const int64_t nb = (a.dst_row + a.n_tok - 1) / kKeyTile - a.dst_row / kKeyTile + 1;
+    if (nb > blocks) blocks = nb;
+  }
+  if (blocks > 65535) return (int)hipErrorInvalidValue;
+  const dim3 grid((unsigned)n, (unsigned)blocks, (unsigned)ls.Hkv);
+  if (ls.D == 128) hipLaunchKernelGGL((kv_append_fp8_kernel<128, NI>), grid, dim3(256), 0, st, P);
+  else hipLaunchKernelGGL((kv_append_fp8_kernel<64, NI>), grid, dim3(128), 0, st, P);
+  return (int)hipGetLastError();
 }
 
 int launch_append_fp8(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new, const void* v_new,
@@ -1270,31 +1335,13 @@ int launch_append_fp8(const LayerShape& ls, void* cache_k, void* cache_v, const 
   hipStream_t st = (hipStream_t)stream;
   if (ls.D != 128 && ls.D != 64) return (int)hipErrorInvalidValue;
   for (int base = 0; base < n_items; base += kMaxAppendItems) {
-    Append8Params P;
-    P.cache_k = (uint8_t*)cache_k;
-    P.cache_v = (uint8_t*)cache_v;
-    P.k_new = (const uint16_t*)k_new;
-    P.v_new = (const uint16_t*)v_new;
-    P.k_inv = k_inv;
-    P.v_inv = v_inv;
-    P.Hkv = ls.Hkv;
     const int n = n_items - base < kMaxAppendItems ? n_items - base : kMaxAppendItems;
-    P.n_items = n;
-    int64_t blocks = 0;   // 64-token blocks the longest run of this launch touches
-    for (int i = 0; i < n; ++i) {
-      const AppendItem& a = items[base + i];
-      P.items[i] = a;
-      const int64_t nb = (a.dst_row + a.n_tok - 1) / kKeyTile - a.dst_row / kKeyTile + 1;
-      if (nb > blocks) blocks = nb;
-    }
-    if (blocks > 65535) return (int)hipErrorInvalidValue;
-    dim3 grid((unsigned)n, (unsigned)blocks, (unsigned)ls.Hkv);
     const int pair = prof_begin(2, st);
-    if (ls.D == 128) hipLaunchKernelGGL(kv_append_fp8_kernel<128>, grid, dim3(256), 0, st, P);
-    else hipLaunchKernelGGL(kv_append_fp8_kernel<64>, grid, dim3(128), 0, st, P);
+    const int e = n <= kFewItems
+                      ? launch_append_fp8_list<kFewItems>(ls, cache_k, cache_v, k_new, v_new, k_inv, v_inv, items + base, n, st)
+                      : launch_append_fp8_list<kMaxAppendItems>(ls, cache_k, cache_v, k_new, v_new, k_inv, v_inv, items + base, n, st);
     prof_end(pair, st);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
+    if (e) return e;
   }
   return 0;
 }

@@ -91,6 +91,8 @@ __global__ __launch_bounds__(256) void rope_kernel(const RopeParams P) {
 // The same rotation as the epilogue of the layer's fused QKV projection: one pass over
 // the projection's output rows [q heads | k heads | v heads] writes the rotated queries
 // to their own array and the rotated keys and the values straight into the cache slabs.
+constexpr int kFewQkvItems = 64;     // the short list: kernel arguments are written across the bus for every launch
+template <int NI>
 struct QkvParams {
   const uint16_t* qkv;   // [rows][Hq + 2 Hkv][D]
   uint16_t* q_out;       // [rows][Hq][D]
@@ -99,12 +101,12 @@ struct QkvParams {
   double log2_base;
   int32_t Hq, Hkv;
   int32_t n_items;
-  QkvItem items[kMaxQkvItems];
+  QkvItem items[NI];
 };
-static_assert(sizeof(QkvParams) <= 32768, "kernel arguments are kept within 32 KiB");
+static_assert(sizeof(QkvParams<kMaxQkvItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
-template <int D>
-__global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams P) {
+template <int D, int NI>
+__global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams<NI> P) {
   constexpr int HALF = D / 2;
   constexpr int UPH = HALF / 8;
   __shared__ float cs[kRopeTok][HALF][2];
@@ -156,32 +158,38 @@ __global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams P)
   }
 }
 
+template <int NI>
+static int launch_qkv_list(const LayerShape& ls, const void* qkv, void* q_out, void* cache_k, void* cache_v,
+                           const QkvItem* items, int n, double theta_base, hipStream_t st) {
+  QkvParams<NI> P;
+  P.qkv = (const uint16_t*)qkv;
+  P.q_out = (uint16_t*)q_out;
+  P.cache_k = (uint16_t*)cache_k;
+  P.cache_v = (uint16_t*)cache_v;
+  P.log2_base = log2(theta_base);
+  P.Hq = ls.Hq;
+  P.Hkv = ls.Hkv;
+  P.n_items = n;
+  int mt = 0;
+  for (int i = 0; i < n; ++i) {
+    P.items[i] = items[i];
+    if (items[i].n_tok > mt) mt = items[i].n_tok;
+  }
+  const dim3 grid((unsigned)n, (unsigned)((mt + kRopeTok - 1) / kRopeTok)), block(256);
+  if (ls.D == 128) hipLaunchKernelGGL((qkv_rope_append_kernel<128, NI>), grid, block, 0, st, P);
+  else hipLaunchKernelGGL((qkv_rope_append_kernel<64, NI>), grid, block, 0, st, P);
+  return (int)hipGetLastError();
+}
+
 int launch_qkv_rope_append(const LayerShape& ls, const void* qkv, void* q_out, void* cache_k, void* cache_v,
                            const QkvItem* items, int n_items, double theta_base, void* stream) {
   hipStream_t st = (hipStream_t)stream;
   for (int base = 0; base < n_items; base += kMaxQkvItems) {
-    QkvParams P;
-    P.qkv = (const uint16_t*)qkv;
-    P.q_out = (uint16_t*)q_out;
-    P.cache_k = (uint16_t*)cache_k;
-    P.cache_v = (uint16_t*)cache_v;
-    P.log2_base = log2(theta_base);
-    P.Hq = ls.Hq;
-    P.Hkv = ls.Hkv;
     const int n = n_items - base < kMaxQkvItems ? n_items - base : kMaxQkvItems;
-    P.n_items = n;
-    int mt = 0;
-    for (int i = 0; i < n; ++i) {
-      P.items[i] = items[base + i];
-      if (items[base + i].n_tok > mt) mt = items[base + i].n_tok;
-    }
-    dim3 grid((unsigned)n, (unsigned)((mt + kRopeTok - 1) / kRopeTok)), block(256);
-    if (ls.D == 128)
-      hipLaunchKernelGGL(qkv_rope_append_kernel<128>, grid, block, 0, st, P);
-    else
-      hipLaunchKernelGGL(qkv_rope_append_kernel<64>, grid, block, 0, st, P);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return (int)e;
+    const int e = n <= kFewQkvItems
+                      ? launch_qkv_list<kFewQkvItems>(ls, qkv, q_out, cache_k, cache_v, items + base, n, theta_base, st)
+                      : launch_qkv_list<kMaxQkvItems>(ls, qkv, q_out, cache_k, cache_v, items + base, n, theta_base, st);
+    if (e) return e;
   }
   return 0;
 }
