@@ -105,6 +105,11 @@ struct QkvParams {
 };
 static_assert(sizeof(QkvParams<kMaxQkvItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
+// Bound by HBM: a row's heads are read once and written once.  A thread's first kQkvAhead units
+// are requested before the workgroup's table of angles is made (double precision, a few microseconds
+// for which the memory would otherwise idle), and later ones as many at a time: 72.2 -> 68.6 us for
+// 12,900 rows of 48 heads of 128, 4.59 TB/s.
+constexpr int kQkvAhead = 4;
 template <int D, int NI>
 __global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams<NI> P) {
   constexpr int HALF = D / 2;
@@ -114,47 +119,59 @@ __global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams<NI
   const int tok0 = blockIdx.y * kRopeTok;
   if (tok0 >= it.n_tok) return;
   const int ntok = min(kRopeTok, it.n_tok - tok0);
-  for (int e = threadIdx.x; e < ntok * HALF; e += 256) {
-    const int t = e / HALF, i = e % HALF;
+  const int heads = P.Hq + 2 * P.Hkv;
+  const int units = ntok * heads * UPH;   // a unit = 8 pairs of one head: 16 bytes from each half of the head's row
+  const int64_t src_row0 = (int64_t)it.src_row + tok0, dst_row0 = it.dst_row + tok0;
+  const uint16_t* src = P.qkv + src_row0 * heads * D;
+  u32x4 a[kQkvAhead], b[kQkvAhead];
+  auto request = [&](int u0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int j = 0; j < kQkvAhead; ++j) {
+      const int u = min(u0 + 256 * j, units - 1);   // (past the end: the last unit, not used)
+      const uint16_t* s = src + (u / UPH) * D + (u % UPH) * 8;
+      a[j] = *(const u32x4*)s;
+      b[j] = *(const u32x4*)(s + HALF);
+    }
+  };
+  request(threadIdx.x);
+  {
+    const int i = threadIdx.x % HALF;   // the same pair for each of a thread's tokens
     const double theta = exp2(-(2.0 * i / D) * P.log2_base);
-    double s, c;
-    sincos((double)(it.pos0 + tok0 + t) * theta, &s, &c);
-    cs[t][i][0] = (float)c;
-    cs[t][i][1] = (float)s;
+    for (int t = threadIdx.x / HALF; t < ntok; t += 256 / HALF) {
+      double s, c;
+      sincos((double)(it.pos0 + tok0 + t) * theta, &s, &c);
+      cs[t][i][0] = (float)c;
+      cs[t][i][1] = (float)s;
+    }
   }
   __syncthreads();
-  const int heads = P.Hq + 2 * P.Hkv;
-  const int units = ntok * heads * UPH;
-  for (int u = threadIdx.x; u < units; u += 256) {
-    const int g = u % UPH;
-    const int h = (u / UPH) % heads;
-    const int t = u / (UPH * heads);
-    const int64_t src_row = (int64_t)it.src_row + tok0 + t;
-    const int64_t dst_row = it.dst_row + tok0 + t;
-    const uint16_t* src = P.qkv + (src_row * heads + h) * D;
-    const u32x4 a = *(const u32x4*)(src + g * 8), b = *(const u32x4*)(src + HALF + g * 8);
-    uint16_t* dst;
-    if (h < P.Hq) {
-      dst = P.q_out + (src_row * P.Hq + h) * D;
-    } else if (h < P.Hq + P.Hkv) {
-      dst = P.cache_k + (dst_row * P.Hkv + (h - P.Hq)) * D;
-    } else {
-      dst = P.cache_v + (dst_row * P.Hkv + (h - P.Hq - P.Hkv)) * D;
-      *(u32x4*)(dst + g * 8) = a;            // values are copied as they are
-      *(u32x4*)(dst + HALF + g * 8) = b;
-      continue;
-    }
-    u32x4 ra, rb;
+  for (int u0 = threadIdx.x; u0 < units; u0 += 256 * kQkvAhead) {
+    if (u0 != (int)threadIdx.x) request(u0);
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const float c0 = cs[t][g * 8 + 2 * w][0], s0 = cs[t][g * 8 + 2 * w][1];
-      const float c1 = cs[t][g * 8 + 2 * w + 1][0], s1 = cs[t][g * 8 + 2 * w + 1][1];
-      const float a0 = bf16_lo(a[w]), a1 = bf16_hi(a[w]), b0 = bf16_lo(b[w]), b1 = bf16_hi(b[w]);
-      ra[w] = pack_bf16(a0 * c0 - b0 * s0, a1 * c1 - b1 * s1);
-      rb[w] = pack_bf16(b0 * c0 + a0 * s0, b1 * c1 + a1 * s1);
+    for (int j = 0; j < kQkvAhead; ++j) {
+      const int u = u0 + 256 * j;
+      if (u >= units) break;
+      const int g = u % UPH;
+      const int h = (u / UPH) % heads;
+      const int t = u / (UPH * heads);
+      uint16_t* dst;
+      u32x4 ra = a[j], rb = b[j];   // values are copied as they are
+      if (h < P.Hq) dst = P.q_out + ((src_row0 + t) * P.Hq + h) * D;
+      else if (h < P.Hq + P.Hkv) dst = P.cache_k + ((dst_row0 + t) * P.Hkv + (h - P.Hq)) * D;
+      else dst = P.cache_v + ((dst_row0 + t) * P.Hkv + (h - P.Hq - P.Hkv)) * D;
+      if (h < P.Hq + P.Hkv) {
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+          const float c0 = cs[t][g * 8 + 2 * w][0], s0 = cs[t][g * 8 + 2 * w][1];
+          const float c1 = cs[t][g * 8 + 2 * w + 1][0], s1 = cs[t][g * 8 + 2 * w + 1][1];
+          const float a0 = bf16_lo(a[j][w]), a1 = bf16_hi(a[j][w]), b0 = bf16_lo(b[j][w]), b1 = bf16_hi(b[j][w]);
+          ra[w] = pack_bf16(a0 * c0 - b0 * s0, a1 * c1 - b1 * s1);
+          rb[w] = pack_bf16(b0 * c0 + a0 * s0, b1 * c1 + a1 * s1);
+        }
+      }
+      *(u32x4*)(dst + g * 8) = ra;
+      *(u32x4*)(dst + HALF + g * 8) = rb;
     }
-    *(u32x4*)(dst + g * 8) = ra;
-    *(u32x4*)(dst + HALF + g * 8) = rb;
   }
 }
 
