@@ -346,3 +346,19 @@ def test_peaked_softmax_moves_the_reference_often(gpu, gain, split):
     finally:
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
     print(f"peaked softmax gain {gain}: max abs err {mx:.3e}, mean {mean:.3e}")
+
+
+# --------------------------------------------------------------------------- work lists at their limits
+
+@pytest.mark.parametrize("B,split", [(64, 1), (65, 1), (96, 1), (97, 1), (48, 2), (49, 2), (64, 2), (65, 2)])
+def test_work_lists_on_either_side_of_the_short_lists(gpu, B, split):
+    """64 and 65 append runs, 96 and 97 whole attention pieces, 96 and 98 pieces of cut tiles, 64 and 65 merged tiles:
+    the largest passes that travel in the short lists of the kernel arguments and the smallest ones in the long lists."""
+    binding, episode, torch = gpu
+    ep = build_episode(small_cfg(B, 4, 1, 64, 3, seed=60 + B), threads=2,
+                       lengths=(np.full(B, 61, np.int32) + np.arange(B, dtype=np.int32) % 3 * 40, np.full(B, 7, np.int32)))
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        run_and_check(gpu, ep, oracle_uniform_chunks(ep.prompt_len, ep.resp_len, 3), None, f"B={B} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)

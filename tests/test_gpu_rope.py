@@ -223,3 +223,33 @@ def test_rotation_of_pairs_that_cancel(gpu):
     # crosses a bf16 rounding boundary in about one element in a hundred)
     check_rotation(tq.cpu().numpy().view(np.uint16), qb, pos, base, "q (cancelling pairs)", count_bit_differences=False)
     check_rotation(tk.cpu().numpy().view(np.uint16), kb, pos, base, "k (cancelling pairs)", count_bit_differences=False)
+
+
+@pytest.mark.parametrize("B,D", [(64, 128), (65, 128), (64, 64), (65, 64)])
+def test_qkv_epilogue_work_lists_on_either_side_of_the_short_list(gpu, B, D):
+    """64 runs travel in the short list of the kernel arguments, 65 in the long one; rows 1 .. 21 per run."""
+    binding, torch = gpu
+    rng = np.random.default_rng(B + D)
+    Hq, Hkv, base = 3, 1, 10000.0
+    q_len = 1 + np.arange(B, dtype=np.int32) % 21
+    kv_before = (np.arange(B, dtype=np.int32) * 37) % 500
+    slot_begin = np.concatenate([[0], np.cumsum(kv_before + q_len + 2)]).astype(np.int64)
+    cu = np.concatenate([[0], np.cumsum(q_len)]).astype(np.int32)
+    n = int(cu[-1])
+    qkv = draw_bits(rng, (n, Hq + 2 * Hkv, D))
+    dev = torch.device("cuda:0")
+    ck = torch.full((int(slot_begin[-1]), Hkv, D), -1, dtype=torch.int16, device=dev)
+    cv = torch.full_like(ck, -1)
+    cache = binding.KVCache(ck, cv, slot_begin, kv_before.copy())
+    q_out = torch.full((n, Hq, D), -1, dtype=torch.int16, device=dev)
+    binding.oppo_qkv_rope_append(binding.make_desc(Hq, Hkv, D, 1.0 / np.sqrt(D)), cache, cu,
+                                 torch.from_numpy(qkv.view(np.int16)).to(dev), q_out, base)
+    torch.cuda.synchronize()
+    pos = pass_positions(kv_before, q_len)
+    slots = np.concatenate([int(slot_begin[i]) + int(kv_before[i]) + np.arange(q_len[i]) for i in range(B)])
+    gk, gv = ck.cpu().numpy().view(np.uint16), cv.cpu().numpy().view(np.uint16)
+    check_rotation(q_out.cpu().numpy().view(np.uint16), qkv[:, :Hq], pos, base, "q")
+    check_rotation(gk[slots], qkv[:, Hq:Hq + Hkv], pos, base, "k")
+    assert np.array_equal(gv[slots], qkv[:, Hq + Hkv:]), "v"
+    others = np.setdiff1d(np.arange(len(gk)), slots)
+    assert (gk[others] == 0xFFFF).all() and (gv[others] == 0xFFFF).all(), "other cache slots were written"
