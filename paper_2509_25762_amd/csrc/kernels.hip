@@ -37,7 +37,8 @@ typedef __attribute__((ext_vector_type(8))) int i32x8;
 
 // Work lists travel in the kernel arguments, which the host writes anew for every launch, across
 // the bus: 31 KiB of them are most of a small call.  Each of these kernels therefore exists with
-// a short list as well, and the launcher takes the short one whenever the work fits it.
+// a short list as well, and the launcher takes the short one whenever the work fits it (a step of
+// 4 sequences x 32 tokens: 16.2 us with the long list, 14.9 with the short one).
 constexpr int kFewAttnItems = 96;
 constexpr int kFewItems = 64;    // merge and append items
 
