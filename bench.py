@@ -650,7 +650,7 @@ def qkv_proj_bench(args, cfg, torch, ob) -> int:
                       "steps": steps, "warmup": warmup, "ms_per_step": f["ms"], "higher_is_better": True, "dtype": "bf16", "data": "synthetic",
                       "config": {"workload": workload},
                       "roofline": {"bound": "mfma", "achieved": f["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                                   "frac": f["frac_of_mfma_peak"], "traffic": None, "kernel": "qkv_proj_kernel"},
+                                   "frac": f["frac_of_mfma_peak"], "traffic": None, "kernel": "qkv_proj_phased_kernel"},
                       "paths": res}))
     return 0
 
@@ -1174,7 +1174,7 @@ def main() -> int:
         f = pr["fused_projection_rope_append"]
         nxt["qkv_proj"] = {"workload": wl, "value": f["tflops"], "unit": "TFLOP/s", "ms": f["ms"], "dtype": "bf16",
                            "roofline": {"bound": "mfma", "achieved": f["tflops"], "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
-                                        "frac": f["frac_of_mfma_peak"], "kernel": "qkv_proj_kernel"}}
+                                        "frac": f["frac_of_mfma_peak"], "kernel": "qkv_proj_phased_kernel"}}
         line["next_rows"] = nxt
     line["cpu_baseline"] = baseline
     print(json.dumps(line))
