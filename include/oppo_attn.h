@@ -510,6 +510,15 @@ int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_bef
                     int32_t* n_items);
 
 /*
+ * Diagnostic: the launches oppo_qkv_proj_rope_append would make of its GEMM for a pass of
+ * rows new rows.  Nothing is enqueued; no GPU needed.  launches receives 4 int32 per launch:
+ *   {rows, rows of a tile, 1 if the phased kernel runs it, rounds of one tile per compute unit}
+ * and *n how many there are (0 for no rows, else 1 or 2; the pass's first rows come first).
+ */
+int oppo_qkv_proj_plan_debug(const oppo_attn_desc* desc, int32_t rows, int32_t hidden, int32_t* launches /* [2][4] */,
+                             int32_t* n);
+
+/*
  * Per-kernel timing for benchmarks.  While enabled, every kernel launch of the
  * library is bracketed by two HIP events recorded on the launch stream (this
  * costs a little, so leave it off in production).  oppo_profile_read waits for

@@ -30,7 +30,7 @@ OPT_NUM_CUS = 2
 
 EXPORTS = [
     "oppo_chunk_schedule", "oppo_kv_append", "oppo_chunk_prefill_attn", "oppo_chunk_step", "oppo_full_prefill_ref",
-    "oppo_workspace_bytes", "oppo_set_option", "oppo_plan_debug", "oppo_last_error", "oppo_version", "oppo_rope", "oppo_qkv_rope_append", "oppo_qkv_proj_rope_append", "oppo_qkv_proj_workspace_bytes",
+    "oppo_workspace_bytes", "oppo_set_option", "oppo_plan_debug", "oppo_qkv_proj_plan_debug", "oppo_last_error", "oppo_version", "oppo_rope", "oppo_qkv_rope_append", "oppo_qkv_proj_rope_append", "oppo_qkv_proj_workspace_bytes",
     "oppo_profile_enable", "oppo_profile_read", "oppo_profile_read_each", "oppo_profile_host", "oppo_chunk_step_noalloc", "oppo_static_scratch_bytes",
     "oppo_kv_append_fp8", "oppo_chunk_prefill_attn_fp8",
     "oppo_pool_create", "oppo_pool_destroy", "oppo_pool_acquire", "oppo_pool_release", "oppo_pool_slot_of",
@@ -128,6 +128,8 @@ def load() -> ctypes.CDLL:
     lib.oppo_plan_debug.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32, i32p, i32p, ctypes.c_size_t, i32p,
                                     ctypes.c_int32, i32p]
     lib.oppo_plan_debug.restype = ctypes.c_int
+    lib.oppo_qkv_proj_plan_debug.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32, ctypes.c_int32, i32p, i32p]
+    lib.oppo_qkv_proj_plan_debug.restype = ctypes.c_int
     lib.oppo_profile_enable.argtypes = [ctypes.c_int]
     lib.oppo_profile_enable.restype = ctypes.c_int
     lib.oppo_profile_read.argtypes = [ctypes.POINTER(ctypes.c_double), i32p]
@@ -640,3 +642,11 @@ def oppo_plan_debug(desc: AttnDesc, kv_before, q_len, workspace_bytes: int, max_
     _check(load().oppo_plan_debug(ctypes.byref(desc), kvb.shape[0], _i32p(kvb), _i32p(ql), workspace_bytes,
                                   items.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), max_items, ctypes.byref(n)))
     return items[: n.value].copy()
+
+
+def oppo_qkv_proj_plan_debug(desc: AttnDesc, rows: int, hidden: int) -> list:
+    """GEMM launches of a projection pass: (rows, rows of a tile, phased kernel, rounds) each (diagnostic)."""
+    out = np.zeros((2, 4), dtype=np.int32)
+    n = ctypes.c_int32(0)
+    _check(load().oppo_qkv_proj_plan_debug(ctypes.byref(desc), rows, hidden, _i32p(out.reshape(-1)), ctypes.byref(n)))
+    return [(int(r), int(h), bool(p), int(k)) for r, h, p, k in out[: n.value]]

@@ -26,6 +26,49 @@ int fail(int code, const char* fmt, ...) {
   va_end(ap);
   return code;
 }
+
+// Tiles of the projection.  One workgroup runs per compute unit, so the k loops take ceil(tiles / 256) rounds; what
+// a tile costs besides (its first operands' arrival, the rotation, the stores) shares the memory and goes with the
+// number of tiles.  us of a launch ~ launch + tile * tiles / 256 + k_tile * rounds * (hidden / 64), with coefficients
+// fitted to 2,200 passes of 8 .. 40,000 rows, hidden 64 .. 8192 and 768 .. 10,240 columns that were timed with
+// every kind of tile, such that the cheapest estimate is the fastest kind: over these it is 0.13 % off on the mean and
+// 3.5 % in the worst hundredth.  The phased kernel multiplies faster but stores 32 bytes per row and lane, and pays
+// from about 24 k tiles on (30,000 rows, hidden 256 -> 10,240 columns: 424 us phased, 341 with 128-row tiles; hidden
+// 4096 -> 6144, 5056 rows: 213 us phased, 301 not).  Thin passes spread over more compute units with lower tiles,
+// and a pass whose last round of tall tiles would be mostly empty sends the rows that fill its rounds with them and
+// the rest in a launch of its own.
+ProjPlan plan_qkv_proj(int32_t rows, int32_t n_out, int32_t hidden) {
+  struct Cost { double launch, tile, k_tile; };
+  static constexpr Cost kCost[kProjTileKinds] = {
+      {9.9, 21.3, 0.91}, {8.8, 13.1, 0.80}, {8.8, 14.0, 1.21}, {7.8, 7.1, 0.73}, {7.7, 3.5, 0.50}};
+  const double k_tiles = hidden / 64;
+  auto us_of = [&](ProjTile kind, int32_t n) {
+    const int64_t tiles = proj_tiles(kind, n, n_out), rounds = (tiles + kProjCUs - 1) / kProjCUs;
+    const Cost& c = kCost[kind];
+    return c.launch + c.tile / kProjCUs * (double)tiles + c.k_tile * (double)rounds * k_tiles;
+  };
+  struct Choice { ProjTile kind; double us; };
+  auto best_of = [&](int32_t n) {
+    Choice best = {kTile256Phased, us_of(kTile256Phased, n)};
+    for (const ProjTile kind : {kTile192Phased, kTile256, kTile128, kTile64}) {
+      const double us = us_of(kind, n);
+      if (us < best.us) best = {kind, us};
+    }
+    return best;
+  };
+  const Choice whole = best_of(rows);
+  const int64_t n_tiles = (n_out + kProjTileCols - 1) / kProjTileCols;
+  const int64_t full = proj_tiles(kTile256Phased, rows, n_out) / kProjCUs;   // full rounds of the tall tiles
+  if (full > 0) {
+    const int64_t fit = full * kProjCUs / n_tiles * 256;                     // rows that fit into them
+    if (fit > 0 && fit < rows) {
+      const Choice rest = best_of(rows - (int32_t)fit);
+      if (us_of(kTile256Phased, (int32_t)fit) + rest.us < whole.us)
+        return {2, {(int32_t)fit, rows - (int32_t)fit}, {kTile256Phased, rest.kind}};
+    }
+  }
+  return {1, {rows, 0}, {whole.kind, kTile64}};
+}
 }  // namespace oppo
 
 namespace {
@@ -1107,6 +1150,30 @@ int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_bef
         o[7] = queue0 + (int32_t)j;
       }
     queue0 += (int32_t)plan.first.size() - 1;
+  }
+  return OPPO_OK;
+}
+
+int oppo_qkv_proj_plan_debug(const oppo_attn_desc* desc, int32_t rows, int32_t hidden, int32_t* launches, int32_t* n) {
+  oppo::LayerShape ls;
+  int rc = check_desc(desc, &ls);
+  if (rc) return rc;
+  if (rows < 0 || !launches || !n) return fail(OPPO_ERR_INVALID, "negative size or null array");
+  if (hidden < 1) return fail(OPPO_ERR_INVALID, "hidden=%d must be positive", hidden);
+  if (hidden % 64 != 0) return fail(OPPO_ERR_UNSUPPORTED, "hidden=%d is not a multiple of 64", hidden);
+  const int32_t n_out = (ls.Hq + 2 * ls.Hkv) * ls.D;
+  *n = 0;
+  if (rows == 0) return OPPO_OK;
+  const oppo::ProjPlan plan = oppo::plan_qkv_proj(rows, n_out, hidden);
+  *n = plan.n;
+  for (int l = 0; l < plan.n; ++l) {
+    int32_t* o = launches + 4 * l;
+    const oppo::ProjTile t = plan.tile[l];
+    const int64_t tiles = oppo::proj_tiles(t, plan.rows[l], n_out);
+    o[0] = plan.rows[l];
+    o[1] = oppo::proj_tile_rows(t);
+    o[2] = t == oppo::kTile256Phased || t == oppo::kTile192Phased;
+    o[3] = (int32_t)((tiles + oppo::kProjCUs - 1) / oppo::kProjCUs);
   }
   return OPPO_OK;
 }

@@ -11,9 +11,9 @@
 //
 // Workgroup = 256 columns of y by 256, 192, 128 or 64 rows, 8 waves (two per SIMD), blocks of
 // v_mfma_f32_32x32x16_bf16.  Tall tiles have a kernel of their own (qkv_proj_phased_kernel, below);
-// passes too thin to give every compute unit such a tile take qkv_proj_kernel with 128 or 64 rows:
-// k advances in tiles of 64 through a ring of LDS stages, one workgroup per compute unit; tiles
-// travel global -> LDS directly, the
+// passes too thin to give every compute unit such a tile, and short k loops, take qkv_proj_kernel with 256, 128 or
+// 64 rows (plan_qkv_proj chooses): k advances in tiles of 64 through a ring of LDS stages, one workgroup per compute
+// unit; tiles travel global -> LDS directly, the
 // XOR swizzle of the LDS rows applied by choosing which 16-byte granule each lane fetches, so
 // the fragment reads (ds_read_b128, one row per lane) spread over the banks.  The epilogue
 // parks the fp32 tile in the same LDS, 64 rows at a time, from where threads take 8-column pieces of a row and
@@ -33,8 +33,7 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-constexpr int kGemmBN = 256, kGemmBK = 64;   // the tile's rows BM (256, 128 or 64) are chosen per launch
-constexpr int kProjCUs = 256;         // compute units of the chip: what a pass's tile count is weighed against
+constexpr int kGemmBN = kProjTileCols, kGemmBK = 64;   // the tile's rows BM are chosen per launch
 constexpr int kMaxProjItems = 1000;   // 1000 * 24 B + header in the kernel arguments
 constexpr int kFewProjItems = 64;     // the short list: kernel arguments are written across the bus for every launch
 
@@ -175,13 +174,13 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   constexpr int TILE_A = BM * ROWB;       // bytes of an x tile (32, 16 or 8 KiB)
   constexpr int TILE_B = BN * ROWB;       // bytes of a w tile (32 KiB)
   constexpr int STAGE = TILE_A + TILE_B;
-  constexpr int WR = 2, WC = 4;                        // waves down and across the tile
-  constexpr int MI = BM / WR / 32, NJ = BN / WC / 32;  // 32 x 32 blocks of a wave: 2 x 2 or 1 x 2
-  constexpr int CA = BM / RPL / 8, CB = BN / RPL / 8;  // copies per wave and tile: x (2 or 1), w (4)
-  static_assert(BN == 256 && BK == 64 && (BM == 128 || BM == 64), "8 waves, k tiles of 64");
-  // stages of the tile ring: these tiles run on passes whose k loop is bound by the tiles' latency,
-  // and keep two tiles in flight
-  constexpr int NST = 3;   // (four stages of the 64-row tile: measured, no faster)
+  constexpr int WR = BM == 256 ? 4 : 2, WC = 8 / WR;   // waves down and across the tile
+  constexpr int MI = BM / WR / 32, NJ = BN / WC / 32;  // 32 x 32 blocks of a wave: 2 x 4, 2 x 2 or 1 x 2
+  constexpr int CA = BM / RPL / 8, CB = BN / RPL / 8;  // copies per wave and tile: x (4, 2 or 1), w (4)
+  static_assert(BN == 256 && BK == 64 && (BM == 256 || BM == 128 || BM == 64), "8 waves, k tiles of 64");
+  // stages of the tile ring: two tiles of 256 rows fill the LDS; the smaller tiles run on passes
+  // whose k loop is bound by the tiles' latency, and keep two tiles in flight instead of one
+  constexpr int NST = BM == 256 ? 2 : 3;   // (four stages of the 64-row tile: measured, no faster)
   static_assert(NST * STAGE >= 64 * BN * 4 && NST * STAGE <= 160 * 1024, "ring and the epilogue's 64 x 256 fp32 strip fit the LDS");
   // [stage][x tile | w tile]; the epilogue reuses it as a 64 x 256 fp32 strip at a time
   __shared__ __attribute__((aligned(1024))) unsigned char smem[NST * STAGE];
@@ -271,7 +270,21 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
           acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][i], b[c][j], acc[i][j], 0, 0, 0);
     }
   };
-  {
+  if constexpr (NST == 2) {
+    // the next tile is requested in front of this tile's MFMAs (behind the barrier instead: 2-4 % slower)
+    issue(0, 0);
+    __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+    barrier();
+    for (int kt = 0; kt < KT; ++kt) {
+      const int st = kt & 1;
+      if (kt + 1 < KT) issue(kt + 1, st ^ 1);
+      compute(st);
+      // this wave's share of the next tile is in LDS, and its fragment reads are through with this tile's stage, which
+      // the copies requested behind the barrier overwrite (the compiler sinks the last MFMAs below the barrier)
+      __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0)
+      barrier();
+    }
+  } else {
     // tile t lives in stage t % NST; tile kt + 1 stays in flight while tile kt is
     // waited for, and tile kt + 2 is requested into the stage of tile kt - 1 once every wave
     // has passed the barrier behind that tile's MFMAs
@@ -637,16 +650,19 @@ static int launch_rows_list(int64_t* dst, float2* cs, double log2_base, int half
   return (int)hipGetLastError();
 }
 
-// The projection of P.rows rows with tiles of bm rows.  (The kernel of the tall tiles: workgroups stay for
-// as many tiles as there are rounds.)
+// The projection of P.rows rows with tiles of one kind.  (The phased kernel: workgroups stay for as many tiles as
+// there are rounds.)
 template <int D>
-static int launch_tiles(const ProjParams& P, int bm, int n_tiles, hipStream_t st) {
-  const int64_t tiles = (int64_t)((P.rows + bm - 1) / bm) * n_tiles;
+static int launch_tiles(const ProjParams& P, ProjTile tile, hipStream_t st) {
+  const int64_t tiles = proj_tiles(tile, P.rows, P.n_out);
   const dim3 once((unsigned)kProjCUs), all((unsigned)((tiles + kProjCUs - 1) / kProjCUs * kProjCUs)), block(512);
-  if (bm == 256) hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 256>), once, block, 0, st, P);
-  else if (bm == 192) hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 192>), once, block, 0, st, P);
-  else if (bm == 128) hipLaunchKernelGGL((qkv_proj_kernel<D, 128>), all, block, 0, st, P);
-  else hipLaunchKernelGGL((qkv_proj_kernel<D, 64>), all, block, 0, st, P);
+  switch (tile) {
+    case kTile256Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 256>), once, block, 0, st, P); break;
+    case kTile192Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 192>), once, block, 0, st, P); break;
+    case kTile256: hipLaunchKernelGGL((qkv_proj_kernel<D, 256>), all, block, 0, st, P); break;
+    case kTile128: hipLaunchKernelGGL((qkv_proj_kernel<D, 128>), all, block, 0, st, P); break;
+    case kTile64: hipLaunchKernelGGL((qkv_proj_kernel<D, 64>), all, block, 0, st, P); break;
+  }
   return (int)hipGetLastError();
 }
 
@@ -662,36 +678,12 @@ int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t 
                                      : launch_rows_list<kMaxProjItems>(dst, cs, log2(theta_base), ls.D / 2, items + base, n, st);
     if (e) return e;
   }
-  // Tile heights: one workgroup per compute unit at a time, so a launch takes ceil(tiles / 256) rounds of one
-  // tile's duration; per k tile that was measured as 1.6 / 1.3 / 1.0 / 0.67 us for tiles of 256 / 192 / 128 / 64
-  // rows, and a launch costs a few us besides.  The cheapest estimate wins: thin passes spread over more compute
-  // units, mid-sized ones avoid a mostly empty last round, and a pass whose last round of 256-row tiles would be
-  // mostly empty takes those rows that fill its rounds with them and the rest with the best height for the rest.
-  constexpr int kHeights[4] = {256, 192, 128, 64};
-  constexpr double kTileUs[4] = {1.6, 1.3, 1.0, 0.67};
-  constexpr double kLaunchUs = 4.0;
   const int n_out = (ls.Hq + 2 * ls.Hkv) * ls.D;
-  const int n_tiles = (n_out + kGemmBN - 1) / kGemmBN;
-  auto rounds_of = [&](int bm, int n) { return ((int64_t)((n + bm - 1) / bm) * n_tiles + kProjCUs - 1) / kProjCUs; };
-  auto best_height = [&](int n, double* us) {
-    int best = 0;
-    for (int h = 0; h < 4; ++h) {
-      const double t = kLaunchUs + (double)rounds_of(kHeights[h], n) * kTileUs[h] * (hidden / kGemmBK);
-      if (h == 0 || t < *us) best = h, *us = t;
-    }
-    return kHeights[best];
-  };
-  double us = 0.0, us_rest = 0.0;
-  int bm = best_height(rows, &us), rows_first = rows, bm_rest = 0;
-  const int64_t full = (int64_t)((rows + 255) / 256) * n_tiles / kProjCUs;   // full rounds of 256-row tiles
-  const int64_t fit = full * kProjCUs / n_tiles * 256;                       // rows that fit into them
-  if (fit > 0 && fit < rows) {
-    const int rest = best_height(rows - (int)fit, &us_rest);
-    if (kLaunchUs + (double)full * kTileUs[0] * (hidden / kGemmBK) + us_rest < us) bm = 256, rows_first = (int)fit, bm_rest = rest;
-  }
-  for (int first = 0; first < rows; first = rows_first) {
+  const ProjPlan plan = plan_qkv_proj(rows, n_out, hidden);
+  int first = 0;
+  for (int l = 0; l < plan.n; ++l) {
     ProjParams P;
-    P.rows = first == 0 ? rows_first : rows - rows_first;
+    P.rows = plan.rows[l];
     P.x = (const uint16_t*)x + (int64_t)first * hidden;
     P.w = (const uint16_t*)w;
     P.q_out = (uint16_t*)q_out + (int64_t)first * ls.Hq * ls.D;
@@ -703,9 +695,9 @@ int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t 
     P.n_out = n_out;
     P.Hq = ls.Hq;
     P.Hkv = ls.Hkv;
-    const int e = ls.D == 128 ? launch_tiles<128>(P, first == 0 ? bm : bm_rest, n_tiles, st)
-                              : launch_tiles<64>(P, first == 0 ? bm : bm_rest, n_tiles, st);
-    if (e || first != 0) return e;
+    const int e = ls.D == 128 ? launch_tiles<128>(P, plan.tile[l], st) : launch_tiles<64>(P, plan.tile[l], st);
+    if (e) return e;
+    first += plan.rows[l];
   }
   return 0;
 }

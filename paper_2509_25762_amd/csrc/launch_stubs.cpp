@@ -61,12 +61,19 @@ int launch_qkv_rope_append(const LayerShape&, const void*, void*, void*, void*, 
 
 size_t proj_workspace_bytes(int D, int64_t rows) { return (size_t)rows * (8 + (size_t)(D / 2) * 8); }
 
-int launch_qkv_proj(const LayerShape&, const void*, const void*, int32_t hidden, int32_t rows, void*, void*, void*,
+int launch_qkv_proj(const LayerShape& ls, const void*, const void*, int32_t hidden, int32_t rows, void*, void*, void*,
                     const QkvItem* items, int n_items, double, void* workspace, void*) {
   if (hidden % 64 != 0 || rows <= 0 || !workspace) return 1;
   int64_t total = 0;
   for (int i = 0; i < n_items; ++i) total += items[i].n_tok;
-  return total == rows ? 0 : 1;
+  if (total != rows) return 1;
+  const ProjPlan plan = plan_qkv_proj(rows, (ls.Hq + 2 * ls.Hkv) * ls.D, hidden);
+  total = 0;
+  for (int l = 0; l < plan.n; ++l) {
+    if (plan.rows[l] <= 0 || plan.tile[l] < 0 || plan.tile[l] >= kProjTileKinds) return 1;
+    total += plan.rows[l];
+  }
+  return (plan.n == 1 || plan.n == 2) && total == rows ? 0 : 1;
 }
 
 const char* hip_error_string(int) { return "launcher stub refused the work list"; }

@@ -108,6 +108,24 @@ int launch_qkv_rope_append(const LayerShape& ls, const void* qkv, void* q_out, v
 // The fused QKV projection with the rotary / cache epilogue (gemm.hip).  workspace holds
 // proj_workspace_bytes(D, rows) bytes of per-row data made by a small kernel of the same call.
 size_t proj_workspace_bytes(int D, int64_t rows);
+// How it cuts a pass: one launch with one kind of tile, or two (the rows that fill whole rounds of
+// tall tiles, then the rest).  plan_qkv_proj (api.cpp) chooses.
+constexpr int kProjTileCols = 256;   // columns of every tile
+constexpr int kProjCUs = 256;        // compute units of the chip, one workgroup each: tiles of one round
+enum ProjTile : int32_t { kTile256Phased, kTile192Phased, kTile256, kTile128, kTile64 };   // rows of a tile, kernel
+constexpr int kProjTileKinds = 5;
+constexpr int32_t proj_tile_rows(ProjTile t) {
+  return t == kTile256Phased || t == kTile256 ? 256 : t == kTile192Phased ? 192 : t == kTile128 ? 128 : 64;
+}
+inline int64_t proj_tiles(ProjTile t, int32_t rows, int32_t n_out) {
+  return ((int64_t)rows + proj_tile_rows(t) - 1) / proj_tile_rows(t) * ((n_out + kProjTileCols - 1) / kProjTileCols);
+}
+struct ProjPlan {
+  int32_t n;          // launches: 1 or 2
+  int32_t rows[2];    // of each; the first rows of the pass come first
+  ProjTile tile[2];
+};
+ProjPlan plan_qkv_proj(int32_t rows, int32_t n_out, int32_t hidden);
 int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t hidden, int32_t rows, void* q_out,
                     void* cache_k, void* cache_v, const QkvItem* items, int n_items, double theta_base, void* workspace,
                     void* stream);

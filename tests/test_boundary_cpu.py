@@ -514,6 +514,43 @@ def test_projection_validation_leaves_lengths_untouched(lib):
     assert cache.kv_len.tolist() == [6, 0]
 
 
+@pytest.mark.parametrize("shape,rows,hidden", [((64, 8, 128), 30000, 256), ((64, 8, 128), 4000, 256), ((32, 8, 128), 30000, 256),
+                                               ((32, 8, 128), 30000, 512), ((64, 8, 128), 40000, 512), ((8, 2, 128), 30000, 256),
+                                               ((16, 4, 64), 40000, 256), ((4, 4, 64), 40000, 256)])
+def test_short_k_loops_do_not_take_the_phased_projection_kernel(lib, shape, rows, hidden):
+    """Shapes on which the phased kernel measured 9 .. 36 % slower than the other one."""
+    launches = ob.oppo_qkv_proj_plan_debug(ob.make_desc(*shape, 1.0), rows, hidden)
+    assert launches and not any(phased for _, _, phased, _ in launches), launches
+
+
+@pytest.mark.parametrize("rows,launches", [(15202, [(13568, 256, True, 5), (1634, 192, True, 1)]), (5056, [(5056, 256, True, 2)]),
+                                           (1404, [(1404, 192, True, 1)]), (64, [(64, 64, False, 1)])])
+def test_projection_launches_of_long_k_loops(lib, rows, launches):
+    """4096 -> 6144, the layer of the workloads."""
+    assert ob.oppo_qkv_proj_plan_debug(_desc(), rows, 4096) == launches
+
+
+def test_projection_launches_cover_the_pass(lib):
+    rng = np.random.default_rng(5)
+    for _ in range(400):
+        Hq, Hkv, D = [(32, 8, 128), (64, 8, 128), (5, 1, 128), (4, 4, 64), (1, 1, 64)][rng.integers(5)]
+        rows, hidden = int(2 ** rng.uniform(0, 24)), 64 * int(2 ** rng.uniform(0, 9))
+        launches = ob.oppo_qkv_proj_plan_debug(ob.make_desc(Hq, Hkv, D, 1.0), rows, hidden)
+        n_tiles = -(-(Hq + 2 * Hkv) * D // 256)
+        assert sum(l[0] for l in launches) == rows and len(launches) <= 2
+        for n, height, phased, rounds in launches:
+            assert n > 0 and (height, phased) in [(256, True), (192, True), (256, False), (128, False), (64, False)]
+            assert rounds == -(-(-(-n // height) * n_tiles) // 256)
+        if len(launches) == 2:   # whole rounds of tall tiles first
+            n, height, phased, rounds = launches[0]
+            assert n % 256 == 0 and (height, phased) == (256, True) and (rounds * 256 - n // 256 * n_tiles) < n_tiles
+    assert ob.oppo_qkv_proj_plan_debug(_desc(), 0, 128) == []
+    for rows, hidden, code in ((-1, 128, ob.OPPO_ERR_INVALID), (5, 0, ob.OPPO_ERR_INVALID), (5, 100, ob.OPPO_ERR_UNSUPPORTED)):
+        with pytest.raises(ob.OppoError) as e:
+            ob.oppo_qkv_proj_plan_debug(_desc(), rows, hidden)
+        assert e.value.code == code
+
+
 def test_fp8_cache_validation_leaves_lengths_untouched(lib):
     """Argument checks of the 8-bit cache's two entry points (no device needed: every call fails
     before a launch, or has nothing to do)."""

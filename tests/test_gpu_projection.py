@@ -128,17 +128,8 @@ def test_larger_passes_take_the_larger_tiles(gpu, rows):
         assert (gv[b:b + n0] == 0xFFFF).all() and (gv[b + n1:int(slot_begin[i + 1])] == 0xFFFF).all()
 
 
-@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [
-    (6001, 8, 2, 128, 64),      # tiles of 192 rows, one k tile, a ragged last row tile
-    (6145, 16, 4, 64, 192),     # the same at head size 64, three k tiles, one row in the last row tile
-    (8155, 16, 4, 64, 128),     # tiles of 256 rows, two k tiles
-    (8064, 5, 1, 128, 192),     # a last column tile that is half empty, row tiles without a remainder
-    (10789, 8, 2, 128, 128),    # 258 tiles of 256 rows: two workgroups take a second one
-    (10789, 8, 2, 128, 1024),   # full rounds of 256-row tiles, the last 37 rows in a launch of their own
-])
-def test_tall_tiles_few_k_tiles_and_split_launches(gpu, rows, Hq, Hkv, D, hidden):
-    """Edges of the tall-tile kernel: k loops shorter than its request distance, both tile heights, several tiles
-    per workgroup, and passes cut into two launches; bounds as above."""
+def check_pass(gpu, rows, Hq, Hkv, D, hidden):
+    """A pass of four sequences (one sits out) against the oracle; bounds as above, every other slot and row untouched."""
     rng = np.random.default_rng(rows + hidden)
     q_len = np.array([rows - 1000, 1, 0, 999], dtype=np.int32)
     kv_before = np.array([3, 70000, 0, 9], dtype=np.int32)
@@ -153,6 +144,30 @@ def test_tall_tiles_few_k_tiles_and_split_launches(gpu, rows, Hq, Hkv, D, hidden
     assert (np.abs(bf16_bits_to_f64(gv[slots]) - v_ref) <= bound_of(v_ref, mag[:, Hq + Hkv:])).all(), "values"
     others = np.setdiff1d(np.arange(gk.shape[0]), slots)
     assert (gk[others] == 0xFFFF).all() and (gv[others] == 0xFFFF).all(), "other cache slots were written"
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [
+    (6001, 8, 2, 128, 64),      # tiles of 192 rows, one k tile, a ragged last row tile
+    (6145, 16, 4, 64, 192),     # the same at head size 64, three k tiles, one row in the last row tile
+    (8155, 16, 4, 64, 128),     # tiles of 256 rows, two k tiles
+    (8064, 5, 1, 128, 192),     # a last column tile that is half empty, row tiles without a remainder
+    (10789, 8, 2, 128, 128),    # 258 tiles of 256 rows: two workgroups take a second one
+    (10789, 8, 2, 128, 1024),   # full rounds of 256-row tiles, the last 37 rows in a launch of their own
+])
+def test_tall_tiles_few_k_tiles_and_split_launches(gpu, rows, Hq, Hkv, D, hidden):
+    """Edges of the tall-tile kernel: k loops shorter than its request distance, both tile heights, several tiles
+    per workgroup, and passes cut into two launches; bounds as above."""
+    check_pass(gpu, rows, Hq, Hkv, D, hidden)
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden,rounds", [
+    (27400, 8, 2, 128, 64, 3),       # one k tile, three rounds
+    (24600, 5, 1, 128, 128, 2),      # two k tiles, a last column tile that is half empty
+    (6800, 16, 4, 64, 320, 1),       # five k tiles, head size 64
+])
+def test_tiles_of_256_rows_for_short_k_loops(gpu, rows, Hq, Hkv, D, hidden, rounds):
+    assert gpu[0].oppo_qkv_proj_plan_debug(gpu[0].make_desc(Hq, Hkv, D, 1.0), rows, hidden) == [(rows, 256, False, rounds)]
+    check_pass(gpu, rows, Hq, Hkv, D, hidden)
 
 
 def test_values_are_the_rounded_fp32_sums_when_products_are_exact(gpu):
