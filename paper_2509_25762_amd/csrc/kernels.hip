@@ -1089,6 +1089,15 @@ static void prof_end(int pair, hipStream_t st) {
   (void)hipEventRecord(g_prof_events[(size_t)pair].b, st);
   g_prof_events[(size_t)pair].closed = true;
 }
+// One launch, and nothing else, between the two events (kind < 0: not timed): the arguments are filled in before, and
+// what is refused before its launch leaves no pair behind.
+template <typename Kernel, typename Params>
+static int launch_timed(int kind, Kernel kernel, dim3 grid, dim3 block, hipStream_t st, const Params& P) {
+  const int pair = kind >= 0 ? prof_begin(kind, st) : -1;
+  hipLaunchKernelGGL(kernel, grid, block, 0, st, P);
+  prof_end(pair, st);
+  return (int)hipGetLastError();
+}
 int profile_enable(int on) {
   std::lock_guard<std::mutex> lock(g_prof_mu);
   g_prof_on = on != 0;
@@ -1161,7 +1170,7 @@ int static_scratch(void** ptr) {
 
 template <int NI>
 static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool append, const AttnItem* items, int n_items,
-                                 const uint16_t* first, int n_queues, hipStream_t st) {
+                                 const uint16_t* first, int n_queues, hipStream_t st, int kind) {
   if (n_items > NI || n_queues > n_items) return (int)hipErrorInvalidValue;
   AttnParams<NI> P;
   static_cast<AttnFields&>(P) = F;
@@ -1171,16 +1180,14 @@ static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool
   if (ls.fp8) {
     // (the 8-bit cache is filled by its own append kernel)
     if (append) return (int)hipErrorInvalidValue;
-    if (ls.D == 128) hipLaunchKernelGGL((attn_fwd_fp8_kernel<128, NI>), grid, block, 0, st, P);
-    else hipLaunchKernelGGL((attn_fwd_fp8_kernel<64, NI>), grid, block, 0, st, P);
-  } else if (ls.D == 128) {
-    if (append) hipLaunchKernelGGL((attn_fwd_kernel<128, true, NI>), grid, block, 0, st, P);
-    else hipLaunchKernelGGL((attn_fwd_kernel<128, false, NI>), grid, block, 0, st, P);
-  } else {
-    if (append) hipLaunchKernelGGL((attn_fwd_kernel<64, true, NI>), grid, block, 0, st, P);
-    else hipLaunchKernelGGL((attn_fwd_kernel<64, false, NI>), grid, block, 0, st, P);
+    return ls.D == 128 ? launch_timed(kind, attn_fwd_fp8_kernel<128, NI>, grid, block, st, P)
+                       : launch_timed(kind, attn_fwd_fp8_kernel<64, NI>, grid, block, st, P);
   }
-  return (int)hipGetLastError();
+  if (ls.D == 128)
+    return append ? launch_timed(kind, attn_fwd_kernel<128, true, NI>, grid, block, st, P)
+                  : launch_timed(kind, attn_fwd_kernel<128, false, NI>, grid, block, st, P);
+  return append ? launch_timed(kind, attn_fwd_kernel<64, true, NI>, grid, block, st, P)
+                : launch_timed(kind, attn_fwd_kernel<64, false, NI>, grid, block, st, P);
 }
 
 int launch_attention(const LayerShape& ls, const void* q, void* k, void* v, const void* k_new, const void* v_new,
@@ -1217,17 +1224,16 @@ int launch_attention(const LayerShape& ls, const void* q, void* k, void* v, cons
   }
   F.n_queues = n_queues;
   F.g_magic = (65536u + (uint32_t)ls.G - 1u) / (uint32_t)ls.G;
-  const int pair = timed ? prof_begin(0, st) : -1;
-  const int rc = n_items <= kFewAttnItems
-                     ? launch_attention_list<kFewAttnItems>(ls, F, k_new != nullptr, items, n_items, first, n_queues, st)
-                     : launch_attention_list<kMaxAttnItems>(ls, F, k_new != nullptr, items, n_items, first, n_queues, st);
-  prof_end(pair, st);
-  return rc;
+  const bool append = k_new != nullptr;
+  const int kind = timed ? 0 : -1;
+  return n_items <= kFewAttnItems
+             ? launch_attention_list<kFewAttnItems>(ls, F, append, items, n_items, first, n_queues, st, kind)
+             : launch_attention_list<kMaxAttnItems>(ls, F, append, items, n_items, first, n_queues, st, kind);
 }
 
 template <int NI>
 static int launch_combine_list(const LayerShape& ls, void* out, const float* part_o, const float* part_ml,
-                               const CombineItem* items, int n, hipStream_t st) {
+                               const CombineItem* items, int n, hipStream_t st, int kind) {
   CombineParams<NI> P;
   P.out = (uint16_t*)out;
   P.part_o = part_o;
@@ -1244,16 +1250,13 @@ static int launch_combine_list(const LayerShape& ls, void* out, const float* par
   const dim3 grid((unsigned)(n * ls.Hkv), (unsigned)(kTileRows / rpb)), block(256);
   int max_split = 0;
   for (int i = 0; i < n; ++i) max_split = items[i].nsplit > max_split ? items[i].nsplit : max_split;
-  if (ls.D == 128) {
-    if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<128, 4, NI>), grid, block, 0, st, P);
-    else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<128, 8, NI>), grid, block, 0, st, P);
-    else hipLaunchKernelGGL((combine_kernel<128, kMaxSplit, NI>), grid, block, 0, st, P);
-  } else {
-    if (max_split <= 4) hipLaunchKernelGGL((combine_kernel<64, 4, NI>), grid, block, 0, st, P);
-    else if (max_split <= 8) hipLaunchKernelGGL((combine_kernel<64, 8, NI>), grid, block, 0, st, P);
-    else hipLaunchKernelGGL((combine_kernel<64, kMaxSplit, NI>), grid, block, 0, st, P);
-  }
-  return (int)hipGetLastError();
+  if (ls.D == 128)
+    return max_split <= 4   ? launch_timed(kind, combine_kernel<128, 4, NI>, grid, block, st, P)
+           : max_split <= 8 ? launch_timed(kind, combine_kernel<128, 8, NI>, grid, block, st, P)
+                            : launch_timed(kind, combine_kernel<128, kMaxSplit, NI>, grid, block, st, P);
+  return max_split <= 4   ? launch_timed(kind, combine_kernel<64, 4, NI>, grid, block, st, P)
+         : max_split <= 8 ? launch_timed(kind, combine_kernel<64, 8, NI>, grid, block, st, P)
+                          : launch_timed(kind, combine_kernel<64, kMaxSplit, NI>, grid, block, st, P);
 }
 
 int launch_combine(const LayerShape& ls, void* out, const float* part_o, const float* part_ml,
@@ -1261,10 +1264,9 @@ int launch_combine(const LayerShape& ls, void* out, const float* part_o, const f
   hipStream_t st = (hipStream_t)stream;
   for (int base = 0; base < n_items; base += kMaxCombineItems) {
     const int n = n_items - base < kMaxCombineItems ? n_items - base : kMaxCombineItems;
-    const int pair = timed ? prof_begin(1, st) : -1;
-    const int e = n <= kFewItems ? launch_combine_list<kFewItems>(ls, out, part_o, part_ml, items + base, n, st)
-                                 : launch_combine_list<kMaxCombineItems>(ls, out, part_o, part_ml, items + base, n, st);
-    prof_end(pair, st);
+    const int kind = timed ? 1 : -1;
+    const int e = n <= kFewItems ? launch_combine_list<kFewItems>(ls, out, part_o, part_ml, items + base, n, st, kind)
+                                 : launch_combine_list<kMaxCombineItems>(ls, out, part_o, part_ml, items + base, n, st, kind);
     if (e) return e;
   }
   return 0;
@@ -1286,8 +1288,7 @@ static int launch_append_list(const LayerShape& ls, void* cache_k, void* cache_v
     if (items[i].n_tok > mt) mt = items[i].n_tok;
   }
   const dim3 grid((unsigned)n, (unsigned)((mt + kAppendTok - 1) / kAppendTok), 2), block(256);
-  hipLaunchKernelGGL(kv_append_kernel<NI>, grid, block, 0, st, P);
-  return (int)hipGetLastError();
+  return launch_timed(2, kv_append_kernel<NI>, grid, block, st, P);
 }
 
 int launch_append(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new,
@@ -1296,10 +1297,8 @@ int launch_append(const LayerShape& ls, void* cache_k, void* cache_v, const void
   (void)max_tok;
   for (int base = 0; base < n_items; base += kMaxAppendItems) {
     const int n = n_items - base < kMaxAppendItems ? n_items - base : kMaxAppendItems;
-    const int pair = prof_begin(2, st);
     const int e = n <= kFewItems ? launch_append_list<kFewItems>(ls, cache_k, cache_v, k_new, v_new, items + base, n, st)
                                  : launch_append_list<kMaxAppendItems>(ls, cache_k, cache_v, k_new, v_new, items + base, n, st);
-    prof_end(pair, st);
     if (e) return e;
   }
   return 0;
@@ -1326,9 +1325,8 @@ static int launch_append_fp8_list(const LayerShape& ls, void* cache_k, void* cac
   }
   if (blocks > 65535) return (int)hipErrorInvalidValue;
   const dim3 grid((unsigned)n, (unsigned)blocks, (unsigned)ls.Hkv);
-  if (ls.D == 128) hipLaunchKernelGGL((kv_append_fp8_kernel<128, NI>), grid, dim3(256), 0, st, P);
-  else hipLaunchKernelGGL((kv_append_fp8_kernel<64, NI>), grid, dim3(128), 0, st, P);
-  return (int)hipGetLastError();
+  return ls.D == 128 ? launch_timed(2, kv_append_fp8_kernel<128, NI>, grid, dim3(256), st, P)
+                     : launch_timed(2, kv_append_fp8_kernel<64, NI>, grid, dim3(128), st, P);
 }
 
 int launch_append_fp8(const LayerShape& ls, void* cache_k, void* cache_v, const void* k_new, const void* v_new,
@@ -1337,11 +1335,9 @@ int launch_append_fp8(const LayerShape& ls, void* cache_k, void* cache_v, const 
   if (ls.D != 128 && ls.D != 64) return (int)hipErrorInvalidValue;
   for (int base = 0; base < n_items; base += kMaxAppendItems) {
     const int n = n_items - base < kMaxAppendItems ? n_items - base : kMaxAppendItems;
-    const int pair = prof_begin(2, st);
     const int e = n <= kFewItems
                       ? launch_append_fp8_list<kFewItems>(ls, cache_k, cache_v, k_new, v_new, k_inv, v_inv, items + base, n, st)
                       : launch_append_fp8_list<kMaxAppendItems>(ls, cache_k, cache_v, k_new, v_new, k_inv, v_inv, items + base, n, st);
-    prof_end(pair, st);
     if (e) return e;
   }
   return 0;

@@ -341,3 +341,19 @@ def test_full_size_small_chunk_workload_through_the_8_bit_cache(gpu):
     err = np.concatenate(errs)
     print(f"config 3 through the 8-bit cache: {err.size} sampled elements, max abs {err.max():.3e} mean abs {err.mean():.3e}", flush=True)
     assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
+
+
+def test_a_refused_append_is_not_counted_as_a_launch(gpu):
+    """A run of more 64-token blocks than a grid has is refused before its launch: no duration is recorded for it."""
+    binding, _, _ = gpu
+    n = 65536 * 64
+    cache = binding.KVCacheFp8(0x1000, 0x2000, np.array([0, n]), 0.01, 0.01)   # (the addresses are never used)
+    binding.oppo_profile_enable(True)
+    try:
+        binding.oppo_profile_read()
+        with pytest.raises(binding.OppoError) as e:
+            binding.oppo_kv_append_fp8(binding.make_desc(1, 1, 64, 0.125), cache, [0, n], 0x3000, 0x4000)
+        assert e.value.code == binding.OPPO_ERR_HIP and cache.kv_len.tolist() == [0]
+        assert set(binding.oppo_profile_read()[1].values()) == {0}
+    finally:
+        binding.oppo_profile_enable(False)
