@@ -11,6 +11,7 @@ import pytest
 
 from oracle import chunk_schedule as oracle_schedule
 from paper_2509_25762_amd import binding as ob
+from test_gpu_projection import PASSES
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -521,6 +522,11 @@ def test_short_k_loops_do_not_take_the_phased_projection_kernel(lib, shape, rows
     """Shapes on which the phased kernel measured 9 .. 36 % slower than the other one."""
     launches = ob.oppo_qkv_proj_plan_debug(ob.make_desc(*shape, 1.0), rows, hidden)
     assert launches and not any(phased for _, _, phased, _ in launches), launches
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden,launches", PASSES)
+def test_projection_passes_take_the_launches_their_gpu_tests_are_for(lib, rows, Hq, Hkv, D, hidden, launches):
+    assert ob.oppo_qkv_proj_plan_debug(ob.make_desc(Hq, Hkv, D, 1.0), rows, hidden) == launches
 
 
 @pytest.mark.parametrize("rows,launches", [(15202, [(13568, 256, True, 5), (1634, 192, True, 1)]), (5056, [(5056, 256, True, 2)]),

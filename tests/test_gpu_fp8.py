@@ -343,6 +343,24 @@ def test_full_size_small_chunk_workload_through_the_8_bit_cache(gpu):
     assert err.max() <= MAX_ABS and err.mean() <= MEAN_ABS
 
 
+@pytest.mark.parametrize("B,D", [(64, 128), (65, 128), (64, 64), (65, 64), (96, 128), (97, 128), (96, 64), (97, 64)])
+def test_work_lists_on_either_side_of_the_short_lists(gpu, B, D):
+    """64 and 65 appended runs, 96 and 97 whole attention pieces: the largest passes that travel in the short lists of
+    the kernel arguments and the smallest ones in the long lists."""
+    binding, _, _ = gpu
+    ep = build_episode(Config(98, "fp8 lists", 60 + B, B, 4, 1, D, 3, ("uniform", 61, 141), ("fixed", 7)), threads=2)
+    ks, vs = amax_scale(ep.k), amax_scale(ep.v)
+    chunks = uniform_chunks(ep.prompt_len, ep.resp_len, 3)
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, 1)
+    try:
+        se = run_gpu(gpu, ep, chunks, ks, vs)
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+    cache, ref = oracle_run(ep, chunks, se.slot_begin, ks, vs)
+    check_codes(se, cache)
+    check_outputs(se, ref, f"fp8 lists B={B} D={D}")
+
+
 def test_a_refused_append_is_not_counted_as_a_launch(gpu):
     """A run of more 64-token blocks than a grid has is refused before its launch: no duration is recorded for it."""
     binding, _, _ = gpu

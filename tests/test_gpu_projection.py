@@ -4,8 +4,10 @@ against the oracle's projection -> rotation -> one-shot prefill.
 
 Tolerance of the projection: the kernel accumulates bf16 products in fp32 (MFMA), rotates in fp32 and
 rounds once to bf16, so |gpu - oracle| <= 2^-8 |oracle| (half a bf16 ulp at most) plus the fp32
-accumulation and rotation error, bounded by 2^-19 * sum_k |x_k| |w_k| of the columns involved
-(hidden <= 1024 here; a sum of n fp32-rounded terms is off by at most ~n 2^-24 of the sum of magnitudes).
+accumulation and rotation error, bounded by 2^-19 * sum_k |x_k| |w_k| of the columns involved: a sum over
+hidden takes N = hidden / 16 matrix instructions, each rounding a partial sum to within 2^-24 of itself; those of
+independent N(0, 1) terms stay below ~4.5 sqrt(16 i) against 10 N of the sum of magnitudes, so that even roundings
+which all point one way come to 1.2 sqrt(N) 2^-24 of it: 17 * 2^-24 at hidden 3072, the longest here, of 32 * 2^-24.
 Keys and values are compared where they land: in the cache, whose other slots must stay untouched."""
 import numpy as np
 import pytest
@@ -97,7 +99,7 @@ def test_projection_epilogue_matches_the_oracle_on_a_ragged_pass(gpu, Hq, Hkv, D
 @pytest.mark.parametrize("rows", [4091, 8155])
 def test_larger_passes_take_the_larger_tiles(gpu, rows):
     """The launch picks the tile height from the pass's size: 64 rows for the thin passes above, 128 rows for
-    ~4K rows x 6 column tiles and 256 rows for ~8K (the estimate in launch_qkv_proj); both with a ragged last
+    ~4K rows x 6 column tiles and 256 rows for ~8K (plan_qkv_proj chooses); both with a ragged last
     row tile and sequences of uneven length, against the oracle as above."""
     Hq, Hkv, D, hidden, base = 8, 2, 128, 256, 10000.0
     rng = np.random.default_rng(900 + rows)
@@ -128,11 +130,9 @@ def test_larger_passes_take_the_larger_tiles(gpu, rows):
         assert (gv[b:b + n0] == 0xFFFF).all() and (gv[b + n1:int(slot_begin[i + 1])] == 0xFFFF).all()
 
 
-def check_pass(gpu, rows, Hq, Hkv, D, hidden):
-    """A pass of four sequences (one sits out) against the oracle; bounds as above, every other slot and row untouched."""
-    rng = np.random.default_rng(rows + hidden)
-    q_len = np.array([rows - 1000, 1, 0, 999], dtype=np.int32)
-    kv_before = np.array([3, 70000, 0, 9], dtype=np.int32)
+def check_run(gpu, rng, Hq, Hkv, D, hidden, kv_before, q_len):
+    """A pass against the oracle, bounds as above; every other slot and row untouched."""
+    rows = int(q_len.sum())
     xb, wb, cu, slot_begin, cache, gq, gk, gv = run_projection(gpu, rng, Hq, Hkv, D, hidden, kv_before, q_len, 10000.0)
     q_ref, k_ref, v_ref = qkv_projection_rope(xb, wb, pass_positions(kv_before, q_len), Hq, Hkv, D, 10000.0)
     mag = (np.abs(bf16_bits_to_f64(xb)) @ np.abs(bf16_bits_to_f64(wb)).T).reshape(rows, Hq + 2 * Hkv, D)
@@ -146,28 +146,65 @@ def check_pass(gpu, rows, Hq, Hkv, D, hidden):
     assert (gk[others] == 0xFFFF).all() and (gv[others] == 0xFFFF).all(), "other cache slots were written"
 
 
-@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [
-    (6001, 8, 2, 128, 64),      # tiles of 192 rows, one k tile, a ragged last row tile
-    (6145, 16, 4, 64, 192),     # the same at head size 64, three k tiles, one row in the last row tile
-    (8155, 16, 4, 64, 128),     # tiles of 256 rows, two k tiles
-    (8064, 5, 1, 128, 192),     # a last column tile that is half empty, row tiles without a remainder
-    (10789, 8, 2, 128, 128),    # 258 tiles of 256 rows: two workgroups take a second one
-    (10789, 8, 2, 128, 1024),   # full rounds of 256-row tiles, the last 37 rows in a launch of their own
-])
-def test_tall_tiles_few_k_tiles_and_split_launches(gpu, rows, Hq, Hkv, D, hidden):
-    """Edges of the tall-tile kernel: k loops shorter than its request distance, both tile heights, several tiles
-    per workgroup, and passes cut into two launches; bounds as above."""
+def check_pass(gpu, rows, Hq, Hkv, D, hidden):
+    """... of four sequences, one of which sits out."""
+    check_run(gpu, np.random.default_rng(rows + hidden), Hq, Hkv, D, hidden, np.array([3, 70000, 0, 9], dtype=np.int32),
+              np.array([rows - 1000, 1, 0, 999], dtype=np.int32))
+
+
+# Passes by the launches they have to take: (rows, Hq, Hkv, D, hidden, [(rows, tile rows, phased, rounds), ..]).
+# That the library still cuts them so is asserted here and, without a GPU, in test_boundary_cpu.py.
+PASSES = [
+    # tiles of 64 and 128 rows
+    (6001, 8, 2, 128, 64, [(6001, 64, False, 3)]),           # one k tile, a ragged last row tile
+    (6145, 16, 4, 64, 192, [(6145, 64, False, 3)]),          # one row in the last row tile
+    (8155, 16, 4, 64, 128, [(8155, 64, False, 3)]),
+    (8064, 5, 1, 128, 192, [(8064, 128, False, 1)]),         # a last column tile that is half empty, row tiles without a remainder
+    (10789, 8, 2, 128, 128, [(10789, 128, False, 2)]),
+    (10789, 8, 2, 128, 1024, [(10789, 128, False, 2)]),      # three stages of the ring, 16 k tiles, two rounds
+    # tiles of 256 rows for short k loops
+    (27400, 8, 2, 128, 64, [(27400, 256, False, 3)]),        # one k tile, three rounds
+    (24600, 5, 1, 128, 128, [(24600, 256, False, 2)]),       # two k tiles, a last column tile that is half empty
+    (6800, 16, 4, 64, 320, [(6800, 256, False, 1)]),         # five k tiles, head size 64
+    # the phased kernel with tiles of 192 rows: odd and even k tiles, counted waits on every one in the middle
+    (5617, 8, 2, 128, 320, [(5617, 192, True, 1)]),
+    (6001, 8, 2, 128, 576, [(6001, 192, True, 1)]),
+    (5521, 16, 4, 64, 512, [(5521, 192, True, 1)]),
+    (16600, 3, 1, 64, 320, [(16600, 192, True, 1)]),         # columns of one whole tile and a quarter
+    (8300, 5, 1, 128, 512, [(8300, 192, True, 1)]),          # ... of three and a half
+    (11041, 8, 2, 128, 512, [(11041, 192, True, 2)]),        # workgroups with a second tile
+    (11041, 16, 4, 64, 576, [(11041, 192, True, 2)]),
+    (16600, 5, 1, 128, 512, [(16600, 192, True, 2)]),        # ... and a half-empty column
+    # the phased kernel with tiles of 256 rows
+    (8155, 8, 2, 128, 1536, [(8155, 256, True, 1)]),
+    (8155, 16, 4, 64, 1600, [(8155, 256, True, 1)]),         # 25 k tiles
+    (12301, 5, 1, 128, 1536, [(12301, 256, True, 1)]),       # a half-empty column
+    (16600, 8, 2, 128, 1536, [(16600, 256, True, 2)]),       # workgroups with a second tile
+    (16600, 16, 4, 64, 1600, [(16600, 256, True, 2)]),
+    # passes cut into two launches: both heights and both kernels as the second
+    (3682, 64, 8, 128, 1536, [(3072, 256, True, 2), (610, 128, False, 1)]),
+    (5014, 64, 8, 128, 1536, [(4864, 256, True, 3), (150, 64, False, 1)]),
+    (5125, 33, 3, 128, 3072, [(3072, 256, True, 1), (2053, 192, True, 1)]),
+    (7937, 65, 5, 64, 1536, [(6656, 256, True, 2), (1281, 128, False, 1)]),
+    (5384, 65, 5, 64, 3072, [(3328, 256, True, 1), (2056, 192, True, 1)]),
+]
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden,launches", PASSES)
+def test_every_kind_of_tile_and_cut(gpu, rows, Hq, Hkv, D, hidden, launches):
+    assert gpu[0].oppo_qkv_proj_plan_debug(gpu[0].make_desc(Hq, Hkv, D, 1.0), rows, hidden) == launches
     check_pass(gpu, rows, Hq, Hkv, D, hidden)
 
 
-@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden,rounds", [
-    (27400, 8, 2, 128, 64, 3),       # one k tile, three rounds
-    (24600, 5, 1, 128, 128, 2),      # two k tiles, a last column tile that is half empty
-    (6800, 16, 4, 64, 320, 1),       # five k tiles, head size 64
-])
-def test_tiles_of_256_rows_for_short_k_loops(gpu, rows, Hq, Hkv, D, hidden, rounds):
-    assert gpu[0].oppo_qkv_proj_plan_debug(gpu[0].make_desc(Hq, Hkv, D, 1.0), rows, hidden) == [(rows, 256, False, rounds)]
-    check_pass(gpu, rows, Hq, Hkv, D, hidden)
+@pytest.mark.parametrize("B,Hq,Hkv,D,hidden", [(64, 3, 1, 128, 64), (65, 3, 1, 128, 64), (64, 4, 4, 64, 128), (65, 4, 4, 64, 128),
+                                               (1001, 2, 1, 64, 64)])
+def test_row_lists_on_either_side_of_their_limits(gpu, B, Hq, Hkv, D, hidden):
+    """64 sequences travel in the short list of the row kernel's arguments, 65 in the long one, 1001 in two of them;
+    1 .. 9 rows each (the row kernel takes 8 at a time), every third one up to 70,000 tokens in."""
+    rng = np.random.default_rng(B + D)
+    q_len = (1 + np.arange(B) % 9).astype(np.int32)
+    kv_before = ((np.arange(B) * 37) % 50 + (np.arange(B) % 3 == 0) * (70000 if B < 100 else 100)).astype(np.int32)
+    check_run(gpu, rng, Hq, Hkv, D, hidden, kv_before, q_len)
 
 
 def test_values_are_the_rounded_fp32_sums_when_products_are_exact(gpu):
