@@ -1172,7 +1172,7 @@ int oppo_qkv_proj_plan_debug(const oppo_attn_desc* desc, int32_t rows, int32_t h
     const int64_t tiles = oppo::proj_tiles(t, plan.rows[l], n_out);
     o[0] = plan.rows[l];
     o[1] = oppo::proj_tile_rows(t);
-    o[2] = t == oppo::kTile256Phased || t == oppo::kTile192Phased;
+    o[2] = oppo::proj_tile_phased(t);
     o[3] = (int32_t)((tiles + oppo::kProjCUs - 1) / oppo::kProjCUs);
   }
   return OPPO_OK;

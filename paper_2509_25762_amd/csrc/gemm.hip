@@ -570,7 +570,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     const int row_first = tile_m * BM + (ln & 31);
     const int head = tile_n * (BN / D) + (D == 128 ? wn >> 1 : wn);      // one head per wave
     const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 16 * (ln >> 5);      // the lane's first column of the head
-    block += (int)gridDim.x;
+    block += (int)gridDim.x;   // (past the last tile where every workgroup has one)
     const bool more = order.at(block, &tile_m, &tile_n);
     if (more) {
       open_tile();
@@ -650,18 +650,31 @@ static int launch_rows_list(int64_t* dst, float2* cs, double log2_base, int half
   return (int)hipGetLastError();
 }
 
-// The projection of P.rows rows with tiles of one kind.  (The phased kernel: workgroups stay for as many tiles as
-// there are rounds.)
+// Whether the stream may use every compute unit (the legacy stream has no mask; an error counts as yes).
+static bool has_whole_chip(hipStream_t st) {
+  if (!st) return true;
+  uint32_t mask[kProjCUs / 32] = {};
+  if (hipExtStreamGetCUMask(st, kProjCUs / 32, mask) != hipSuccess) {
+    (void)hipGetLastError();
+    return true;
+  }
+  int n = 0;
+  for (uint32_t m : mask) n += __builtin_popcount(m);
+  return n >= kProjCUs;
+}
+
+// The projection of P.rows rows with tiles of one kind.
 template <int D>
 static int launch_tiles(const ProjParams& P, ProjTile tile, hipStream_t st) {
   const int64_t tiles = proj_tiles(tile, P.rows, P.n_out);
-  const dim3 once((unsigned)kProjCUs), all((unsigned)((tiles + kProjCUs - 1) / kProjCUs * kProjCUs)), block(512);
+  const bool whole_chip = tiles <= kProjCUs || !proj_tile_phased(tile) || has_whole_chip(st);
+  const dim3 grid((unsigned)proj_workgroups(tile, tiles, whole_chip)), block(512);
   switch (tile) {
-    case kTile256Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 256>), once, block, 0, st, P); break;
-    case kTile192Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 192>), once, block, 0, st, P); break;
-    case kTile256: hipLaunchKernelGGL((qkv_proj_kernel<D, 256>), all, block, 0, st, P); break;
-    case kTile128: hipLaunchKernelGGL((qkv_proj_kernel<D, 128>), all, block, 0, st, P); break;
-    case kTile64: hipLaunchKernelGGL((qkv_proj_kernel<D, 64>), all, block, 0, st, P); break;
+    case kTile256Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 256>), grid, block, 0, st, P); break;
+    case kTile192Phased: hipLaunchKernelGGL((qkv_proj_phased_kernel<D, 192>), grid, block, 0, st, P); break;
+    case kTile256: hipLaunchKernelGGL((qkv_proj_kernel<D, 256>), grid, block, 0, st, P); break;
+    case kTile128: hipLaunchKernelGGL((qkv_proj_kernel<D, 128>), grid, block, 0, st, P); break;
+    case kTile64: hipLaunchKernelGGL((qkv_proj_kernel<D, 64>), grid, block, 0, st, P); break;
   }
   return (int)hipGetLastError();
 }

@@ -117,6 +117,7 @@ constexpr int kProjTileKinds = 5;
 constexpr int32_t proj_tile_rows(ProjTile t) {
   return t == kTile256Phased || t == kTile256 ? 256 : t == kTile192Phased ? 192 : t == kTile128 ? 128 : 64;
 }
+constexpr bool proj_tile_phased(ProjTile t) { return t == kTile256Phased || t == kTile192Phased; }
 inline int64_t proj_tiles(ProjTile t, int32_t rows, int32_t n_out) {
   return ((int64_t)rows + proj_tile_rows(t) - 1) / proj_tile_rows(t) * ((n_out + kProjTileCols - 1) / kProjTileCols);
 }
@@ -126,6 +127,13 @@ struct ProjPlan {
   ProjTile tile[2];
 };
 ProjPlan plan_qkv_proj(int32_t rows, int32_t n_out, int32_t hidden);
+// Workgroups of a launch.  The phased kernel's stay for a tile of every round, which is 2-3 % faster than one tile each
+// as long as all of them run at once.  Where a stream may use part of the chip only (a mask of compute units), the
+// workgroups that come second would start with all their tiles still to do: 30,000 rows, hidden 1536 -> 6144 on 224
+// compute units 900 us, with one tile per workgroup 637.
+inline int64_t proj_workgroups(ProjTile t, int64_t tiles, bool whole_chip) {
+  return whole_chip && proj_tile_phased(t) ? kProjCUs : (tiles + kProjCUs - 1) / kProjCUs * kProjCUs;
+}
 int launch_qkv_proj(const LayerShape& ls, const void* x, const void* w, int32_t hidden, int32_t rows, void* q_out,
                     void* cache_k, void* cache_v, const QkvItem* items, int n_items, double theta_base, void* workspace,
                     void* stream);

@@ -15,6 +15,7 @@
 #include <vector>
 
 #include "../include/oppo_attn.h"
+#include "../paper_2509_25762_amd/csrc/oppo_internal.h"
 
 static int g_failed = 0;
 #define CHECK(cond)                                                        \
@@ -269,8 +270,20 @@ static void pool_and_scheduler() {
   CHECK(oppo_sched_destroy(s) == OPPO_OK);
 }
 
+// A workgroup of the phased projection kernel stays for several tiles only where all workgroups run at once.
+static void projection_workgroups() {
+  using namespace oppo;
+  for (const ProjTile t : {kTile256Phased, kTile192Phased, kTile256, kTile128, kTile64})
+    for (const int64_t tiles : {(int64_t)1, (int64_t)255, (int64_t)256, (int64_t)257, (int64_t)1416, (int64_t)40000}) {
+      const int64_t rounded = (tiles + 255) / 256 * 256;
+      CHECK(proj_workgroups(t, tiles, false) == rounded);
+      CHECK(proj_workgroups(t, tiles, true) == (proj_tile_phased(t) ? 256 : rounded));
+    }
+}
+
 int main() {
   abi_errors();
+  projection_workgroups();
   fp8_cache_errors();
   planner_fuzz();
   pool_and_scheduler();

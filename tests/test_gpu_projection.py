@@ -9,6 +9,8 @@ hidden takes N = hidden / 16 matrix instructions, each rounding a partial sum to
 independent N(0, 1) terms stay below ~4.5 sqrt(16 i) against 10 N of the sum of magnitudes, so that even roundings
 which all point one way come to 1.2 sqrt(N) 2^-24 of it: 17 * 2^-24 at hidden 3072, the longest here, of 32 * 2^-24.
 Keys and values are compared where they land: in the cache, whose other slots must stay untouched."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -194,6 +196,34 @@ PASSES = [
 def test_every_kind_of_tile_and_cut(gpu, rows, Hq, Hkv, D, hidden, launches):
     assert gpu[0].oppo_qkv_proj_plan_debug(gpu[0].make_desc(Hq, Hkv, D, 1.0), rows, hidden) == launches
     check_pass(gpu, rows, Hq, Hkv, D, hidden)
+
+
+@pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [(16600, 8, 2, 128, 1536), (11041, 16, 4, 64, 576), (3682, 64, 8, 128, 1536)])
+def test_a_stream_confined_to_part_of_the_chip(gpu, rows, Hq, Hkv, D, hidden):
+    """On such a stream (here 192 compute units) every tile of the phased kernel has a workgroup of its own instead of one
+    that stays for several: the same bits as on an ordinary stream."""
+    binding, torch = gpu
+    assert binding.oppo_qkv_proj_plan_debug(binding.make_desc(Hq, Hkv, D, 1.0), rows, hidden)[0][2:] == (True, 2)
+    hip = ctypes.CDLL("libamdhip64.so")
+    words = (ctypes.c_uint32 * 8)(*([0xFFFFFFFF] * 6 + [0, 0]))
+    handle = ctypes.c_void_p()
+    if hip.hipExtStreamCreateWithCUMask(ctypes.byref(handle), 8, words) != 0 or not handle.value:
+        pytest.skip("no masks of compute units here")
+    dev = torch.device("cuda:0")
+    x = torch.randn((rows, hidden), device=dev, dtype=torch.bfloat16)
+    w = torch.randn(((Hq + 2 * Hkv) * D, hidden), device=dev, dtype=torch.bfloat16) * hidden ** -0.5
+    desc = binding.make_desc(Hq, Hkv, D, 1.0)
+    got = []
+    for stream in (torch.cuda.Stream(), torch.cuda.ExternalStream(handle.value)):
+        cache = binding.KVCache(torch.zeros((rows, Hkv, D), device=dev, dtype=torch.bfloat16),
+                                torch.zeros((rows, Hkv, D), device=dev, dtype=torch.bfloat16), [0, rows])
+        q = torch.zeros((rows, Hq, D), device=dev, dtype=torch.bfloat16)
+        ws = torch.empty(binding.oppo_qkv_proj_workspace_bytes(desc, rows), dtype=torch.uint8, device=dev)
+        torch.cuda.synchronize()
+        binding.oppo_qkv_proj_rope_append(desc, cache, [0, rows], x, hidden, w, q, ws, stream=stream)
+        torch.cuda.synchronize()
+        got.append((q, cache.k, cache.v))
+    assert got[0][0].any() and all(torch.equal(a, b) for a, b in zip(*got))
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,hidden", [(64, 3, 1, 128, 64), (65, 3, 1, 128, 64), (64, 4, 4, 64, 128), (65, 4, 4, 64, 128),
