@@ -650,9 +650,9 @@ static int launch_rows_list(int64_t* dst, float2* cs, double log2_base, int half
   return (int)hipGetLastError();
 }
 
-// Whether the stream may use every compute unit (the legacy stream has no mask; an error counts as yes).
+// Whether the stream may use every compute unit (the default streams have no mask; an error counts as yes).
 static bool has_whole_chip(hipStream_t st) {
-  if (!st) return true;
+  if (!st || st == hipStreamLegacy || st == hipStreamPerThread) return true;
   uint32_t mask[kProjCUs / 32] = {};
   if (hipExtStreamGetCUMask(st, kProjCUs / 32, mask) != hipSuccess) {
     (void)hipGetLastError();

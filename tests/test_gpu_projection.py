@@ -201,7 +201,8 @@ def test_every_kind_of_tile_and_cut(gpu, rows, Hq, Hkv, D, hidden, launches):
 @pytest.mark.parametrize("rows,Hq,Hkv,D,hidden", [(16600, 8, 2, 128, 1536), (11041, 16, 4, 64, 576), (3682, 64, 8, 128, 1536)])
 def test_a_stream_confined_to_part_of_the_chip(gpu, rows, Hq, Hkv, D, hidden):
     """On such a stream (here 192 compute units) every tile of the phased kernel has a workgroup of its own instead of one
-    that stays for several: the same bits as on an ordinary stream."""
+    that stays for several: the same bits as on an ordinary stream, and as on the default streams (0, 1 and 2: the null,
+    legacy and per-thread stream), which are no objects with a mask."""
     binding, torch = gpu
     assert binding.oppo_qkv_proj_plan_debug(binding.make_desc(Hq, Hkv, D, 1.0), rows, hidden)[0][2:] == (True, 2)
     hip = ctypes.CDLL("libamdhip64.so")
@@ -214,7 +215,7 @@ def test_a_stream_confined_to_part_of_the_chip(gpu, rows, Hq, Hkv, D, hidden):
     w = torch.randn(((Hq + 2 * Hkv) * D, hidden), device=dev, dtype=torch.bfloat16) * hidden ** -0.5
     desc = binding.make_desc(Hq, Hkv, D, 1.0)
     got = []
-    for stream in (torch.cuda.Stream(), torch.cuda.ExternalStream(handle.value)):
+    for stream in (torch.cuda.Stream(), torch.cuda.ExternalStream(handle.value), 0, 1, 2):
         cache = binding.KVCache(torch.zeros((rows, Hkv, D), device=dev, dtype=torch.bfloat16),
                                 torch.zeros((rows, Hkv, D), device=dev, dtype=torch.bfloat16), [0, rows])
         q = torch.zeros((rows, Hq, D), device=dev, dtype=torch.bfloat16)
@@ -223,7 +224,7 @@ def test_a_stream_confined_to_part_of_the_chip(gpu, rows, Hq, Hkv, D, hidden):
         binding.oppo_qkv_proj_rope_append(desc, cache, [0, rows], x, hidden, w, q, ws, stream=stream)
         torch.cuda.synchronize()
         got.append((q, cache.k, cache.v))
-    assert got[0][0].any() and all(torch.equal(a, b) for a, b in zip(*got))
+    assert got[0][0].any() and all(torch.equal(a, b) for other in got[1:] for a, b in zip(got[0], other))
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,hidden", [(64, 3, 1, 128, 64), (65, 3, 1, 128, 64), (64, 4, 4, 64, 128), (65, 4, 4, 64, 128),
