@@ -35,7 +35,7 @@ typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 constexpr int kGemmBN = kProjTileCols, kGemmBK = 64;   // the tile's rows BM are chosen per launch
 constexpr int kMaxProjItems = 1000;   // 1000 * 24 B + header in the kernel arguments
-constexpr int kFewProjItems = 64;     // the short list: kernel arguments are written across the bus for every launch
+constexpr int kFewProjItems = 64;     // the short list (see kFewAttnItems): 64 sequences 15.2 us a call, 65 16.4
 
 // Per-row data of a pass, made by proj_rows_kernel in the caller's workspace:
 //   dst[rows]            int64  cache row (token slot) the row's keys and values go to
@@ -372,9 +372,10 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
 // several tiles, requesting the next tile's first operands before they store the current one.
 // Tiles of 192 rows are the same with a second x half of 64 rows (M1 = 1 block of 32 rows per wave
 // instead of 2); its LDS rows stay where the 128-row half has each wave row's first block.
-// Measured, 15,099 rows, 4096 -> 6144: 662 us (1150 TFLOP/s) with tiles of 256 rows in the loop of
-// qkv_proj_kernel, 604 (1260) here; 2048 rows 115 / 94 us.  Tiles of 192 rows against those of
-// 256: 1400 rows 78 / 87 us, 2700 146 / 181.
+// Measured in one run, 4096 -> 6144, tiles of 256 rows in the loop of qkv_proj_kernel / here: 13,568 rows (five full
+// rounds) 559 / 514 us (1330 TFLOP/s), 15,099 rows 640 / 597, 2048 rows 96 / 93; back to back for longer the clocks
+// fall and 15,202 rows take 679 / 642.  Tiles of 192 rows against those of 256: 1404 rows 75 / 80 us, 2700 146 / 170,
+// 6144 252 / 275.  A tile's fixed cost is the price: where the k loop is short, qkv_proj_kernel is faster (plan_qkv_proj).
 template <int D, int BM>
 __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P) {
   static_assert(BM == 256 || BM == 192, "x halves of 128 and 128 or 64 rows");
@@ -395,9 +396,10 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
   if (!order.at(block, &tile_m, &tile_n)) return;
 
   // copies: copies 2 h, 2 h + 1 of a wave belong to half h of the tile, 8 LDS rows each, swizzled
-  // as in qkv_proj_kernel (a second x half of 64 rows takes one copy per wave).  LDS row 128 j + 32 wn + l of w holds the column that MFMA row l of
-  // wave column wn and half j stands for: MFMA row 8 a + 4 h + b is column 16 h + 4 a + b of its
-  // 32 (register i of lane half h is then column 16 h + i), the halves j are D/2 columns apart.
+  // as in qkv_proj_kernel (a second x half of 64 rows takes one copy per wave).  LDS row 128 j + 32 wn + l
+  // of w holds the column that MFMA row l of wave column wn and half j stands for: MFMA row 8 a + 4 h + b
+  // is column 16 h + 4 a + b of its 32 (register i of lane half h is then column 16 h + i), the halves j
+  // are D/2 columns apart.
   // (Lane-dependent values that only matter between tiles are recomputed there from a copy of the
   // lane number that the optimiser cannot see through, instead of living in registers meanwhile.)
   auto lane_now = [&]() __attribute__((always_inline)) -> int {

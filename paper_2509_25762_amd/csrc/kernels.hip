@@ -36,9 +36,12 @@ typedef __attribute__((ext_vector_type(4))) int i32x4;
 typedef __attribute__((ext_vector_type(8))) int i32x8;
 
 // Work lists travel in the kernel arguments, which the host writes anew for every launch, across
-// the bus: 31 KiB of them are most of a small call.  Each of these kernels therefore exists with
-// a short list as well, and the launcher takes the short one whenever the work fits it (a step of
-// 4 sequences x 32 tokens: 16.2 us with the long list, 14.9 with the short one).
+// the bus, at their full length however few items are in use.  Each of these kernels therefore exists with
+// a short list as well, and the launcher takes the short one whenever the work fits it.  A step of
+// 4 sequences x 32 tokens takes 16.6 us with the long list and 14.8 with the short one; at the lists' limits,
+// one-row sequences, us per call: 64 / 65 appended 11.5 / 12.0 (8-bit 11.1 / 11.8), attention in 96 / 97 pieces
+// 82.6 / 84.3, in 96 / 98 pieces that are merged 36.4 / 38.5.  (Replayed from a captured
+// graph both lists take the same time.)
 constexpr int kFewAttnItems = 96;
 constexpr int kFewItems = 64;    // merge and append items
 

@@ -91,7 +91,7 @@ __global__ __launch_bounds__(256) void rope_kernel(const RopeParams P) {
 // The same rotation as the epilogue of the layer's fused QKV projection: one pass over
 // the projection's output rows [q heads | k heads | v heads] writes the rotated queries
 // to their own array and the rotated keys and the values straight into the cache slabs.
-constexpr int kFewQkvItems = 64;     // the short list: kernel arguments are written across the bus for every launch
+constexpr int kFewQkvItems = 64;     // the short list (see kFewAttnItems): 64 one-row runs 11.3 us a call, 65 12.5
 template <int NI>
 struct QkvParams {
   const uint16_t* qkv;   // [rows][Hq + 2 Hkv][D]
@@ -107,8 +107,9 @@ static_assert(sizeof(QkvParams<kMaxQkvItems>) <= 32768, "kernel arguments are ke
 
 // Bound by HBM: a row's heads are read once and written once.  A thread's first kQkvAhead units
 // are requested before the workgroup's table of angles is made (double precision, a few microseconds
-// for which the memory would otherwise idle), and later ones as many at a time: 72.2 -> 68.6 us for
-// 12,900 rows of 48 heads of 128, 4.59 TB/s.
+// for which the memory would otherwise idle), and later ones as many at a time: 72.0 -> 68.6 us for
+// 12,967 rows of 48 heads of 128, 4.65 TB/s from pass to pass (the kernel's own duration is 54.6 us).  The number of
+// runs hardly matters: 14,720 rows as 64, 230 or 460 runs 76.7, 76.8 and 77.2 us.
 constexpr int kQkvAhead = 4;
 template <int D, int NI>
 __global__ __launch_bounds__(256) void qkv_rope_append_kernel(const QkvParams<NI> P) {
