@@ -111,18 +111,27 @@ struct TileOrder {
   int m_tiles, n_tiles;
   __device__ __forceinline__ TileOrder(const ProjParams& P, int bm, int bn)
       : m_tiles((P.rows + bm - 1) / bm), n_tiles((P.n_out + bn - 1) / bn) {}
+  // FEW: passes with few tiles come this way too.  A division is a tenth of a microsecond in front of the first
+  // request, out of 7 for the smallest passes: those that the pass's size makes trivial are left out.
+  template <bool FEW>
   __device__ __forceinline__ bool at(int block, int* tile_m, int* tile_n) const {
     const int first = block & ~255, left = m_tiles * n_tiles - first;
     const int share = left >= 256 ? 32 : (left + 7) / 8;   // an XCD's tiles of this round
     const int mine = (block / 8) % 32, in_round = (block % 8) * share + mine;
     if (mine >= share || in_round >= left) return false;
     const int pos = first + in_round;
-    const int strip = pos / (4 * m_tiles), in_strip = pos % (4 * m_tiles);    // strips of 4 column tiles
+    if (FEW && m_tiles == 1) {
+      *tile_m = 0;
+      *tile_n = pos;
+      return true;
+    }
+    const int strip = FEW && n_tiles <= 4 ? 0 : pos / (4 * m_tiles), in_strip = pos - 4 * m_tiles * strip;   // strips of 4 column tiles
     const int width = min(4, n_tiles - 4 * strip);
-    const int mg = in_strip / (8 * width), in_group = in_strip % (8 * width);
+    const int mg = FEW && m_tiles <= 8 ? 0 : in_strip / (8 * width), in_group = in_strip - 8 * width * mg;
     const int height = min(8, m_tiles - 8 * mg);
-    *tile_m = 8 * mg + in_group % height;
-    *tile_n = 4 * strip + in_group / height;
+    const int across = FEW && height == 8 ? in_group >> 3 : in_group / height;
+    *tile_m = 8 * mg + in_group - height * across;
+    *tile_n = 4 * strip + across;
     return true;
   }
 };
@@ -190,7 +199,7 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
   const int wm = wave / WC, wn = wave % WC;    // the wave's (32 MI) x (32 NJ) part of the tile
   const TileOrder order(P, BM, BN);
   int tile_m, tile_n;
-  if (!order.at((int)blockIdx.x, &tile_m, &tile_n)) return;
+  if (!order.at<true>((int)blockIdx.x, &tile_m, &tile_n)) return;
   const int64_t m0 = (int64_t)tile_m * BM, n0 = (int64_t)tile_n * BN;
 
   // ---- loads: a wave-wide copy moves 8 rows (8 x 128 B); wave w moves rows 8 (w + 8 i) .. of
@@ -393,7 +402,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
   const TileOrder order(P, BM, BN);
   int tile_m, tile_n;
   int block = (int)blockIdx.x;
-  if (!order.at(block, &tile_m, &tile_n)) return;
+  if (!order.at<false>(block, &tile_m, &tile_n)) return;
 
   // copies: copies 2 h, 2 h + 1 of a wave belong to half h of the tile, 8 LDS rows each, swizzled
   // as in qkv_proj_kernel (a second x half of 64 rows takes one copy per wave).  LDS row 128 j + 32 wn + l
@@ -573,7 +582,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     const int head = tile_n * (BN / D) + (D == 128 ? wn >> 1 : wn);      // one head per wave
     const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 16 * (ln >> 5);      // the lane's first column of the head
     block += (int)gridDim.x;   // (past the last tile where every workgroup has one)
-    const bool more = order.at(block, &tile_m, &tile_n);
+    const bool more = order.at<false>(block, &tile_m, &tile_n);
     if (more) {
       open_tile();
       issue_first();

@@ -228,10 +228,11 @@ def test_a_stream_confined_to_part_of_the_chip(gpu, rows, Hq, Hkv, D, hidden):
 
 
 @pytest.mark.parametrize("B,Hq,Hkv,D,hidden", [(64, 3, 1, 128, 64), (65, 3, 1, 128, 64), (64, 4, 4, 64, 128), (65, 4, 4, 64, 128),
-                                               (1001, 2, 1, 64, 64)])
+                                               (1001, 2, 1, 64, 64), (9, 12, 2, 128, 64), (110, 12, 2, 128, 64)])
 def test_row_lists_on_either_side_of_their_limits(gpu, B, Hq, Hkv, D, hidden):
     """64 sequences travel in the short list of the row kernel's arguments, 65 in the long one, 1001 in two of them;
-    1 .. 9 rows each (the row kernel takes 8 at a time), every third one up to 70,000 tokens in."""
+    1 .. 9 rows each (the row kernel takes 8 at a time), every third one up to 70,000 tokens in.  The last two: one row
+    tile and nine (a group of eight and one of a single tile) by eight column tiles."""
     rng = np.random.default_rng(B + D)
     q_len = (1 + np.arange(B) % 9).astype(np.int32)
     kv_before = ((np.arange(B) * 37) % 50 + (np.arange(B) % 3 == 0) * (70000 if B < 100 else 100)).astype(np.int32)
