@@ -9,9 +9,9 @@
 // rounded once to bf16 and written to q_out / to the sequence's cache slab; value heads go
 // to the cache as they are.  The projection's output never exists in memory.
 //
-// Workgroup = 256 columns of y by 256, 192, 128 or 64 rows, 8 waves (two per SIMD), blocks of
-// v_mfma_f32_32x32x16_bf16.  Tall tiles have a kernel of their own (qkv_proj_phased_kernel, below);
-// passes too thin to give every compute unit such a tile, and short k loops, take qkv_proj_kernel with 256, 128 or
+// Workgroup = 256 columns of y by 256, 192, 128 or 64 rows, 8 waves (two per SIMD).
+// Tall tiles have a kernel of their own (qkv_proj_phased_kernel, below, v_mfma_f32_16x16x32_bf16);
+// passes too thin to give every compute unit such a tile, and short k loops, take qkv_proj_kernel (v_mfma_f32_32x32x16_bf16) with 256, 128 or
 // 64 rows (plan_qkv_proj chooses): k advances in tiles of 64 through a ring of LDS stages, one workgroup per compute
 // unit; tiles travel global -> LDS directly, the
 // XOR swizzle of the LDS rows applied by choosing which 16-byte granule each lane fetches, so
@@ -361,7 +361,7 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
 // other group's memory instructions.  A wave computes 128 x 64, as four quadrants of 64 x 32 (two
 // halves of the x tile by two of the w tile), and a phase is
 //     read the fragments the quadrant still needs; request one half tile (two copies per wave);
-//     barrier; the quadrant's 8 MFMAs (32x32x16); barrier
+//     barrier; the quadrant's 16 MFMAs (16x16x32); barrier
 // with, for k tile t,   phase   reads              quadrant   requests
 //                         0     x0                 x0 w0      x1 of tile t + 1
 //                         1     w1                 x0 w1      w0 of tile t + 2
@@ -374,11 +374,14 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
 // a wave waits for its own copies in the phase before the one that reads them, with the five
 // requests made since still in flight, and the barrier that follows makes the half tile complete
 // for every wave of either group.
-// The product is computed transposed (w rows as the A operand), so a lane owns one row of y, and
-// the w rows are dealt to LDS rows such that it holds 16 consecutive columns of a head and, in
+// The MFMAs are 16x16x32 ones: the chip runs this loop against its power limit, and they take less of it than
+// 32x32x16 ones (on N(0, 1) operands, MFMAs alone: 1990-2050 against 1750 TFLOP/s; this kernel, 4096 -> 6144, 13,000 rows
+// back to back: 566 us against 625).
+// The product is computed transposed (w rows as the A operand), so a lane owns one row of y per block, and
+// the w rows are dealt to LDS rows such that it holds 8 consecutive columns of a head and, in
 // the accumulators of the other w half, their rotation partners D/2 further on: rotation and
-// stores (32 bytes per row and lane) need neither LDS nor barriers, and workgroups stay for
-// several tiles, requesting the next tile's first operands before they store the current one.
+// stores (16 bytes per row and lane, the four lanes of a row side by side) need neither LDS nor barriers, and workgroups
+// stay for several tiles, requesting the next tile's first operands before they store the current one.
 // Tiles of 192 rows are the same with a second x half of 64 rows (M1 = 1 block of 32 rows per wave
 // instead of 2); its LDS rows stay where the 128-row half has each wave row's first block.
 // Measured in one run, 4096 -> 6144, tiles of 256 rows in the loop of qkv_proj_kernel / here: 13,568 rows (five full
@@ -396,7 +399,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
   __shared__ __attribute__((aligned(1024))) unsigned char smem[4 * TILE];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, hi = lane >> 5;
+  const int l16 = lane & 15, grp = lane >> 4;
   const uint32_t wave_u = (uint32_t)__builtin_amdgcn_readfirstlane(wave);
   const int wm = (int)(wave_u >> 2), wn = (int)(wave_u & 3);   // wm is also the wave's group
   const TileOrder order(P, BM, BN);
@@ -406,9 +409,9 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 
   // copies: copies 2 h, 2 h + 1 of a wave belong to half h of the tile, 8 LDS rows each, swizzled
   // as in qkv_proj_kernel (a second x half of 64 rows takes one copy per wave).  LDS row 128 j + 32 wn + l
-  // of w holds the column that MFMA row l of wave column wn and half j stands for: MFMA row 8 a + 4 h + b
-  // is column 16 h + 4 a + b of its 32 (register i of lane half h is then column 16 h + i), the halves j
-  // are D/2 columns apart.
+  // of w holds the column that row l % 16 of MFMA block l / 16 of wave column wn and half j stands for: row 4 g + b of
+  // block c is column 8 g + 4 c + b of the wave's 32 (the registers of lane group g are then columns 8 g .. 8 g + 7), the
+  // halves j are D/2 columns apart.
   // (Lane-dependent values that only matter between tiles are recomputed there from a copy of the
   // lane number that the optimiser cannot see through, instead of living in registers meanwhile.)
   auto lane_now = [&]() __attribute__((always_inline)) -> int {
@@ -424,7 +427,7 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int r = RPL * ((int)wave_u + 8 * i) + lrow;
-      const int col = 16 * ((r >> 2) & 1) + 4 * ((r >> 3) & 3) + (r & 3), wc = (r >> 5) & 3, j = r >> 7;
+      const int col = 8 * ((r >> 2) & 3) + 4 * ((r >> 4) & 1) + (r & 3), wc = (r >> 5) & 3, j = r >> 7;
       const int n = D == 128 ? (wc >> 1) * 128 + j * 64 + (wc & 1) * 32 + col : wc * 64 + j * 32 + col;
       // rows past the end of x / w repeat the last valid row (their products are never stored)
       const int rx = i < 2 || M1 == 2 ? r : 128 + RPL * (int)wave_u + lrow;   // (32 rows per wave row: 128 + 32 wm + ..)
@@ -484,41 +487,45 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
     else __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
   };
 
-  // fragments: rows 32 * block + l32 of the wave's part of a half tile, elements 16 kk + 8 hi ..
+  // fragments: rows 16 * block + l16 of the wave's part of a half tile, elements 32 kk + 8 grp ..
   typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
-  lds_cptr pa[4], pb[4];
+  lds_cptr pa[2], pb[2];
 #pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint32_t g = (((uint32_t)(kk * 2 + hi)) ^ (uint32_t)((l32 >> 1) % NGR)) * 16u;
-    uint32_t a = smem0 + (uint32_t)((wm * 64 + l32) * ROWB) + g;
-    uint32_t b = smem0 + (uint32_t)(B_AREA + (wn * 32 + l32) * ROWB) + g;
+  for (int kk = 0; kk < 2; ++kk) {
+    const uint32_t g = (((uint32_t)(kk * 4 + grp)) ^ (uint32_t)((l16 >> 1) % NGR)) * 16u;
+    uint32_t a = smem0 + (uint32_t)((wm * 64 + l16) * ROWB) + g;
+    uint32_t b = smem0 + (uint32_t)(B_AREA + (wn * 32 + l16) * ROWB) + g;
     asm volatile("" : "+v"(a), "+v"(b));   // (one register each: stage, half and block are immediate offsets)
     pa[kk] = (lds_cptr)(uintptr_t)a;
     pb[kk] = (lds_cptr)(uintptr_t)b;
   }
-  // x fragments [block][kk] of the half at hand; w fragments [set][kk]: tile t has its w0 in set t & 1, its w1 in the other
-  bf16x8 a[2][4], b[2][4];
+  // x fragments [block][kk] of the half at hand; w fragments [set][block][kk]: tile t has its w0 in set t & 1, its w1 in the other
+  bf16x8 a[4][2], b[2][2][2];
   auto read_x = [&](int stage, int h) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int i = 0; i < (h == 0 ? 2 : M1); ++i)
-        a[i][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pa[kk] + stage * TILE + h * HALF_TILE + i * 32 * ROWB);
+      for (int i = 0; i < (h == 0 ? 4 : 2 * M1); ++i)
+        a[i][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pa[kk] + stage * TILE + h * HALF_TILE + i * 16 * ROWB);
   };
   auto read_w = [&](int set, int stage, int h) __attribute__((always_inline)) {
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
-      b[set][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pb[kk] + stage * TILE + h * HALF_TILE);
+    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        b[set][c][kk] = *(const __attribute__((address_space(3))) bf16x8*)(pb[kk] + stage * TILE + h * HALF_TILE + c * 16 * ROWB);
   };
   auto reads_done = [&]() __attribute__((always_inline)) { __builtin_amdgcn_s_waitcnt(0xC07F); };   // lgkmcnt(0)
-  f32x16 acc[2][2][2];   // [x half][block][w half]
+  f32x4 acc[2][4][2][2];   // [x half][block of 16 rows][w half][block of 16 w rows]
   auto quadrant = [&](int h, int j, int set) __attribute__((always_inline)) {
     __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-    for (int kk = 0; kk < 4; ++kk)
+    for (int kk = 0; kk < 2; ++kk)
 #pragma unroll
-      for (int i = 0; i < (h == 0 ? 2 : M1); ++i)
-        acc[h][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[set][kk], a[i][kk], acc[h][i][j], 0, 0, 0);
+      for (int i = 0; i < (h == 0 ? 4 : 2 * M1); ++i)
+#pragma unroll
+        for (int c = 0; c < 2; ++c)
+          acc[h][i][j][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[set][c][kk], a[i][kk], acc[h][i][j][c], 0, 0, 0);
     __builtin_amdgcn_s_setprio(0);
   };
   auto k_tile = [&](int t, auto ST) __attribute__((always_inline)) {
@@ -560,11 +567,11 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int i = 0; i < 2; ++i)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[h][i][j][r] = 0.f;
+          for (int c = 0; c < 2; ++c) acc[h][i][j][c] = f32x4{0.f, 0.f, 0.f, 0.f};
     barrier();
     read_w(0, 0, 0);
     reads_done();
@@ -578,9 +585,9 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
 
     // ---- the next tile's operands, and this tile's rows: cache slots and rotation angles
     const int ln = lane_now();
-    const int row_first = tile_m * BM + (ln & 31);
+    const int row_first = tile_m * BM + (ln & 15);
     const int head = tile_n * (BN / D) + (D == 128 ? wn >> 1 : wn);      // one head per wave
-    const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 16 * (ln >> 5);      // the lane's first column of the head
+    const int e0 = (D == 128 ? (wn & 1) * 32 : 0) + 8 * (ln >> 4);       // the lane's first column of the head
     block += (int)gridDim.x;   // (past the last tile where every workgroup has one)
     const bool more = order.at<false>(block, &tile_m, &tile_n);
     if (more) {
@@ -588,53 +595,56 @@ __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P
       issue_first();
     }
     const bool turned = head < P.Hq + P.Hkv;   // queries and keys
+    constexpr int NQ = 4 + 2 * M1;   // row blocks of the wave
     auto row_of = [&](int q) __attribute__((always_inline)) -> int {   // row of row block q of the wave
-      return row_first + (q < 2 ? wm * 64 + q * 32 : 128 + wm * 32 * M1 + (q - 2) * 32);
+      return row_first + (q < 4 ? wm * 64 + q * 16 : 128 + wm * 32 * M1 + (q - 4) * 16);
     };
-    uint16_t* out[2 + M1];
-#pragma unroll
-    for (int q = 0; q < 2 + M1; ++q) {
-      const int64_t row = min(row_of(q), P.rows - 1);
-      if (head < P.Hq) out[q] = P.q_out + (row * P.Hq + head) * D + e0;
-      else if (turned) out[q] = P.cache_k + (P.dst[row] * P.Hkv + (head - P.Hq)) * D + e0;
-      else out[q] = P.cache_v + (P.dst[row] * P.Hkv + (head - P.Hq - P.Hkv)) * D + e0;
-    }
-    // step s: 8 of the 16 columns (and their partners) of row block s / 2; the angles one step ahead
+    // row block q: the lane's 8 columns (and their partners); the angles and the cache slot one block ahead
     float2 cs[2][8];
-    auto load_cs = [&](int st, float2* c) __attribute__((always_inline)) {
-      const float2* src = P.cs + (int64_t)min(row_of(st >> 1), P.rows - 1) * HALF + e0 + (st & 1) * 8;
+    int64_t slot[2];
+    auto load_row = [&](int q) __attribute__((always_inline)) {
+      const int64_t row = min(row_of(q), P.rows - 1);
+      slot[q & 1] = head < P.Hq ? row : P.dst[row];
+      if (!turned) return;
+      const float2* src = P.cs + row * HALF + e0;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) c[e] = src[e];
+      for (int e = 0; e < 8; ++e) cs[q & 1][e] = src[e];
     };
-    if (turned) load_cs(0, cs[0]);
+    uint16_t* const base = head < P.Hq ? P.q_out + (int64_t)head * D + e0
+                           : turned    ? P.cache_k + (int64_t)(head - P.Hq) * D + e0
+                                       : P.cache_v + (int64_t)(head - P.Hq - P.Hkv) * D + e0;
+    const int64_t stride = (int64_t)(head < P.Hq ? P.Hq : P.Hkv) * D;
+    load_row(0);
     __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0), before the first store: see `landed`
 #pragma unroll
-    for (int st = 0; st < 2 * (2 + M1); ++st) {
-      const f32x16& u = acc[st >> 2][(st >> 1) & 1][0];
-      const f32x16& v = acc[st >> 2][(st >> 1) & 1][1];
-      const int f = (st & 1) * 8;
+    for (int q = 0; q < NQ; ++q) {
+      const f32x4(&u)[2] = acc[q >> 2][q & 3][0];
+      const f32x4(&v)[2] = acc[q >> 2][q & 3][1];
       u32x4 ra, rb;
+      if (q + 1 < NQ) load_row(q + 1);
       if (turned) {
-        if (st + 1 < 2 * (2 + M1)) load_cs(st + 1, cs[(st + 1) & 1]);
-        const float2* c = cs[st & 1];
+        const float2* c = cs[q & 1];
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          const int e = 2 * w;
-          ra[w] = gemm_pack_bf16(u[f + e] * c[e].x - v[f + e] * c[e].y, u[f + e + 1] * c[e + 1].x - v[f + e + 1] * c[e + 1].y);
-          rb[w] = gemm_pack_bf16(v[f + e] * c[e].x + u[f + e] * c[e].y, v[f + e + 1] * c[e + 1].x + u[f + e + 1] * c[e + 1].y);
+          const int e = 2 * w, f = e & 3;
+          const f32x4 &x = u[w >> 1], &y = v[w >> 1];
+          ra[w] = gemm_pack_bf16(x[f] * c[e].x - y[f] * c[e].y, x[f + 1] * c[e + 1].x - y[f + 1] * c[e + 1].y);
+          rb[w] = gemm_pack_bf16(y[f] * c[e].x + x[f] * c[e].y, y[f + 1] * c[e + 1].x + x[f + 1] * c[e + 1].y);
         }
       } else {
 #pragma unroll
         for (int w = 0; w < 4; ++w) {
-          ra[w] = gemm_pack_bf16(u[f + 2 * w], u[f + 2 * w + 1]);
-          rb[w] = gemm_pack_bf16(v[f + 2 * w], v[f + 2 * w + 1]);
+          const int f = 2 * (w & 1);
+          ra[w] = gemm_pack_bf16(u[w >> 1][f], u[w >> 1][f + 1]);
+          rb[w] = gemm_pack_bf16(v[w >> 1][f], v[w >> 1][f + 1]);
         }
       }
-      if (row_of(st >> 1) < P.rows && head < heads) {
-        *(u32x4*)(out[st >> 1] + f) = ra;
-        *(u32x4*)(out[st >> 1] + f + HALF) = rb;
+      if (row_of(q) < P.rows && head < heads) {
+        uint16_t* out = base + slot[q & 1] * stride;
+        *(u32x4*)out = ra;
+        *(u32x4*)(out + HALF) = rb;
       }
-      __builtin_amdgcn_sched_barrier(0);   // (one step's values at a time in the registers)
+      __builtin_amdgcn_sched_barrier(0);   // (one block's values at a time in the registers)
     }
     if (!more) break;
   }
