@@ -4,12 +4,15 @@
 //   * the query tile packs TM tokens x G q-heads of the kv-head into 256 rows
 //     (row r = head r % G of token r / G);
 //     wave w owns rows [32w, 32w+32).  The transposed product S^T = K Q^T is
-//     computed with v_mfma_f32_32x32x16_bf16 (K as the A operand from LDS, Q^T
-//     as the B operand held in registers), so one lane owns one query column:
+//     computed with v_mfma_f32_16x16x32_bf16 (K as the A operand from LDS, Q^T
+//     as the B operand held in registers), so one lane owns two query columns:
 //     the softmax statistics are per-lane scalars and the probabilities land
 //     in the B-operand layout of the second product O^T = V^T P^T without any
 //     cross-lane movement.  V^T fragments come from the token-major V tile in
 //     LDS through the transposing LDS read (ds_read_b64_tr_b16).
+//     (The chip runs this work against its power limit, and a multiplication in this shape
+//     takes less of it than in 32x32x16: loops of nothing but MFMAs on N(0, 1) operands
+//     sustain 1990-2050 and 1750 TFLOP/s.)
 //   * keys are streamed in tiles of 64 with an online softmax (running max and
 //     sum in fp32, exp2 domain with the scale folded in).
 //   * causal mask aligned to the end of the cache: the tile's token t at
@@ -28,6 +31,7 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
@@ -181,21 +185,25 @@ __device__ __forceinline__ long bf16x8_to_fp8x8(bf16x8 x, float mult) {
 // reads those cache rows).
 template <int D, bool APPEND, int NI>
 __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
-  constexpr int NT = 512;            // threads
+  constexpr int NW = 8, NT = 64 * NW;   // waves, threads
+  // 16-column blocks of a wave.  (Four waves of 64 columns would halve the fragment reads; their loop alone, one wave per
+  // SIMD with nothing to fill its gaps, sustains 1382 TFLOP/s beside this one's 1368, and boundaries would cost more.)
+  constexpr int NCB = 2;
+  constexpr int WROWS = 16 * NCB;    // packed rows of a wave
   constexpr int NG = D / 8;          // 16-byte granules per K/V row
-  constexpr int KK = D / 16;         // k-steps of S^T = K Q^T
-  constexpr int DB = D / 32;         // 32-row blocks of O^T
+  constexpr int KK = D / 32;         // k-steps of S^T = K Q^T
+  constexpr int DB = D / 16;         // 16-row blocks of O^T
   constexpr int BN = kKeyTile;
   constexpr int ROWB = D * 2;        // bytes per K/V row in LDS
   constexpr int TILE_BYTES = BN * ROWB;
   constexpr int VSWZ_MASK = NG / 4 - 1;
   constexpr int NSTAGE = 4;
   constexpr int RPI = 1024 / ROWB;     // tile rows one wave-wide 16-byte load covers
-  constexpr int IPW = BN / RPI / 8;    // such loads per wave, per tile, for K and again for V
-  constexpr int KDEPTH = KK / 2;     // K fragments kept in flight (half a unit ahead: four MFMA steps cover the
+  constexpr int IPW = BN / RPI / NW;   // such loads per wave, per tile, for K and again for V
+  constexpr int KDEPTH = KK;         // K fragments kept in flight (half a unit ahead: four MFMA steps cover the
                                      // LDS latency several times over, and a whole unit costs 16 more registers)
-  constexpr int VDEPTH = DB;         // V^T fragments kept in flight
-  static_assert(IPW >= 1 && NT == 512, "tile smaller than the workgroup");
+  constexpr int VDEPTH = DB / 2;     // V^T fragments kept in flight
+  static_assert(IPW >= 1, "tile smaller than the workgroup");
 
   // K stages and V stages are two arrays of at most 64 KiB each, so that every
   // fragment read is "per-lane base register + immediate offset" (the LDS
@@ -206,8 +214,8 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
-  const int l32 = lane & 31;
-  const int hi = lane >> 5;
+  const int l16 = lane & 15;
+  const int grp = lane >> 4;
   const int Hq = P.Hq, Hkv = P.Hkv, G = P.G, TM = P.TM;
   const int kvh = blockIdx.x % Hkv;
   const int queue = blockIdx.x / Hkv;
@@ -242,8 +250,8 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return r;
   };
 
-  // ---- this lane's query column (row of the packed (token, head) tile) --------------
-  bf16x8 qf[KK];
+  // ---- this lane's two query columns (rows l16 and 16 + l16 of the wave's 32) --------
+  bf16x8 qf[NCB][KK];
 
   // ---- cooperative K/V tile loads ------------------------------------------------
   // Tiles travel global -> LDS directly (global_load_lds_dwordx4): a wave-wide
@@ -256,7 +264,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   uint32_t goffk[IPW], goffv[IPW];   // byte offsets of this lane's granules in a full tile
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
-    const int r = (wave + 8 * i) * RPI + lrow;
+    const int r = (wave + NW * i) * RPI + lrow;
     goffk[i] = (uint32_t)(r * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
     goffv[i] = (uint32_t)(r * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
   }
@@ -288,22 +296,23 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   auto roff_of = [&](int ln) __attribute__((always_inline)) -> uint32_t {
     return (uint32_t)((ln / NS) * RB + (((ln % NS) ^ ((ln / NS) & (NS - 1))) * 16));
   };
-  // column side: the row of lane ln, (ln & 31), lies in chunk (ln & 31) / RPC; cx_of = its swizzle
+  // column side: row 16 * cb + ln % 16 lies in the K part (cb = 0) or the V part (cb = 1) of the area; cx_of = its swizzle
   auto cx_of = [&](int ln) __attribute__((always_inline)) -> uint32_t { return (uint32_t)(ln & (NS - 1)) * 16u; };
   auto area_of = [&](int stage, int k) __attribute__((always_inline)) -> uint32_t {   // chunk k of the area in `stage`
     return ((k / IPW) ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
-           (uint32_t)((k % IPW) * 8192);
+           (uint32_t)((k % IPW) * (NW * 1024));
   };
-  auto carea_of = [&](int stage, int ln) __attribute__((always_inline)) -> uint32_t {   // the row of lane ln in its chunk
-    const int row = ln & 31;
-    return (((row / RPC) / IPW) ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
-           (uint32_t)(((row / RPC) % IPW) * 8192 + (row % RPC) * RB);
+  static_assert(RPC * IPW == WROWS / 2, "half of the column blocks per part");
+  auto carea_of = [&](int stage, int cb, int ln) __attribute__((always_inline)) -> uint32_t {   // that row in its chunk
+    const int row = ln & 15;
+    return (cb >= NCB / 2 ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
+           (uint32_t)((cb % (NCB / 2) * (16 / RPC) + row / RPC) * (NW * 1024) + (row % RPC) * RB);
   };
   // rows wave*32 + k*RPC + ln/NS of the packed tile -> (q-head of the group, token):
   // row R is head R % G of token R / G, so the rows of a tile of n tokens are the
   // first n * G ones (and rows from TM * G on, if G does not divide 256, are never used)
   auto row_of = [&](int ln, int k, int* hk, int* tk) __attribute__((always_inline)) {
-    const int R = (int)(wave_rows >> 10) * 32 + ln / NS + k * RPC;   // (wave number as a scalar)
+    const int R = (int)(wave_rows >> 10) * WROWS + ln / NS + k * RPC;   // (wave number as a scalar)
     const int t = (int)(((uint32_t)R * P.g_magic) >> 16);            // R / G
     *tk = t;
     *hk = R - t * G;
@@ -324,17 +333,18 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   auto q_collect = [&](int stage) __attribute__((always_inline)) {
     const int ln = lane_now();
     const uint32_t roff = roff_of(ln);
-    const uint32_t cbase = carea_of(stage, ln);
-    const uint32_t cxh = cx_of(ln) ^ ((uint32_t)(ln >> 5) * 16u);   // the lane's slots are 2*kl + hi, swizzled
+    const uint32_t cxg = cx_of(ln) ^ ((uint32_t)(ln >> 4) * 16u);   // the lane's slots are 4*kl + grp, swizzled
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int k = 0; k < 2 * IPW; ++k)
         *(__attribute__((address_space(3))) u32x4*)(lds_ptr)(uintptr_t)(area_of(stage, k) + roff) = qraw[h][k];
 #pragma unroll
-      for (int kl = 0; kl < KK / 2; ++kl)
-        qf[h * (KK / 2) + kl] = *(const __attribute__((address_space(3))) bf16x8*)(lds_ptr)(uintptr_t)(
-            cbase + ((uint32_t)(kl * 32) ^ cxh));
+      for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int kl = 0; kl < KK / 2; ++kl)
+          qf[cb][h * (KK / 2) + kl] = *(const __attribute__((address_space(3))) bf16x8*)(lds_ptr)(uintptr_t)(
+              carea_of(stage, cb, ln) + ((uint32_t)(kl * 64) ^ cxg));
     }
   };
   // The request cursor walks the workgroup's tile stream (all tiles of piece
@@ -372,12 +382,12 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       // lane number, so the two sources fill one tile with complementary lane masks
 #pragma unroll
       for (int i = 0; i < IPW; ++i) {
-        const int r = (wave + 8 * i) * RPI + lrow;
+        const int r = (wave + NW * i) * RPI + lrow;
         const int rc = min(r, last);   // rows past the range repeat the last key
         const uint32_t ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
         const uint32_t ov = (uint32_t)(rc * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
-        const uint32_t lk = lds_addr_of(&sk[stage][0]) + wave_rows_now + i * 8192u;
-        const uint32_t lv = lds_addr_of(&sv[stage][0]) + wave_rows_now + i * 8192u;
+        const uint32_t lk = lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u);
+        const uint32_t lv = lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u);
         if (rc < c_cached) {
           async_copy16((const void*)c_k, ok, lk);
           async_copy16((const void*)(c_k + k_to_v), ov, lv);
@@ -394,13 +404,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int i = 0; i < IPW; ++i) {
         uint32_t ok = goffk[i], ov = goffv[i];
         if (last < BN - 1) {  // ragged last tile: rows past the range repeat the last key
-          const int r = (wave + 8 * i) * RPI + lrow;
+          const int r = (wave + NW * i) * RPI + lrow;
           const int rc = min(r, last);
           ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
           ov = (uint32_t)(rc * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
         }
-        async_copy16((const void*)bk, ok, lds_addr_of(&sk[stage][0]) + wave_rows_now + i * 8192u);
-        async_copy16((const void*)bv, ov, lds_addr_of(&sv[stage][0]) + wave_rows_now + i * 8192u);
+        async_copy16((const void*)bk, ok, lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u));
+        async_copy16((const void*)bv, ov, lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u));
       }
     }
     c_k += tile_step;
@@ -429,38 +439,37 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // (made opaque to the optimiser, which would otherwise fold the array address
   // into each read and rebuild the sum with a vector instruction every time)
   typedef const __attribute__((address_space(3))) unsigned char* lds_cptr;
-  lds_cptr kptr[KK];   // K fragment of k-step kk, key block 0 (block 1 is +32 rows)
+  lds_cptr kptr[KK];   // K fragment of k-step kk, keys 0 .. 15 of a tile
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
-    uint32_t a = lds_addr_of(&sk[0][0]) + (uint32_t)(l32 * ROWB + (((kk * 2 + hi) ^ (l32 % NG)) * 16));
+    uint32_t a = lds_addr_of(&sk[0][0]) + (uint32_t)(l16 * ROWB + (((kk * 4 + grp) ^ (l16 % NG)) * 16));
     asm volatile("" : "+v"(a));
     kptr[kk] = (lds_cptr)(uintptr_t)a;
   }
-  lds_cptr vptr[DB];   // V^T fragment of d-block db, keys 4*hi.. of a 16-key group
+  lds_cptr vptr[DB / 2];   // V^T fragments of d-blocks 2 * i (and 2 * i + 1, 32 bytes on), keys 4 * grp .. of a tile
   {
-    const int j = lane & 15;
-    const int half16 = (lane >> 4) & 1;
-    const int vrow = 4 * hi + (j >> 2);
+    const int vrow = 4 * grp + (l16 >> 2);
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int lg = db * 4 + 2 * half16 + ((j & 3) >> 1);
-      uint32_t a = lds_addr_of(&sv[0][0]) + (uint32_t)(vrow * ROWB + ((lg ^ ((vrow & VSWZ_MASK) << 2)) * 16) + (j & 1) * 8);
+    for (int i = 0; i < DB / 2; ++i) {
+      const int lg = i * 4 + ((l16 & 3) >> 1);
+      uint32_t a = lds_addr_of(&sv[0][0]) + (uint32_t)(vrow * ROWB + ((lg ^ ((vrow & VSWZ_MASK) << 2)) * 16) + (l16 & 1) * 8);
       asm volatile("" : "+v"(a));
-      vptr[db] = (lds_cptr)(uintptr_t)a;
+      vptr[i] = (lds_cptr)(uintptr_t)a;
     }
   }
-  // K fragment (A operand of S^T = K Q^T): keys kb*32 + l32, elements kk*16 + 8*hi..;
+  // K fragment (A operand of S^T = K Q^T) of step j = (k-step j / 2, 16-key block j % 2) of the 32-key
+  // unit (stage, kb): keys kb*32 + (j % 2)*16 + l16, elements (j / 2)*32 + 8*grp..;
   // `off` = stage * TILE_BYTES (an immediate in the main loop)
-  auto ldk = [&](int off, int kb, int kk) __attribute__((always_inline)) -> bf16x8 {
-    return *(const __attribute__((address_space(3))) bf16x8*)(kptr[kk] + off + kb * 32 * ROWB);
+  auto ldk = [&](int off, int kb, int j) __attribute__((always_inline)) -> bf16x8 {
+    return *(const __attribute__((address_space(3))) bf16x8*)(kptr[j / 2] + off + (2 * kb + j % 2) * 16 * ROWB);
   };
-  // V^T fragment (A operand of O^T += V^T P^T) of step j = (16-key group, d-block)
-  // of the 32-key unit (stage, kb)
+  // V^T fragment (A operand of O^T += V^T P^T) of d-block j of the 32-key unit (stage, kb): the eight
+  // contraction indices of lane group grp are keys 4*grp .. and 16 + 4*grp .., as S^T leaves them in P^T
   auto ldv = [&](int off, int kb, int j) __attribute__((always_inline)) -> bf16x8 {
-    lds_cptr vp = vptr[j % DB] + off + (2 * kb + j / DB) * 16 * ROWB;
+    lds_cptr vp = vptr[j / 2] + off + kb * 32 * ROWB + (j % 2) * 32;
     union { struct { s16x4 a, b; } h; bf16x8 v; } cat;
     cat.h.a = lds_read_tr16_l(vp);
-    cat.h.b = lds_read_tr16_l(vp + 8 * ROWB);
+    cat.h.b = lds_read_tr16_l(vp + 16 * ROWB);
     return cat.v;
   };
 
@@ -469,55 +478,60 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // stay far inside the fp32 / bf16 range, relative precision does not depend on
   // the reference, and the maximum is not needed on the common path.
   constexpr float kRowSumLimit = 16777216.0f;
-  const bf16x2 ones2 = {(__bf16)1.0f, (__bf16)1.0f};
 
   // ------------------------------------------------------------------------------
   // Main loop, software-pipelined over 32-key units (two per 64-key tile).  The
   // body of unit u issues, interleaved instruction by instruction,
-  //   * the MFMAs of S^T for unit u+1            (one dependent chain),
-  //   * the MFMAs of O^T += V^T P^T for unit u-1 (DB independent chains),
+  //   * the MFMAs of S^T for unit u+1            (four dependent chains: two key by two column blocks),
+  //   * the MFMAs of O^T += V^T P^T for unit u-1 (2 * DB independent ones),
   //   * the exp2 / bf16 rounding / row-sum vector work of unit u,
   // so the matrix pipe always has an independent MFMA to run and the vector ALU
-  // work (about three instructions per MFMA) is spread evenly under it.
-  constexpr int QS = KK;          // S^T MFMAs per unit
-  constexpr int PS = 2 * DB;      // O^T MFMAs per unit
-  constexpr int PPS = 8 / QS;     // probability pairs handled per step
+  // work (five instructions, two of them exp2, per four MFMAs) is spread evenly under it.
+  // Against the same loop on 32x32x16 MFMAs with v_dot2 row sums, one run, us: 64 x 256 rows on 262 .. 1017 keys 243 -> 235,
+  // prompts of 512 .. 2048 tokens 555 -> 534, 4 x 512 rows on 4096 .. 9999 keys 169 -> 160, 64/8 heads as above 1827 -> 1738.
+  constexpr int QS = 2 * KK;      // K fragments of a unit, two S^T MFMAs (one per column block) each
+  constexpr int PS = DB;          // V^T fragments of a unit, two O^T MFMAs each
+  constexpr int PPS = 4 * NCB / QS;   // probability pairs handled per step
   static_assert(QS == PS && QS % KDEPTH == 0 && PS % VDEPTH == 0, "pipeline shape");
 
-  f32x16 o[DB];
-  f32x16 s[2];                                   // s[u & 1] = S^T of unit u
+  f32x4 o[DB][NCB];                              // [d-block][column block]
+  f32x4 s[2][2][NCB];                            // s[u & 1][16-key block][column block] = S^T of unit u
   bf16x8 ka[KDEPTH];                             // K fragments in flight: step j of a unit sits in ka[j % KDEPTH]
   bf16x8 vf[VDEPTH];                             // V^T fragments in flight, likewise
-  union { bf16x2 h[8]; bf16x8 v[2]; } pf[2];     // pf[u & 1] = probabilities of unit u, B-operand layout
-  float m_run, l_run, mc, rs0 = 0.f, rs1 = 0.f;
+  union { bf16x2 h[4 * NCB]; bf16x8 v[NCB]; } pf[2];   // pf[u & 1].v[column block] = probabilities of unit u, B-operand layout
+  float m_run[NCB], l_run[NCB], mc[NCB], rs[NCB];
 
   // state of the piece being computed
   AttnItem it = piece(p_first);
-  int lim = 0;       // last key this lane's column may see, minus 4 * (lane / 32): compared with the key
-                     // of the lane's register r of the other 32-lane half, see the mask in unit_body
+  int lim[NCB];      // last key each of the lane's columns may see, minus 4 * grp: compared with the key
+                     // that lane group 0 has in the same register, see the mask in unit_body
   int min_lim = 0;   // smallest such limit in the workgroup: units entirely below it need no mask
 
-  // probabilities 2p, 2p+1 of the unit in s[cur]: exp2, round to bf16, add to the
-  // row sum (the sum uses the rounded values, like the numerator does)
-  // The empty asm statement pins the work to its place in the instruction stream: the
-  // results are "used" by it, and such statements keep their order.  (The inputs are read
-  // from the score registers as they are: a statement that "defines" them as well costs a
-  // register copy per score, because the scores have to survive for a possible redo.)
-  auto exp_pair = [&](int cur, int pr) __attribute__((always_inline)) {
-    const float x0 = s[cur][2 * pr], x1 = s[cur][2 * pr + 1];
-    const float p0 = fast_exp2(fmaf(x0, c, -mc));
-    const float p1 = fast_exp2(fmaf(x1, c, -mc));
+  // Pair pr of a unit's scores, and so of its probabilities: keys 2 * (pr % 2) and the next of 16-key block
+  // (pr / 2) % 2, column block pr / 4.
+  auto score = [&](int cur, int pr, int e) __attribute__((always_inline)) -> float {   // its exponent e = 0, 1
+    return fmaf(s[cur][(pr / 2) % 2][pr / 4][2 * (pr % 2) + e], c, -mc[pr / 4]);
+  };
+  auto round_pair = [&](int cur, int pr, float p0, float p1) __attribute__((always_inline)) {
     bf16x2 pk;
     pk[0] = (__bf16)p0;
     pk[1] = (__bf16)p1;
-    if (pr & 1) {
-      rs1 = __builtin_amdgcn_fdot2_f32_bf16(pk, ones2, rs1, false);
-      asm volatile("" : "+v"(pk), "+v"(rs1));
-    } else {
-      rs0 = __builtin_amdgcn_fdot2_f32_bf16(pk, ones2, rs0, false);
-      asm volatile("" : "+v"(pk), "+v"(rs0));
-    }
+    // (an empty asm statement pins the work to its place in the instruction stream: the
+    // results are "used" by it, and such statements keep their order)
+    asm volatile("" : "+v"(pk));
     pf[cur].h[pr] = pk;
+  };
+  // Row sums over the unit's 32 keys, taken over the rounded values like the numerator, by the matrix cores: every
+  // lane of a column receives its sum.  The vector unit has no room for it (unpacking and adding is four instructions a
+  // pair), and v_dot2_f32_bf16, one instruction a pair, does not run beside MFMAs: a loop of one 32x32x16 MFMA and four
+  // of them takes 61 cycles, with four of any other vector instruction 32.  64/8 heads, 1024 rows on up to 8192 keys, one run:
+  // unpacked adds 1909 us, v_dot2 at the unit's end 1830, here 1775 (32x32x16 MFMAs with v_dot2 between them: 1886).
+  bf16x8 ones;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+  asm volatile("" : "+v"(ones));   // (four registers, not rebuilt in every unit)
+  auto row_sum = [&](int cur, int cb) __attribute__((always_inline)) -> float {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[cur].v[cb], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0)[0];
   };
 
   // Body of unit u.  BC = position of the unit in the LDS ring (stage, key half),
@@ -534,81 +548,115 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     const int key0 = it.k_begin + 32 * u;
     if (key0 + 31 > min_lim) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        // register r holds key key0 + 8 * (r / 4) + 4 * (lane / 32) + r % 4
-        if (key0 + 8 * (r >> 2) + (r & 3) > lim) s[cur][r] = -INFINITY;
-      }
+      for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          // register e % 4 of key block e / 4 holds key key0 + 16 * (e / 4) + 4 * grp + e % 4
+          if (key0 + 16 * (e / 4) + e % 4 > lim[cb]) s[cur][e / 4][cb][e % 4] = -INFINITY;
+        }
     }
     // The probabilities of this unit are formed against the reference value m_run
     // the column already has (no maximum is taken first); only if a row sum comes
     // out too large - always for a column's first visible keys, otherwise almost
     // never - the unit is redone against its true maximum, see below.
-    rs0 = 0.f;
-    rs1 = 0.f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[nxt][r] = 0.f;
+    for (int e = 0; e < 2 * NCB; ++e) s[nxt][e % 2][e / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+    // An MFMA of this shape leaves the vector unit 8 of its 16 cycles: two instructions, or one exp2.  A step is four
+    // MFMAs with PPS pairs' work dealt to them accordingly; a pair's exponents are formed one step ahead.
+    float y0[PPS], y1[PPS], p0[PPS], p1[PPS];
+#pragma unroll
+    for (int j = 0; j < PPS; ++j) {
+      y0[j] = score(cur, j, 0);
+      y1[j] = score(cur, j, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
 #pragma unroll
     for (int i = 0; i < QS; ++i) {
-      s[nxt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i % KDEPTH], qf[i], s[nxt], 0, 0, 0);
+      s[nxt][i % 2][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[0][i / 2], s[nxt][i % 2][0], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < PPS; ++j) {
+        p0[j] = fast_exp2(y0[j]);
+        asm volatile("" : "+v"(p0[j]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      s[nxt][i % 2][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[1][i / 2], s[nxt][i % 2][1], 0, 0, 0);
       ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(st_n * TILE_BYTES, kb_n, i + KDEPTH)
                                          : ldk(st_nn * TILE_BYTES, kb_nn, i + KDEPTH - QS);
-      o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % VDEPTH], pf[nxt].v[i / DB], o[i % DB], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < PPS; ++j)
+        if (i + 1 < QS) {
+          y0[j] = score(cur, (i + 1) * PPS + j, 0);
+          asm volatile("" : "+v"(y0[j]));
+        }
+      __builtin_amdgcn_sched_barrier(0);
+      o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[0], o[i][0], 0, 0, 0);
+#pragma unroll
+      for (int j = 0; j < PPS; ++j) {
+        p1[j] = fast_exp2(y1[j]);
+        asm volatile("" : "+v"(p1[j]));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      o[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[1], o[i][1], 0, 0, 0);
       vf[i % VDEPTH] = (i + VDEPTH < PS) ? ldv(st_p * TILE_BYTES, kb_p, i + VDEPTH)
                                          : ldv(st_c * TILE_BYTES, kb_c, i + VDEPTH - PS);
 #pragma unroll
-      for (int jj = 0; jj < PPS; ++jj) exp_pair(cur, i * PPS + jj);
-      // within the step: an MFMA, the K fragment read, half of the vector work, the
-      // other MFMA, the two transposed V reads, the rest of the vector work
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x402, 3 * PPS, 0);
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
-      __builtin_amdgcn_sched_group_barrier(0x402, 3 * PPS, 0);
+      for (int j = 0; j < PPS; ++j) {
+        if (i + 1 < QS) {
+          y1[j] = score(cur, (i + 1) * PPS + j, 1);
+          asm volatile("" : "+v"(y1[j]));
+        }
+        round_pair(cur, i * PPS + j, p0[j], p1[j]);
+      }
       __builtin_amdgcn_sched_barrier(0);
     }
-    float rs = rs0 + rs1;
+    __builtin_amdgcn_s_setprio(0);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
     // pin the vector work above to this block: without a use here the compiler
     // sinks it below the branch that follows, away from the MFMAs it should hide under
-    asm volatile("" : "+v"(pf[cur].v[0]), "+v"(pf[cur].v[1]), "+v"(rs));
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) asm volatile("" : "+v"(pf[cur].v[cb]), "+v"(rs[cb]));
     __builtin_amdgcn_sched_barrier(0);
     if (u == 0) {
       // the O^T MFMAs of a piece's first body belong to no unit (zero probabilities
       // times whatever the ring stage held): the accumulation starts here
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db) 
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] = 0.f;
+        for (int cb = 0; cb < NCB; ++cb) o[db][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (__any(rs > kRowSumLimit)) {
+    if (__any(fmaxf(rs[0], rs[1]) > kRowSumLimit)) {
       // Some column saw a score far above its reference (or has no reference yet):
-      // take the unit's true maximum (one query column per lane, its key halves in
-      // lanes l and l^32), move every column's reference up to it, redo the unit's
+      // take the unit's true maximum (a column's keys are spread over the four lanes that
+      // share l16), move every column's reference up to it, redo the unit's
       // probabilities, and rescale what has been accumulated so far - unit u-1
       // included, whose MFMAs above still used the old reference.
-      float mx4[4];
+      float alpha[NCB];
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        mx4[q4] = fmaxf(fmaxf(fmaxf(s[cur][q4], s[cur][4 + q4]), s[cur][8 + q4]), s[cur][12 + q4]);
-      float mx = fmaxf(fmaxf(fmaxf(mx4[0], mx4[1]), mx4[2]), mx4[3]);
-      mx = fmaxf(mx, swap_halves(mx));
-      const float m_new = fmaxf(m_run, mx);
-      const float alpha = fast_exp2((m_run - m_new) * c);
-      m_run = m_new;
-      mc = m_run * c;
-      l_run *= alpha;
-      rs0 = 0.f;
-      rs1 = 0.f;
+      for (int cb = 0; cb < NCB; ++cb) {
+        const f32x4 &x = s[cur][0][cb], &y = s[cur][1][cb];
+        float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
+        mx = fmaxf(mx, swap_halves(mx));
+        mx = fmaxf(mx, __shfl_xor(mx, 16));
+        const float m_new = fmaxf(m_run[cb], mx);
+        alpha[cb] = fast_exp2((m_run[cb] - m_new) * c);
+        m_run[cb] = m_new;
+        mc[cb] = m_new * c;
+        l_run[cb] *= alpha[cb];
+      }
 #pragma unroll
-      for (int pr = 0; pr < 8; ++pr) exp_pair(cur, pr);
-      rs = rs0 + rs1;
+      for (int pr = 0; pr < 4 * NCB; ++pr) round_pair(cur, pr, fast_exp2(score(cur, pr, 0)), fast_exp2(score(cur, pr, 1)));
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
 #pragma unroll
       for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] *= alpha;
+        for (int cb = 0; cb < NCB; ++cb) o[db][cb] *= alpha[cb];
     }
-    l_run += rs;
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) l_run[cb] += rs[cb];
   };
 
   // iteration = one tile = units 2t and 2t+1 of the piece (U units in all); TC is
@@ -621,7 +669,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // requests its share of every key tile and joins the barriers, and leaves the
   // matrix and vector units of its SIMD to the waves that have rows.
   auto has_rows = [&](const AttnItem& a) __attribute__((always_inline)) -> bool {
-    return (int)(wave_rows >> 10) * 32 < tokens_of(a) * G;
+    return (int)(wave_rows >> 10) * WROWS < tokens_of(a) * G;
   };
   bool act = true;
   auto iteration = [&](auto TC, int t) __attribute__((always_inline)) {
@@ -649,25 +697,32 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     // (per-lane values that only matter here are recomputed from an opaque copy of the
     // lane number, see lane_now)
     const int ln_top = lane_now();
-    const int r_tile = (int)(wave_rows >> 10) * 32 + (ln_top & 31);   // the lane's row of the packed tile
-    const int tok = (int)(((uint32_t)r_tile * P.g_magic) >> 16);     // its token within the tile (r_tile / G)
-    const int tokc = min(tok, tokens_of(it) - 1);
-    lim = min(it.pos0 + tokc, it.k_end - 1) - 4 * (ln_top >> 5);
+#pragma unroll
+    for (int cb = 0; cb < NCB; ++cb) {
+      const int r_tile = (int)(wave_rows >> 10) * WROWS + 16 * cb + (ln_top & 15);   // the column's row of the packed tile
+      const int tok = (int)(((uint32_t)r_tile * P.g_magic) >> 16);               // its token within the tile (r_tile / G)
+      lim[cb] = min(it.pos0 + min(tok, tokens_of(it) - 1), it.k_end - 1) - 4 * (ln_top >> 4);
+    }
     min_lim = min(it.pos0, it.k_end - 1);
     const int nkeys = it.k_end - it.k_begin;
     const int nt = (nkeys + BN - 1) / BN;
     U = (nkeys + 31) / 32;
-    m_run = -1e30f;
-    l_run = 0.f;
     {
       float c_now = c;
       asm volatile("" : "+s"(c_now));
-      mc = m_run * c_now;
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        m_run[cb] = -1e30f;
+        l_run[cb] = 0.f;
+        mc[cb] = -1e30f * c_now;
+      }
     }
     // the accumulators start undefined (they are cleared after the first body, see
     // unit_body); saying so ends their live range at the previous piece's epilogue
 #pragma unroll
-    for (int db = 0; db < DB; ++db) asm volatile("" : "=v"(o[db]));
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) asm volatile("" : "=v"(o[db][cb]));
 
     // Whatever this wave still has in flight (the previous piece's stores, the tiles
     // requested ahead) is awaited here, on the path of every wave: left to the compiler,
@@ -682,11 +737,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
       for (int j = 0; j < KDEPTH; ++j) ka[j] = ldk(off0, 0, j);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s[0][r] = 0.f;
+      for (int e = 0; e < 2 * NCB; ++e) s[0][e % 2][e / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
       // ring position of unit 0 is 2*ph: s[] and pf[] are indexed by its parity, 0
 #pragma unroll
       for (int i = 0; i < QS; ++i) {
-        s[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ka[i % KDEPTH], qf[i], s[0], 0, 0, 0);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          s[0][i % 2][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[cb][i / 2], s[0][i % 2][cb], 0, 0, 0);
         ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(off0, 0, i + KDEPTH) : ldk(off0, 1, i + KDEPTH - QS);
         __builtin_amdgcn_sched_barrier(0);
       }
@@ -694,7 +751,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int j = 0; j < VDEPTH; ++j) vf[j] = ldv(offm, 1, j);
       const bf16x2 z2 = {(__bf16)0.0f, (__bf16)0.0f};
 #pragma unroll
-      for (int j = 0; j < 8; ++j) pf[1].h[j] = z2;
+      for (int j = 0; j < 4 * NCB; ++j) pf[1].h[j] = z2;
     }
 
     // tiles of the piece, the loop unrolled over the four ring stages
@@ -747,17 +804,17 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     };
     auto park = [&](int slot, const u32x4& x) __attribute__((always_inline)) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[1][4 * slot + e] = __uint_as_float(x[e]);
+      for (int e = 0; e < 4; ++e) s[1][slot % 2][slot / 2][e] = __uint_as_float(x[e]);
     };
     auto unpark = [&](int slot) __attribute__((always_inline)) -> u32x4 {
       u32x4 x;
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(s[1][4 * slot + e]);
+      for (int e = 0; e < 4; ++e) x[e] = __float_as_uint(s[1][slot % 2][slot / 2][e]);
       return x;
     };
     if (cp_on) {
 #pragma unroll
-      for (int ps = 0; ps < 2; ++ps) {
+      for (int ps = 0; ps < NCB; ++ps) {
         const int row = ps * CP_ROWS + cp_row;
         if (row < tokens_of(done)) {
           park(2 * ps, *(const u32x4*)(P.k_new + cp_src(row)));
@@ -774,28 +831,36 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       // the fragments preloaded by the last body belong to this unit already; its
       // probabilities are pf[ul & 1] (picked as values: an array indexed at run time
       // would be put into scratch memory)
-      bf16x8 e0 = pf[0].v[0], e1 = pf[0].v[1], d0 = pf[1].v[0], d1 = pf[1].v[1];
-      asm volatile("" : "+v"(e0), "+v"(e1), "+v"(d0), "+v"(d1));
       const bool odd = (ul & 1) != 0;
-      const bf16x8 pl[2] = {odd ? d0 : e0, odd ? d1 : e1};
+      bf16x8 pl[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        bf16x8 e0 = pf[0].v[cb], d0 = pf[1].v[cb];
+        asm volatile("" : "+v"(e0), "+v"(d0));
+        pl[cb] = odd ? d0 : e0;
+      }
 #pragma unroll
       for (int i = 0; i < PS; ++i) {
-        o[i % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[i % VDEPTH], pl[i / DB], o[i % DB], 0, 0, 0);
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          o[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pl[cb], o[i][cb], 0, 0, 0);
         if (i + VDEPTH < PS) vf[i % VDEPTH] = ldv(off, kb, i + VDEPTH);
       }
     }
 
     // ---- epilogue ---------------------------------------------------------------------
-    const float l_tot = l_run + __shfl_xor(l_run, 32);
     if (done.part < 0) {
       // final rows, turned around in the wave's staging area.  They (and the appended cache
       // rows further down) are stored with the non-temporal hint: nothing in this launch reads
       // them again, and lines that do not linger dirty in the level-2 cache need no write-back
       // when the kernel ends.
-      const float inv = 1.0f / l_tot;
+      float inv[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) inv[cb] = 1.0f / l_run[cb];
       const int ln = lane_now();
       const uint32_t roff = roff_of(ln), cx = cx_of(ln);
-      const uint32_t wbase = carea_of(st_area, ln) + (uint32_t)(ln >> 5) * 8u;
+      // the lane's four elements of a d-block are half (grp % 2) of slot 2 * (block) + grp / 2
+      const uint32_t cxg = cx ^ ((uint32_t)(ln >> 5) * 16u), half8 = (uint32_t)((ln >> 4) & 1) * 8u;
       int grow[2 * IPW];                // head-row (token * Hq + head) of the row in out, -1: not a row of this tile
 #pragma unroll
       for (int k = 0; k < 2 * IPW; ++k) {
@@ -806,13 +871,14 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
 #pragma unroll
-        for (int dbl = 0; dbl < DB / 2; ++dbl)
+        for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-          for (int b = 0; b < 4; ++b) {
+          for (int dbl = 0; dbl < DB / 2; ++dbl) {
             bf16x4 w;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[h * (DB / 2) + dbl][4 * b + e] * inv);
-            *(__attribute__((address_space(3))) bf16x4*)(lds_ptr)(uintptr_t)(wbase + ((uint32_t)((dbl * 4 + b) * 16) ^ cx)) = w;
+            for (int e = 0; e < 4; ++e) w[e] = (__bf16)(o[h * (DB / 2) + dbl][cb][e] * inv[cb]);
+            *(__attribute__((address_space(3))) bf16x4*)(lds_ptr)(uintptr_t)(carea_of(st_area, cb, ln) + half8 +
+                                                                            ((uint32_t)(dbl * 32) ^ cxg)) = w;
           }
 #pragma unroll
         for (int k = 0; k < 2 * IPW; ++k) {
@@ -823,35 +889,28 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       }
     } else {
       const int lnp = lane_now();
-      const int hip = lnp >> 5;
-      const int64_t slot = ((int64_t)done.part * Hkv + kvh) * kTileRows + (int)(wave_rows >> 10) * 32 + (lnp & 31);
-      float* po = P.part_o + slot * D;
+      const int64_t slot0 = ((int64_t)done.part * Hkv + kvh) * kTileRows + (int)(wave_rows >> 10) * WROWS + (lnp & 15);
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+      for (int cb = 0; cb < NCB; ++cb) {
+        float* po = P.part_o + (slot0 + 16 * cb) * D + 4 * (lnp >> 4);
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-          float4 w;
-          w.x = o[db][4 * b + 0];
-          w.y = o[db][4 * b + 1];
-          w.z = o[db][4 * b + 2];
-          w.w = o[db][4 * b + 3];
-          *(float4*)(po + db * 32 + 8 * b + 4 * hip) = w;
+        for (int db = 0; db < DB; ++db) *(f32x4*)(po + db * 16) = o[db][cb];
+        if (lnp < 16) {
+          P.part_ml[(slot0 + 16 * cb) * 2 + 0] = m_run[cb];
+          P.part_ml[(slot0 + 16 * cb) * 2 + 1] = l_run[cb];
         }
-      if (hip == 0) {
-        P.part_ml[slot * 2 + 0] = m_run;
-        P.part_ml[slot * 2 + 1] = l_tot;
       }
     }
     if (cp_on) {
 #pragma unroll
-      for (int ps = 0; ps < 2; ++ps) {
+      for (int ps = 0; ps < NCB; ++ps) {
         const int row = ps * CP_ROWS + cp_row;
         if (row < tokens_of(done)) {
           __builtin_nontemporal_store(unpark(2 * ps), (u32x4*)(P.k + cp_dst(row)));
           __builtin_nontemporal_store(unpark(2 * ps + 1), (u32x4*)(P.v + cp_dst(row)));
         }
       }
-      for (int row = 2 * CP_ROWS + cp_row; row < tokens_of(done); row += CP_ROWS) {
+      for (int row = NCB * CP_ROWS + cp_row; row < tokens_of(done); row += CP_ROWS) {
         const u32x4 a = *(const u32x4*)(P.k_new + cp_src(row));
         const u32x4 b = *(const u32x4*)(P.v_new + cp_src(row));
         __builtin_nontemporal_store(a, (u32x4*)(P.k + cp_dst(row)));
