@@ -218,6 +218,45 @@ def test_short_tiles_leave_waves_without_rows(gpu, G, D, split):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
+LENGTHS = [1, 31, 32, 33, 64, 225, 255, 256, 257, 300, 513, 1030]
+
+
+@pytest.mark.parametrize("G,Hkv,D,C,P,split", [
+    (4, 2, 128, 1, LENGTHS, 0), (4, 2, 128, 4, LENGTHS, 3), (4, 2, 128, 5, LENGTHS, 0), (4, 2, 128, 8, [1700, 1570], 0),
+    (4, 1, 128, 8, [1700, 6400], 3), (8, 1, 128, 2, LENGTHS, 0), (3, 3, 128, 5, LENGTHS, 0), (5, 2, 64, 3, LENGTHS, 2),
+    (1, 4, 64, 16, LENGTHS, 0), (1, 4, 64, 17, LENGTHS, 0), (1, 4, 64, 32, LENGTHS, 2), (1, 4, 64, 33, LENGTHS, 0),
+    (16, 1, 64, 2, LENGTHS, 0), (16, 2, 128, 1, LENGTHS, 0)])
+def test_few_rows_per_sequence(gpu, G, Hkv, D, C, P, split):
+    """Passes whose tiles have up to 16 or 32 packed rows (and one row more): contexts around the units of 32 keys and the
+    rounds of 256 that eight waves share, the chunk's own keys inside a unit or across two, ranges whole and cut."""
+    binding, episode, torch = gpu
+    B = len(P)
+    P, R = np.array(P, np.int32), np.full(B, 2 * C, np.int32) + np.arange(B, dtype=np.int32) % 2
+    ep = build_episode(small_cfg(B, G * Hkv, Hkv, D, C, seed=900 + G + C), threads=2, lengths=(P, R))
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        run_and_check(gpu, ep, oracle_uniform_chunks(P, R, C), None, f"G={G} D={D} C={C} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+
+
+@pytest.mark.parametrize("C,split", [(1, 0), (4, 3)])
+def test_few_rows_with_peaked_softmax(gpu, C, split):
+    """Few rows per sequence, logits of +-40 nats: the waves' shares of a piece meet with very different references, and
+    a wave moves its own again and again."""
+    binding, episode, torch = gpu
+    ep = build_episode(small_cfg(3, 8, 2, 128, C, seed=3141), threads=2,
+                       lengths=(np.array([300, 70, 1500], np.int32), np.full(3, 3 * C, np.int32)))
+    for t in (ep.q, ep.k):
+        nz = (t & 0x7F80) != 0                                  # times 4, zeros and subnormals as they are
+        t[nz] = (t[nz] + (2 << 7)).astype(np.uint16)
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        run_and_check(gpu, ep, oracle_uniform_chunks(ep.prompt_len, ep.resp_len, C), None, f"peaked C={C} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+
+
 def test_empty_batch_and_all_finished(gpu):
     binding, episode, torch = gpu
     cfg = small_cfg(3, 8, 2, 128, 32)
