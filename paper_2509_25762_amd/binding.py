@@ -89,27 +89,28 @@ def load() -> ctypes.CDLL:
     vp = ctypes.c_void_p
     lib.oppo_chunk_schedule.argtypes = [ctypes.c_int32, i32p, i32p, ctypes.c_int32, ctypes.c_int32, i32p, i32p, i32p]
     lib.oppo_chunk_schedule.restype = ctypes.c_int
-    lib.oppo_kv_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, vp, vp]
+    # (the calls of every pass take cu_q as bytes: numpy's ctypes pointers cost microseconds)
+    lib.oppo_kv_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, vp, vp]
     lib.oppo_kv_append.restype = ctypes.c_int
-    lib.oppo_qkv_rope_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, vp,
+    lib.oppo_qkv_rope_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, vp,
                                          ctypes.c_double, vp]
     lib.oppo_qkv_rope_append.restype = ctypes.c_int
-    lib.oppo_qkv_proj_rope_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, ctypes.c_int32,
+    lib.oppo_qkv_proj_rope_append.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, ctypes.c_int32,
                                               vp, vp, ctypes.c_double, vp, ctypes.c_size_t, vp]
     lib.oppo_qkv_proj_rope_append.restype = ctypes.c_int
     lib.oppo_qkv_proj_workspace_bytes.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32]
     lib.oppo_qkv_proj_workspace_bytes.restype = ctypes.c_size_t
-    lib.oppo_chunk_prefill_attn.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, vp,
+    lib.oppo_chunk_prefill_attn.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, vp,
                                             vp, ctypes.c_size_t, vp]
     lib.oppo_chunk_prefill_attn.restype = ctypes.c_int
-    lib.oppo_chunk_step.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, vp, vp, vp,
+    lib.oppo_chunk_step.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, vp, vp, vp,
                                     vp, ctypes.c_size_t, vp]
     lib.oppo_chunk_step.restype = ctypes.c_int
-    lib.oppo_chunk_step_noalloc.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), i32p, vp, vp, vp, vp, vp]
+    lib.oppo_chunk_step_noalloc.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheStruct), vp, vp, vp, vp, vp, vp]
     lib.oppo_chunk_step_noalloc.restype = ctypes.c_int
-    lib.oppo_kv_append_fp8.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheFp8Struct), i32p, vp, vp, vp]
+    lib.oppo_kv_append_fp8.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheFp8Struct), vp, vp, vp, vp]
     lib.oppo_kv_append_fp8.restype = ctypes.c_int
-    lib.oppo_chunk_prefill_attn_fp8.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheFp8Struct), i32p, vp, vp, vp,
+    lib.oppo_chunk_prefill_attn_fp8.argtypes = [ctypes.POINTER(AttnDesc), ctypes.POINTER(KVCacheFp8Struct), vp, vp, vp, vp,
                                                 ctypes.c_size_t, vp]
     lib.oppo_chunk_prefill_attn_fp8.restype = ctypes.c_int
     lib.oppo_static_scratch_bytes.argtypes = []
@@ -225,6 +226,8 @@ def _need_cache(desc, cache, name: str = "cache") -> None:
 def _stream_ptr(stream) -> Optional[int]:
     if stream is None:
         import torch
+        if hasattr(torch._C, "_cuda_getCurrentRawStream"):   # the address alone, without a stream object around it
+            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
         return torch.cuda.current_stream().cuda_stream
     if isinstance(stream, int):
         return stream
@@ -525,20 +528,23 @@ def oppo_workspace_bytes(desc: AttnDesc, max_batch: int, max_q_tokens: int) -> i
     return int(load().oppo_workspace_bytes(ctypes.byref(desc), max_batch, max_q_tokens))
 
 
-def _need_rows(desc: AttnDesc, cu: np.ndarray, **bufs) -> None:
-    """q / out hold cu[-1] rows of Hq heads, k_new / v_new of Hkv heads, qkv of Hq + 2 Hkv."""
-    rows = int(cu[-1]) if cu.shape[0] else 0
-    heads = {"q": desc.num_q_heads, "out": desc.num_q_heads, "q_out": desc.num_q_heads, "k_new": desc.num_kv_heads,
-             "v_new": desc.num_kv_heads, "qkv": desc.num_q_heads + 2 * desc.num_kv_heads}
-    for name, t in bufs.items():
-        _need(t, rows * heads[name] * desc.head_dim * 2, name)
+def _need_rows(desc: AttnDesc, cu: np.ndarray, q=None, k_new=None, v_new=None, out=None, qkv=None, q_out=None) -> None:
+    """q / out / q_out hold cu[-1] rows of Hq heads, k_new / v_new of Hkv heads, qkv of Hq + 2 Hkv."""
+    head_rows = (int(cu[-1]) if cu.shape[0] else 0) * desc.head_dim * 2
+    nq, nkv = head_rows * desc.num_q_heads, head_rows * desc.num_kv_heads
+    _need(q, nq, "q")
+    _need(k_new, nkv, "k_new")
+    _need(v_new, nkv, "v_new")
+    _need(out, nq, "out")
+    _need(qkv, nq + 2 * nkv, "qkv")
+    _need(q_out, nq, "q_out")
 
 
 def oppo_kv_append(desc: AttnDesc, cache: KVCache, cu_q, k_new, v_new, stream=None) -> None:
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, k_new=k_new, v_new=v_new)
     _need_cache(desc, cache)
-    _check(load().oppo_kv_append(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(k_new),
+    _check(load().oppo_kv_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(k_new),
                                  _dev_ptr(v_new), _stream_ptr(stream)))
 
 
@@ -547,7 +553,7 @@ def oppo_qkv_rope_append(desc: AttnDesc, cache: KVCache, cu_q, qkv, q_out, theta
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, qkv=qkv, q_out=q_out)
     _need_cache(desc, cache)
-    _check(load().oppo_qkv_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(qkv),
+    _check(load().oppo_qkv_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(qkv),
                                        _dev_ptr(q_out), float(theta_base), _stream_ptr(stream)))
 
 
@@ -566,7 +572,7 @@ def oppo_qkv_proj_rope_append(desc: AttnDesc, cache: KVCache, cu_q, x, hidden: i
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().oppo_qkv_proj_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(x), hidden,
+    _check(load().oppo_qkv_proj_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(x), hidden,
                                             _dev_ptr(w), _dev_ptr(q_out), float(theta_base), _dev_ptr(workspace), ws_bytes,
                                             _stream_ptr(stream)))
 
@@ -577,7 +583,7 @@ def oppo_chunk_prefill_attn(desc: AttnDesc, cache: KVCache, cu_q, q, out, worksp
     _need_rows(desc, cu, q=q, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_prefill_attn(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(q),
+    _check(load().oppo_chunk_prefill_attn(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
                                           _dev_ptr(out), _dev_ptr(workspace), ws_bytes, _stream_ptr(stream)))
 
 
@@ -587,7 +593,7 @@ def oppo_chunk_step(desc: AttnDesc, cache: KVCache, cu_q, q, k_new, v_new, out, 
     _need_rows(desc, cu, q=q, k_new=k_new, v_new=v_new, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_step(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(q),
+    _check(load().oppo_chunk_step(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
                                   _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(out), _dev_ptr(workspace), ws_bytes,
                                   _stream_ptr(stream)))
 
@@ -596,7 +602,7 @@ def oppo_kv_append_fp8(desc: AttnDesc, cache: KVCacheFp8, cu_q, k_new, v_new, st
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, k_new=k_new, v_new=v_new)
     _need_cache(desc, cache)
-    _check(load().oppo_kv_append_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(k_new),
+    _check(load().oppo_kv_append_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(k_new),
                                      _dev_ptr(v_new), _stream_ptr(stream)))
 
 
@@ -606,7 +612,7 @@ def oppo_chunk_prefill_attn_fp8(desc: AttnDesc, cache: KVCacheFp8, cu_q, q, out,
     _need_rows(desc, cu, q=q, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_prefill_attn_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(q),
+    _check(load().oppo_chunk_prefill_attn_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
                                               _dev_ptr(out), _dev_ptr(workspace), ws_bytes, _stream_ptr(stream)))
 
 
@@ -615,7 +621,7 @@ def oppo_chunk_step_noalloc(desc: AttnDesc, cache: KVCache, cu_q, q, k_new, v_ne
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, q=q, k_new=k_new, v_new=v_new, out=out)
     _need_cache(desc, cache)
-    _check(load().oppo_chunk_step_noalloc(ctypes.byref(desc), ctypes.byref(cache.struct), _i32p(cu), _dev_ptr(q),
+    _check(load().oppo_chunk_step_noalloc(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
                                           _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(out), _stream_ptr(stream)))
 
 

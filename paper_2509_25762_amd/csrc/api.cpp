@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cmath>
+#include <cstdlib>
 #include <mutex>
 #include <vector>
 
@@ -226,6 +227,62 @@ struct QTile { int seq; int32_t j0, n_tok, keys, ntile; };
 // Key tiles [t0, t1) of query tile `tile`, run by `queue`; rank = place in the scheduling order.
 struct Piece { int tile; int t0, t1; int queue; int rank; };
 
+// The most and the least loaded of n queues, kept while single loads change: two tournaments over the queue numbers
+// (ties go to the lower number), O(log n) per change.
+class Extremes {
+ public:
+  explicit Extremes(const std::vector<float>& load) : load_(load), base_(1) {
+    const int n = (int)load.size();
+    while (base_ < n) base_ *= 2;
+    least_.assign((size_t)(2 * base_), -1);
+    most_.assign((size_t)(2 * base_), -1);
+    for (int j = 0; j < n; ++j) least_[(size_t)(base_ + j)] = most_[(size_t)(base_ + j)] = j;
+    for (int k = base_ - 1; k >= 1; --k) play(k);
+  }
+  int least() const { return least_[1]; }
+  int most() const { return most_[1]; }
+  void changed(int j) {
+    for (int k = (base_ + j) / 2; k >= 1; k /= 2) play(k);
+  }
+
+ private:
+  void play(int k) {
+    const int a = least_[(size_t)(2 * k)], b = least_[(size_t)(2 * k + 1)];   // (only the right one may be missing)
+    least_[(size_t)k] = b >= 0 && load_[(size_t)b] < load_[(size_t)a] ? b : a;
+    const int c = most_[(size_t)(2 * k)], d = most_[(size_t)(2 * k + 1)];
+    most_[(size_t)k] = d >= 0 && load_[(size_t)d] > load_[(size_t)c] ? d : c;
+  }
+  const std::vector<float>& load_;
+  int base_;
+  std::vector<int> least_, most_;
+};
+
+// Which pieces each queue holds, in the order they came: one linked list per queue over the piece numbers, in four arrays
+// (a vector per queue costs its allocations: 128 queues spent 20 us on them).
+class QueueLists {
+ public:
+  QueueLists(size_t queues, size_t pieces) : head_(queues, -1), tail_(queues, -1), next_(pieces, -1), prev_(pieces, -1) {}
+  int first(int q) const { return head_[(size_t)q]; }
+  int last(int q) const { return tail_[(size_t)q]; }
+  int after(int x) const { return next_[(size_t)x]; }
+  void append(int q, int x) {
+    if ((size_t)x >= next_.size()) next_.resize((size_t)x + 1, -1), prev_.resize((size_t)x + 1, -1);
+    const int t = tail_[(size_t)q];
+    prev_[(size_t)x] = t;
+    next_[(size_t)x] = -1;
+    (t < 0 ? head_[(size_t)q] : next_[(size_t)t]) = x;
+    tail_[(size_t)q] = x;
+  }
+  void remove(int q, int x) {
+    const int p = prev_[(size_t)x], n = next_[(size_t)x];
+    (p < 0 ? head_[(size_t)q] : next_[(size_t)p]) = n;
+    (n < 0 ? tail_[(size_t)q] : prev_[(size_t)n]) = p;
+  }
+
+ private:
+  std::vector<int> head_, tail_, next_, prev_;
+};
+
 // Plans one launch for the query tiles [lo, hi).
 //
 // The kernel runs one persistent workgroup per (queue, kv-head); the planner
@@ -339,9 +396,14 @@ class LaunchPlanner {
     std::vector<float> load((size_t)Q_, 0.f);
     int rank = 0;
     auto len_of = [&](int32_t a) { return pcs[(size_t)a].t1 - pcs[(size_t)a].t0; };
-    int qs[oppo::kMaxQueues];
+    Extremes ends(load);
+    // Groups of cached_g queues, each sorted as below, for as long as the gangs have one size; those a gang went to are
+    // sorted anew (-1).
+    int cached_g = 0, cached_step = 0;
+    std::vector<int> sorted;     // [group][cached_g]
+    std::vector<char> stale;
     // the queues st, st+1, .. of a group of g, least loaded first (ties: lowest index)
-    auto group_sorted = [&](int st, int g) {
+    auto group_sorted = [&](int* qs, int st, int g) {
       for (int m = 0; m < g; ++m) {
         const int qn = (st + m) % Q_;
         int k = m;
@@ -357,29 +419,42 @@ class LaunchPlanner {
         std::stable_sort(m_begin, m_end, [&](int32_t a, int32_t b) { return len_of(a) > len_of(b); });
       for (int32_t* m0 = m_begin; m0 < m_end; m0 += Q_) {
         const int g = (int)std::min<ptrdiff_t>(Q_, m_end - m0);
-        int best_start = 0;
-        if (g == 1) {
-          for (int st = 1; st < Q_; ++st)
-            if (load[(size_t)st] < load[(size_t)best_start]) best_start = st;
-        } else {
-          int step = 1;   // largest divisor of Q that does not exceed the gang
-          for (int d = 1; d <= g; ++d)
-            if (Q_ % d == 0) step = d;
-          float best = 0.f;
-          best_start = -1;
-          for (int st = 0; st < Q_; st += step) {
-            group_sorted(st, g);
-            float mx = 0.f;
-            for (int m = 0; m < g; ++m) mx = std::max(mx, load[(size_t)qs[m]] + (float)len_of(m0[m]));
-            if (best_start < 0 || mx < best) best = mx, best_start = st;
-          }
-        }
-        group_sorted(best_start, g);
-        for (int m = 0; m < g; ++m) {
-          Piece& pc = pcs[(size_t)m0[m]];
-          pc.queue = qs[m];
+        auto give = [&](int32_t a, int queue) {
+          Piece& pc = pcs[(size_t)a];
+          pc.queue = queue;
           pc.rank = rank++;
-          load[(size_t)pc.queue] += cost(pc);
+          load[(size_t)queue] += cost(pc);
+          ends.changed(queue);
+        };
+        if (g == 1) {
+          const int queue = ends.least();
+          give(*m0, queue);
+          for (int st = 0; cached_g > 0 && st < Q_; st += cached_step)
+            if ((queue - st + Q_) % Q_ < cached_g) stale[(size_t)(st / cached_step)] = 1;
+          continue;
+        }
+        if (g != cached_g) {
+          cached_g = g;
+          for (int d = 1; d <= g; ++d)
+            if (Q_ % d == 0) cached_step = d;   // largest divisor of Q that does not exceed the gang
+          sorted.resize((size_t)(Q_ / cached_step * g));
+          stale.assign((size_t)(Q_ / cached_step), 1);
+        }
+        float best = 0.f;
+        int best_group = -1;
+        for (int k = 0; k < Q_ / cached_step; ++k) {
+          int* qs = sorted.data() + (size_t)(k * g);
+          if (stale[(size_t)k]) group_sorted(qs, k * cached_step, g), stale[(size_t)k] = 0;
+          float mx = 0.f;
+          for (int m = 0; m < g && (best_group < 0 || mx < best); ++m)
+            mx = std::max(mx, load[(size_t)qs[m]] + (float)len_of(m0[m]));
+          if (best_group < 0 || mx < best) best = mx, best_group = k;
+        }
+        const int* qs = sorted.data() + (size_t)(best_group * g);
+        for (int m = 0; m < g; ++m) give(m0[m], qs[m]);
+        for (int k = 0; k < Q_ / cached_step; ++k) {   // groups with a queue of this one
+          const int apart = std::abs(k - best_group) * cached_step;
+          if (std::min(apart, Q_ - apart) < g) stale[(size_t)k] = 1;
         }
       }
     }
@@ -395,45 +470,44 @@ class LaunchPlanner {
   // sorted by cost.
   void exchange(std::vector<Piece>& pcs) const {
     std::vector<float> load((size_t)Q_, 0.f);
-    std::vector<std::vector<int>> on((size_t)Q_);
+    QueueLists on((size_t)Q_, pcs.size());
     std::vector<int> per_seq(seqs_.size(), 0);
     for (size_t x = 0; x < pcs.size(); ++x) {
       load[(size_t)pcs[x].queue] += cost(pcs[x]);
-      on[(size_t)pcs[x].queue].push_back((int)x);
+      on.append(pcs[x].queue, (int)x);
       ++per_seq[(size_t)seq_of(pcs[x])];
     }
+    Extremes ends(load);
     // does `queue` hold a piece of x's sequence other than `except`?  (only sequences with
     // several pieces need the scan)
     auto holds = [&](int queue, int x, int except) {
       if (per_seq[(size_t)seq_of(pcs[(size_t)x])] < 2) return false;
-      for (int z : on[(size_t)queue])
+      for (int z = on.first(queue); z >= 0; z = on.after(z))
         if (z != except && z != x && seq_of(pcs[(size_t)z]) == seq_of(pcs[(size_t)x])) return true;
       return false;
     };
     auto move = [&](int x, int from, int to) {
-      std::vector<int>& f = on[(size_t)from];
-      f.erase(std::find(f.begin(), f.end(), x));
-      on[(size_t)to].push_back(x);
+      on.remove(from, x);
+      on.append(to, x);
       pcs[(size_t)x].queue = to;
       load[(size_t)from] -= cost(pcs[(size_t)x]), load[(size_t)to] += cost(pcs[(size_t)x]);
+      ends.changed(from);
+      ends.changed(to);
     };
     std::vector<int> sorted_b;
     for (int round = 0; round < 4 * Q_; ++round) {
-      int a = 0, b = 0;
-      for (int j = 1; j < Q_; ++j) {
-        if (load[(size_t)j] > load[(size_t)a]) a = j;
-        if (load[(size_t)j] < load[(size_t)b]) b = j;
-      }
+      const int a = ends.most(), b = ends.least();
       const float gap = load[(size_t)a] - load[(size_t)b];
       if (gap < 1.0f) break;   // nothing can gain the half tile a move has to gain
       float best = load[(size_t)a] - 0.5f;
       int bx = -1, by = -1;
-      sorted_b = on[(size_t)b];
+      sorted_b.clear();
+      for (int y = on.first(b); y >= 0; y = on.after(y)) sorted_b.push_back(y);
       std::sort(sorted_b.begin(), sorted_b.end(), [&](int p, int q) {
         const float cp = cost(pcs[(size_t)p]), cq = cost(pcs[(size_t)q]);
         return cp < cq || (cp == cq && p < q);
       });
-      for (int x : on[(size_t)a]) {
+      for (int x = on.first(a); x >= 0; x = on.after(x)) {
         const float cx = cost(pcs[(size_t)x]);
         if (std::max(load[(size_t)a] - cx, load[(size_t)b] + cx) < best && !holds(b, x, -1))
           best = std::max(load[(size_t)a] - cx, load[(size_t)b] + cx), bx = x, by = -1;
@@ -467,33 +541,32 @@ class LaunchPlanner {
     const size_t n = hi_ - lo_;
     std::vector<float> load((size_t)Q_, 0.f);
     std::vector<int> n_of_tile(n, 0);
-    std::vector<std::vector<int>> on((size_t)Q_);   // pieces of each queue, by rank
+    std::vector<int> by_rank(pcs.size());   // (the gangs' ranks are the numbers 0 .. pieces - 1)
     for (size_t k = 0; k < pcs.size(); ++k) {
       load[(size_t)pcs[k].queue] += cost(pcs[k]);
       ++n_of_tile[(size_t)pcs[k].tile - lo_];
-      on[(size_t)pcs[k].queue].push_back((int)k);
+      by_rank[(size_t)pcs[k].rank] = (int)k;
     }
-    for (std::vector<int>& v : on)
-      std::sort(v.begin(), v.end(), [&](int p, int q) { return pcs[(size_t)p].rank < pcs[(size_t)q].rank; });
+    QueueLists on((size_t)Q_, pcs.size() + (size_t)Q_);   // pieces of each queue, by rank
+    for (int k : by_rank) on.append(pcs[(size_t)k].queue, k);
+    Extremes ends(load);
     size_t n_partial = 0;
     int rank = (int)pcs.size();
     for (int added = 0, moves = 0; added + 1 < Q_ && moves < 8 * Q_; ++moves) {
-      int a = 0, b = 0;
-      for (int j = 1; j < Q_; ++j) {
-        if (load[(size_t)j] > load[(size_t)a]) a = j;
-        if (load[(size_t)j] < load[(size_t)b]) b = j;
-      }
+      const int a = ends.most(), b = ends.least();
       const float gap = load[(size_t)a] - load[(size_t)b];
-      if (on[(size_t)a].empty()) break;
-      const int last = on[(size_t)a].back();   // the piece queue a runs last
+      const int last = on.last(a);   // the piece queue a runs last
+      if (last < 0) break;
       const int len = pcs[(size_t)last].t1 - pcs[(size_t)last].t0;
       const bool whole = n_of_tile[(size_t)pcs[(size_t)last].tile - lo_] == 1;
       const float own = (float)len + kPieceTiles + (whole ? 0.f : kPartialTiles);
       if (own < gap) {   // the whole piece moves
         load[(size_t)a] -= own;
         load[(size_t)b] += own;
-        on[(size_t)a].pop_back();
-        on[(size_t)b].push_back(last);
+        ends.changed(a);
+        ends.changed(b);
+        on.remove(a, last);
+        on.append(b, last);
         pcs[(size_t)last].queue = b;
         pcs[(size_t)last].rank = rank++;
         continue;
@@ -510,7 +583,9 @@ class LaunchPlanner {
       pcs[(size_t)last].t1 = t1 - x;
       load[(size_t)a] += fresh - (float)x;
       load[(size_t)b] += (float)x + kPieceTiles + kPartialTiles;
-      on[(size_t)b].push_back((int)pcs.size());
+      ends.changed(a);
+      ends.changed(b);
+      on.append(b, (int)pcs.size());
       pcs.push_back(Piece{pcs[(size_t)last].tile, t1 - x, t1, b, rank++});
       ++added;
     }
@@ -556,15 +631,29 @@ class LaunchPlanner {
   // Pieces in launch order (grouped by queue), partial slots, merge items.
   void emit(const std::vector<Piece>& chosen, size_t* next_slot, Plan* plan) const {
     const size_t n = hi_ - lo_;
+    // by queue, and within a queue by rank, input order or length: two counting sorts (ranks are all different)
     std::vector<size_t> idx(chosen.size());
-    for (size_t i = 0; i < idx.size(); ++i) idx[i] = i;
-    auto len_of = [&](size_t a) { return chosen[a].t1 - chosen[a].t0; };
-    std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
-      if (chosen[a].queue != chosen[b].queue) return chosen[a].queue < chosen[b].queue;
-      if (opt_.order == 1) return a < b;
-      if (opt_.order == 2) return len_of(a) < len_of(b);
-      return chosen[a].rank < chosen[b].rank;
-    });
+    if (opt_.order == 1 || opt_.order == 2) {
+      for (size_t i = 0; i < idx.size(); ++i) idx[i] = i;
+      if (opt_.order == 2)
+        std::stable_sort(idx.begin(), idx.end(), [&](size_t a, size_t b) {
+          return chosen[a].t1 - chosen[a].t0 < chosen[b].t1 - chosen[b].t0;
+        });
+    } else {
+      int most = -1;
+      for (const Piece& pc : chosen) most = std::max(most, pc.rank);
+      std::vector<int> at((size_t)(most + 1), -1);
+      for (size_t i = 0; i < chosen.size(); ++i) at[(size_t)chosen[i].rank] = (int)i;
+      size_t k = 0;
+      for (int i : at)
+        if (i >= 0) idx[k++] = (size_t)i;
+    }
+    {
+      std::vector<size_t> next((size_t)Q_ + 1, 0), in(idx);
+      for (const Piece& pc : chosen) ++next[(size_t)pc.queue + 1];
+      for (int j = 0; j < Q_; ++j) next[(size_t)j + 1] += next[(size_t)j];
+      for (size_t a : in) idx[next[(size_t)chosen[a].queue]++] = a;
+    }
     // partial slots: the pieces of a split tile take consecutive slots in key order
     std::vector<int32_t> slot_of(chosen.size(), -1);
     {
@@ -622,6 +711,9 @@ class LaunchPlanner {
 void make_plans(const Options& opt, const oppo::LayerShape& ls, const std::vector<SeqView>& seqs, size_t slots_avail,
                 std::vector<Plan>* plans) {
   std::vector<QTile> tiles;
+  size_t n_tiles = 0;
+  for (const SeqView& s : seqs) n_tiles += (size_t)((s.q_len + ls.TM - 1) / ls.TM);
+  tiles.reserve(n_tiles);
   for (size_t i = 0; i < seqs.size(); ++i) {
     const SeqView& s = seqs[i];
     for (int32_t j0 = 0; j0 < s.q_len; j0 += ls.TM) {

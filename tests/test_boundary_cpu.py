@@ -3,6 +3,7 @@ declares, validates arguments before touching the GPU, and its host logic
 (chunk schedule, work planner) agrees with the oracle / with first principles.
 No kernel is launched here."""
 import ctypes
+import hashlib
 import os
 import re
 
@@ -615,3 +616,26 @@ def test_fp8_cache_validation_leaves_lengths_untouched(lib):
         ob.oppo_kv_append_fp8(desc, ok, [0, 1, 2], kv, Dev(2 * 8 * 128 * 2 - 1), stream=0)
     with pytest.raises(ValueError, match="out holds"):
         ob.oppo_chunk_prefill_attn_fp8(desc, ok, [0, 1, 1], Dev(32 * 128 * 2), Dev(32 * 128 * 2 - 2), stream=0)
+
+
+def test_plans_are_these_plans(lib):
+    """The planner's choices over passes of all shapes, to the piece: where its bookkeeping changes, they must not.
+    (The digest was taken with the loads searched queue by queue and a vector of pieces per queue.)"""
+    rng = np.random.default_rng(20)
+    digest = hashlib.sha256()
+    try:
+        for _ in range(120):
+            hq, hkv, d = [(32, 8, 128), (64, 8, 128), (8, 2, 128), (4, 4, 64), (6, 2, 128), (5, 5, 64)][rng.integers(6)]
+            B = int(np.exp(rng.uniform(0, np.log(300))))
+            kvb = rng.integers(0, int(np.exp(rng.uniform(np.log(2), np.log(9000)))), size=B)
+            C = int(np.exp(rng.uniform(0, np.log(1500))))
+            ql = np.full(B, C) if rng.random() < 0.5 else rng.integers(0, C + 1, size=B)
+            for option, value in ((ob.OPT_SPLIT_KV, [0, 0, 0, 1, 3][rng.integers(5)]), (ob.OPT_ORDER, [0, 0, 1, 2][rng.integers(4)]),
+                                  (ob.OPT_NUM_CUS, [256, 256, 304, 60][rng.integers(4)])):
+                ob.oppo_set_option(option, value)
+            digest.update(ob.oppo_plan_debug(ob.make_desc(hq, hkv, d, 0.1), kvb, ql, 1 << 30).tobytes())
+    finally:
+        ob.oppo_set_option(ob.OPT_SPLIT_KV, 0)
+        ob.oppo_set_option(ob.OPT_ORDER, 0)
+        ob.oppo_set_option(ob.OPT_NUM_CUS, 256)
+    assert digest.hexdigest() == "efafc39d4addf4b4c248852543fa9e92361a6dca3ca77ee3d43589f1a6670f23"
