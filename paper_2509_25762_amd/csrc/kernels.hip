@@ -508,7 +508,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   AttnItem it = piece(p_first);
   int lim[NCB];      // last key each of the lane's columns may see, minus 4 * grp: compared with the key
                      // that lane group 0 has in the same register, see the mask in unit_body
-  int min_lim = 0;   // smallest such limit in the workgroup: units entirely below it need no mask
+  int min_lim = 0;   // smallest such limit in the wave: units entirely below it need no mask
 
   // Pair pr of a unit's scores, and so of its probabilities: keys 2 * (pr % 2) and the next of 16-key block
   // (pr / 2) % 2, column block pr / 4.
@@ -666,6 +666,11 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // the tile's ring stage.  The tile two places down the stream is requested at
   // its start and awaited at its end, before the barrier after which the next
   // iteration starts reading the tile in between.
+  // U: the units of the piece up to the last key that any of the wave's rows may see.  The causal limit of a tile's rows
+  // differs by up to its number of tokens, so the first waves are through before the last; they go on requesting
+  // tiles and joining barriers and leave the matrix cores, and the power, to the others.  One run, us, every wave to the
+  // piece's end / so: prompts of 512 .. 2048 tokens 527 / 520, of 233 .. 570 147 / 144, of 305 .. 737 with 16/4 heads of 64
+  // 108 / 104, 64 x 256 rows on 262 .. 1017 keys 232 / 229.
   int U = 0;
   // A wave whose 32 rows all lie beyond the tile's tokens (a short tile fills the
   // first n_tok * G rows only) does none of the arithmetic of the piece: it still
@@ -706,10 +711,16 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       const int tok = (int)(((uint32_t)r_tile * P.g_magic) >> 16);               // its token within the tile (r_tile / G)
       lim[cb] = min(it.pos0 + min(tok, tokens_of(it) - 1), it.k_end - 1) - 4 * (ln_top >> 4);
     }
-    min_lim = min(it.pos0, it.k_end - 1);
     const int nkeys = it.k_end - it.k_begin;
     const int nt = (nkeys + BN - 1) / BN;
-    U = (nkeys + 31) / 32;
+    {
+      const int row0 = (int)(wave_rows >> 10) * WROWS, row1 = min(row0 + WROWS, tokens_of(it) * G) - 1;   // (act: row0 <= row1)
+      const int tok0 = (int)(((uint32_t)row0 * P.g_magic) >> 16), tok1 = (int)(((uint32_t)max(row1, 0) * P.g_magic) >> 16);
+      min_lim = min(it.pos0 + tok0, it.k_end - 1);
+      // (a piece that starts behind what the wave's rows see: one unit, all of it masked)
+      U = max(min(it.pos0 + tok1, it.k_end - 1) - it.k_begin, 0) / 32 + 1;
+    }
+    const int nt_own = act ? (U + 1) / 2 : 0;   // tiles with such a unit
     {
       float c_now = c;
       asm volatile("" : "+s"(c_now));
@@ -758,7 +769,32 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     }
 
     // tiles of the piece, the loop unrolled over the four ring stages
-    const int tau1 = ph + nt;
+    // O^T += V^T P^T of the last unit
+    auto drain = [&]() __attribute__((always_inline)) {
+      const int ul = U - 1;
+      const int off = (((ul >> 1) + ph) & 3) * TILE_BYTES;
+      const int kb = ul & 1;
+      // the fragments preloaded by the last body belong to this unit already; its
+      // probabilities are pf[ul & 1] (picked as values: an array indexed at run time
+      // would be put into scratch memory)
+      const bool odd = (ul & 1) != 0;
+      bf16x8 pl[NCB];
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        bf16x8 e0 = pf[0].v[cb], d0 = pf[1].v[cb];
+        asm volatile("" : "+v"(e0), "+v"(d0));
+        pl[cb] = odd ? d0 : e0;
+      }
+#pragma unroll
+      for (int i = 0; i < PS; ++i) {
+#pragma unroll
+        for (int cb = 0; cb < NCB; ++cb)
+          o[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pl[cb], o[i][cb], 0, 0, 0);
+        if (i + VDEPTH < PS) vf[i % VDEPTH] = ldv(off, kb, i + VDEPTH);
+      }
+    };
+    const int tau1 = ph + nt_own;
+    const bool early = act && nt_own < nt;   // (the last unit's values are overwritten two iterations on)
     if (act) {
       for (int tb = 0; tb < tau1; tb += 4) {
         if (tb >= ph) iteration(std::integral_constant<int, 0>{}, tb - ph);
@@ -766,13 +802,16 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
         if (tb + 2 >= ph && tb + 2 < tau1) iteration(std::integral_constant<int, 2>{}, tb + 2 - ph);
         if (tb + 3 >= ph && tb + 3 < tau1) iteration(std::integral_constant<int, 3>{}, tb + 3 - ph);
       }
-    } else {
-      // (the same requests, waits and barriers as `iteration`, nothing else)
-      for (int t = 0; t < nt; ++t) {
-        issue_next((ph + t + 2) & 3);
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-        wg_barrier();
+      if (early) {
+        drain();
+        __builtin_amdgcn_s_waitcnt(0xC07F);   // lgkmcnt(0): its reads are through before the barriers behind which the stage is refilled
       }
+    }
+    // (the same requests, waits and barriers as `iteration`, nothing else)
+    for (int t = nt_own; t < nt; ++t) {
+      issue_next((ph + t + 2) & 3);
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+      wg_barrier();
     }
 
     // request the next piece's Q rows; they are collected after the epilogue
@@ -826,30 +865,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       }
     }
 
-    // ---- drain: O^T += V^T P^T of the last unit ----------------------------------------
-    {
-      const int ul = U - 1;
-      const int off = (((ul >> 1) + ph) & 3) * TILE_BYTES;
-      const int kb = ul & 1;
-      // the fragments preloaded by the last body belong to this unit already; its
-      // probabilities are pf[ul & 1] (picked as values: an array indexed at run time
-      // would be put into scratch memory)
-      const bool odd = (ul & 1) != 0;
-      bf16x8 pl[NCB];
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        bf16x8 e0 = pf[0].v[cb], d0 = pf[1].v[cb];
-        asm volatile("" : "+v"(e0), "+v"(d0));
-        pl[cb] = odd ? d0 : e0;
-      }
-#pragma unroll
-      for (int i = 0; i < PS; ++i) {
-#pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
-          o[i][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pl[cb], o[i][cb], 0, 0, 0);
-        if (i + VDEPTH < PS) vf[i % VDEPTH] = ldv(off, kb, i + VDEPTH);
-      }
-    }
+    if (!early) drain();
 
     // ---- epilogue ---------------------------------------------------------------------
     if (done.part < 0) {

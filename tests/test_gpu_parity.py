@@ -257,6 +257,22 @@ def test_few_rows_with_peaked_softmax(gpu, C, split):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
+@pytest.mark.parametrize("G,D,split", [(1, 128, 0), (1, 64, 2), (4, 128, 0), (4, 128, 3), (8, 128, 0), (16, 64, 0), (3, 128, 2)])
+def test_waves_that_end_before_the_piece(gpu, G, D, split):
+    """Tall tiles on contexts of every remainder modulo the 32-key unit and the 64-key tile: the waves of a tile see their last
+    keys up to eight units apart, and in a cut piece behind the first waves' limits they see none."""
+    binding, episode, torch = gpu
+    tm = 256 // G
+    P = np.array([1, 15, 31, 32, 33, 63, 64, 65, 97, 130, 250], np.int32)
+    R = np.full(len(P), tm + max(1, tm // 3), np.int32)
+    ep = build_episode(small_cfg(len(P), 2 * G, 2, D, tm, seed=1100 + G), threads=2, lengths=(P, R))
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        run_and_check(gpu, ep, oracle_uniform_chunks(P, R, tm), None, f"G={G} D={D} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+
+
 def test_empty_batch_and_all_finished(gpu):
     binding, episode, torch = gpu
     cfg = small_cfg(3, 8, 2, 128, 32)
