@@ -653,10 +653,12 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int pr = 0; pr < 4 * NCB; ++pr) round_pair(cur, pr, fast_exp2(score(cur, pr, 0)), fast_exp2(score(cur, pr, 1)));
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
+      if (u != 0) {   // (a piece's first unit always comes here and has accumulated nothing)
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
+        for (int db = 0; db < DB; ++db)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) o[db][cb] *= alpha[cb];
+          for (int cb = 0; cb < NCB; ++cb) o[db][cb] *= alpha[cb];
+      }
     }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) l_run[cb] += rs[cb];
