@@ -32,10 +32,10 @@ int fail(int code, const char* fmt, ...) {
 // a tile costs besides (its first operands' arrival, the rotation, the stores) shares the memory and goes with the
 // number of tiles.  us of a launch ~ launch + tile * tiles / 256 + k_tile * rounds * (hidden / 64), with coefficients
 // fitted to 2,200 passes of 8 .. 40,000 rows, hidden 64 .. 8192 and 768 .. 10,240 columns that were timed with
-// every kind of tile, such that the cheapest estimate is the fastest kind: over these it is 0.13 % off on the mean and
-// 3.5 % in the worst hundredth.  The phased kernel multiplies faster but stores 32 bytes per row and lane, and pays
-// from about 24 k tiles on (30,000 rows, hidden 256 -> 10,240 columns: 424 us phased, 341 with 128-row tiles; 13,568
-// rows, hidden 4096 -> 6144: 514 us phased, 559 not).  Thin passes spread over more compute units with lower tiles,
+// every kind of tile, such that the cheapest estimate is the fastest kind.  (Since its MFMAs changed the phased kernel is
+// faster than these say: over 13,660 other passes the choice is 0.6 % off on the mean, new coefficients would bring that
+// to 0.2 %.)  The phased kernel multiplies faster and costs more per tile, so it pays on long k loops (us, phased / not:
+// 30,941 rows, hidden 256 -> 10,240 columns 352 / 347; 13,510 rows, hidden 4480 -> 6144 531 / 618).  Thin passes spread over more compute units with lower tiles,
 // and a pass whose last round of tall tiles would be mostly empty sends the rows that fill its rounds with them and
 // the rest in a launch of its own (56 of the 2,200: 0.92 to 1.03 of the best single launch, 0.983 on the mean).
 ProjPlan plan_qkv_proj(int32_t rows, int32_t n_out, int32_t hidden) {

@@ -395,10 +395,10 @@ __global__ __launch_bounds__(512) void qkv_proj_kernel(const ProjParams P) {
 // stay for several tiles, requesting the next tile's first operands before they store the current one.
 // Tiles of 192 rows are the same with a second x half of 64 rows (M1 = 1 block of 32 rows per wave
 // instead of 2); its LDS rows stay where the 128-row half has each wave row's first block.
-// Measured in one run, 4096 -> 6144, tiles of 256 rows in the loop of qkv_proj_kernel / here: 13,568 rows (five full
-// rounds) 559 / 514 us (1330 TFLOP/s), 15,099 rows 640 / 597, 2048 rows 96 / 93; back to back for longer the clocks
-// fall and 15,202 rows take 679 / 642.  Tiles of 192 rows against those of 256: 1404 rows 75 / 80 us, 2700 146 / 170,
-// 6144 252 / 275.  A tile's fixed cost is the price: where the k loop is short, qkv_proj_kernel is faster (plan_qkv_proj).
+// Measured in one run, -> 6144 columns, tiles of 256 rows in the loop of qkv_proj_kernel / here: 13,510 rows of 4480
+// 618 / 531 us (1400 TFLOP/s), 6223 of 4352 330 / 289, 2477 of 4288 119 / 105, 1482 of 3968 93 / 84.  Tiles of 256 rows
+// against those of 192: 1482 rows 84 / 75 us, 2477 105 / 155, 5612 of 3968 256 / 229.
+// A tile's fixed cost is the price: where the k loop is short, qkv_proj_kernel is faster (plan_qkv_proj).
 template <int D, int BM>
 __global__ __launch_bounds__(512) void qkv_proj_phased_kernel(const ProjParams P) {
   static_assert(BM == 256 || BM == 192, "x halves of 128 and 128 or 64 rows");

@@ -44,8 +44,9 @@ typedef __attribute__((ext_vector_type(8))) int i32x8;
 // Work lists travel in the kernel arguments, which the host writes anew for every launch, across
 // the bus, at their full length however few items are in use.  Each of these kernels therefore exists with
 // a short list as well, and the launcher takes the short one whenever the work fits it.  A step of
-// 4 sequences x 32 tokens takes 16.6 us with the long list and 14.8 with the short one; at the lists' limits,
-// one-row sequences, us per call: 64 / 65 appended 11.5 / 12.0 (8-bit 11.1 / 11.8), attention in 96 / 97 pieces
+// 4 sequences x 32 tokens took 16.6 us with the long list and 14.8 with the short one when the call itself took 5 us
+// longer than it does now; at the lists' limits,
+// one-row sequences, us per call (likewise): 64 / 65 appended 11.5 / 12.0 (8-bit 11.1 / 11.8), attention in 96 / 97 pieces
 // 82.6 / 84.3, in 96 / 98 pieces that are merged 36.4 / 38.5.  (Replayed from a captured
 // graph both lists take the same time.)
 constexpr int kFewAttnItems = 96;
