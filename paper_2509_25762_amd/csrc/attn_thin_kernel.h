@@ -94,18 +94,20 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
     const bool mixed = APPEND && r_cached > 0 && r_cached < UK && r_cached <= last;
     const bool all_new = APPEND && r_cached <= 0;
     const uintptr_t bk = all_new ? r_kn : r_k, bv = bk + (all_new ? kn_to_vn : k_to_v);
+    int ln = lane;
+    asm volatile("" : "+v"(ln));   // (offsets are formed here, not kept in registers)
 #pragma unroll
     for (int b = 0; b < 2; ++b) {
-      const int row = min(16 * b + l16, last);
-      const uint32_t off = (uint32_t)row * row_bytes + (uint32_t)grp * 16u;
+      const int row = min(16 * b + (ln & 15), last);
+      const uint32_t off = (uint32_t)row * row_bytes + (uint32_t)(ln >> 4) * 16u;
       const uintptr_t from = mixed && row >= r_cached ? r_kn : bk;
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) kf[b][kk] = *(const bf16x8*)(from + off + kk * 64);
     }
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-      const int row = min(RPV * i + lane / NG, last);
-      const uint32_t off = (uint32_t)row * row_bytes + (uint32_t)(lane % NG) * 16u;
+      const int row = min(RPV * i + ln / NG, last);
+      const uint32_t off = (uint32_t)row * row_bytes + (uint32_t)(ln % NG) * 16u;
       vr[i] = *(const u32x4*)((mixed && row >= r_cached ? r_kn + kn_to_vn : bv) + off);
     }
     r_left -= UK * NW;
@@ -149,8 +151,7 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
   // depend on it): always at its first visible keys, otherwise almost never.
   constexpr float kMaxLog2Weight = 24.0f;
   f32x4 o[DB][NCB];
-  f32x4 l_run[NCB];    // row sums over the rounded weights, by MFMAs with a matrix of ones (every register the same)
-  float m_run[NCB], mc[NCB];
+  float m_run[NCB], l_run[NCB], mc[NCB];   // l_run: row sums over the rounded weights, by MFMAs with a matrix of ones
 
   AttnItem it = piece(p_first);
   open();
@@ -158,14 +159,11 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
   load_q(it);
   for (int p = p_first;;) {
     const int n_rows = tokens_of(it) * G;
-    int lim[NCB];   // last key each of the lane's columns may see, minus 4 * grp
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) {
-      const int t = (int)(((uint32_t)(16 * cb + l16) * P.g_magic) >> 16);
-      lim[cb] = min(it.pos0 + min(t, tokens_of(it) - 1), it.k_end - 1) - 4 * grp;
       m_run[cb] = -1e30f;
       mc[cb] = -1e30f * c;
-      l_run[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      l_run[cb] = 0.f;
 #pragma unroll
       for (int db = 0; db < DB; ++db) o[db][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
@@ -191,11 +189,17 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
       asm volatile("" ::: "memory");
       request();
       if (key0 + UK - 1 > min_lim) {
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // (the limits are formed here, not kept in registers)
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb)
+        for (int cb = 0; cb < NCB; ++cb) {
+          // last key the lane's column may see, minus 4 * grp
+          const int t = (int)(((uint32_t)(16 * cb + (ln & 15)) * P.g_magic) >> 16);
+          const int lim = min(it.pos0 + min(t, tokens_of(it) - 1), it.k_end - 1) - 4 * (ln >> 4);
 #pragma unroll
           for (int e = 0; e < 8; ++e)
-            if (key0 + 16 * (e / 4) + e % 4 > lim[cb]) s[e / 4][cb][e % 4] = -INFINITY;
+            if (key0 + 16 * (e / 4) + e % 4 > lim) s[e / 4][cb][e % 4] = -INFINITY;
+        }
       }
       float mx[NCB];
 #pragma unroll
@@ -223,7 +227,7 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
       for (int cb = 0; cb < NCB; ++cb) {
 #pragma unroll
         for (int e = 0; e < 8; ++e) pf[cb].h[e / 2][e % 2] = (__bf16)fast_exp2(fmaf(s[e / 4][cb][e % 4], c, -mc[cb]));
-        l_run[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[cb].v, l_run[cb], 0, 0, 0);
+        l_run[cb] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[cb].v, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0)[0];
       }
 #pragma unroll
       for (int db = 0; db < DB; ++db) {
@@ -246,7 +250,7 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
     }
     if (grp == 0) {
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) stats[wave][16 * cb + l16] = float2{m_run[cb], l_run[cb][0]};
+      for (int cb = 0; cb < NCB; ++cb) stats[wave][16 * cb + l16] = float2{m_run[cb], l_run[cb]};
     }
     barrier();
 #pragma unroll
