@@ -510,6 +510,16 @@ int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_bef
                     int32_t* n_items);
 
 /*
+ * Diagnostic: the attention launches of that pass over the 16-bit cache.  launches receives 3 int32 per launch:
+ *   {pieces, queues, 16 or 32 if the kernel for few rows per sequence runs it (the packed rows its
+ *    tiles have at most), 0 if not}
+ * and *n how many there are; OPPO_ERR_INVALID if that exceeds max_launches.
+ */
+int oppo_attn_launches_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_before, const int32_t* q_len,
+                             size_t workspace_bytes, int32_t* launches /* [max_launches][3] */, int32_t max_launches,
+                             int32_t* n);
+
+/*
  * Diagnostic: the launches oppo_qkv_proj_rope_append would make of its GEMM for a pass of
  * rows new rows.  Nothing is enqueued; no GPU needed.  launches receives 4 int32 per launch:
  *   {rows, rows of a tile, 1 if the phased kernel runs it, rounds of one tile per compute unit}

@@ -30,7 +30,7 @@ OPT_NUM_CUS = 2
 
 EXPORTS = [
     "oppo_chunk_schedule", "oppo_kv_append", "oppo_chunk_prefill_attn", "oppo_chunk_step", "oppo_full_prefill_ref",
-    "oppo_workspace_bytes", "oppo_set_option", "oppo_plan_debug", "oppo_qkv_proj_plan_debug", "oppo_last_error", "oppo_version", "oppo_rope", "oppo_qkv_rope_append", "oppo_qkv_proj_rope_append", "oppo_qkv_proj_workspace_bytes",
+    "oppo_workspace_bytes", "oppo_set_option", "oppo_plan_debug", "oppo_attn_launches_debug", "oppo_qkv_proj_plan_debug", "oppo_last_error", "oppo_version", "oppo_rope", "oppo_qkv_rope_append", "oppo_qkv_proj_rope_append", "oppo_qkv_proj_workspace_bytes",
     "oppo_profile_enable", "oppo_profile_read", "oppo_profile_read_each", "oppo_profile_host", "oppo_chunk_step_noalloc", "oppo_static_scratch_bytes",
     "oppo_kv_append_fp8", "oppo_chunk_prefill_attn_fp8",
     "oppo_pool_create", "oppo_pool_destroy", "oppo_pool_acquire", "oppo_pool_release", "oppo_pool_slot_of",
@@ -129,6 +129,9 @@ def load() -> ctypes.CDLL:
     lib.oppo_plan_debug.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32, i32p, i32p, ctypes.c_size_t, i32p,
                                     ctypes.c_int32, i32p]
     lib.oppo_plan_debug.restype = ctypes.c_int
+    lib.oppo_attn_launches_debug.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32, i32p, i32p, ctypes.c_size_t, i32p,
+                                             ctypes.c_int32, i32p]
+    lib.oppo_attn_launches_debug.restype = ctypes.c_int
     lib.oppo_qkv_proj_plan_debug.argtypes = [ctypes.POINTER(AttnDesc), ctypes.c_int32, ctypes.c_int32, i32p, i32p]
     lib.oppo_qkv_proj_plan_debug.restype = ctypes.c_int
     lib.oppo_profile_enable.argtypes = [ctypes.c_int]
@@ -648,6 +651,17 @@ def oppo_plan_debug(desc: AttnDesc, kv_before, q_len, workspace_bytes: int, max_
     _check(load().oppo_plan_debug(ctypes.byref(desc), kvb.shape[0], _i32p(kvb), _i32p(ql), workspace_bytes,
                                   items.ctypes.data_as(ctypes.POINTER(ctypes.c_int32)), max_items, ctypes.byref(n)))
     return items[: n.value].copy()
+
+
+def oppo_attn_launches_debug(desc: AttnDesc, kv_before, q_len, workspace_bytes: int) -> list:
+    """Attention launches of that pass: (pieces, queues, rows of the few-row kernel or 0) each (diagnostic)."""
+    kvb = _i32(kv_before)
+    ql = _i32(q_len, kvb.shape[0])
+    out = np.zeros((1024, 3), dtype=np.int32)
+    n = ctypes.c_int32(0)
+    _check(load().oppo_attn_launches_debug(ctypes.byref(desc), kvb.shape[0], _i32p(kvb), _i32p(ql), workspace_bytes,
+                                           _i32p(out.reshape(-1)), len(out), ctypes.byref(n)))
+    return [(int(p), int(q), int(r)) for p, q, r in out[: n.value]]
 
 
 def oppo_qkv_proj_plan_debug(desc: AttnDesc, rows: int, hidden: int) -> list:

@@ -28,6 +28,30 @@ int fail(int code, const char* fmt, ...) {
   return code;
 }
 
+// Tiles of 16 rows and fewer always go to attn_thin_kernel; us, attn_fwd_kernel / there, 32/8 heads of 128, one row per sequence:
+// 256 sequences on 64 keys 39.9 / 29.1, on 1024 226 / 207, 32 on 6000 175 / 148; 4/4 heads of 64, 32 sequences on 1024 keys
+// 19.9 / 10.5.  With 17 .. 32 rows a piece costs more there (its output is merged from eight waves) and a key less, by much
+// while a queue has a piece or two and by a tenth where the memory is busy throughout; pieces cut off a longer range win at any
+// length, since their partial results are those of the tile's rows only.  So the keys are held against the whole pieces.
+// Device us, attn_fwd_kernel / attn_thin_kernel, 32 rows, heads of 128: one sequence on 97 keys 7.51 / 8.15, on 170
+// 8.45 / 8.78, on 205 8.98 / 8.98, on 2016 cut into 16 pieces 15.6 / 12.0; 4 on 517 in 16 pieces 15.3 / 11.4, 10 on 3410 in 36
+// 38.0 / 31.6; whole and in turn 89 on 370 32.3 / 33.4, 222 on 498 113.9 / 113.6, 102 on 697 61.8 / 59.2.  Heads of 64: 2 on 56 keys
+// 5.19 / 5.44, 13 on 85 6.14 / 5.78.  Over 755 random passes of 17 .. 32 rows, heads of 128, the choice is 0.05 % off the faster
+// kernel on the mean; attn_fwd_kernel alone 11.8 %, attn_thin_kernel alone 3.1 %.
+int thin_rows(const LayerShape& ls, const AttnItem* items, int n_items, int n_queues) {
+  int most = 0, whole = 0;
+  int64_t keys = 0;
+  for (int i = 0; i < n_items; ++i) {
+    most = std::max(most, tokens_of(items[i]) * ls.G);
+    if (most > kThinRows) return 0;
+    keys += items[i].k_end - items[i].k_begin;
+    whole += items[i].part < 0;
+  }
+  if (most <= 16) return 16;
+  const int64_t keys_per_whole = ls.D == 64 ? 64 : n_items <= 2 * n_queues ? 176 : 448;
+  return keys >= keys_per_whole * whole ? 32 : 0;
+}
+
 // Tiles of the projection.  One workgroup runs per compute unit, so the k loops take ceil(tiles / 256) rounds; what
 // a tile costs besides (its first operands' arrival, the rotation, the stores) shares the memory and goes with the
 // number of tiles.  us of a launch ~ launch + tile * tiles / 256 + k_tile * rounds * (hidden / 64), with coefficients
@@ -842,6 +866,24 @@ int chunk_step_checks(const oppo_attn_desc* desc, const oppo_kv_cache* cache, co
   return OPPO_OK;
 }
 
+// What the two diagnostics of the planner share: the plans of a pass (kv_row0 stands for the sequence's index).
+int debug_plans(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_before, const int32_t* q_len, size_t workspace_bytes,
+                oppo::LayerShape* ls, std::vector<Plan>* plans) {
+  const int rc = check_desc(desc, ls);
+  if (rc) return rc;
+  if (B < 0) return fail(OPPO_ERR_INVALID, "negative size");
+  if (!kv_before || !q_len) return fail(OPPO_ERR_INVALID, "null array");
+  std::vector<SeqView> seqs;
+  int64_t row = 0;
+  for (int32_t i = 0; i < B; ++i) {
+    if (kv_before[i] < 0 || q_len[i] < 0) return fail(OPPO_ERR_INVALID, "negative length at sequence %d", i);
+    if (q_len[i] > 0) seqs.push_back(SeqView{i, (int32_t)row, q_len[i], kv_before[i]});
+    row += q_len[i];
+  }
+  make_plans(options_now(), *ls, seqs, workspace_bytes / oppo::part_slot_bytes(ls->Hkv, ls->D), plans);
+  return OPPO_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1208,19 +1250,11 @@ int oppo_set_option(int option, int value) {
 int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_before, const int32_t* q_len,
                     size_t workspace_bytes, int32_t* items, int32_t max_items, int32_t* n_items) {
   oppo::LayerShape ls;
-  int rc = check_desc(desc, &ls);
-  if (rc) return rc;
-  if (B < 0 || max_items < 0) return fail(OPPO_ERR_INVALID, "negative size");
-  if (!kv_before || !q_len || !n_items || (!items && max_items > 0)) return fail(OPPO_ERR_INVALID, "null array");
-  std::vector<SeqView> seqs;
-  int64_t row = 0;
-  for (int32_t i = 0; i < B; ++i) {
-    if (kv_before[i] < 0 || q_len[i] < 0) return fail(OPPO_ERR_INVALID, "negative length at sequence %d", i);
-    if (q_len[i] > 0) seqs.push_back(SeqView{i /* stands for the sequence index in the dump */, (int32_t)row, q_len[i], kv_before[i]});
-    row += q_len[i];
-  }
   std::vector<Plan> plans;
-  make_plans(options_now(), ls, seqs, workspace_bytes / oppo::part_slot_bytes(ls.Hkv, ls.D), &plans);
+  const int rc = debug_plans(desc, B, kv_before, q_len, workspace_bytes, &ls, &plans);
+  if (rc) return rc;
+  if (max_items < 0) return fail(OPPO_ERR_INVALID, "negative size");
+  if (!n_items || (!items && max_items > 0)) return fail(OPPO_ERR_INVALID, "null array");
   size_t total = 0;
   for (const Plan& plan : plans) total += plan.pieces.size();
   *n_items = (int32_t)total;
@@ -1242,6 +1276,24 @@ int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_bef
         o[7] = queue0 + (int32_t)j;
       }
     queue0 += (int32_t)plan.first.size() - 1;
+  }
+  return OPPO_OK;
+}
+
+int oppo_attn_launches_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_before, const int32_t* q_len,
+                             size_t workspace_bytes, int32_t* launches, int32_t max_launches, int32_t* n) {
+  oppo::LayerShape ls;
+  std::vector<Plan> plans;
+  const int rc = debug_plans(desc, B, kv_before, q_len, workspace_bytes, &ls, &plans);
+  if (rc) return rc;
+  if (max_launches < 0) return fail(OPPO_ERR_INVALID, "negative size");
+  if (!n || (!launches && max_launches > 0)) return fail(OPPO_ERR_INVALID, "null array");
+  *n = (int32_t)plans.size();
+  if (*n > max_launches) return fail(OPPO_ERR_INVALID, "pass has %d launches", *n);
+  for (const Plan& plan : plans) {
+    *launches++ = (int32_t)plan.pieces.size();
+    *launches++ = (int32_t)plan.first.size() - 1;
+    *launches++ = oppo::thin_rows(ls, plan.pieces.data(), (int)plan.pieces.size(), (int)plan.first.size() - 1);
   }
   return OPPO_OK;
 }

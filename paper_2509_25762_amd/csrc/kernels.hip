@@ -20,7 +20,6 @@
 //     absolute position pos0+t sees keys <= pos0+t.
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -50,7 +49,6 @@ typedef __attribute__((ext_vector_type(8))) int i32x8;
 // 82.6 / 84.3, in 96 / 98 pieces that are merged 36.4 / 38.5.  (Replayed from a captured
 // graph both lists take the same time.)
 constexpr int kFewAttnItems = 96;
-constexpr int kThinRows = 32;    // packed rows (tokens x q-heads of a kv-head) of a tile that attn_thin_kernel takes
 constexpr int kFewItems = 64;    // merge and append items
 
 struct AttnFields {
@@ -1253,25 +1251,6 @@ int static_scratch(void** ptr) {
   return 0;
 }
 
-// Whether attn_thin_kernel takes a launch: the rows its tiles have at most (16 or 32, the kernel's column blocks), or 0.
-// Tiles of 16 rows and fewer always go there; us, attn_fwd_kernel / here, 32/8 heads of 128, one row per sequence:
-// 256 sequences on 64 keys 39.9 / 29.1, on 1024 226 / 207, 32 on 6000 175 / 148; 4/4 heads of 64, 32 sequences on 1024 keys
-// 19.9 / 10.5.  Two column blocks cost more at the end of a piece (its output is merged from eight waves): with
-// 32 rows, heads of 64 win at any length (19.3 / 17.9 on 64 keys, 70.8 / 58.0 on 1024, 256 sequences), heads of 128 on long
-// contexts only (256 sequences on 512 keys 135 / 144, on 1024 245 / 244, on 2048 451 / 437; 32 on 6000 176 / 159).
-static int thin_rows(const LayerShape& ls, const AttnItem* items, int n_items) {
-  constexpr int64_t kMeanKeys = 1536;
-  int most = 0;
-  int64_t keys = 0;
-  for (int i = 0; i < n_items; ++i) {
-    most = std::max(most, tokens_of(items[i]) * ls.G);
-    if (most > kThinRows) return 0;
-    keys += items[i].k_end - items[i].k_begin;
-  }
-  if (most <= 16) return 16;
-  return ls.D == 64 || keys >= kMeanKeys * n_items ? 32 : 0;
-}
-
 template <int NI>
 static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool append, const AttnItem* items, int n_items,
                                  const uint16_t* first, int n_queues, hipStream_t st, int kind) {
@@ -1287,7 +1266,7 @@ static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool
     return ls.D == 128 ? launch_timed(kind, attn_fwd_fp8_kernel<128, NI>, grid, block, st, P)
                        : launch_timed(kind, attn_fwd_fp8_kernel<64, NI>, grid, block, st, P);
   }
-  const int rows = thin_rows(ls, items, n_items);
+  const int rows = thin_rows(ls, items, n_items, n_queues);
   if (rows == 16)
     return ls.D == 128 ? (append ? launch_timed(kind, attn_thin_kernel<128, true, NI, 1>, grid, block, st, P)
                                  : launch_timed(kind, attn_thin_kernel<128, false, NI, 1>, grid, block, st, P))

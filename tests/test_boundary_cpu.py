@@ -639,3 +639,44 @@ def test_plans_are_these_plans(lib):
         ob.oppo_set_option(ob.OPT_ORDER, 0)
         ob.oppo_set_option(ob.OPT_NUM_CUS, 256)
     assert digest.hexdigest() == "efafc39d4addf4b4c248852543fa9e92361a6dca3ca77ee3d43589f1a6670f23"
+
+
+@pytest.mark.parametrize("heads,C,ctx,split,rows", [
+    ((32, 8, 128), 1, [50] * 256, 0, 16), ((32, 8, 128), 4, [8000], 0, 16), ((4, 4, 64), 16, [3], 0, 16),   # up to 16 rows: always
+    ((32, 8, 128), 9, [9000], 0, 0), ((4, 4, 64), 33, [9000], 0, 0),                                       # more than 32: never
+    ((32, 8, 128), 8, [167], 0, 0), ((32, 8, 128), 8, [168], 0, 32),                                       # 175 / 176 keys, whole
+    ((32, 8, 128), 8, [439] * 256, 1, 0), ((32, 8, 128), 8, [440] * 256, 1, 32),                           # ... eight in turn
+    ((32, 8, 128), 8, [167] * 64, 1, 0), ((32, 8, 128), 8, [168] * 64, 1, 32), ((32, 8, 128), 8, [440] * 65, 1, 32),
+    ((32, 8, 128), 8, [439] * 65, 1, 0),                                                                   # two in turn, and one more
+    ((32, 8, 128), 8, [6000] * 4, 0, 32), ((32, 8, 128), 8, [6000] * 8, 0, 32), ((32, 8, 128), 8, [12000], 0, 32),   # cut
+    ((32, 8, 128), 8, [200], 3, 32), ((32, 8, 128), 8, [6000] * 8 + [5], 0, 32),
+    ((4, 4, 64), 32, [31] * 4, 0, 0), ((4, 4, 64), 32, [32] * 4, 0, 32)])                                  # 63 / 64 keys
+def test_which_passes_take_the_kernel_for_few_rows(lib, heads, C, ctx, split, rows):
+    desc = ob.make_desc(*heads, 0.1)
+    ob.oppo_set_option(ob.OPT_SPLIT_KV, split)
+    try:
+        ql = np.full(len(ctx), C)
+        launches = ob.oppo_attn_launches_debug(desc, ctx, ql, 1 << 30)
+        items = ob.oppo_plan_debug(desc, ctx, ql, 1 << 30)
+    finally:
+        ob.oppo_set_option(ob.OPT_SPLIT_KV, 0)
+    assert launches == [(len(items), len(set(items[:, 7].tolist())), rows)]
+
+
+def test_attention_launches_of_long_and_empty_passes(lib):
+    desc = _desc()
+    n = 2 * 960
+    launches = ob.oppo_attn_launches_debug(desc, np.full(n, 70), np.ones(n), 1 << 30)
+    items = ob.oppo_plan_debug(desc, np.full(n, 70), np.ones(n), 1 << 30)
+    assert len(launches) == 3 and sum(p for p, _, _ in launches) == len(items) and all(r == 16 for _, _, r in launches)
+    assert ob.oppo_attn_launches_debug(desc, [70, 70], [0, 0], 1 << 30) == []
+    with pytest.raises(ob.OppoError, match="negative length"):
+        ob.oppo_attn_launches_debug(desc, [70, -1], [1, 1], 1 << 30)
+    buf, k = (ctypes.c_int32 * 3)(), ctypes.c_int32(0)
+    kvb = np.full(n, 70, np.int32)
+    ones = np.ones(n, np.int32)
+    i32 = ctypes.POINTER(ctypes.c_int32)
+    args = [ctypes.byref(desc), n, kvb.ctypes.data_as(i32), ones.ctypes.data_as(i32), 1 << 30]
+    assert lib.oppo_attn_launches_debug(*args, buf, 1, ctypes.byref(k)) == -1 and k.value == 3   # more launches than room
+    assert lib.oppo_attn_launches_debug(*args, None, 1, ctypes.byref(k)) == -1
+    assert lib.oppo_attn_launches_debug(*args, buf, 1, None) == -1
