@@ -29,6 +29,7 @@ __global__ __launch_bounds__(512) void attn_thin_kernel(const AttnParams<NI> P) 
   __shared__ __attribute__((aligned(1024))) unsigned char areas[NW][AREA];
   __shared__ float2 stats[NW][ROWS];  // (reference, row sum) of each wave's share
   __shared__ __attribute__((aligned(16))) AttnItem spiece[NI];
+  static_assert(sizeof(areas) + sizeof(stats) + sizeof(spiece) <= 160 * 1024, "a compute unit's LDS");   // (all of it: 128, 960, 2)
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
