@@ -51,8 +51,10 @@ SETTLE_MS = 200.0            # load the GPU has seen before a timed region start
 # what the same counters read for a plain copy of known size: written by `bench.py --traffic-from`
 # into this file together with a fingerprint of the kernel and planner sources it was measured on.
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic.json")
-TRAFFIC_SOURCES = ["paper_2509_25762_amd/csrc/kernels.hip", "paper_2509_25762_amd/csrc/api.cpp",
-                   "paper_2509_25762_amd/csrc/oppo_internal.h"]
+TRAFFIC_SOURCES = ["paper_2509_25762_amd/csrc/" + name for name in
+                   ("kernels.hip", "attn_thin_kernel.h", "attn_fp8_kernel.h", "api.cpp", "oppo_internal.h")]
+# the attention kernels over the 16-bit cache: a pass of few rows per sequence takes the second one
+TRAFFIC_KERNELS = ("attn_fwd_kernel", "attn_thin_kernel")
 
 
 def source_fingerprint() -> str:
@@ -1462,7 +1464,7 @@ def traffic_from(args) -> int:
                 for row in csv.DictReader(f):
                     name = row.get("Kernel_Name", "")
                     val = float(row.get("Counter_Value", 0.0))
-                    key = ("attn" if "attn_fwd_kernel" in name else "append" if "kv_append_kernel" in name else None)
+                    key = ("attn" if any(k in name for k in TRAFFIC_KERNELS) else "append" if "kv_append_kernel" in name else None)
                     if key:
                         acc.setdefault(key, []).append(val)
         return acc
@@ -1478,7 +1480,7 @@ def traffic_from(args) -> int:
     true_kib = 2.0 * rows0 * c2.num_kv_heads * c2.head_dim * 2 / 1024.0
     f_scale = true_kib / max(cal_f["append"])
     w_scale = true_kib / max(cal_w["append"])
-    out = {"unit": "bytes per attn_fwd_kernel launch (HBM reads + writes), response-pass launches averaged",
+    out = {"unit": "bytes per attention launch (HBM reads + writes), response-pass launches averaged",
            "method": "rocprofv3 --pmc FETCH_SIZE and --pmc WRITE_SIZE (KiB per dispatch), each scaled by what the same counter "
                      "reads for the append kernel of the full-batch pass of config 2 in a --two-call run (a plain copy of known size)",
            "fetch_scale": f_scale, "write_scale": w_scale, "source_fingerprint": source_fingerprint(), "configs": {}}

@@ -94,3 +94,40 @@ def test_timing_model_of_the_generating_side():
     assert pass_generation_time([], [], m) == pytest.approx(m.handoff_s)
     # smaller chunks: same decode steps, more hand-offs
     assert sum(generation_times(P, R, 1, m)) == pytest.approx(sum(g) + 5 * m.handoff_s)
+
+
+def test_traffic_counters_cover_every_attention_kernel(tmp_path, monkeypatch):
+    """bench.py's traffic file: its fingerprint covers every source of the kernels, and the average takes the launches
+    of both attention kernels, whole episodes of them (a dropped launch would shift the episodes)."""
+    import argparse
+    import json
+    import os
+    import re
+    import bench
+    csrc = os.path.join(bench.ROOT, "paper_2509_25762_amd", "csrc")
+    with open(os.path.join(csrc, "kernels.hip")) as f:
+        included = re.findall(r'#include "([^"]+)"', f.read())
+    assert len(included) >= 3
+    assert {os.path.join(csrc, name) for name in included} <= {os.path.join(bench.ROOT, rel) for rel in bench.TRAFFIC_SOURCES}
+
+    cfg = CONFIGS[2]
+    P, R = draw_lengths(cfg)
+    T = -(-int(R.max()) // cfg.chunk)
+    copied = 2.0 * int(np.minimum(cfg.chunk, R).sum()) * cfg.num_kv_heads * cfg.head_dim * 2 / 1024.0
+
+    def write(name, rows):
+        with open(tmp_path / f"{name}_counter_collection.csv", "w") as f:
+            f.write("Kernel_Name,Counter_Value\n" + "".join(f'"{k}",{v}\n' for k, v in rows))
+
+    for side in ("fetch", "write"):
+        write(f"cal_{side}", [("void oppo::kv_append_kernel<64>(P)", copied)])
+        # four prompts, then two episodes whose last two passes take the few-row kernel
+        thin = [("void oppo::attn_thin_kernel<128, true, 96, 1>(P)", 10.0)] * 2
+        episode = [("void oppo::attn_fwd_kernel<128, true, 96>(P)", 100.0)] * (T - 2) + [("void oppo::combine_kernel<128>(P)", 7.0)] + thin
+        write(f"cfg2_{side}", [("void oppo::attn_fwd_kernel<128, true, 96>(P)", 1e6)] * 4 + 2 * episode)
+    monkeypatch.setattr(bench, "TRAFFIC_FILE", str(tmp_path / "traffic.json"))
+    assert bench.traffic_from(argparse.Namespace(traffic_from=str(tmp_path), copies=4)) == 0
+    with open(tmp_path / "traffic.json") as f:
+        entry = json.load(f)["configs"]["2"]
+    assert entry["launches_averaged"] == 2 * T
+    assert abs(entry["fetch_KiB"] - (100.0 * (T - 2) + 20.0) / T) < 1e-9
