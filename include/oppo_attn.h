@@ -511,9 +511,10 @@ int oppo_plan_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_bef
 
 /*
  * Diagnostic: the attention launches of that pass over the 16-bit cache.  launches receives 3 int32 per launch:
- *   {pieces, queues, 16 or 32 if the kernel for few rows per sequence runs it (the packed rows its
- *    tiles have at most), 0 if not}
- * and *n how many there are; OPPO_ERR_INVALID if that exceeds max_launches.
+ *   {pieces, queues, kernel}
+ * the kernel by the packed rows (tokens x q-heads of a kv-head) that a tile may have in it: 16 or 32 for
+ * the one for few rows per sequence, 128 or 256 for the general one.
+ * *n receives how many there are; OPPO_ERR_INVALID if that exceeds max_launches.
  */
 int oppo_attn_launches_debug(const oppo_attn_desc* desc, int32_t B, const int32_t* kv_before, const int32_t* q_len,
                              size_t workspace_bytes, int32_t* launches /* [max_launches][3] */, int32_t max_launches,

@@ -654,7 +654,7 @@ def oppo_plan_debug(desc: AttnDesc, kv_before, q_len, workspace_bytes: int, max_
 
 
 def oppo_attn_launches_debug(desc: AttnDesc, kv_before, q_len, workspace_bytes: int) -> list:
-    """Attention launches of that pass: (pieces, queues, rows of the few-row kernel or 0) each (diagnostic)."""
+    """Attention launches of that pass: (pieces, queues, rows a tile may have in the kernel) each (diagnostic)."""
     kvb = _i32(kv_before)
     ql = _i32(q_len, kvb.shape[0])
     out = np.zeros((1024, 3), dtype=np.int32)

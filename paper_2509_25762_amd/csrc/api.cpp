@@ -28,28 +28,29 @@ int fail(int code, const char* fmt, ...) {
   return code;
 }
 
-// Tiles of 16 rows and fewer always go to attn_thin_kernel; us, attn_fwd_kernel / there, 32/8 heads of 128, one row per sequence:
-// 256 sequences on 64 keys 39.9 / 29.1, on 1024 226 / 207, 32 on 6000 175 / 148; 4/4 heads of 64, 32 sequences on 1024 keys
-// 19.9 / 10.5.  With 17 .. 32 rows a piece costs more there (its output is merged from eight waves) and a key less, by much
-// while a queue has a piece or two and by a tenth where the memory is busy throughout; pieces cut off a longer range win at any
-// length, since their partial results are those of the tile's rows only.  So the keys are held against the whole pieces.
-// Device us, attn_fwd_kernel / attn_thin_kernel, 32 rows, heads of 128: one sequence on 97 keys 7.51 / 8.15, on 170
-// 8.45 / 8.78, on 205 8.98 / 8.98, on 2016 cut into 16 pieces 15.6 / 12.0; 4 on 517 in 16 pieces 15.3 / 11.4, 10 on 3410 in 36
-// 38.0 / 31.6; whole and in turn 89 on 370 32.3 / 33.4, 222 on 498 113.9 / 113.6, 102 on 697 61.8 / 59.2.  Heads of 64: 2 on 56 keys
-// 5.19 / 5.44, 13 on 85 6.14 / 5.78.  Over 755 random passes of 17 .. 32 rows, heads of 128, the choice is 0.05 % off the faster
-// kernel on the mean; attn_fwd_kernel alone 11.8 %, attn_thin_kernel alone 3.1 %.
-int thin_rows(const LayerShape& ls, const AttnItem* items, int n_items, int n_queues) {
-  int most = 0, whole = 0;
-  int64_t keys = 0;
+// attn_fwd_kernel with one column block per wave wherever the tiles allow it: a wave that has its SIMD to itself is bound by the
+// issue of its instructions.  Device us, two blocks / one, 32/8 heads of 128, one sequence, not cut: 40 rows on 2050 keys 37.4 / 29.5,
+// 112 rows on 278 10.5 / 9.1; over 1226 random passes of 33 .. 128 rows one block takes 0.73 to 1.005 of the time, 0.86 on the mean.
+// attn_thin_kernel takes less time per key and more per piece that it stores whole (the rows are merged from eight waves); device
+// us, attn_fwd_kernel with one block / attn_thin_kernel, 32/8 heads of 128, contexts of one length in turn or side by side:
+// up to 16 rows it always runs (one row, 256 sequences on 1024 keys 226 / 207 against two blocks; 4 rows, 43 on 75 8.75 / 8.21; 8
+// rows, 64 on 115 10.8 / 10.1; 16 rows, 28 on 60 5.78 / 5.86; over 627 passes 0.7 % off the faster one on the mean, the other 11.8 %);
+// with 32 rows, 67 sequences on 963 keys 51.6 / 53.5, 189 on 1213 202 / 196, 58 on 1321 66.5 / 62.5; cut, one on 575 in 5 pieces
+// 9.3 / 10.3, 3 on 2121 in 32 16.0 / 14.2 (64/8 heads): cut pieces are not counted, and whole ones at 1024 keys each.  Over 1053
+// passes of 17 .. 32 rows, heads of 128, that is 0.3 % off the faster one (always 14 %, never 3.7 %).  Heads of 64 go there from
+// one tile of keys on, 32 rows, 2 sequences on 73 keys 4.65 / 5.48, 20 on 483 8.8 / 7.6 (its weights meet eight references instead of
+// one, so its results are a tenth closer to exact ones); 2.5 % off the faster one over 177 passes (always 4.6 %, never 6.4 %).
+int kernel_rows(const LayerShape& ls, const AttnItem* items, int n_items) {
+  int most = 0;
+  int64_t keys = 0, whole = 0;
   for (int i = 0; i < n_items; ++i) {
     most = std::max(most, tokens_of(items[i]) * ls.G);
-    if (most > kThinRows) return 0;
+    if (most > kHalfRows) return kTileRows;
     keys += items[i].k_end - items[i].k_begin;
     whole += items[i].part < 0;
   }
   if (most <= 16) return 16;
-  const int64_t keys_per_whole = ls.D == 64 ? 64 : n_items <= 2 * n_queues ? 176 : 448;
-  return keys >= keys_per_whole * whole ? 32 : 0;
+  return most <= kThinRows && keys >= (ls.D == 64 ? 64 : 1024) * whole ? kThinRows : kHalfRows;
 }
 
 // Tiles of the projection.  One workgroup runs per compute unit, so the k loops take ceil(tiles / 256) rounds; what
@@ -1293,7 +1294,7 @@ int oppo_attn_launches_debug(const oppo_attn_desc* desc, int32_t B, const int32_
   for (const Plan& plan : plans) {
     *launches++ = (int32_t)plan.pieces.size();
     *launches++ = (int32_t)plan.first.size() - 1;
-    *launches++ = oppo::thin_rows(ls, plan.pieces.data(), (int)plan.pieces.size(), (int)plan.first.size() - 1);
+    *launches++ = oppo::kernel_rows(ls, plan.pieces.data(), (int)plan.pieces.size());
   }
   return OPPO_OK;
 }

@@ -4,9 +4,10 @@
 // Attention (per workgroup = one AttnItem x one kv-head), 8 waves of 64 lanes:
 //   * the query tile packs TM tokens x G q-heads of the kv-head into 256 rows
 //     (row r = head r % G of token r / G);
-//     wave w owns rows [32w, 32w+32).  The transposed product S^T = K Q^T is
+//     wave w owns rows [32w, 32w+32), or [16w, 16w+16) where no tile of a launch
+//     has more than 128.  The transposed product S^T = K Q^T is
 //     computed with v_mfma_f32_16x16x32_bf16 (K as the A operand from LDS, Q^T
-//     as the B operand held in registers), so one lane owns two query columns:
+//     as the B operand held in registers), so one lane owns two query columns (or one):
 //     the softmax statistics are per-lane scalars and the probabilities land
 //     in the B-operand layout of the second product O^T = V^T P^T without any
 //     cross-lane movement.  V^T fragments come from the token-major V tile in
@@ -185,12 +186,13 @@ __device__ __forceinline__ long bf16x8_to_fp8x8(bf16x8 x, float mult) {
 // takes them from k_new / v_new, and the piece that starts a query tile's key
 // range also copies the tile's token rows into the cache (nothing in this launch
 // reads those cache rows).
-template <int D, bool APPEND, int NI>
+// NCB: 16-column blocks of a wave.  (Four waves of 64 columns would halve the fragment reads; their loop alone, one wave per
+// SIMD with nothing to fill its gaps, sustains 1382 TFLOP/s beside 1368 with two blocks, and boundaries would cost more.)
+// One block where no tile has more than 128 rows (kernel_rows): with two blocks only one wave of a SIMD would have rows, and a
+// wave alone is bound by the issue of its own instructions (64 keys take it 1.0 us, two waves 1.3 us).
+template <int D, bool APPEND, int NI, int NCB>
 __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   constexpr int NW = 8, NT = 64 * NW;   // waves, threads
-  // 16-column blocks of a wave.  (Four waves of 64 columns would halve the fragment reads; their loop alone, one wave per
-  // SIMD with nothing to fill its gaps, sustains 1382 TFLOP/s beside this one's 1368, and boundaries would cost more.)
-  constexpr int NCB = 2;
   constexpr int WROWS = 16 * NCB;    // packed rows of a wave
   constexpr int NG = D / 8;          // 16-byte granules per K/V row
   constexpr int KK = D / 32;         // k-steps of S^T = K Q^T
@@ -206,6 +208,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
                                      // LDS latency several times over, and a whole unit costs 16 more registers)
   constexpr int VDEPTH = DB / 2;     // V^T fragments kept in flight
   static_assert(IPW >= 1, "tile smaller than the workgroup");
+  static_assert(NCB == 1 || NCB == 2, "staging area, vector work of a step");
 
   // K stages and V stages are two arrays of at most 64 KiB each, so that every
   // fragment read is "per-lane base register + immediate offset" (the LDS
@@ -252,7 +255,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return r;
   };
 
-  // ---- this lane's two query columns (rows l16 and 16 + l16 of the wave's 32) --------
+  // ---- this lane's query columns (rows l16 and 16 + l16 of the wave's 16 or 32) ------
   bf16x8 qf[NCB][KK];
 
   // ---- cooperative K/V tile loads ------------------------------------------------
@@ -279,11 +282,12 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // therefore travel as whole row pieces (16 bytes per lane, consecutive lanes on
   // consecutive addresses) and are turned around in LDS, half of D at a time.  The
   // staging area is the part of a ring stage that this very wave fills with its
-  // next tile request (2*IPW chunks of 1 KiB), used at a time when the stage's last
+  // next tile request (2*IPW chunks of 1 KiB, of which NCB*IPW are needed), used at a time when the stage's last
   // readers have passed a barrier: no other wave is involved, no barrier needed.
   constexpr int RB = D;             // bytes of a row per round (half a row)
   constexpr int NS = RB / 16;       // 16-byte slots of a row per round
   constexpr int RPC = 1024 / RB;    // rows per 1 KiB chunk
+  constexpr int NCH = NCB * IPW;    // chunks
   typedef __attribute__((address_space(3))) unsigned char* lds_ptr;
   // The lane-dependent offsets below are needed at piece boundaries only.  They are
   // derived from a copy of the lane number that the optimiser cannot see through,
@@ -304,13 +308,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return ((k / IPW) ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
            (uint32_t)((k % IPW) * (NW * 1024));
   };
-  static_assert(RPC * IPW == WROWS / 2, "half of the column blocks per part");
+  static_assert(RPC * IPW == 16, "a column block per part");
   auto carea_of = [&](int stage, int cb, int ln) __attribute__((always_inline)) -> uint32_t {   // that row in its chunk
     const int row = ln & 15;
-    return (cb >= NCB / 2 ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
-           (uint32_t)((cb % (NCB / 2) * (16 / RPC) + row / RPC) * (NW * 1024) + (row % RPC) * RB);
+    return (cb ? lds_addr_of(&sv[0][0]) : lds_addr_of(&sk[0][0])) + (uint32_t)stage * TILE_BYTES + wave_rows +
+           (uint32_t)(row / RPC * (NW * 1024) + row % RPC * RB);
   };
-  // rows wave*32 + k*RPC + ln/NS of the packed tile -> (q-head of the group, token):
+  // rows wave*WROWS + k*RPC + ln/NS of the packed tile -> (q-head of the group, token):
   // row R is head R % G of token R / G, so the rows of a tile of n tokens are the
   // first n * G ones (and rows from TM * G on, if G does not divide 256, are never used)
   auto row_of = [&](int ln, int k, int* hk, int* tk) __attribute__((always_inline)) {
@@ -319,11 +323,11 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     *tk = t;
     *hk = R - t * G;
   };
-  u32x4 qraw[2][2 * IPW];   // Q row pieces on their way: [half of D][chunk]
+  u32x4 qraw[2][NCH];   // Q row pieces on their way: [half of D][chunk]
   auto q_request = [&](const AttnItem& a) __attribute__((always_inline)) {
     const int ln = lane_now();
 #pragma unroll
-    for (int k = 0; k < 2 * IPW; ++k) {
+    for (int k = 0; k < NCH; ++k) {
       int hk, tk;
       row_of(ln, k, &hk, &tk);
       // rows beyond the tile repeat a valid row; their columns are never stored
@@ -339,7 +343,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
-      for (int k = 0; k < 2 * IPW; ++k)
+      for (int k = 0; k < NCH; ++k)
         *(__attribute__((address_space(3))) u32x4*)(lds_ptr)(uintptr_t)(area_of(stage, k) + roff) = qraw[h][k];
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb)
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // prompts of 512 .. 2048 tokens 555 -> 534, 4 x 512 rows on 4096 .. 9999 keys 169 -> 160, 64/8 heads as above 1827 -> 1738.
   constexpr int QS = 2 * KK;      // K fragments of a unit, two S^T MFMAs (one per column block) each
   constexpr int PS = DB;          // V^T fragments of a unit, two O^T MFMAs each
-  constexpr int PPS = 4 * NCB / QS;   // probability pairs handled per step
+  constexpr int PPS = NCB == 2 ? 8 / QS : 1;   // two blocks: probability pairs handled per step
   static_assert(QS == PS && QS % KDEPTH == 0 && PS % VDEPTH == 0, "pipeline shape");
 
   f32x4 o[DB][NCB];                              // [d-block][column block]
@@ -564,54 +568,88 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
     for (int e = 0; e < 2 * NCB; ++e) s[nxt][e % 2][e / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // An MFMA of this shape leaves the vector unit 8 of its 16 cycles: two instructions, or one exp2.  A step is four
-    // MFMAs with PPS pairs' work dealt to them accordingly; a pair's exponents are formed one step ahead.
-    float y0[PPS], y1[PPS], p0[PPS], p1[PPS];
+    if constexpr (NCB == 1) {
+      // A step is two MFMAs and the work of EPS of the unit's eight weights; their exponents are formed one step ahead.
+      constexpr int EPS = 8 / QS;
+      float y[8], w[8];
 #pragma unroll
-    for (int j = 0; j < PPS; ++j) {
-      y0[j] = score(cur, j, 0);
-      y1[j] = score(cur, j, 1);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-    for (int i = 0; i < QS; ++i) {
-      s[nxt][i % 2][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[0][i / 2], s[nxt][i % 2][0], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < PPS; ++j) {
-        p0[j] = fast_exp2(y0[j]);
-        asm volatile("" : "+v"(p0[j]));
-      }
+      for (int e = 0; e < EPS; ++e) y[e] = score(cur, e / 2, e % 2);
       __builtin_amdgcn_sched_barrier(0);
-      s[nxt][i % 2][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[1][i / 2], s[nxt][i % 2][1], 0, 0, 0);
-      ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(st_n * TILE_BYTES, kb_n, i + KDEPTH)
-                                         : ldk(st_nn * TILE_BYTES, kb_nn, i + KDEPTH - QS);
+      __builtin_amdgcn_s_setprio(1);
 #pragma unroll
-      for (int j = 0; j < PPS; ++j)
-        if (i + 1 < QS) {
-          y0[j] = score(cur, (i + 1) * PPS + j, 0);
-          asm volatile("" : "+v"(y0[j]));
+      for (int i = 0; i < QS; ++i) {
+        s[nxt][i % 2][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[0][i / 2], s[nxt][i % 2][0], 0, 0, 0);
+        ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(st_n * TILE_BYTES, kb_n, i + KDEPTH)
+                                           : ldk(st_nn * TILE_BYTES, kb_nn, i + KDEPTH - QS);
+#pragma unroll
+        for (int e = i * EPS; e < (i + 1) * EPS; ++e) {
+          w[e] = fast_exp2(y[e]);
+          asm volatile("" : "+v"(w[e]));
         }
-      __builtin_amdgcn_sched_barrier(0);
-      o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[0], o[i][0], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[0], o[i][0], 0, 0, 0);
+        vf[i % VDEPTH] = (i + VDEPTH < PS) ? ldv(st_p * TILE_BYTES, kb_p, i + VDEPTH)
+                                           : ldv(st_c * TILE_BYTES, kb_c, i + VDEPTH - PS);
 #pragma unroll
-      for (int j = 0; j < PPS; ++j) {
-        p1[j] = fast_exp2(y1[j]);
-        asm volatile("" : "+v"(p1[j]));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-      o[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[1], o[i][1], 0, 0, 0);
-      vf[i % VDEPTH] = (i + VDEPTH < PS) ? ldv(st_p * TILE_BYTES, kb_p, i + VDEPTH)
-                                         : ldv(st_c * TILE_BYTES, kb_c, i + VDEPTH - PS);
-#pragma unroll
-      for (int j = 0; j < PPS; ++j) {
-        if (i + 1 < QS) {
-          y1[j] = score(cur, (i + 1) * PPS + j, 1);
-          asm volatile("" : "+v"(y1[j]));
+        for (int e = (i + 1) * EPS; e < (i + 2) * EPS && e < 8; ++e) {
+          y[e] = score(cur, e / 2, e % 2);
+          asm volatile("" : "+v"(y[e]));
         }
-        round_pair(cur, i * PPS + j, p0[j], p1[j]);
+#pragma unroll
+        for (int e = i * EPS; e < (i + 1) * EPS; ++e)
+          if (e % 2 == 1) round_pair(cur, e / 2, w[e - 1], w[e]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    } else {
+      // An MFMA of this shape leaves the vector unit 8 of its 16 cycles: two instructions, or one exp2.  A step is four
+      // MFMAs with PPS pairs' work dealt to them accordingly; a pair's exponents are formed one step ahead.
+      float y0[PPS], y1[PPS], p0[PPS], p1[PPS];
+#pragma unroll
+      for (int j = 0; j < PPS; ++j) {
+        y0[j] = score(cur, j, 0);
+        y1[j] = score(cur, j, 1);
       }
       __builtin_amdgcn_sched_barrier(0);
+      __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+      for (int i = 0; i < QS; ++i) {
+        s[nxt][i % 2][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[0][i / 2], s[nxt][i % 2][0], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < PPS; ++j) {
+          p0[j] = fast_exp2(y0[j]);
+          asm volatile("" : "+v"(p0[j]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        s[nxt][i % 2][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[1][i / 2], s[nxt][i % 2][1], 0, 0, 0);
+        ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(st_n * TILE_BYTES, kb_n, i + KDEPTH)
+                                           : ldk(st_nn * TILE_BYTES, kb_nn, i + KDEPTH - QS);
+#pragma unroll
+        for (int j = 0; j < PPS; ++j)
+          if (i + 1 < QS) {
+            y0[j] = score(cur, (i + 1) * PPS + j, 0);
+            asm volatile("" : "+v"(y0[j]));
+          }
+        __builtin_amdgcn_sched_barrier(0);
+        o[i][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[0], o[i][0], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < PPS; ++j) {
+          p1[j] = fast_exp2(y1[j]);
+          asm volatile("" : "+v"(p1[j]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        o[i][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf[i % VDEPTH], pf[nxt].v[1], o[i][1], 0, 0, 0);
+        vf[i % VDEPTH] = (i + VDEPTH < PS) ? ldv(st_p * TILE_BYTES, kb_p, i + VDEPTH)
+                                           : ldv(st_c * TILE_BYTES, kb_c, i + VDEPTH - PS);
+#pragma unroll
+        for (int j = 0; j < PPS; ++j) {
+          if (i + 1 < QS) {
+            y1[j] = score(cur, (i + 1) * PPS + j, 1);
+            asm volatile("" : "+v"(y1[j]));
+          }
+          round_pair(cur, i * PPS + j, p0[j], p1[j]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     __builtin_amdgcn_s_setprio(0);
 #pragma unroll
@@ -625,11 +663,11 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       // the O^T MFMAs of a piece's first body belong to no unit (zero probabilities
       // times whatever the ring stage held): the accumulation starts here
 #pragma unroll
-      for (int db = 0; db < DB; ++db) 
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) o[db][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (__any(fmaxf(rs[0], rs[1]) > kRowSumLimit)) {
+    if (__any(fmaxf(rs[0], rs[NCB - 1]) > kRowSumLimit)) {
       // Some column saw a score far above its reference (or has no reference yet):
       // take the unit's true maximum (a column's keys are spread over the four lanes that
       // share l16), move every column's reference up to it, redo the unit's
@@ -652,7 +690,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int pr = 0; pr < 4 * NCB; ++pr) round_pair(cur, pr, fast_exp2(score(cur, pr, 0)), fast_exp2(score(cur, pr, 1)));
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
-      if (u != 0) {   // (a piece's first unit always comes here and has accumulated nothing)
+      if (u != 0) {   // (a piece's first unit has accumulated nothing; it comes here unless all its keys are masked)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -673,7 +711,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // piece's end / so: prompts of 512 .. 2048 tokens 527 / 520, of 233 .. 570 147 / 144, of 305 .. 737 with 16/4 heads of 64
   // 108 / 104, 64 x 256 rows on 262 .. 1017 keys 232 / 229.
   int U = 0;
-  // A wave whose 32 rows all lie beyond the tile's tokens (a short tile fills the
+  // A wave whose rows all lie beyond the tile's tokens (a short tile fills the
   // first n_tok * G rows only) does none of the arithmetic of the piece: it still
   // requests its share of every key tile and joins the barriers, and leaves the
   // matrix and vector units of its SIMD to the waves that have rows.
@@ -825,7 +863,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     } else {
       // (defined on every path, so that the values are not kept alive across the key loop)
 #pragma unroll
-      for (int k = 0; k < 2 * IPW; ++k) qraw[0][k] = qraw[1][k] = u32x4{0u, 0u, 0u, 0u};
+      for (int k = 0; k < NCH; ++k) qraw[0][k] = qraw[1][k] = u32x4{0u, 0u, 0u, 0u};
     }
     const int st_area = (ph + nt + 2) & 3;   // the stage the next tile request goes to
 
@@ -881,9 +919,9 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       const uint32_t roff = roff_of(ln), cx = cx_of(ln);
       // the lane's four elements of a d-block are half (grp % 2) of slot 2 * (block) + grp / 2
       const uint32_t cxg = cx ^ ((uint32_t)(ln >> 5) * 16u), half8 = (uint32_t)((ln >> 4) & 1) * 8u;
-      int grow[2 * IPW];                // head-row (token * Hq + head) of the row in out, -1: not a row of this tile
+      int grow[NCH];                    // head-row (token * Hq + head) of the row in out, -1: not a row of this tile
 #pragma unroll
-      for (int k = 0; k < 2 * IPW; ++k) {
+      for (int k = 0; k < NCH; ++k) {
         int hk, tk;
         row_of(ln, k, &hk, &tk);
         grow[k] = tk < tokens_of(done) ? (done.q_row0 + tk) * Hq + kvh * G + hk : -1;
@@ -901,7 +939,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
                                                                             ((uint32_t)(dbl * 32) ^ cxg)) = w;
           }
 #pragma unroll
-        for (int k = 0; k < 2 * IPW; ++k) {
+        for (int k = 0; k < NCH; ++k) {
           const u32x4 val = *(const __attribute__((address_space(3))) u32x4*)(lds_ptr)(uintptr_t)(
               area_of(st_area, k) + roff);
           if (grow[k] >= 0) __builtin_nontemporal_store(val, (u32x4*)(P.out + (int64_t)grow[k] * D + (ln % NS) * 8 + h * (D / 2)));
@@ -1266,7 +1304,7 @@ static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool
     return ls.D == 128 ? launch_timed(kind, attn_fwd_fp8_kernel<128, NI>, grid, block, st, P)
                        : launch_timed(kind, attn_fwd_fp8_kernel<64, NI>, grid, block, st, P);
   }
-  const int rows = thin_rows(ls, items, n_items, n_queues);
+  const int rows = kernel_rows(ls, items, n_items);
   if (rows == 16)
     return ls.D == 128 ? (append ? launch_timed(kind, attn_thin_kernel<128, true, NI, 1>, grid, block, st, P)
                                  : launch_timed(kind, attn_thin_kernel<128, false, NI, 1>, grid, block, st, P))
@@ -1277,11 +1315,16 @@ static int launch_attention_list(const LayerShape& ls, const AttnFields& F, bool
                                  : launch_timed(kind, attn_thin_kernel<128, false, NI, 2>, grid, block, st, P))
                        : (append ? launch_timed(kind, attn_thin_kernel<64, true, NI, 2>, grid, block, st, P)
                                  : launch_timed(kind, attn_thin_kernel<64, false, NI, 2>, grid, block, st, P));
+  if (rows == 128)
+    return ls.D == 128 ? (append ? launch_timed(kind, attn_fwd_kernel<128, true, NI, 1>, grid, block, st, P)
+                                 : launch_timed(kind, attn_fwd_kernel<128, false, NI, 1>, grid, block, st, P))
+                       : (append ? launch_timed(kind, attn_fwd_kernel<64, true, NI, 1>, grid, block, st, P)
+                                 : launch_timed(kind, attn_fwd_kernel<64, false, NI, 1>, grid, block, st, P));
   if (ls.D == 128)
-    return append ? launch_timed(kind, attn_fwd_kernel<128, true, NI>, grid, block, st, P)
-                  : launch_timed(kind, attn_fwd_kernel<128, false, NI>, grid, block, st, P);
-  return append ? launch_timed(kind, attn_fwd_kernel<64, true, NI>, grid, block, st, P)
-                : launch_timed(kind, attn_fwd_kernel<64, false, NI>, grid, block, st, P);
+    return append ? launch_timed(kind, attn_fwd_kernel<128, true, NI, 2>, grid, block, st, P)
+                  : launch_timed(kind, attn_fwd_kernel<128, false, NI, 2>, grid, block, st, P);
+  return append ? launch_timed(kind, attn_fwd_kernel<64, true, NI, 2>, grid, block, st, P)
+                : launch_timed(kind, attn_fwd_kernel<64, false, NI, 2>, grid, block, st, P);
 }
 
 int launch_attention(const LayerShape& ls, const void* q, void* k, void* v, const void* k_new, const void* v_new,

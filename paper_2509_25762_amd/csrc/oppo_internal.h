@@ -84,10 +84,10 @@ struct LayerShape {
   int32_t fp8 = 0;          // keys and values are E4M3 codes (values in blocks of 64 tokens)
 };
 
-// Whether attn_thin_kernel takes a launch (16-bit cache): the packed rows its tiles have at most, 16 or 32 (one or two
-// column blocks), or 0 (attn_fwd_kernel).  (api.cpp)
-constexpr int kThinRows = 32;
-int thin_rows(const LayerShape& ls, const AttnItem* items, int n_items, int n_queues);
+// The kernel that takes an attention launch over the 16-bit cache, by the packed rows that its tiles may have: 16 and 32,
+// attn_thin_kernel with one and with two column blocks; 128 and kTileRows, attn_fwd_kernel likewise.  (api.cpp)
+constexpr int kThinRows = 32, kHalfRows = kTileRows / 2;
+int kernel_rows(const LayerShape& ls, const AttnItem* items, int n_items);
 
 // Launchers (kernels.hip).  Return a hipError_t as int (0 = success).
 // k_new / v_new null: keys and values come from k / v alone.  Otherwise the

@@ -642,16 +642,15 @@ def test_plans_are_these_plans(lib):
 
 
 @pytest.mark.parametrize("heads,C,ctx,split,rows", [
-    ((32, 8, 128), 1, [50] * 256, 0, 16), ((32, 8, 128), 4, [8000], 0, 16), ((4, 4, 64), 16, [3], 0, 16),   # up to 16 rows: always
-    ((32, 8, 128), 9, [9000], 0, 0), ((4, 4, 64), 33, [9000], 0, 0),                                       # more than 32: never
-    ((32, 8, 128), 8, [167], 0, 0), ((32, 8, 128), 8, [168], 0, 32),                                       # 175 / 176 keys, whole
-    ((32, 8, 128), 8, [439] * 256, 1, 0), ((32, 8, 128), 8, [440] * 256, 1, 32),                           # ... eight in turn
-    ((32, 8, 128), 8, [167] * 64, 1, 0), ((32, 8, 128), 8, [168] * 64, 1, 32), ((32, 8, 128), 8, [440] * 65, 1, 32),
-    ((32, 8, 128), 8, [439] * 65, 1, 0),                                                                   # two in turn, and one more
-    ((32, 8, 128), 8, [6000] * 4, 0, 32), ((32, 8, 128), 8, [6000] * 8, 0, 32), ((32, 8, 128), 8, [12000], 0, 32),   # cut
-    ((32, 8, 128), 8, [200], 3, 32), ((32, 8, 128), 8, [6000] * 8 + [5], 0, 32),
-    ((4, 4, 64), 32, [31] * 4, 0, 0), ((4, 4, 64), 32, [32] * 4, 0, 32)])                                  # 63 / 64 keys
-def test_which_passes_take_the_kernel_for_few_rows(lib, heads, C, ctx, split, rows):
+    ((32, 8, 128), 1, [50] * 256, 0, 16), ((32, 8, 128), 4, [8000], 0, 16), ((4, 4, 64), 16, [3], 0, 16),      # up to 16 rows
+    ((32, 8, 128), 8, [1015] * 64, 1, 128), ((32, 8, 128), 8, [1016] * 64, 1, 32),                             # 1023 / 1024 keys
+    ((32, 8, 128), 8, [1000, 1032], 1, 32), ((32, 8, 128), 8, [1000, 1031], 1, 128),                           # on the mean
+    ((32, 8, 128), 8, [6000] * 4, 0, 32), ((32, 8, 128), 8, [12000], 0, 32), ((32, 8, 128), 8, [200], 3, 32),  # cut
+    ((32, 8, 128), 8, [6000] * 8 + [5], 0, 32), ((4, 4, 64), 32, [31] * 4, 0, 128), ((4, 4, 64), 32, [32] * 4, 0, 32),
+    ((32, 8, 128), 9, [9000], 0, 128), ((32, 8, 128), 32, [9000] * 5, 0, 128), ((32, 8, 128), 33, [9000], 0, 256),
+    ((4, 4, 64), 33, [9], 0, 128), ((4, 4, 64), 128, [9], 0, 128), ((4, 4, 64), 129, [9], 0, 256), ((6, 2, 128), 42, [5], 0, 128),
+    ((6, 2, 128), 43, [5], 0, 256)])
+def test_which_kernel_takes_a_pass(lib, heads, C, ctx, split, rows):
     desc = ob.make_desc(*heads, 0.1)
     ob.oppo_set_option(ob.OPT_SPLIT_KV, split)
     try:

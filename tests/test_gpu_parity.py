@@ -219,7 +219,7 @@ def test_short_tiles_leave_waves_without_rows(gpu, G, D, split):
 
 
 def launches_of(binding, ep, chunks, t=1):
-    """(pieces, queues, rows of the few-row kernel or 0) of the launches of pass t, with the workspace that a
+    """(pieces, queues, rows a tile may have in the kernel) of the launches of pass t, with the workspace that a
     StreamedEpisode has."""
     cfg = ep.cfg
     desc = binding.make_desc(cfg.num_q_heads, cfg.num_kv_heads, cfg.head_dim, cfg.softmax_scale)
@@ -231,11 +231,13 @@ LENGTHS = [1, 31, 32, 33, 64, 225, 255, 256, 257, 300, 513, 1030]
 
 
 @pytest.mark.parametrize("G,Hkv,D,C,P,split,rows", [
-    (4, 2, 128, 1, LENGTHS, 0, 16), (4, 2, 128, 4, LENGTHS, 3, 16), (4, 2, 128, 5, LENGTHS, 0, 32), (4, 2, 128, 5, LENGTHS[:5], 0, 0),
-    (4, 2, 128, 8, [1700, 1570], 0, 32), (4, 2, 128, 8, [1700, 1570], 1, 32), (4, 1, 128, 8, [1700, 6400], 3, 32),
-    (8, 1, 128, 2, LENGTHS, 0, 16), (8, 1, 128, 3, LENGTHS, 1, 32), (3, 3, 128, 5, LENGTHS, 0, 16), (3, 3, 128, 9, LENGTHS, 2, 32),
-    (5, 2, 64, 3, LENGTHS, 2, 16), (1, 4, 64, 16, LENGTHS, 0, 16), (1, 4, 64, 17, LENGTHS, 0, 32), (1, 4, 64, 32, LENGTHS, 2, 32),
-    (1, 4, 64, 32, [31, 1, 20], 0, 0), (1, 4, 64, 33, LENGTHS, 0, 0), (16, 1, 64, 2, LENGTHS, 0, 32), (16, 2, 128, 1, LENGTHS, 0, 16)])
+    (4, 2, 128, 1, LENGTHS, 0, 16), (4, 2, 128, 4, LENGTHS, 3, 16), (4, 2, 128, 1, [20, 5, 30], 0, 16),
+    (4, 2, 128, 5, [300, 1030, 257, 513], 2, 32), (4, 2, 128, 8, [1700, 1570], 0, 32), (4, 2, 128, 8, [1700, 1570], 1, 32),
+    (4, 1, 128, 8, [1700, 6400], 3, 32), (4, 2, 128, 5, LENGTHS[:5], 0, 128), (8, 1, 128, 2, LENGTHS, 0, 16),
+    (8, 1, 128, 3, LENGTHS[6:] + [1200, 2000], 1, 128), (8, 1, 128, 3, [1500, 1023, 700], 1, 32), (3, 3, 128, 5, LENGTHS, 0, 16),
+    (3, 3, 128, 9, [255, 1025, 385], 2, 32), (5, 2, 64, 3, LENGTHS, 2, 16), (1, 4, 64, 16, LENGTHS, 0, 16), (1, 4, 64, 17, LENGTHS, 0, 32),
+    (1, 4, 64, 32, LENGTHS, 2, 32), (1, 4, 64, 32, [31, 1, 20], 0, 128), (1, 4, 64, 33, LENGTHS, 0, 128),
+    (16, 1, 64, 2, LENGTHS, 0, 32), (16, 2, 128, 1, LENGTHS, 0, 16), (2, 1, 64, 9, [9, 4], 0, 128)])
 def test_few_rows_per_sequence(gpu, G, Hkv, D, C, P, split, rows):
     """Passes whose tiles have up to 16 or 32 packed rows (and one row more): contexts around the units of 32 keys and the
     rounds of 256 that eight waves share, the chunk's own keys inside a unit or across two, ranges whole and cut; rows = the
@@ -253,11 +255,11 @@ def test_few_rows_per_sequence(gpu, G, Hkv, D, C, P, split, rows):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
-@pytest.mark.parametrize("G,D,C,B,rows", [(4, 128, 1, 97, 16), (4, 128, 8, 97, 32), (2, 64, 3, 97, 16), (2, 64, 16, 97, 32)])
-def test_few_rows_with_the_long_work_list(gpu, G, D, C, B, rows):
+@pytest.mark.parametrize("G,D,C,B,P0,rows", [(4, 128, 1, 97, 176, 16), (4, 128, 8, 97, 1000, 32), (2, 64, 3, 97, 176, 16), (2, 64, 16, 97, 176, 32)])
+def test_few_rows_with_the_long_work_list(gpu, G, D, C, B, P0, rows):
     """More pieces than the short list holds, one and two column blocks, either head size."""
     binding, episode, torch = gpu
-    P = np.full(B, 176, np.int32) + np.arange(B, dtype=np.int32) % 5 * 45
+    P = np.full(B, P0, np.int32) + np.arange(B, dtype=np.int32) % 5 * 45
     ep = build_episode(small_cfg(B, G, 1, D, C, seed=1300 + D + C), threads=2, lengths=(P, np.full(B, 2 * C, np.int32)))
     chunks = oracle_uniform_chunks(P, ep.resp_len, C)
     binding.oppo_set_option(binding.OPT_SPLIT_KV, 1)
@@ -268,13 +270,14 @@ def test_few_rows_with_the_long_work_list(gpu, G, D, C, B, rows):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
-@pytest.mark.parametrize("C,split,rows", [(1, 0, 16), (4, 3, 16), (8, 0, 32), (5, 3, 32), (8, 1, 32)])
-def test_few_rows_with_peaked_softmax(gpu, C, split, rows):
+@pytest.mark.parametrize("C,last,split,rows", [(1, 1500, 0, 16), (4, 1500, 3, 16), (8, 1500, 0, 32), (5, 1500, 3, 32), (8, 3000, 1, 32),
+                                               (8, 1500, 1, 128), (32, 1500, 0, 128), (19, 1500, 3, 128)])
+def test_few_rows_with_peaked_softmax(gpu, C, last, split, rows):
     """Few rows per sequence, logits of +-40 nats: the waves' shares of a piece meet with very different references, and
-    a wave moves its own again and again."""
+    a wave moves its own again and again.  (128: the general kernel with one column block per wave.)"""
     binding, episode, torch = gpu
     ep = build_episode(small_cfg(3, 8, 2, 128, C, seed=3141), threads=2,
-                       lengths=(np.array([300, 70, 1500], np.int32), np.full(3, 3 * C, np.int32)))
+                       lengths=(np.array([300, 70, last], np.int32), np.full(3, 3 * C, np.int32)))
     for t in (ep.q, ep.k):
         nz = (t & 0x7F80) != 0                                  # times 4, zeros and subnormals as they are
         t[nz] = (t[nz] + (2 << 7)).astype(np.uint16)
@@ -283,6 +286,26 @@ def test_few_rows_with_peaked_softmax(gpu, C, split, rows):
     try:
         assert [r for _, _, r in launches_of(binding, ep, chunks)] == [rows]
         run_and_check(gpu, ep, chunks, None, f"peaked C={C} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+
+
+@pytest.mark.parametrize("G,Hkv,D,C,split,rows", [
+    (4, 2, 128, 9, 0, 128), (4, 2, 128, 32, 1, 128), (4, 2, 128, 32, 3, 128), (4, 2, 128, 33, 0, 256), (8, 1, 128, 16, 0, 128),
+    (3, 2, 128, 42, 2, 128), (3, 2, 128, 43, 0, 256), (1, 2, 128, 128, 1, 128), (1, 2, 128, 129, 0, 256), (1, 4, 64, 49, 0, 128),
+    (1, 4, 64, 128, 3, 128), (5, 1, 64, 25, 0, 128), (16, 1, 64, 8, 1, 128), (2, 2, 64, 64, 0, 128), (2, 2, 64, 65, 0, 256)])
+def test_tiles_of_half_the_rows(gpu, G, Hkv, D, C, split, rows):
+    """Tiles of up to 128 packed rows, 16 to a wave (and one token more, 32 to a wave): waves with no row, one row and all;
+    whole and cut ranges; the chunk's own rows copied in several rounds."""
+    binding, episode, torch = gpu
+    B = len(LENGTHS)
+    P, R = np.array(LENGTHS, np.int32), np.full(B, C + max(1, C // 3), np.int32)
+    ep = build_episode(small_cfg(B, G * Hkv, Hkv, D, C, seed=1500 + G + C), threads=2, lengths=(P, R))
+    chunks = oracle_uniform_chunks(P, R, C)
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        assert [r for _, _, r in launches_of(binding, ep, chunks)] == [rows]
+        run_and_check(gpu, ep, chunks, None, f"G={G} D={D} C={C} split={split}")
     finally:
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
@@ -435,19 +458,19 @@ def test_peaked_softmax_moves_the_reference_often(gpu, gain, split):
 
 # --------------------------------------------------------------------------- work lists at their limits
 
-@pytest.mark.parametrize("C", [3, 9])
+@pytest.mark.parametrize("C", [3, 9, 33])
 @pytest.mark.parametrize("B,split", [(64, 1), (65, 1), (96, 1), (97, 1), (48, 2), (49, 2), (64, 2), (65, 2)])
 def test_work_lists_on_either_side_of_the_short_lists(gpu, B, split, C):
     """64 and 65 append runs, 96 and 97 whole attention pieces, 96 and 98 pieces of cut tiles, 64 and 65 merged tiles:
     the largest passes that travel in the short lists of the kernel arguments and the smallest ones in the long lists;
-    tiles of 12 rows (the kernel for few rows) and of 36."""
+    tiles of 12 rows (the kernel for few rows), of 36 and of 132."""
     binding, episode, torch = gpu
     ep = build_episode(small_cfg(B, 4, 1, 64, C, seed=60 + B), threads=2,
                        lengths=(np.full(B, 61, np.int32) + np.arange(B, dtype=np.int32) % 3 * 40, np.full(B, 2 * C + 1, np.int32)))
     chunks = oracle_uniform_chunks(ep.prompt_len, ep.resp_len, C)
     binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
     try:
-        assert [(p, r) for p, _, r in launches_of(binding, ep, chunks, t=2)] == [(B * split, 16 if C == 3 else 0)]
+        assert [(p, r) for p, _, r in launches_of(binding, ep, chunks, t=2)] == [(B * split, {3: 16, 9: 128, 33: 256}[C])]
         run_and_check(gpu, ep, chunks, None, f"B={B} split={split} C={C}")
     finally:
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
