@@ -51,27 +51,31 @@ struct ProjRowsParams {
 };
 static_assert(sizeof(ProjRowsParams<kMaxProjItems>) <= 32768, "kernel arguments are kept within 32 KiB");
 
-// grid = (items, pieces of (256 / half) * kRowsRun tokens); 256 threads.  Angles in double precision (they reach
+// grid = (items, pieces of (256 / half) * RUN tokens); 256 threads.  Angles in double precision (they reach
 // tens of thousands of radians for the fastest pair), kept as fp32.  Bound by the double-precision sines: a thread takes
-// kRowsRun consecutive tokens of one pair, forms sine and cosine of the first one's angle and of the pair's step, and turns
+// RUN consecutive tokens of one pair, forms sine and cosine of the first one's angle and of the pair's step, and turns
 // the one by the other (some 1e-16 of error a turn, far below the rounding to fp32).  With a sine per token 14,000 rows of
 // chunks of 64, hidden 704, took 230 us a layer pass, with runs of 2, 4, 8 225.4, 224.9, 224.0; thin passes (hidden 4096)
-// 134.9, 134.1, 134.6, 135.1.
+// 134.9, 134.1, 134.6, 135.1.  Up to an angle per thread of two full waves on every SIMD (kOneByOne) it is the length of one
+// thread's work that counts, and each angle has its own sine: against runs of 4 -0.2 us for 1 .. 64 rows, -0.3 for 513 .. 1024
+// (passes of 5 .. 9 us); heads of 128, 1025 .. 2048 rows -0.2 and 2049 .. 4096 rows +0.3, heads of 64 -0.25 and -0.04, 4097 .. 8192 rows
+// +0.2, 16,385 .. 40,000 +2.4.
 constexpr int kRowsRun = 4;
-template <int NI>
+constexpr int64_t kOneByOne = 256 * 4 * 2 * 64;
+template <int NI, int RUN>
 __global__ __launch_bounds__(256) void proj_rows_kernel(const ProjRowsParams<NI> P) {
   const QkvItem it = P.items[blockIdx.x];
-  const int tok0 = (blockIdx.y * (256 / P.half) + threadIdx.x / P.half) * kRowsRun;
-  const int ntok = min(kRowsRun, it.n_tok - tok0);
+  const int tok0 = (blockIdx.y * (256 / P.half) + threadIdx.x / P.half) * RUN;
+  const int ntok = min(RUN, it.n_tok - tok0);
   if (ntok <= 0) return;
   const int i = threadIdx.x % P.half;
   const int64_t row = (int64_t)it.src_row + tok0;
   const double theta = exp2(-(double)i / P.half * P.log2_base);
-  double s, c, st, ct;
+  double s, c, st = 0.0, ct = 1.0;
   sincos((double)(it.pos0 + tok0) * theta, &s, &c);
-  sincos(theta, &st, &ct);
+  if (RUN > 1) sincos(theta, &st, &ct);
 #pragma unroll
-  for (int t = 0; t < kRowsRun; ++t) {
+  for (int t = 0; t < RUN; ++t) {
     if (t < ntok) {
       P.cs[(row + t) * P.half + i] = make_float2((float)c, (float)s);
       if (i == 0) P.dst[row + t] = it.dst_row + tok0 + t;
@@ -674,12 +678,17 @@ static int launch_rows_list(int64_t* dst, float2* cs, double log2_base, int half
   R.half = half;
   R.n_items = n;
   int mt = 0;
+  int64_t rows = 0;
   for (int i = 0; i < n; ++i) {
     R.items[i] = items[i];
     if (items[i].n_tok > mt) mt = items[i].n_tok;
+    rows += items[i].n_tok;
   }
-  const int block_rows = 256 / half * kRowsRun;
-  hipLaunchKernelGGL(proj_rows_kernel<NI>, dim3((unsigned)n, (unsigned)((mt + block_rows - 1) / block_rows)), dim3(256), 0, st, R);
+  const bool runs = rows * half > kOneByOne;
+  const int block_rows = 256 / half * (runs ? kRowsRun : 1);
+  const dim3 grid((unsigned)n, (unsigned)((mt + block_rows - 1) / block_rows)), block(256);
+  if (runs) hipLaunchKernelGGL((proj_rows_kernel<NI, kRowsRun>), grid, block, 0, st, R);
+  else hipLaunchKernelGGL((proj_rows_kernel<NI, 1>), grid, block, 0, st, R);
   return (int)hipGetLastError();
 }
 

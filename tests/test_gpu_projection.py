@@ -239,6 +239,16 @@ def test_row_lists_on_either_side_of_their_limits(gpu, B, Hq, Hkv, D, hidden):
     check_run(gpu, rng, Hq, Hkv, D, hidden, kv_before, q_len)
 
 
+@pytest.mark.parametrize("rows,Hq,Hkv,D", [(2048, 3, 1, 128), (2049, 3, 1, 128), (4096, 2, 1, 64), (4097, 2, 1, 64)])
+def test_angles_one_by_one_and_in_runs(gpu, rows, Hq, Hkv, D):
+    """Up to two waves on every SIMD with a thread per angle each angle has its own sine, beyond that runs of four tokens share
+    one.  Runs of every remainder, at positions where the fastest pair has turned thousands of times."""
+    q_len = np.array([1, 2, 3, 4, 5, 6, 7, 8, 9, 0, 63, 65, 300], dtype=np.int32)
+    q_len = np.append(q_len, rows - q_len.sum()).astype(np.int32)
+    kv_before = np.array([0, 65536 * 4, 1, 70001, 17, 2, 90002, 5, 131071, 3, 40003, 8, 0, 20001], dtype=np.int32)
+    check_run(gpu, np.random.default_rng(rows), Hq, Hkv, D, 64, kv_before, q_len)
+
+
 def test_values_are_the_rounded_fp32_sums_when_products_are_exact(gpu):
     """Small integers: every product and partial sum is exact in fp32, so value heads (no rotation) and
     the rows at position 0 (rotation by 0) must be bit-exact, whatever the order of accumulation."""
