@@ -20,10 +20,12 @@ int launch_attention(const LayerShape& ls, const void*, void*, void*, const void
   if (first[0] != 0 || first[n_queues] != n_items) return 1;
   for (int j = 0; j < n_queues; ++j)
     if (first[j] >= first[j + 1]) return 1;   // empty queues never reach the kernel
+  const int most_rows = ls.fp8 ? kTileRows : kernel_rows(ls, items, n_items);
+  if (most_rows != 16 && most_rows != kThinRows && most_rows != kHalfRows && most_rows != kTileRows) return 1;
   for (int i = 0; i < n_items; ++i) {
     const AttnItem& a = items[i];
     const int n = tokens_of(a);
-    if (n < 1 || n > ls.TM) return 1;
+    if (n < 1 || n > ls.TM || n * ls.G > most_rows) return 1;
     if (a.k_begin < 0 || a.k_begin % kKeyTile != 0 || a.k_end <= a.k_begin || a.k_end > a.pos0 + n) return 1;
     if (a.part >= 0 && !part_o) return 1;
     if (ls.fp8 && a.kv_row0 % kKeyTile != 0) return 1;
