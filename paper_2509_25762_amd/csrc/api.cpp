@@ -55,14 +55,15 @@ int kernel_rows(const LayerShape& ls, const AttnItem* items, int n_items) {
 
 // Tiles of the projection.  One workgroup runs per compute unit, so the k loops take ceil(tiles / 256) rounds; what
 // a tile costs besides (its first operands' arrival, the rotation, the stores) shares the memory and goes with the
-// number of tiles.  us of a launch ~ launch + tile * tiles / 256 + k_tile * rounds * (hidden / 64), with coefficients
+// number of tiles.  us of a launch ~ launch + tile * tiles / 256 + k_tile * rounds * (hidden / 64).  The coefficients were
 // fitted to 2,200 passes of 8 .. 40,000 rows, hidden 64 .. 8192 and 768 .. 10,240 columns that were timed with
-// every kind of tile, such that the cheapest estimate is the fastest kind.  (Since its MFMAs changed the phased kernel is
-// faster than these say: over 13,660 other passes the choice is 0.6 % off on the mean, new coefficients would bring that
-// to 0.2 %.)  The phased kernel multiplies faster and costs more per tile, so it pays on long k loops (us, phased / not:
-// 30,941 rows, hidden 256 -> 10,240 columns 352 / 347; 13,510 rows, hidden 4480 -> 6144 531 / 618).  Thin passes spread over more compute units with lower tiles,
-// and a pass whose last round of tall tiles would be mostly empty sends the rows that fill its rounds with them and
-// the rest in a launch of its own (56 of the 2,200: 0.92 to 1.03 of the best single launch, 0.983 on the mean).
+// every kind of tile, such that the cheapest estimate was the fastest kind, while the phased kernel's MFMAs were 32x32x16.
+// With 16x16x32 it is faster than they say: over 13,660 other passes the choice is 0.6 % off the fastest kind on the mean (the
+// best coefficients found: 0.2 %).  The phased kernel multiplies faster and costs more per tile, so it pays on long k loops (us, phased /
+// not: 30,941 rows, hidden 256 -> 10,240 columns 352 / 347; 13,510 rows, hidden 4480 -> 6144 531 / 618).  Thin passes spread over
+// more compute units with lower tiles, and a pass whose last round of tall tiles would be mostly empty sends the rows that fill
+// its rounds with them and the rest in a launch of its own (56 of the 2,200; 0.92 to 1.03 of the best single launch, 0.983 on
+// the mean, with the phased kernel as it was then).
 ProjPlan plan_qkv_proj(int32_t rows, int32_t n_out, int32_t hidden) {
   struct Cost { double launch, tile, k_tile; };
   static constexpr Cost kCost[kProjTileKinds] = {
