@@ -232,7 +232,7 @@ LENGTHS = [1, 31, 32, 33, 64, 225, 255, 256, 257, 300, 513, 1030]
 
 @pytest.mark.parametrize("G,Hkv,D,C,P,split,rows", [
     (4, 2, 128, 1, LENGTHS, 0, 16), (4, 2, 128, 4, LENGTHS, 3, 16), (4, 2, 128, 1, [20, 5, 30], 0, 16),
-    (4, 2, 128, 5, [300, 1030, 257, 513], 2, 32), (4, 2, 128, 8, [1700, 1570], 0, 32), (4, 2, 128, 8, [1700, 1570], 1, 32),
+    (4, 2, 128, 5, LENGTHS, 0, 128), (4, 2, 128, 5, [300, 1030, 257, 513], 2, 32), (4, 2, 128, 8, [1700, 1570], 0, 32), (4, 2, 128, 8, [1700, 1570], 1, 32),
     (4, 1, 128, 8, [1700, 6400], 3, 32), (4, 2, 128, 5, LENGTHS[:5], 0, 128), (8, 1, 128, 2, LENGTHS, 0, 16),
     (8, 1, 128, 3, LENGTHS[6:] + [1200, 2000], 1, 128), (8, 1, 128, 3, [1500, 1023, 700], 1, 32), (3, 3, 128, 5, LENGTHS, 0, 16),
     (3, 3, 128, 9, [255, 1025, 385], 2, 32), (5, 2, 64, 3, LENGTHS, 2, 16), (1, 4, 64, 16, LENGTHS, 0, 16), (1, 4, 64, 17, LENGTHS, 0, 32),
