@@ -200,7 +200,6 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   constexpr int BN = kKeyTile;
   constexpr int ROWB = D * 2;        // bytes per K/V row in LDS
   constexpr int TILE_BYTES = BN * ROWB;
-  constexpr int VSWZ_MASK = NG / 4 - 1;
   constexpr int NSTAGE = 4;
   constexpr int RPI = 1024 / ROWB;     // tile rows one wave-wide 16-byte load covers
   constexpr int IPW = BN / RPI / NW;   // such loads per wave, per tile, for K and again for V
@@ -266,12 +265,17 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   const int row_stride = Hkv * D;  // elements between consecutive tokens
   const int lrow = lane / NG;
   const int pg = lane % NG;
+  // Swizzle of a value row's granules: the transposing reads take 32 lanes at a time, 32 bytes of each of eight rows, and these
+  // then lie in eight different parts of the 64 banks.  (With rows 4 apart in the same one a third of the LDS cycles were
+  // conflicts, SQ_LDS_BANK_CONFLICT 1.34e8 of SQ_LDS_IDX_ACTIVE 4.05e8 on 16 x 1024 rows of 64/8 heads; the time is the same to
+  // 0.3 %, the LDS is not what the loop waits for.)
+  auto vswz = [](int r) __attribute__((always_inline)) { return (r / (256 / ROWB) % (NG / 2)) * 2; };
   uint32_t goffk[IPW], goffv[IPW];   // byte offsets of this lane's granules in a full tile
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
     const int r = (wave + NW * i) * RPI + lrow;
     goffk[i] = (uint32_t)(r * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
-    goffv[i] = (uint32_t)(r * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
+    goffv[i] = (uint32_t)(r * row_stride + ((pg ^ vswz(r)) * 8)) * 2u;
   }
   const uint32_t wave_rows = (uint32_t)__builtin_amdgcn_readfirstlane(wave) * 1024u;
 
@@ -376,14 +380,14 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   };
   cursor_open();
   auto issue_next = [&](int stage) __attribute__((always_inline)) {
-    if (c_piece >= p_last) return;
+    if (__builtin_expect(c_piece >= p_last, 0)) return;
     const int last = c_left - 1;
     // (LDS addresses are formed here from a copy of the wave's offset that the optimiser
     // cannot see through: otherwise it keeps one precomputed address per stage, array and
     // load in scalar registers for the whole kernel, and those run out)
     uint32_t wave_rows_now = wave_rows;
     asm volatile("" : "+s"(wave_rows_now));
-    if (APPEND && c_cached > 0 && c_cached < BN && c_cached <= last) {
+    if (__builtin_expect(APPEND && c_cached > 0 && c_cached < BN && c_cached <= last, 0)) {
       // cache rows, then chunk rows: each lane's 16 bytes land at the LDS address of its
       // lane number, so the two sources fill one tile with complementary lane masks
 #pragma unroll
@@ -391,7 +395,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
         const int r = (wave + NW * i) * RPI + lrow;
         const int rc = min(r, last);   // rows past the range repeat the last key
         const uint32_t ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
-        const uint32_t ov = (uint32_t)(rc * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
+        const uint32_t ov = (uint32_t)(rc * row_stride + ((pg ^ vswz(r)) * 8)) * 2u;
         const uint32_t lk = lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u);
         const uint32_t lv = lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u);
         if (rc < c_cached) {
@@ -409,11 +413,11 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
       for (int i = 0; i < IPW; ++i) {
         uint32_t ok = goffk[i], ov = goffv[i];
-        if (last < BN - 1) {  // ragged last tile: rows past the range repeat the last key
+        if (__builtin_expect(last < BN - 1, 0)) {  // ragged last tile: rows past the range repeat the last key
           const int r = (wave + NW * i) * RPI + lrow;
           const int rc = min(r, last);
           ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
-          ov = (uint32_t)(rc * row_stride + ((pg ^ ((r & VSWZ_MASK) << 2)) * 8)) * 2u;
+          ov = (uint32_t)(rc * row_stride + ((pg ^ vswz(r)) * 8)) * 2u;
         }
         async_copy16((const void*)bk, ok, lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u));
         async_copy16((const void*)bv, ov, lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u));
@@ -425,7 +429,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       c_cached -= BN;
     }
     c_left -= BN;
-    if (c_left <= 0) {
+    if (__builtin_expect(c_left <= 0, 0)) {
       ++c_piece;
       if (c_piece < p_last) cursor_open();
     }
@@ -452,15 +456,15 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     asm volatile("" : "+v"(a));
     kptr[kk] = (lds_cptr)(uintptr_t)a;
   }
-  lds_cptr vptr[DB / 2];   // V^T fragments of d-blocks 2 * i (and 2 * i + 1, 32 bytes on), keys 4 * grp .. of a tile
+  lds_cptr vptr[DB];   // V^T fragment of a d-block, keys 4 * grp .. of a tile
   {
     const int vrow = 4 * grp + (l16 >> 2);
 #pragma unroll
-    for (int i = 0; i < DB / 2; ++i) {
-      const int lg = i * 4 + ((l16 & 3) >> 1);
-      uint32_t a = lds_addr_of(&sv[0][0]) + (uint32_t)(vrow * ROWB + ((lg ^ ((vrow & VSWZ_MASK) << 2)) * 16) + (l16 & 1) * 8);
+    for (int j = 0; j < DB; ++j) {
+      const int lg = j * 2 + ((l16 & 3) >> 1);
+      uint32_t a = lds_addr_of(&sv[0][0]) + (uint32_t)(vrow * ROWB + ((lg ^ vswz(vrow)) * 16) + (l16 & 1) * 8);
       asm volatile("" : "+v"(a));
-      vptr[i] = (lds_cptr)(uintptr_t)a;
+      vptr[j] = (lds_cptr)(uintptr_t)a;
     }
   }
   // K fragment (A operand of S^T = K Q^T) of step j = (k-step j / 2, 16-key block j % 2) of the 32-key
@@ -472,7 +476,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // V^T fragment (A operand of O^T += V^T P^T) of d-block j of the 32-key unit (stage, kb): the eight
   // contraction indices of lane group grp are keys 4*grp .. and 16 + 4*grp .., as S^T leaves them in P^T
   auto ldv = [&](int off, int kb, int j) __attribute__((always_inline)) -> bf16x8 {
-    lds_cptr vp = vptr[j / 2] + off + kb * 32 * ROWB + (j % 2) * 32;
+    lds_cptr vp = vptr[j] + off + kb * 32 * ROWB;
     union { struct { s16x4 a, b; } h; bf16x8 v; } cat;
     cat.h.a = lds_read_tr16_l(vp);
     cat.h.b = lds_read_tr16_l(vp + 16 * ROWB);
@@ -493,6 +497,10 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   //   * the exp2 / bf16 rounding / row-sum vector work of unit u,
   // so the matrix pipe always has an independent MFMA to run and the vector ALU
   // work (five instructions, two of them exp2, per four MFMAs) is spread evenly under it.
+  // What is rare in the loop is marked so (__builtin_expect), and the compiler puts it behind the kernel: the common path of an
+  // iteration is one straight piece of code.  Behind a barrier both waves of a SIMD run the same scalar code, and every taken
+  // branch is a gap in its MFMAs.  One run, us, without / with: 64 x 256 rows on 262 .. 1017 keys 226.5 / 225.3, prompts of
+  // 512 .. 2048 tokens 515 / 505, 64/8 heads, 1024 rows on up to 8192 keys 1724 / 1716.
   // Against the same loop on 32x32x16 MFMAs with v_dot2 row sums, one run, us: 64 x 256 rows on 262 .. 1017 keys 243 -> 235,
   // prompts of 512 .. 2048 tokens 555 -> 534, 4 x 512 rows on 4096 .. 9999 keys 169 -> 160, 64/8 heads as above 1827 -> 1738.
   constexpr int QS = 2 * KK;      // K fragments of a unit, two S^T MFMAs (one per column block) each
@@ -540,6 +548,26 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[cur].v[cb], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0)[0];
   };
 
+  // Causal / range mask of the unit in s[cur], which starts at key key0, if it crosses a limit.
+  auto mask = [&](int cur, int key0) __attribute__((always_inline)) {
+    if (__builtin_expect(key0 + 31 > min_lim, 0)) {
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          // register e % 4 of key block e / 4 holds key key0 + 16 * (e / 4) + 4 * grp + e % 4
+          if (key0 + 16 * (e / 4) + e % 4 > lim[cb]) s[cur][e / 4][cb][e % 4] = -INFINITY;
+        }
+    }
+  };
+  // Largest score of a column in that unit (its keys are spread over the four lanes that share l16).
+  auto unit_max = [&](int cur, int cb) __attribute__((always_inline)) -> float {
+    const f32x4 &x = s[cur][0][cb], &y = s[cur][1][cb];
+    float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
+    mx = fmaxf(mx, swap_halves(mx));
+    return fmaxf(mx, __shfl_xor(mx, 16));
+  };
+
   // Body of unit u.  BC = position of the unit in the LDS ring (stage, key half),
   // a compile-time value, so that every fragment read has an immediate offset.
   auto unit_body = [&](auto BC, int u) __attribute__((always_inline)) {
@@ -550,21 +578,11 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     constexpr int st_p = ((b + 7) % 8) / 2, kb_p = (b + 7) % 2; // unit u-1
     constexpr int cur = b % 2, nxt = cur ^ 1;
 
-    // ---- causal / range mask on units that cross a limit -------------------------
-    const int key0 = it.k_begin + 32 * u;
-    if (key0 + 31 > min_lim) {
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          // register e % 4 of key block e / 4 holds key key0 + 16 * (e / 4) + 4 * grp + e % 4
-          if (key0 + 16 * (e / 4) + e % 4 > lim[cb]) s[cur][e / 4][cb][e % 4] = -INFINITY;
-        }
-    }
+    mask(cur, it.k_begin + 32 * u);
     // The probabilities of this unit are formed against the reference value m_run
-    // the column already has (no maximum is taken first); only if a row sum comes
-    // out too large - always for a column's first visible keys, otherwise almost
-    // never - the unit is redone against its true maximum, see below.
+    // the column already has (no maximum is taken first: the first one is that of the piece's first unit, taken in front of the
+    // loop, where forming that unit twice took another 0.5 % of a pass); only if a row sum comes out too large - always for a
+    // column's first visible keys if they come later, otherwise almost never - the unit is redone against its true maximum, see below.
 #pragma unroll
     for (int e = 0; e < 2 * NCB; ++e) s[nxt][e % 2][e / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -659,7 +677,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) asm volatile("" : "+v"(pf[cur].v[cb]), "+v"(rs[cb]));
     __builtin_amdgcn_sched_barrier(0);
-    if (u == 0) {
+    if (__builtin_expect(u == 0, 0)) {
       // the O^T MFMAs of a piece's first body belong to no unit (zero probabilities
       // times whatever the ring stage held): the accumulation starts here
 #pragma unroll
@@ -667,20 +685,15 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb) o[db][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
-    if (__any(fmaxf(rs[0], rs[NCB - 1]) > kRowSumLimit)) {
+    if (__builtin_expect(__any(fmaxf(rs[0], rs[NCB - 1]) > kRowSumLimit), 0)) {
       // Some column saw a score far above its reference (or has no reference yet):
-      // take the unit's true maximum (a column's keys are spread over the four lanes that
-      // share l16), move every column's reference up to it, redo the unit's
+      // take the unit's true maximum, move every column's reference up to it, redo the unit's
       // probabilities, and rescale what has been accumulated so far - unit u-1
       // included, whose MFMAs above still used the old reference.
       float alpha[NCB];
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        const f32x4 &x = s[cur][0][cb], &y = s[cur][1][cb];
-        float mx = fmaxf(fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])), fmaxf(fmaxf(y[0], y[1]), fmaxf(y[2], y[3])));
-        mx = fmaxf(mx, swap_halves(mx));
-        mx = fmaxf(mx, __shfl_xor(mx, 16));
-        const float m_new = fmaxf(m_run[cb], mx);
+        const float m_new = fmaxf(m_run[cb], unit_max(cur, cb));
         alpha[cb] = fast_exp2((m_run[cb] - m_new) * c);
         m_run[cb] = m_new;
         mc[cb] = m_new * c;
@@ -690,7 +703,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int pr = 0; pr < 4 * NCB; ++pr) round_pair(cur, pr, fast_exp2(score(cur, pr, 0)), fast_exp2(score(cur, pr, 1)));
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
-      if (u != 0) {   // (a piece's first unit has accumulated nothing; it comes here unless all its keys are masked)
+      if (u != 0) {   // (a piece's first unit has accumulated nothing)
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -723,7 +736,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     constexpr int ts = decltype(TC)::value;
     issue_next((ts + 2) % NSTAGE);
     unit_body(std::integral_constant<int, 2 * ts>{}, 2 * t);
-    if (2 * t + 1 < U) unit_body(std::integral_constant<int, 2 * ts + 1>{}, 2 * t + 1);
+    if (__builtin_expect(2 * t + 1 < U, 1)) unit_body(std::integral_constant<int, 2 * ts + 1>{}, 2 * t + 1);
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the requested tile is in LDS
     wg_barrier();
   };
@@ -760,16 +773,8 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       U = max(min(it.pos0 + tok1, it.k_end - 1) - it.k_begin, 0) / 32 + 1;
     }
     const int nt_own = act ? (U + 1) / 2 : 0;   // tiles with such a unit
-    {
-      float c_now = c;
-      asm volatile("" : "+s"(c_now));
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        m_run[cb] = -1e30f;
-        l_run[cb] = 0.f;
-        mc[cb] = -1e30f * c_now;
-      }
-    }
+    for (int cb = 0; cb < NCB; ++cb) m_run[cb] = mc[cb] = l_run[cb] = 0.f;   // (the first two: below, for waves with rows)
     // the accumulators start undefined (they are cleared after the first body, see
     // unit_body); saying so ends their live range at the previous piece's epilogue
 #pragma unroll
@@ -799,6 +804,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
           s[0][i % 2][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ka[i % KDEPTH], qf[cb][i / 2], s[0][i % 2][cb], 0, 0, 0);
         ka[i % KDEPTH] = (i + KDEPTH < QS) ? ldk(off0, 0, i + KDEPTH) : ldk(off0, 1, i + KDEPTH - QS);
         __builtin_amdgcn_sched_barrier(0);
+      }
+      // the columns' first references
+      mask(0, it.k_begin);
+#pragma unroll
+      for (int cb = 0; cb < NCB; ++cb) {
+        m_run[cb] = fmaxf(-1e30f, unit_max(0, cb));
+        mc[cb] = m_run[cb] * c;
       }
 #pragma unroll
       for (int j = 0; j < VDEPTH; ++j) vf[j] = ldv(offm, 1, j);
@@ -836,10 +848,10 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     const bool early = act && nt_own < nt;   // (the last unit's values are overwritten two iterations on)
     if (act) {
       for (int tb = 0; tb < tau1; tb += 4) {
-        if (tb >= ph) iteration(std::integral_constant<int, 0>{}, tb - ph);
-        if (tb + 1 >= ph && tb + 1 < tau1) iteration(std::integral_constant<int, 1>{}, tb + 1 - ph);
-        if (tb + 2 >= ph && tb + 2 < tau1) iteration(std::integral_constant<int, 2>{}, tb + 2 - ph);
-        if (tb + 3 >= ph && tb + 3 < tau1) iteration(std::integral_constant<int, 3>{}, tb + 3 - ph);
+        if (__builtin_expect(tb >= ph, 1)) iteration(std::integral_constant<int, 0>{}, tb - ph);
+        if (__builtin_expect(tb + 1 >= ph && tb + 1 < tau1, 1)) iteration(std::integral_constant<int, 1>{}, tb + 1 - ph);
+        if (__builtin_expect(tb + 2 >= ph && tb + 2 < tau1, 1)) iteration(std::integral_constant<int, 2>{}, tb + 2 - ph);
+        if (__builtin_expect(tb + 3 >= ph && tb + 3 < tau1, 1)) iteration(std::integral_constant<int, 3>{}, tb + 3 - ph);
       }
       if (early) {
         drain();
