@@ -358,81 +358,90 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     }
   };
   // The request cursor walks the workgroup's tile stream (all tiles of piece
-  // p_first, then of the next piece, ...): all of it is wave-uniform.
-  int c_piece = p_first;        // piece of the next tile to request
-  int c_left = 0;               // keys of that piece not requested yet
-  int c_cached = 0;             // APPEND: how many of them (counted from the next tile on) are in the cache
-  // first row of the next tile, this kv-head, as a byte address in k, and (APPEND) where
-  // that row would be in k_new; the v addresses are a fixed distance away
-  uintptr_t c_k = 0, c_kn = 0;
+  // p_first, then of the next piece, ...): all of it is wave-uniform.  A run of whole tiles from one source (cache or chunk) costs
+  // a request little but its copies, and what else there is to do (a piece's ragged last tile, the one that crosses from
+  // cache to chunk, the next run or piece) is out of the way: behind the barrier that opens an iteration no wave has
+  // anything else to run, so each instruction here, and above all each branch taken, is time in which the matrix cores idle.
+  int run = 0;                 // tiles left of the run
+  uintptr_t r_k = 0, r_v = 0;  // its next tile's first row, this kv-head
+  int c_piece = p_first - 1;   // piece at the cursor
+  int c_key = 0, c_n = 0;      // first key behind the run, and end, of its range, counted from the range's start
+  int c_cached = 0;            // APPEND: how many of these keys are in the cache (may be negative)
+  uintptr_t c_k = 0, c_kn = 0; // key c_key's row in k, and (APPEND) where that row would be in k_new; v is a fixed distance away
   const uintptr_t k_to_v = (uintptr_t)P.v - (uintptr_t)P.k;
   const uintptr_t kn_to_vn = APPEND ? (uintptr_t)P.v_new - (uintptr_t)P.k_new : 0;
   const uintptr_t tile_step = (uintptr_t)BN * row_stride * 2u;
-  auto cursor_open = [&]() __attribute__((always_inline)) {
-    const AttnItem a = piece(c_piece);
-    c_k = (uintptr_t)(P.k + (((int64_t)a.kv_row0 + a.k_begin) * Hkv + kvh) * D);
-    c_left = a.k_end - a.k_begin;
-    if (APPEND) {
-      const int j0 = tile_of(a) * TM;          // the tile's first token within its chunk
-      c_cached = (a.pos0 - j0) - a.k_begin;    // keys before the chunk are cached
-      c_kn = (uintptr_t)(P.k_new + (((int64_t)(a.q_row0 - j0) - c_cached) * Hkv + kvh) * D);
-    }
-  };
-  cursor_open();
-  auto issue_next = [&](int stage) __attribute__((always_inline)) {
-    if (__builtin_expect(c_piece >= p_last, 0)) return;
-    const int last = c_left - 1;
-    // (LDS addresses are formed here from a copy of the wave's offset that the optimiser
-    // cannot see through: otherwise it keeps one precomputed address per stage, array and
-    // load in scalar registers for the whole kernel, and those run out)
+  // (LDS addresses are formed from a copy of the wave's offset that the optimiser
+  // cannot see through: otherwise it keeps one precomputed address per stage, array and
+  // load in scalar registers for the whole kernel, and those run out)
+  auto copy_at = [&](int stage) __attribute__((always_inline)) -> uint32_t {
     uint32_t wave_rows_now = wave_rows;
     asm volatile("" : "+s"(wave_rows_now));
-    if (__builtin_expect(APPEND && c_cached > 0 && c_cached < BN && c_cached <= last, 0)) {
+    return wave_rows_now + (uint32_t)stage * TILE_BYTES;
+  };
+  // The next tile of the run, into `stage`.
+  auto request_plain = [&](int stage) __attribute__((always_inline)) {
+    const uint32_t at = copy_at(stage);
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      async_copy16((const void*)r_k, goffk[i], lds_addr_of(&sk[0][0]) + at + i * (NW * 1024u));
+      async_copy16((const void*)r_v, goffv[i], lds_addr_of(&sv[0][0]) + at + i * (NW * 1024u));
+    }
+    r_k += tile_step;
+    r_v += tile_step;
+    --run;
+  };
+  // At the end of a run: finds the next one (true), or requests the one tile that belongs to none, if there is one (false).
+  auto next_run = [&](int stage) __attribute__((always_inline)) -> bool {
+    if (c_key >= c_n) {
+      if (c_piece + 1 >= p_last) return false;
+      const AttnItem a = piece(++c_piece);
+      c_key = 0;
+      c_n = a.k_end - a.k_begin;
+      c_k = (uintptr_t)(P.k + (((int64_t)a.kv_row0 + a.k_begin) * Hkv + kvh) * D);
+      if (APPEND) {
+        const int j0 = tile_of(a) * TM;          // the tile's first token within its chunk
+        c_cached = (a.pos0 - j0) - a.k_begin;    // keys before the chunk are cached
+        c_kn = (uintptr_t)(P.k_new + (((int64_t)(a.q_row0 - j0) - c_cached) * Hkv + kvh) * D);
+      }
+      // (lgkmcnt(0): where the compiler sees a read of this rare path as outstanding, the common one waits for all of its own)
+      __builtin_amdgcn_s_waitcnt(0xC07F);
+    }
+    const bool fresh = APPEND && c_cached <= c_key;
+    run = ((APPEND && !fresh ? min(c_n, c_cached) : c_n) - c_key) / BN;
+    r_k = fresh ? c_kn : c_k;
+    r_v = r_k + (fresh ? kn_to_vn : k_to_v);
+    const int tiles = max(run, 1);
+    const int last = c_n - c_key - 1, cached = APPEND && !fresh ? c_cached - c_key : BN;
+    const uintptr_t fresh_k = c_kn;
+    c_key += tiles * BN;
+    c_k += (uintptr_t)tiles * tile_step;
+    if (APPEND) c_kn += (uintptr_t)tiles * tile_step;
+    if (run > 0) return true;
+    const int ln = lane_now();
+    const uint32_t at = copy_at(stage);
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) {
+      const int r = ((int)(wave_rows >> 10) + NW * i) * RPI + ln / NG;
+      const int rc = min(r, last);   // ragged last tile: rows past the range repeat the last key
+      const uint32_t ok = (uint32_t)(rc * row_stride + (((ln % NG) ^ (r % NG)) * 8)) * 2u;
+      const uint32_t ov = (uint32_t)(rc * row_stride + (((ln % NG) ^ vswz(r)) * 8)) * 2u;
+      const uint32_t lk = lds_addr_of(&sk[0][0]) + at + i * (NW * 1024u);
+      const uint32_t lv = lds_addr_of(&sv[0][0]) + at + i * (NW * 1024u);
       // cache rows, then chunk rows: each lane's 16 bytes land at the LDS address of its
       // lane number, so the two sources fill one tile with complementary lane masks
-#pragma unroll
-      for (int i = 0; i < IPW; ++i) {
-        const int r = (wave + NW * i) * RPI + lrow;
-        const int rc = min(r, last);   // rows past the range repeat the last key
-        const uint32_t ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
-        const uint32_t ov = (uint32_t)(rc * row_stride + ((pg ^ vswz(r)) * 8)) * 2u;
-        const uint32_t lk = lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u);
-        const uint32_t lv = lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u);
-        if (rc < c_cached) {
-          async_copy16((const void*)c_k, ok, lk);
-          async_copy16((const void*)(c_k + k_to_v), ov, lv);
-        } else {
-          async_copy16((const void*)c_kn, ok, lk);
-          async_copy16((const void*)(c_kn + kn_to_vn), ov, lv);
-        }
-      }
-    } else {
-      const bool all_new = APPEND && c_cached <= 0;
-      const uintptr_t bk = all_new ? c_kn : c_k;
-      const uintptr_t bv = bk + (all_new ? kn_to_vn : k_to_v);
-#pragma unroll
-      for (int i = 0; i < IPW; ++i) {
-        uint32_t ok = goffk[i], ov = goffv[i];
-        if (__builtin_expect(last < BN - 1, 0)) {  // ragged last tile: rows past the range repeat the last key
-          const int r = (wave + NW * i) * RPI + lrow;
-          const int rc = min(r, last);
-          ok = (uint32_t)(rc * row_stride + ((pg ^ (r % NG)) * 8)) * 2u;
-          ov = (uint32_t)(rc * row_stride + ((pg ^ vswz(r)) * 8)) * 2u;
-        }
-        async_copy16((const void*)bk, ok, lds_addr_of(&sk[stage][0]) + wave_rows_now + i * (NW * 1024u));
-        async_copy16((const void*)bv, ov, lds_addr_of(&sv[stage][0]) + wave_rows_now + i * (NW * 1024u));
+      if (!APPEND || rc < cached) {
+        async_copy16((const void*)r_k, ok, lk);
+        async_copy16((const void*)r_v, ov, lv);
+      } else {
+        async_copy16((const void*)fresh_k, ok, lk);
+        async_copy16((const void*)(fresh_k + kn_to_vn), ov, lv);
       }
     }
-    c_k += tile_step;
-    if (APPEND) {
-      c_kn += tile_step;
-      c_cached -= BN;
-    }
-    c_left -= BN;
-    if (__builtin_expect(c_left <= 0, 0)) {
-      ++c_piece;
-      if (c_piece < p_last) cursor_open();
-    }
+    return false;
+  };
+  auto issue_next = [&](int stage) __attribute__((always_inline)) {
+    if (run > 0 || next_run(stage)) request_plain(stage);
   };
   // workgroup barrier without the implied wait for this wave's LDS reads: the only
   // reads still in flight at a barrier are the K fragments of the next tile, whose
@@ -570,7 +579,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
 
   // Body of unit u.  BC = position of the unit in the LDS ring (stage, key half),
   // a compile-time value, so that every fragment read has an immediate offset.
-  auto unit_body = [&](auto BC, int u) __attribute__((always_inline)) {
+  auto unit_body = [&](auto BC, int u, auto at_step) __attribute__((always_inline)) {
     constexpr int b = decltype(BC)::value;
     constexpr int st_c = b / 2, kb_c = b % 2;                   // unit u
     constexpr int st_n = ((b + 1) % 8) / 2, kb_n = (b + 1) % 2; // unit u+1
@@ -617,6 +626,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
         for (int e = i * EPS; e < (i + 1) * EPS; ++e)
           if (e % 2 == 1) round_pair(cur, e / 2, w[e - 1], w[e]);
         __builtin_amdgcn_sched_barrier(0);
+        at_step(i);
       }
     } else {
       // An MFMA of this shape leaves the vector unit 8 of its 16 cycles: two instructions, or one exp2.  A step is four
@@ -667,6 +677,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
           round_pair(cur, i * PPS + j, p0[j], p1[j]);
         }
         __builtin_amdgcn_sched_barrier(0);
+        at_step(i);
       }
     }
     __builtin_amdgcn_s_setprio(0);
@@ -718,6 +729,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // the tile's ring stage.  The tile two places down the stream is requested at
   // its start and awaited at its end, before the barrier after which the next
   // iteration starts reading the tile in between.
+  // (Tiles of a run are requested in the middle of the first body by half of the waves, see first_half.)
   // U: the units of the piece up to the last key that any of the wave's rows may see.  The causal limit of a tile's rows
   // differs by up to its number of tokens, so the first waves are through before the last; they go on requesting
   // tiles and joining barriers and leave the matrix cores, and the power, to the others.  One run, us, every wave to the
@@ -732,11 +744,22 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return (int)(wave_rows >> 10) * WROWS < tokens_of(a) * G;
   };
   bool act = true;
+  // Of the two waves of a SIMD, one requests its share of a tile of a run in front of an iteration's first body and the other in
+  // its middle, so that one of them has MFMAs to run while the other's copies are issued (two thirds of the time between
+  // barrier and first MFMA, 630 cycles of an iteration's 3270, were scalar code and copies that all waves issued at once).  us in
+  // one run, a request in front of both, tile by tile / runs / runs and turns: 64/8 heads, 1024 rows on up to 8192 keys 1845 / 1828
+  // / 1778, prompts of 512 .. 2048 tokens 543 / 541 / 536, 64 x 256 rows on 262 .. 1017 keys 239 / 241 / 239; behind the first body
+  // instead of in its middle the copies come too late where they come from memory (240 us on the last of these).
+  const bool first_half = __builtin_amdgcn_readfirstlane(wave) < 4;
   auto iteration = [&](auto TC, int t) __attribute__((always_inline)) {
     constexpr int ts = decltype(TC)::value;
-    issue_next((ts + 2) % NSTAGE);
-    unit_body(std::integral_constant<int, 2 * ts>{}, 2 * t);
-    if (__builtin_expect(2 * t + 1 < U, 1)) unit_body(std::integral_constant<int, 2 * ts + 1>{}, 2 * t + 1);
+    bool plain = true;
+    if (__builtin_expect(run == 0, 0)) plain = next_run((ts + 2) % NSTAGE);
+    if (first_half && plain) request_plain((ts + 2) % NSTAGE);
+    unit_body(std::integral_constant<int, 2 * ts>{}, 2 * t, [&](int i) __attribute__((always_inline)) {
+      if (i == QS / 2 - 1 && !first_half && plain) request_plain((ts + 2) % NSTAGE);
+    });
+    if (__builtin_expect(2 * t + 1 < U, 1)) unit_body(std::integral_constant<int, 2 * ts + 1>{}, 2 * t + 1, [](int) {});
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the requested tile is in LDS
     wg_barrier();
   };
