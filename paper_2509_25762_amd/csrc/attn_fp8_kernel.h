@@ -42,7 +42,8 @@
 // numerator carry the same factor, which cancels.  The row sum adds the weights before rounding
 // (rounding to nearest is unbiased; turning codes back into numbers would cost more than two
 // additions).  A column's first reference is the maximum of the first unit in which it sees a
-// key; until then it is the arbitrary 0 and the column has accumulated nothing.
+// key, taken in front of the key loop for the piece's first unit; until then it is the arbitrary 0 and the column has
+// accumulated nothing.
 // The values' scale is folded into the final normalisation.
 // Head size 64: the contraction of S^T is one MFMA deep, O^T has two 32-row blocks; a tile of
 // either array is 4 KiB, so waves 0-3 move the keys and waves 4-7 the values.
@@ -217,16 +218,18 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     c_k = (uintptr_t)P.k + (uintptr_t)((((int64_t)a.kv_row0 + a.k_begin) * Hkv + kvh) * D);
     c_v = (uintptr_t)P.v + (uintptr_t)(((((int64_t)a.kv_row0 + a.k_begin) / BN) * Hkv + kvh) * D) * BN;
     c_left = a.k_end - a.k_begin;
+    // (lgkmcnt(0): where the compiler sees a read of this rare path as outstanding, the common one waits for all of its own)
+    __builtin_amdgcn_s_waitcnt(0xC07F);
   };
   cursor_open();
   auto issue_next = [&](int stage) __attribute__((always_inline)) {
-    if (c_piece >= p_last) return;
+    if (__builtin_expect(c_piece >= p_last, 0)) return;
     const int last = c_left - 1;
     uint32_t wave_rows_now = wave_rows;
     asm volatile("" : "+s"(wave_rows_now));
     (void)wave_rows_now;
     uint32_t ok = goffk;
-    if (last < BN - 1) {  // ragged last tile: rows past the range repeat the last key
+    if (__builtin_expect(last < BN - 1, 0)) {  // ragged last tile: rows past the range repeat the last key
       const int rc = min(kr, last);
       ok = (uint32_t)(rc * row_stride + ((kg ^ (((kr >> KSH) & UM) << 1)) * 16));
     }
@@ -238,7 +241,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     c_k += k_step;
     c_v += v_step;
     c_left -= BN;
-    if (c_left <= 0) {
+    if (__builtin_expect(c_left <= 0, 0)) {
       ++c_piece;
       if (c_piece < p_last) cursor_open();
     }
@@ -296,7 +299,10 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
   // interleaved, the two S^T MFMAs of unit u+1, two of the four O^T MFMAs of the PREVIOUS tile
   // (its weights are complete once both of its units are done), and the exp2 / rounding /
   // row-sum vector work of unit u: per MFMA (16 passes) two pairs of weights, 14 vector
-  // instructions.
+  // instructions.  (These count: 256 x 64 rows on 513 .. 2500 keys, append included, 277 us; without forming a piece's first
+  // unit twice 272; with the sums begun by their first pair instead of zero and the test below on scalars 268; with what is rare
+  // marked so 265.  Not the boundaries: with Q rows copied into LDS and output rows out of it a share per iteration, and nothing
+  // awaited between pieces, it was 2 % slower; with requests by turns of the waves as in attn_fwd_kernel 2 % slower.)
   // ------------------------------------------------------------------------------------------
   f32x16 o[DB];
   f32x16 s[2];          // s[u & 1] = S^T of unit u
@@ -306,7 +312,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
   f32x16 negm;          // kBias minus the column's reference (log2 units), in all sixteen registers
   float mref = 0.f;     // the reference
   bool noref = true;    // the column has seen no key of the piece yet
-  bool noref_any = true;
+  uint64_t unseen = 0;  // lanes of such columns (a scalar, like the ballot that it is tested with)
   float l_run, rs0 = 0.f, rs1 = 0.f;
 
   AttnItem it = piece(p_first);
@@ -321,14 +327,32 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     const float p1 = fast_exp2(x1 - shift);
     if (pr & 1) {
       w = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, w, true);
-      rs1 += p0 + p1;
+      rs1 = pr == 1 ? p0 + p1 : rs1 + (p0 + p1);
       asm volatile("" : "+v"(w), "+v"(rs1));
     } else {
       w = __builtin_amdgcn_cvt_pk_fp8_f32(p0, p1, w, false);
-      rs0 += p0 + p1;
+      rs0 = pr == 0 ? p0 + p1 : rs0 + (p0 + p1);
       asm volatile("" : "+v"(w), "+v"(rs0));
     }
     return w;
+  };
+
+  // Causal / range mask of the unit in s[cur]: register r is key key0 + r (+ 32 for the upper lanes).
+  auto mask = [&](int cur, int key0) __attribute__((always_inline)) {
+    if (__builtin_expect(key0 + 47 > min_lim, 0)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r)
+        if (key0 + r > lim) s[cur][r] = -INFINITY;
+    }
+  };
+  // Largest value of the column in that unit (its keys are in lanes l and l ^ 32).
+  auto unit_max = [&](int cur) __attribute__((always_inline)) -> float {
+    float mx4[4];
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      mx4[q4] = fmaxf(fmaxf(fmaxf(s[cur][q4], s[cur][4 + q4]), s[cur][8 + q4]), s[cur][12 + q4]);
+    const float mx = fmaxf(fmaxf(fmaxf(mx4[0], mx4[1]), mx4[2]), mx4[3]);
+    return fmaxf(mx, swap_halves(mx));
   };
 
   // Body of unit u.  BC = position of the unit in the LDS ring (stage, unit of the tile), a
@@ -342,16 +366,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     constexpr int cur = ub, nxt = cur ^ 1;
     constexpr int tp = st_c & 1, tq = tp ^ 1;                    // weight buffers of this tile / the previous one
 
-    // ---- causal / range mask: register i is the tile's key 16 ub + i (+ 32 for the upper lanes) ----
-    const int key0 = it.k_begin + BN * (u >> 1) + 16 * ub;
-    if (key0 + 47 > min_lim) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        if (key0 + r > lim) s[cur][r] = -INFINITY;
-    }
-    rs0 = 0.f;
-    rs1 = 0.f;
-
+    mask(cur, it.k_begin + BN * (u >> 1) + 16 * ub);
     constexpr int PPSN = 8 / KS;   // pairs of weights per step
 #pragma unroll
     for (int i = 0; i < KS; ++i) {
@@ -383,24 +398,19 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     else asm volatile("" : "+v"(pw[tp]), "+v"(rs), "+v"(s[nxt]), "+v"(o[ub]));
     __builtin_amdgcn_sched_barrier(0);
     // (the O^T MFMAs of a piece's first tile multiply zero weights with a tile of valid codes: nothing)
-    const bool over = __any(rs > kRowSumLimit);
-    if (noref_any | over) {   // (noref_any: always at a piece's first unit; no short-circuit: one branch)
-      // A column without a reference yet, or one that saw a score far above its reference: take the
-      // unit's true maximum (one query column per lane, its key halves in lanes l and l^32; the
+    const uint64_t over = __ballot(rs > kRowSumLimit);
+    if (__builtin_expect((over | unseen) != 0, 0)) {   // (no short-circuit: one branch)
+      // A column without a reference yet (it saw no key of the piece's first unit), or one that saw a score far above its
+      // reference: take the unit's true maximum (the
       // registers hold score - reference + kBias), move the references to it - up only, except for a
       // column's first -, redo the unit's weights and rescale what was formed against the old
       // references: the accumulators, and S^T of unit u+1.
-      float mx4[4];
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4)
-        mx4[q4] = fmaxf(fmaxf(fmaxf(s[cur][q4], s[cur][4 + q4]), s[cur][8 + q4]), s[cur][12 + q4]);
-      float mx = fmaxf(fmaxf(fmaxf(mx4[0], mx4[1]), mx4[2]), mx4[3]);
-      mx = fmaxf(mx, swap_halves(mx));
+      const float mx = unit_max(cur);
       const bool seen = mx > -INFINITY;
       const float delta = noref ? (seen ? mx - kBias : 0.f) : fmaxf(mx - kBias, 0.f);
       const float alpha = noref ? 1.0f : fast_exp2(-delta);   // (a column without a reference has accumulated nothing)
       noref = noref && !seen;
-      noref_any = __any(noref);
+      unseen = __ballot(noref);
       mref += delta;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -408,8 +418,6 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
         s[nxt][r] -= delta;
       }
       l_run *= alpha;
-      rs0 = 0.f;
-      rs1 = 0.f;
 #pragma unroll
       for (int pr = 0; pr < 8; ++pr) pw[tp][4 * ub + pr / 2] = exp_pair(cur, pr, pw[tp][4 * ub + pr / 2], delta);
       rs = rs0 + rs1;
@@ -477,7 +485,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     l_run = 0.f;
     mref = 0.f;
     noref = true;
-    noref_any = true;
+    unseen = 0;   // (for waves with rows: below)
 #pragma unroll
     for (int r = 0; r < 16; ++r) negm[r] = kBias;
     // the first tile's bodies run the O^T MFMAs "of the tile before it": with zero weights
@@ -503,17 +511,31 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
         ka[i] = ldk(off0, 1, i);
         __builtin_amdgcn_sched_barrier(0);
       }
+      // the columns' first references: the largest scores of the unit
+      mask(0, it.k_begin);
+      const float mx = unit_max(0);
+      noref = !(mx > -INFINITY);
+      unseen = __ballot(noref);
+      mref = noref ? 0.f : mx - kBias;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        negm[r] -= mref;
+        s[0][r] -= mref;
+      }
 #pragma unroll
       for (int i = 0; i < KS; ++i) vf[i] = ldv(offm, i);
+      // (lgkmcnt(0): these reads come in another order than a body's, and where the compiler sees them as outstanding, every body
+      // begins with a wait for all of the last one's)
+      __builtin_amdgcn_s_waitcnt(0xC07F);
     }
 
     const int tau1 = ph + nt;
     if (act) {
       for (int tb = 0; tb < tau1; tb += 4) {
-        if (tb >= ph) iteration(std::integral_constant<int, 0>{}, tb - ph);
-        if (tb + 1 >= ph && tb + 1 < tau1) iteration(std::integral_constant<int, 1>{}, tb + 1 - ph);
-        if (tb + 2 >= ph && tb + 2 < tau1) iteration(std::integral_constant<int, 2>{}, tb + 2 - ph);
-        if (tb + 3 >= ph && tb + 3 < tau1) iteration(std::integral_constant<int, 3>{}, tb + 3 - ph);
+        if (__builtin_expect(tb >= ph, 1)) iteration(std::integral_constant<int, 0>{}, tb - ph);
+        if (__builtin_expect(tb + 1 >= ph && tb + 1 < tau1, 1)) iteration(std::integral_constant<int, 1>{}, tb + 1 - ph);
+        if (__builtin_expect(tb + 2 >= ph && tb + 2 < tau1, 1)) iteration(std::integral_constant<int, 2>{}, tb + 2 - ph);
+        if (__builtin_expect(tb + 3 >= ph && tb + 3 < tau1, 1)) iteration(std::integral_constant<int, 3>{}, tb + 3 - ph);
       }
     } else {
       for (int t = 0; t < nt; ++t) {
