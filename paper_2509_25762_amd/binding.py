@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import sys
 from typing import Optional
 
 import numpy as np
@@ -194,15 +195,34 @@ def _i32p(arr: Optional[np.ndarray]):
     return arr.ctypes.data_as(ctypes.POINTER(ctypes.c_int32))
 
 
+# The marshalling of a call is a third of the smallest step's time, and each question asked of a tensor or an object made takes
+# a tenth of a microsecond: torch tensors (the usual case, told by their exact type) are asked once for what a check needs, and
+# structures are passed as they are (ctypes takes their addresses itself).  oppo_chunk_step of 4 sequences x 32 tokens, us a call
+# in one run: 9.5 before, 8.7 now.
+_Tensor = None   # torch.Tensor, once torch has been imported
+
+
+def _is_tensor(t) -> bool:
+    global _Tensor
+    if _Tensor is None and "torch" in sys.modules:
+        _Tensor = getattr(sys.modules["torch"], "Tensor", None)
+    return _Tensor is not None and type(t) is _Tensor
+
+
 def _dev_ptr(t) -> Optional[int]:
     """Device address of a torch tensor (or None / a raw int address)."""
-    if t is None:
-        return None
-    if isinstance(t, int):
-        return t
+    if type(t) is not _Tensor:
+        if t is None:
+            return None
+        if isinstance(t, int):
+            return t
     if not t.is_contiguous():
         raise ValueError("device tensors must be contiguous")
     return t.data_ptr()
+
+
+def _nbytes(t) -> int:
+    return 0 if t is None else t.nbytes if type(t) is _Tensor else t.numel() * t.element_size()
 
 
 def _need(t, nbytes: int, name: str) -> None:
@@ -210,28 +230,44 @@ def _need(t, nbytes: int, name: str) -> None:
     The C ABI carries no sizes for device buffers, and an undersized one would be read or
     written out of bounds by a kernel, so it is refused here, where sizes are known.  Raw
     integer addresses cannot be checked and are taken as they are."""
-    if t is None or isinstance(t, int) or nbytes <= 0:
+    if t is None or nbytes <= 0:
         return
-    have = t.numel() * t.element_size()
+    if type(t) is _Tensor or _is_tensor(t):
+        have, on_gpu = t.nbytes, t.is_cuda
+    elif isinstance(t, int):
+        return
+    else:
+        have, on_gpu = t.numel() * t.element_size(), getattr(t, "is_cuda", True) is not False
     if have < nbytes:
         raise ValueError(f"{name} holds {have} bytes, the call needs {nbytes}")
-    if getattr(t, "is_cuda", True) is False:
+    if not on_gpu:
         raise ValueError(f"{name} must be a device tensor")
 
 
-def _need_cache(desc, cache, name: str = "cache") -> None:
+def _need_cache(desc, cache) -> None:
     slots = int(cache.slot_begin[-1]) if len(cache.slot_begin) else 0
     nbytes = slots * desc.num_kv_heads * desc.head_dim * getattr(cache, "element_bytes", 2)
-    _need(getattr(cache, "k", None), nbytes, f"{name}.k")
-    _need(getattr(cache, "v", None), nbytes, f"{name}.v")
+    _need(getattr(cache, "k", None), nbytes, "cache.k")
+    _need(getattr(cache, "v", None), nbytes, "cache.v")
+
+
+_current_stream = None   # the current stream's address, found once
+
+
+def _find_current_stream():
+    import torch
+    if hasattr(torch._C, "_cuda_getCurrentRawStream"):   # the address alone, without a stream object around it
+        raw, device = torch._C._cuda_getCurrentRawStream, torch.cuda.current_device
+        return lambda: raw(device())
+    return lambda: torch.cuda.current_stream().cuda_stream
 
 
 def _stream_ptr(stream) -> Optional[int]:
+    global _current_stream
     if stream is None:
-        import torch
-        if hasattr(torch._C, "_cuda_getCurrentRawStream"):   # the address alone, without a stream object around it
-            return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-        return torch.cuda.current_stream().cuda_stream
+        if _current_stream is None:
+            _current_stream = _find_current_stream()
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
@@ -535,19 +571,17 @@ def _need_rows(desc: AttnDesc, cu: np.ndarray, q=None, k_new=None, v_new=None, o
     """q / out / q_out hold cu[-1] rows of Hq heads, k_new / v_new of Hkv heads, qkv of Hq + 2 Hkv."""
     head_rows = (int(cu[-1]) if cu.shape[0] else 0) * desc.head_dim * 2
     nq, nkv = head_rows * desc.num_q_heads, head_rows * desc.num_kv_heads
-    _need(q, nq, "q")
-    _need(k_new, nkv, "k_new")
-    _need(v_new, nkv, "v_new")
-    _need(out, nq, "out")
-    _need(qkv, nq + 2 * nkv, "qkv")
-    _need(q_out, nq, "q_out")
+    for t, nbytes, name in ((q, nq, "q"), (k_new, nkv, "k_new"), (v_new, nkv, "v_new"), (out, nq, "out"),
+                            (qkv, nq + 2 * nkv, "qkv"), (q_out, nq, "q_out")):
+        if t is not None:
+            _need(t, nbytes, name)
 
 
 def oppo_kv_append(desc: AttnDesc, cache: KVCache, cu_q, k_new, v_new, stream=None) -> None:
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, k_new=k_new, v_new=v_new)
     _need_cache(desc, cache)
-    _check(load().oppo_kv_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(k_new),
+    _check(load().oppo_kv_append(desc, cache.struct, cu.tobytes(), _dev_ptr(k_new),
                                  _dev_ptr(v_new), _stream_ptr(stream)))
 
 
@@ -556,7 +590,7 @@ def oppo_qkv_rope_append(desc: AttnDesc, cache: KVCache, cu_q, qkv, q_out, theta
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, qkv=qkv, q_out=q_out)
     _need_cache(desc, cache)
-    _check(load().oppo_qkv_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(qkv),
+    _check(load().oppo_qkv_rope_append(desc, cache.struct, cu.tobytes(), _dev_ptr(qkv),
                                        _dev_ptr(q_out), float(theta_base), _stream_ptr(stream)))
 
 
@@ -574,29 +608,29 @@ def oppo_qkv_proj_rope_append(desc: AttnDesc, cache: KVCache, cu_q, x, hidden: i
     _need_rows(desc, cu, q_out=q_out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    _check(load().oppo_qkv_proj_rope_append(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(x), hidden,
+    ws_bytes = _nbytes(workspace)
+    _check(load().oppo_qkv_proj_rope_append(desc, cache.struct, cu.tobytes(), _dev_ptr(x), hidden,
                                             _dev_ptr(w), _dev_ptr(q_out), float(theta_base), _dev_ptr(workspace), ws_bytes,
                                             _stream_ptr(stream)))
 
 
 def oppo_chunk_prefill_attn(desc: AttnDesc, cache: KVCache, cu_q, q, out, workspace=None, stream=None) -> None:
     cu = _i32(cu_q, cache.batch + 1)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     _need_rows(desc, cu, q=q, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_prefill_attn(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
+    _check(load().oppo_chunk_prefill_attn(desc, cache.struct, cu.tobytes(), _dev_ptr(q),
                                           _dev_ptr(out), _dev_ptr(workspace), ws_bytes, _stream_ptr(stream)))
 
 
 def oppo_chunk_step(desc: AttnDesc, cache: KVCache, cu_q, q, k_new, v_new, out, workspace=None, stream=None) -> None:
     cu = _i32(cu_q, cache.batch + 1)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     _need_rows(desc, cu, q=q, k_new=k_new, v_new=v_new, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_step(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
+    _check(load().oppo_chunk_step(desc, cache.struct, cu.tobytes(), _dev_ptr(q),
                                   _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(out), _dev_ptr(workspace), ws_bytes,
                                   _stream_ptr(stream)))
 
@@ -605,17 +639,17 @@ def oppo_kv_append_fp8(desc: AttnDesc, cache: KVCacheFp8, cu_q, k_new, v_new, st
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, k_new=k_new, v_new=v_new)
     _need_cache(desc, cache)
-    _check(load().oppo_kv_append_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(k_new),
+    _check(load().oppo_kv_append_fp8(desc, cache.struct, cu.tobytes(), _dev_ptr(k_new),
                                      _dev_ptr(v_new), _stream_ptr(stream)))
 
 
 def oppo_chunk_prefill_attn_fp8(desc: AttnDesc, cache: KVCacheFp8, cu_q, q, out, workspace=None, stream=None) -> None:
     cu = _i32(cu_q, cache.batch + 1)
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     _need_rows(desc, cu, q=q, out=out)
     _need_cache(desc, cache)
     _need(workspace, 1, "workspace")
-    _check(load().oppo_chunk_prefill_attn_fp8(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
+    _check(load().oppo_chunk_prefill_attn_fp8(desc, cache.struct, cu.tobytes(), _dev_ptr(q),
                                               _dev_ptr(out), _dev_ptr(workspace), ws_bytes, _stream_ptr(stream)))
 
 
@@ -624,7 +658,7 @@ def oppo_chunk_step_noalloc(desc: AttnDesc, cache: KVCache, cu_q, q, k_new, v_ne
     cu = _i32(cu_q, cache.batch + 1)
     _need_rows(desc, cu, q=q, k_new=k_new, v_new=v_new, out=out)
     _need_cache(desc, cache)
-    _check(load().oppo_chunk_step_noalloc(ctypes.byref(desc), ctypes.byref(cache.struct), cu.tobytes(), _dev_ptr(q),
+    _check(load().oppo_chunk_step_noalloc(desc, cache.struct, cu.tobytes(), _dev_ptr(q),
                                           _dev_ptr(k_new), _dev_ptr(v_new), _dev_ptr(out), _stream_ptr(stream)))
 
 
@@ -635,7 +669,7 @@ def oppo_static_scratch_bytes() -> int:
 def oppo_full_prefill_ref(desc: AttnDesc, cu_seq, q, k, v, out, workspace=None, stream=None) -> None:
     cu = _i32(cu_seq)
     B = cu.shape[0] - 1
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    ws_bytes = _nbytes(workspace)
     _need_rows(desc, cu, q=q, out=out, k_new=k, v_new=v)
     _need(workspace, 1, "workspace")
     _check(load().oppo_full_prefill_ref(ctypes.byref(desc), B, _i32p(cu), _dev_ptr(q), _dev_ptr(k), _dev_ptr(v),
