@@ -220,6 +220,26 @@ def test_attention_with_split_key_ranges_and_without_workspace(gpu):
     check_outputs(se, ref, "fp8 long forced split")
 
 
+@pytest.mark.parametrize("split", [0, 2, 5])
+def test_columns_that_see_no_key_of_a_pieces_first_unit(gpu, split):
+    """Cut ranges of short contexts: a piece begins behind what some, or all, of a wave's columns see, so these have no
+    reference in front of the key loop and take theirs in a later unit, or none at all."""
+    binding, episode, torch = gpu
+    P = np.array([1, 31, 33, 63, 64, 65, 100, 190], np.int32)
+    R = np.full(len(P), 90, np.int32)
+    ep = build_episode(d128_cfg(len(P), 8, 2, 64, 9, None, None), threads=2, lengths=(P, R))
+    ks, vs = amax_scale(ep.k), amax_scale(ep.v)
+    chunks = uniform_chunks(P, R, 64)
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        se = run_gpu(gpu, ep, chunks, ks, vs)
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+    cache, ref = oracle_run(ep, chunks, se.slot_begin, ks, vs)
+    check_codes(se, cache)
+    check_outputs(se, ref, f"fp8 short contexts split={split}")
+
+
 def test_attention_dominant_keys_and_single_key_rows(gpu):
     """Keys whose scores stand ~6 and ~9 nats above the rest, one in a sequence's first tile and a
     stronger one in its second: the reference is set high at once, moves up again in the middle of

@@ -326,6 +326,21 @@ def test_waves_that_end_before_the_piece(gpu, G, D, split):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
+@pytest.mark.parametrize("G,D,C,split", [(4, 128, 64, 0), (4, 64, 65, 0), (1, 128, 300, 0), (1, 64, 256, 2), (2, 128, 129, 1), (4, 128, 200, 5)])
+def test_runs_of_whole_key_tiles(gpu, G, D, C, split):
+    """Cache and chunk that meet on, one key before and one behind a tile of 64 keys, and chunks of no, one and several whole tiles:
+    runs of every kind end in another run, in the tile that takes from both, in a ragged tile and in the next piece."""
+    binding, episode, torch = gpu
+    P = np.array([1, 62, 63, 64, 65, 127, 128, 129, 191, 192, 320], np.int32)
+    R = np.full(len(P), C + 70, np.int32)
+    ep = build_episode(small_cfg(len(P), 2 * G, 2, D, C, seed=1700 + G + C), threads=2, lengths=(P, R))
+    binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    try:
+        run_and_check(gpu, ep, oracle_uniform_chunks(P, R, C), None, f"G={G} D={D} C={C} split={split}")
+    finally:
+        binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+
+
 def test_empty_batch_and_all_finished(gpu):
     binding, episode, torch = gpu
     cfg = small_cfg(3, 8, 2, 128, 32)
