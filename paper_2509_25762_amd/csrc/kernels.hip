@@ -176,8 +176,8 @@ __device__ __forceinline__ long bf16x8_to_fp8x8(bf16x8 x, float mult) {
 // that consumes them (rolling register buffers ka / vf).
 // K/V tiles go straight from global memory into a ring of four LDS stages, two
 // tiles ahead: the loads of the tile two places further down the workgroup's
-// tile stream are issued after the barrier that opens an iteration, into the
-// stage whose last reader finished before that barrier, and each wave waits for
+// tile stream are issued after the barrier that opens an iteration (by half of the waves in the middle of its first
+// unit), into the stage whose last reader finished before that barrier, and each wave waits for
 // its own loads before the barrier that closes it.  The stream runs across piece
 // boundaries: the first two tiles of the next piece are requested during the last
 // two iterations of the current one, and the next piece's Q fragments are
@@ -726,10 +726,9 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   };
 
   // iteration = one tile = units 2t and 2t+1 of the piece (U units in all); TC is
-  // the tile's ring stage.  The tile two places down the stream is requested at
-  // its start and awaited at its end, before the barrier after which the next
+  // the tile's ring stage.  The tile two places down the stream is requested in
+  // it (see first_half) and awaited at its end, before the barrier after which the next
   // iteration starts reading the tile in between.
-  // (Tiles of a run are requested in the middle of the first body by half of the waves, see first_half.)
   // U: the units of the piece up to the last key that any of the wave's rows may see.  The causal limit of a tile's rows
   // differs by up to its number of tokens, so the first waves are through before the last; they go on requesting
   // tiles and joining barriers and leave the matrix cores, and the power, to the others.  One run, us, every wave to the
