@@ -557,16 +557,26 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[cur].v[cb], f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0)[0];
   };
 
-  // Causal / range mask of the unit in s[cur], which starts at key key0, if it crosses a limit.
+  // Causal / range mask of the unit in s[cur], which starts at key key0, if it crosses a limit.  One register at a time, each
+  // pinned: left to itself the compiler forms all comparisons first, and with scalar registers as scarce as in the append
+  // variants it parks their results in lanes of a vector register (16 to 18 v_writelane and as many v_readlane per masked unit;
+  // 161 scalar spills in the variant for heads of 128 with two column blocks, 35 so).  Time with / without the pin: 4 x 1191
+  // rows on 49 .. 91 keys, 4/4 heads of 64, 0.91; 170 x 196 rows on 161 .. 165 keys, the same heads, 0.95; 64 x 256 rows on
+  // 262 .. 1017 keys, 32/8 heads of 128, 0.997.
   auto mask = [&](int cur, int key0) __attribute__((always_inline)) {
     if (__builtin_expect(key0 + 31 > min_lim, 0)) {
 #pragma unroll
-      for (int cb = 0; cb < NCB; ++cb)
+      for (int cb = 0; cb < NCB; ++cb) {
+        const int left = lim[cb] - key0;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
           // register e % 4 of key block e / 4 holds key key0 + 16 * (e / 4) + 4 * grp + e % 4
-          if (key0 + 16 * (e / 4) + e % 4 > lim[cb]) s[cur][e / 4][cb][e % 4] = -INFINITY;
+          float x = s[cur][e / 4][cb][e % 4];
+          if (16 * (e / 4) + e % 4 > left) x = -INFINITY;
+          asm volatile("" : "+v"(x));
+          s[cur][e / 4][cb][e % 4] = x;
         }
+      }
     }
   };
   // Largest score of a column in that unit (its keys are spread over the four lanes that share l16).
