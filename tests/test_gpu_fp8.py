@@ -220,24 +220,33 @@ def test_attention_with_split_key_ranges_and_without_workspace(gpu):
     check_outputs(se, ref, "fp8 long forced split")
 
 
-@pytest.mark.parametrize("split", [0, 2, 5])
-def test_columns_that_see_no_key_of_a_pieces_first_unit(gpu, split):
-    """Cut ranges of short contexts: a piece begins behind what some, or all, of a wave's columns see, so these have no
-    reference in front of the key loop and take theirs in a later unit, or none at all."""
+@pytest.mark.parametrize("D,split,cus", [(128, 2, 256), (128, 5, 256), (64, 2, 256), (128, 5, 4), (64, 2, 4), (64, 8, 2)])
+def test_columns_that_see_no_key_of_a_piece(gpu, D, split, cus):
+    """Cut ranges of short contexts: a piece begins behind what some, or all, of a wave's columns see.  With few compute units
+    such pieces come before and behind ordinary ones in a workgroup's queue."""
     binding, episode, torch = gpu
     P = np.array([1, 31, 33, 63, 64, 65, 100, 190], np.int32)
     R = np.full(len(P), 90, np.int32)
-    ep = build_episode(d128_cfg(len(P), 8, 2, 64, 9, None, None), threads=2, lengths=(P, R))
+    ep = build_episode(Config(96, "fp8 behind", 977, len(P), 8, 2, D, 64, None, None), threads=2, lengths=(P, R))
     ks, vs = amax_scale(ep.k), amax_scale(ep.v)
     chunks = uniform_chunks(P, R, 64)
     binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    binding.oppo_set_option(binding.OPT_NUM_CUS, cus)
     try:
+        desc = binding.make_desc(8, 2, D, ep.cfg.softmax_scale)
+        items = binding.oppo_plan_debug(desc, P, chunks[1], binding.oppo_workspace_bytes(desc, len(P), int((P + R).sum())))
+        behind, queue = items[:, 4] > items[:, 3], items[:, 7]   # first key, position of the first token
+        assert behind.any()
+        if cus < 256:
+            next_to = [(int(a), int(b)) for a, b, p, q in zip(behind[:-1], behind[1:], queue[:-1], queue[1:]) if p == q]
+            assert (0, 1) in next_to and (1, 0) in next_to
         se = run_gpu(gpu, ep, chunks, ks, vs)
     finally:
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+        binding.oppo_set_option(binding.OPT_NUM_CUS, 256)
     cache, ref = oracle_run(ep, chunks, se.slot_begin, ks, vs)
     check_codes(se, cache)
-    check_outputs(se, ref, f"fp8 short contexts split={split}")
+    check_outputs(se, ref, f"fp8 short contexts D={D} split={split} cus={cus}")
 
 
 def test_attention_dominant_keys_and_single_key_rows(gpu):

@@ -326,19 +326,28 @@ def test_waves_that_end_before_the_piece(gpu, G, D, split):
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
 
 
-@pytest.mark.parametrize("G,D,C,split", [(4, 128, 64, 0), (4, 64, 65, 0), (1, 128, 300, 0), (1, 64, 256, 2), (2, 128, 129, 1), (4, 128, 200, 5)])
-def test_runs_of_whole_key_tiles(gpu, G, D, C, split):
+@pytest.mark.parametrize("G,D,C,split,cus,rows", [
+    (4, 128, 64, 0, 256, 256), (4, 64, 65, 0, 256, 256), (1, 128, 300, 0, 256, 256), (1, 64, 256, 2, 256, 256), (2, 128, 129, 1, 256, 256),
+    (4, 128, 200, 5, 256, 256), (4, 128, 64, 0, 4, 256), (4, 128, 64, 2, 4, 256), (4, 64, 100, 0, 4, 256), (1, 64, 256, 2, 6, 256),
+    (4, 128, 32, 1, 4, 128), (8, 128, 16, 2, 4, 128), (1, 64, 128, 0, 4, 128), (1, 64, 128, 2, 6, 128)])
+def test_runs_of_whole_key_tiles(gpu, G, D, C, split, cus, rows):
     """Cache and chunk that meet on, one key before and one behind a tile of 64 keys, and chunks of no, one and several whole tiles:
-    runs of every kind end in another run, in the tile that takes from both, in a ragged tile and in the next piece."""
+    runs of every kind end in another run, in the tile that takes from both and in a ragged tile.  With few compute units (two
+    or three queues) they also end in the next piece, whose first tiles are requested in the last iterations of the one before."""
     binding, episode, torch = gpu
     P = np.array([1, 62, 63, 64, 65, 127, 128, 129, 191, 192, 320], np.int32)
     R = np.full(len(P), C + 70, np.int32)
     ep = build_episode(small_cfg(len(P), 2 * G, 2, D, C, seed=1700 + G + C), threads=2, lengths=(P, R))
+    chunks = oracle_uniform_chunks(P, R, C)
     binding.oppo_set_option(binding.OPT_SPLIT_KV, split)
+    binding.oppo_set_option(binding.OPT_NUM_CUS, cus)
     try:
-        run_and_check(gpu, ep, oracle_uniform_chunks(P, R, C), None, f"G={G} D={D} C={C} split={split}")
+        (pieces, queues, kernel), = launches_of(binding, ep, chunks)
+        assert kernel == rows and (cus == 256 or pieces >= 3 * queues)
+        run_and_check(gpu, ep, chunks, None, f"G={G} D={D} C={C} split={split} cus={cus}")
     finally:
         binding.oppo_set_option(binding.OPT_SPLIT_KV, 0)
+        binding.oppo_set_option(binding.OPT_NUM_CUS, 256)
 
 
 def test_empty_batch_and_all_finished(gpu):
