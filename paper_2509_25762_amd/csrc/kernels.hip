@@ -753,13 +753,17 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return (int)(wave_rows >> 10) * WROWS < tokens_of(a) * G;
   };
   bool act = true;
-  // Of the two waves of a SIMD, one requests its share of a tile of a run in front of an iteration's first body and the other in
-  // its middle, so that one of them has MFMAs to run while the other's copies are issued (two thirds of the time between
-  // barrier and first MFMA, 630 cycles of an iteration's 3270, were scalar code and copies that all waves issued at once).  us in
-  // one run, a request in front of both, tile by tile / runs / runs and turns: 64/8 heads, 1024 rows on up to 8192 keys 1845 / 1828
-  // / 1778, prompts of 512 .. 2048 tokens 543 / 541 / 536, 64 x 256 rows on 262 .. 1017 keys 239 / 241 / 239; behind the first body
-  // instead of in its middle the copies come too late where they come from memory (240 us on the last of these).
-  const bool first_half = __builtin_amdgcn_readfirstlane(wave) < 4;
+  // Two column blocks, heads of 128: of the two waves of a SIMD, one requests its share of a tile of a run in front of an
+  // iteration's first body and the other in its middle, so that one of them has MFMAs to run while the other's copies are issued
+  // (two thirds of the time between barrier and first MFMA, 630 cycles of an iteration's 3270, were scalar code and copies that
+  // all waves issued at once).  Behind the first body instead of in its middle the copies come too late where they come from memory.
+  // With heads of 64 a body is half as long, and with one column block an iteration mostly waits for its keys: there the later
+  // copies cost more than they give.  Time by turns / all in front, means over random passes (10 to 62 of a kind), contexts up to /
+  // from 1500 tokens: two blocks, heads of 128 0.999 / 0.982 (64/8 heads, 1024 rows on up to 8192 keys 1771 -> 1733 us, 32 prompts
+  // of 512 .. 2048 tokens 525 -> 519, 64 x 256 rows on 262 .. 1017 keys 232 -> 230), heads of 64 1.008 / 1.006; one block, heads
+  // of 128 1.007 / 1.001, heads of 64 1.010 / 1.009 (225 x 26 rows on 235 .. 464 keys, 16/4 heads, 26.4 -> 27.3).
+  constexpr bool kTurns = D == 128 && NCB == 2;
+  const bool first_half = !kTurns || __builtin_amdgcn_readfirstlane(wave) < 4;
   auto iteration = [&](auto TC, int t) __attribute__((always_inline)) {
     constexpr int ts = decltype(TC)::value;
     bool plain = true;
