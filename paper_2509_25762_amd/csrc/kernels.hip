@@ -362,7 +362,12 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // a request little but its copies, and what else there is to do (a piece's ragged last tile, the one that crosses from
   // cache to chunk, the next run or piece) is out of the way: behind the barrier that opens an iteration no wave has
   // anything else to run, so each instruction here, and above all each branch taken, is time in which the matrix cores idle.
-  int run = 0;                 // tiles left of the run
+  // For the same reason what comes next is found behind an iteration's first body and not where it is requested: in front of the
+  // first body short pieces, which have little but ends of runs, paid for it.  us in one run, there / here: 424 rows on 77 .. 203
+  // keys, 8/2 heads of 128, 13.4 / 13.1, 19 x 138 rows on 82 .. 119, 32/8 heads, 20.1 / 19.8, 5 x 93 rows on 465 .. 498, 64/8
+  // heads, 19.2 / 19.0; 1024 rows on up to 8192 keys, 64/8 heads, 1772 / 1775.
+  int run = 0;                 // tiles left of the run; kOneTile: the next tile belongs to no run; kNoTile: there is none
+  constexpr int kOneTile = -1, kNoTile = -2;
   uintptr_t r_k = 0, r_v = 0;  // its next tile's first row, this kv-head
   int c_piece = p_first - 1;   // piece at the cursor
   int c_key = 0, c_n = 0;      // first key behind the run, and end, of its range, counted from the range's start
@@ -370,7 +375,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   uintptr_t c_k = 0, c_kn = 0; // key c_key's row in k, and (APPEND) where that row would be in k_new; v is a fixed distance away
   const uintptr_t k_to_v = (uintptr_t)P.v - (uintptr_t)P.k;
   const uintptr_t kn_to_vn = APPEND ? (uintptr_t)P.v_new - (uintptr_t)P.k_new : 0;
-  const uintptr_t tile_step = (uintptr_t)BN * row_stride * 2u;
+  const uint32_t tile_step = (uint32_t)(BN * row_stride) * 2u;
   // (LDS addresses are formed from a copy of the wave's offset that the optimiser
   // cannot see through: otherwise it keeps one precomputed address per stage, array and
   // load in scalar registers for the whole kernel, and those run out)
@@ -391,10 +396,13 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     r_v += tile_step;
     --run;
   };
-  // At the end of a run: finds the next one (true), or requests the one tile that belongs to none, if there is one (false).
-  auto next_run = [&](int stage) __attribute__((always_inline)) -> bool {
+  // At the end of a run (run = 0): finds what comes next.
+  auto next_run = [&]() __attribute__((always_inline)) {
     if (c_key >= c_n) {
-      if (c_piece + 1 >= p_last) return false;
+      if (c_piece + 1 >= p_last) {
+        run = kNoTile;
+        return;
+      }
       const AttnItem a = piece(++c_piece);
       c_key = 0;
       c_n = a.k_end - a.k_begin;
@@ -409,15 +417,19 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     }
     const bool fresh = APPEND && c_cached <= c_key;
     run = ((APPEND && !fresh ? min(c_n, c_cached) : c_n) - c_key) / BN;
+    if (run == 0) {
+      run = kOneTile;
+      return;
+    }
     r_k = fresh ? c_kn : c_k;
     r_v = r_k + (fresh ? kn_to_vn : k_to_v);
-    const int tiles = max(run, 1);
-    const int last = c_n - c_key - 1, cached = APPEND && !fresh ? c_cached - c_key : BN;
-    const uintptr_t fresh_k = c_kn;
-    c_key += tiles * BN;
-    c_k += (uintptr_t)tiles * tile_step;
-    if (APPEND) c_kn += (uintptr_t)tiles * tile_step;
-    if (run > 0) return true;
+    c_key += run * BN;
+    c_k += (uintptr_t)run * tile_step;
+    if (APPEND) c_kn += (uintptr_t)run * tile_step;
+  };
+  // The tile that belongs to no run, into `stage`.
+  auto request_one = [&](int stage) __attribute__((always_inline)) {
+    const int last = c_n - c_key - 1, cached = APPEND ? c_cached - c_key : BN;
     const int ln = lane_now();
     const uint32_t at = copy_at(stage);
 #pragma unroll
@@ -431,17 +443,22 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       // cache rows, then chunk rows: each lane's 16 bytes land at the LDS address of its
       // lane number, so the two sources fill one tile with complementary lane masks
       if (!APPEND || rc < cached) {
-        async_copy16((const void*)r_k, ok, lk);
-        async_copy16((const void*)r_v, ov, lv);
+        async_copy16((const void*)c_k, ok, lk);
+        async_copy16((const void*)(c_k + k_to_v), ov, lv);
       } else {
-        async_copy16((const void*)fresh_k, ok, lk);
-        async_copy16((const void*)(fresh_k + kn_to_vn), ov, lv);
+        async_copy16((const void*)c_kn, ok, lk);
+        async_copy16((const void*)(c_kn + kn_to_vn), ov, lv);
       }
     }
-    return false;
+    c_key += BN;
+    c_k += tile_step;
+    if (APPEND) c_kn += tile_step;
+    run = 0;
   };
   auto issue_next = [&](int stage) __attribute__((always_inline)) {
-    if (run > 0 || next_run(stage)) request_plain(stage);
+    if (run > 0) request_plain(stage);
+    else if (run == kOneTile) request_one(stage);
+    if (run == 0) next_run();
   };
   // workgroup barrier without the implied wait for this wave's LDS reads: the only
   // reads still in flight at a barrier are the K fragments of the next tile, whose
@@ -766,12 +783,14 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   const bool first_half = !kTurns || __builtin_amdgcn_readfirstlane(wave) < 4;
   auto iteration = [&](auto TC, int t) __attribute__((always_inline)) {
     constexpr int ts = decltype(TC)::value;
-    bool plain = true;
-    if (__builtin_expect(run == 0, 0)) plain = next_run((ts + 2) % NSTAGE);
-    if (first_half && plain) request_plain((ts + 2) % NSTAGE);
+    const bool plain = run > 0;
+    if (__builtin_expect(run == kOneTile, 0)) request_one((ts + 2) % NSTAGE);
+    // (the hint: with turns, the waves that request later are the ones that the others wait for, and they fall through)
+    if (__builtin_expect(first_half && plain, !kTurns)) request_plain((ts + 2) % NSTAGE);
     unit_body(std::integral_constant<int, 2 * ts>{}, 2 * t, [&](int i) __attribute__((always_inline)) {
       if (i == QS / 2 - 1 && !first_half && plain) request_plain((ts + 2) % NSTAGE);
     });
+    if (__builtin_expect(run == 0, 0)) next_run();
     if (__builtin_expect(2 * t + 1 < U, 1)) unit_body(std::integral_constant<int, 2 * ts + 1>{}, 2 * t + 1, [](int) {});
     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): this wave's share of the requested tile is in LDS
     wg_barrier();
@@ -780,6 +799,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // ---- start-up: Q of the first piece, the first two tiles of the stream ------------
   act = has_rows(it);
   q_request(it);
+  next_run();
   issue_next(0);
   issue_next(1);
   q_collect(2);

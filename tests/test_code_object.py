@@ -49,9 +49,9 @@ def test_attention_kernels_spill_no_vector_register(attention_kernels):
         assert k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, name
 
 
-def test_the_masks_comparisons_need_no_spilled_scalars(attention_kernels):
+def test_attention_kernels_spill_few_scalars(attention_kernels):
     """A masked unit compares 8 or 16 registers with the columns' limits.  Formed all at once the results do not fit the
     scalar registers: 159 and 161 spills in the append variants with two column blocks, with reads and writes in every
-    masked unit.  One at a time, what is left (up to 35) is spilled outside of the units."""
+    masked unit.  One at a time, what is left (up to 14) is written in front of the loops and read on their rare paths."""
     for name, k in attention_kernels.items():
-        assert k[".sgpr_spill_count"] <= 40, (name, k[".sgpr_spill_count"])
+        assert k[".sgpr_spill_count"] <= 24, (name, k[".sgpr_spill_count"])
