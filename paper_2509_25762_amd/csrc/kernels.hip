@@ -267,9 +267,15 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   const int pg = lane % NG;
   // Swizzle of a value row's granules: the transposing reads take 32 lanes at a time, 32 bytes of each of eight rows, and these
   // then lie in eight different parts of the 64 banks.  (With rows 4 apart in the same one a third of the LDS cycles were
-  // conflicts, SQ_LDS_BANK_CONFLICT 1.34e8 of SQ_LDS_IDX_ACTIVE 4.05e8 on 16 x 1024 rows of 64/8 heads; the time is the same to
-  // 0.3 %, the LDS is not what the loop waits for.)
-  auto vswz = [](int r) __attribute__((always_inline)) { return (r / (256 / ROWB) % (NG / 2)) * 2; };
+  // conflicts, SQ_LDS_BANK_CONFLICT 1.34e8 of SQ_LDS_IDX_ACTIVE 4.05e8 on 16 x 1024 rows of 64/8 heads; the time of such passes is
+  // the same to 0.3 %, the LDS is not what their loop waits for, but 15 x 15 rows on 413 .. 756 keys take 15.9 -> 15.5 us.)
+  // The halves of a row's 64-byte pieces change places in the rows x / (NG / 4) % 2 = 1, with heads of 128 in all rows of a
+  // wave's load or in none: with every other row so, passes that mostly read are 1 to 2 % slower (us, 32 x 22 rows on 4579 .. 5668
+  // keys, 32/8 heads, 137.9 / 135.1, 223 x 6 rows on 1923 .. 5244, 64/8 heads, 637 / 628), others the same.
+  auto vswz = [](int r) __attribute__((always_inline)) {
+    const int x = r / (256 / ROWB);
+    return x % (NG / 4) * 4 + x / (NG / 4) % 2 * 2;
+  };
   uint32_t goffk[IPW], goffv[IPW];   // byte offsets of this lane's granules in a full tile
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
