@@ -41,9 +41,10 @@
 // stay below the limit, and weights keep full precision down to 2^-10 of the reference; sum and
 // numerator carry the same factor, which cancels.  The row sum adds the weights before rounding
 // (rounding to nearest is unbiased; turning codes back into numbers would cost more than two
-// additions).  A column's first reference is the maximum of the first unit in which it sees a
-// key, taken in front of the key loop for the piece's first unit; until then it is the arbitrary 0 and the column has
-// accumulated nothing.
+// additions).  A column's first reference is the maximum of the piece's first unit, taken in front of the key loop.  The unit
+// holds the piece's first key, and a column sees the keys up to its limit: one that sees no key of this unit sees none of the
+// piece.  Its reference is 0, its weights and sum stay 0, and the merge is told so (a whole range begins with key 0, which
+// every column sees).
 // The values' scale is folded into the final normalisation.
 // Head size 64: the contraction of S^T is one MFMA deep, O^T has two 32-row blocks; a tile of
 // either array is 4 KiB, so waves 0-3 move the keys and waves 4-7 the values.
@@ -311,8 +312,6 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
   i32x8 pw[2];          // pw[tile's ring stage & 1] = the tile's weights, B-operand layout (byte j = key 32 hi + j)
   f32x16 negm;          // kBias minus the column's reference (log2 units), in all sixteen registers
   float mref = 0.f;     // the reference
-  bool noref = true;    // the column has seen no key of the piece yet
-  uint64_t unseen = 0;  // lanes of such columns (a scalar, like the ballot that it is tested with)
   float l_run, rs0 = 0.f, rs1 = 0.f;
 
   AttnItem it = piece(p_first);
@@ -398,19 +397,12 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     else asm volatile("" : "+v"(pw[tp]), "+v"(rs), "+v"(s[nxt]), "+v"(o[ub]));
     __builtin_amdgcn_sched_barrier(0);
     // (the O^T MFMAs of a piece's first tile multiply zero weights with a tile of valid codes: nothing)
-    const uint64_t over = __ballot(rs > kRowSumLimit);
-    if (__builtin_expect((over | unseen) != 0, 0)) {   // (no short-circuit: one branch)
-      // A column without a reference yet (it saw no key of the piece's first unit), or one that saw a score far above its
-      // reference: take the unit's true maximum (the
-      // registers hold score - reference + kBias), move the references to it - up only, except for a
-      // column's first -, redo the unit's weights and rescale what was formed against the old
+    if (__builtin_expect(__any(rs > kRowSumLimit), 0)) {
+      // Some column saw a score far above its reference: take the unit's true maximum (the registers hold score - reference +
+      // kBias), move the references up to it, redo the unit's weights and rescale what was formed against the old
       // references: the accumulators, and S^T of unit u+1.
-      const float mx = unit_max(cur);
-      const bool seen = mx > -INFINITY;
-      const float delta = noref ? (seen ? mx - kBias : 0.f) : fmaxf(mx - kBias, 0.f);
-      const float alpha = noref ? 1.0f : fast_exp2(-delta);   // (a column without a reference has accumulated nothing)
-      noref = noref && !seen;
-      unseen = __ballot(noref);
+      const float delta = fmaxf(unit_max(cur) - kBias, 0.f);
+      const float alpha = fast_exp2(-delta);
       mref += delta;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -484,8 +476,6 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
     const int nt = (nkeys + BN - 1) / BN;
     l_run = 0.f;
     mref = 0.f;
-    noref = true;
-    unseen = 0;   // (for waves with rows: below)
 #pragma unroll
     for (int r = 0; r < 16; ++r) negm[r] = kBias;
     // the first tile's bodies run the O^T MFMAs "of the tile before it": with zero weights
@@ -514,9 +504,7 @@ __global__ __launch_bounds__(512) void attn_fwd_fp8_kernel(const AttnParams<NI> 
       // the columns' first references: the largest scores of the unit
       mask(0, it.k_begin);
       const float mx = unit_max(0);
-      noref = !(mx > -INFINITY);
-      unseen = __ballot(noref);
-      mref = noref ? 0.f : mx - kBias;
+      mref = mx > -INFINITY ? mx - kBias : 0.f;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         negm[r] -= mref;
