@@ -623,8 +623,9 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     mask(cur, it.k_begin + 32 * u);
     // The probabilities of this unit are formed against the reference value m_run
     // the column already has (no maximum is taken first: the first one is that of the piece's first unit, taken in front of the
-    // loop, where forming that unit twice took another 0.5 % of a pass); only if a row sum comes out too large - always for a
-    // column's first visible keys if they come later, otherwise almost never - the unit is redone against its true maximum, see below.
+    // loop, where forming that unit twice took another 0.5 % of a pass); only if a row sum comes out too large, which is rare,
+    // the unit is redone against its true maximum, see below.  (A column sees the keys up to its limit, and the first unit holds
+    // the piece's first: one that sees none of it sees none of the piece.  Its reference stays -1e30 and its sum 0.)
 #pragma unroll
     for (int e = 0; e < 2 * NCB; ++e) s[nxt][e % 2][e / 2] = f32x4{0.f, 0.f, 0.f, 0.f};
 
@@ -730,10 +731,9 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
         for (int cb = 0; cb < NCB; ++cb) o[db][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     if (__builtin_expect(__any(fmaxf(rs[0], rs[NCB - 1]) > kRowSumLimit), 0)) {
-      // Some column saw a score far above its reference (or has no reference yet):
-      // take the unit's true maximum, move every column's reference up to it, redo the unit's
-      // probabilities, and rescale what has been accumulated so far - unit u-1
-      // included, whose MFMAs above still used the old reference.
+      // Some column saw a score far above its reference: take the unit's true maximum, move every
+      // column's reference up to it, redo the unit's probabilities, and rescale what has been accumulated
+      // so far - unit u-1 included, whose MFMAs above still used the old reference.
       float alpha[NCB];
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
@@ -747,12 +747,10 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
       for (int pr = 0; pr < 4 * NCB; ++pr) round_pair(cur, pr, fast_exp2(score(cur, pr, 0)), fast_exp2(score(cur, pr, 1)));
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) rs[cb] = row_sum(cur, cb);
-      if (u != 0) {   // (a piece's first unit has accumulated nothing)
 #pragma unroll
-        for (int db = 0; db < DB; ++db)
+      for (int db = 0; db < DB; ++db)
 #pragma unroll
-          for (int cb = 0; cb < NCB; ++cb) o[db][cb] *= alpha[cb];
-      }
+        for (int cb = 0; cb < NCB; ++cb) o[db][cb] *= alpha[cb];
     }
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb) l_run[cb] += rs[cb];

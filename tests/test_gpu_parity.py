@@ -360,10 +360,10 @@ def test_empty_batch_and_all_finished(gpu):
 
 @pytest.mark.parametrize("split", [0, 1, 3])
 def test_late_dominant_keys_rerun_in_exact_mode(gpu, split):
-    """Keys far into a sequence that outscore its first keys by a wide margin: the
-    kernel's first run of such a piece (weights against the maximum of the first 32
-    keys) sees row sums beyond its limit - or plain overflow - and the piece is run
-    again in the exact mode.  Results must still match the oracle."""
+    """Keys far into a sequence that outscore its first keys by a wide margin: a unit's
+    weights against the reference of the units before it have row sums beyond the
+    limit - or plain overflow - and the unit is redone against its true maximum.
+    Results must still match the oracle."""
     binding, episode, torch = gpu
     cfg = small_cfg(3, 8, 2, 128, 128, seed=4321)
     P, R = np.array([70, 300, 33], np.int32), np.array([200, 140, 128], np.int32)
