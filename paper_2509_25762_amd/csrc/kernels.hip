@@ -776,8 +776,9 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   bool act = true;
   // Two column blocks, heads of 128: of the two waves of a SIMD, one requests its share of a tile of a run in front of an
   // iteration's first body and the other in its middle, so that one of them has MFMAs to run while the other's copies are issued
-  // (two thirds of the time between barrier and first MFMA, 630 cycles of an iteration's 3270, were scalar code and copies that
-  // all waves issued at once).  Behind the first body instead of in its middle the copies come too late where they come from memory.
+  // (of an iteration's 3300 cycles 400 to 590 passed between barrier and first MFMA, in scalar code and copies that all waves
+  // issued at once; now 280 of 2920 in one wave and 120 in the other).  Behind the first body instead of in
+  // its middle the copies come too late where they come from memory.
   // With heads of 64 a body is half as long, and with one column block an iteration mostly waits for its keys: there the later
   // copies cost more than they give.  Time by turns / all in front, means over random passes (10 to 62 of a kind), contexts up to /
   // from 1500 tokens: two blocks, heads of 128 0.999 / 0.982 (64/8 heads, 1024 rows on up to 8192 keys 1771 -> 1733 us, 32 prompts
