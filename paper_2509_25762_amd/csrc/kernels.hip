@@ -774,17 +774,17 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     return (int)(wave_rows >> 10) * WROWS < tokens_of(a) * G;
   };
   bool act = true;
-  // Two column blocks, heads of 128: of the two waves of a SIMD, one requests its share of a tile of a run in front of an
-  // iteration's first body and the other in its middle, so that one of them has MFMAs to run while the other's copies are issued
-  // (of an iteration's 3300 cycles 400 to 590 passed between barrier and first MFMA, in scalar code and copies that all waves
-  // issued at once; now 280 of 2920 in one wave and 120 in the other).  Behind the first body instead of in
-  // its middle the copies come too late where they come from memory.
-  // With heads of 64 a body is half as long, and with one column block an iteration mostly waits for its keys: there the later
-  // copies cost more than they give.  Time by turns / all in front, means over random passes (10 to 62 of a kind), contexts up to /
-  // from 1500 tokens: two blocks, heads of 128 0.999 / 0.982 (64/8 heads, 1024 rows on up to 8192 keys 1771 -> 1733 us, 32 prompts
-  // of 512 .. 2048 tokens 525 -> 519, 64 x 256 rows on 262 .. 1017 keys 232 -> 230), heads of 64 1.008 / 1.006; one block, heads
-  // of 128 1.007 / 1.001, heads of 64 1.010 / 1.009 (225 x 26 rows on 235 .. 464 keys, 16/4 heads, 26.4 -> 27.3).
-  constexpr bool kTurns = D == 128 && NCB == 2;
+  // Heads of 128: of the two waves of a SIMD, one requests its share of a tile of a run in front of an iteration's first body and
+  // the other in its middle, so that one of them has MFMAs to run while the other's copies are issued (of an iteration's 3300
+  // cycles 400 to 590 passed between barrier and first MFMA, in scalar code and copies that all waves issued at once; now 280 of
+  // 2920 in one wave and 120 in the other).  Behind the first body instead of in its middle the copies come too late where they
+  // come from memory.  With heads of 64 a body is half as long, and the later copies cost more than they give.  Time by turns /
+  // all in front, means over random passes (8 to 94 of a kind), contexts up to / from 1500 tokens: two blocks, heads of 128 0.999 /
+  // 0.982 (64/8 heads, 1024 rows on up to 8192 keys 1771 -> 1733 us, 32 prompts of 512 .. 2048 tokens 525 -> 519, 64 x 256 rows on
+  // 262 .. 1017 keys 232 -> 230), heads of 64 1.008 / 1.006; one block, heads of 128 1.001 / 1.002 (0.98 .. 1.02: both ways are
+  // right about as often, so it is left as with two), heads of 64 1.010 / 1.009 (225 x 26 rows on 235 .. 464 keys, 16/4 heads, 26.4 ->
+  // 27.3).
+  constexpr bool kTurns = D == 128;
   const bool first_half = !kTurns || __builtin_amdgcn_readfirstlane(wave) < 4;
   auto iteration = [&](auto TC, int t) __attribute__((always_inline)) {
     constexpr int ts = decltype(TC)::value;
