@@ -790,8 +790,10 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
     constexpr int ts = decltype(TC)::value;
     const bool plain = run > 0;
     if (__builtin_expect(run == kOneTile, 0)) request_one((ts + 2) % NSTAGE);
-    // (the hint: with turns, the waves that request later are the ones that the others wait for, and they fall through)
-    if (__builtin_expect(first_half && plain, !kTurns)) request_plain((ts + 2) % NSTAGE);
+    // (the hint: with two column blocks the waves that request later are the ones that the others wait for, and they fall through;
+    // with one, tiles of up to 64 rows have rows in the first four waves alone: 45 x 10 rows on 751 .. 1695 keys, 8/2 heads, 23.9 us
+    // where these branch away, 23.5 where they do not)
+    if (__builtin_expect(first_half && plain, !kTurns || NCB == 1)) request_plain((ts + 2) % NSTAGE);
     unit_body(std::integral_constant<int, 2 * ts>{}, 2 * t, [&](int i) __attribute__((always_inline)) {
       if (i == QS / 2 - 1 && !first_half && plain) request_plain((ts + 2) % NSTAGE);
     });
