@@ -176,8 +176,8 @@ __device__ __forceinline__ long bf16x8_to_fp8x8(bf16x8 x, float mult) {
 // that consumes them (rolling register buffers ka / vf).
 // K/V tiles go straight from global memory into a ring of four LDS stages, two
 // tiles ahead: the loads of the tile two places further down the workgroup's
-// tile stream are issued after the barrier that opens an iteration (by half of the waves in the middle of its first
-// unit), into the stage whose last reader finished before that barrier, and each wave waits for
+// tile stream are issued after the barrier that opens an iteration (with heads of 128, by half of the waves in the
+// middle of its first unit), into the stage whose last reader finished before that barrier, and each wave waits for
 // its own loads before the barrier that closes it.  The stream runs across piece
 // boundaries: the first two tiles of the next piece are requested during the last
 // two iterations of the current one, and the next piece's Q fragments are
@@ -583,7 +583,7 @@ __global__ __launch_bounds__(512) void attn_fwd_kernel(const AttnParams<NI> P) {
   // Causal / range mask of the unit in s[cur], which starts at key key0, if it crosses a limit.  One register at a time, each
   // pinned: left to itself the compiler forms all comparisons first, and with scalar registers as scarce as in the append
   // variants it parks their results in lanes of a vector register (16 to 18 v_writelane and as many v_readlane per masked unit;
-  // 161 scalar spills in the variant for heads of 128 with two column blocks, 35 so).  Time with / without the pin: 4 x 1191
+  // 161 scalar spills in the variant for heads of 128 with two column blocks, 35 with the pin and the same cursor).  Time with / without the pin: 4 x 1191
   // rows on 49 .. 91 keys, 4/4 heads of 64, 0.91; 170 x 196 rows on 161 .. 165 keys, the same heads, 0.95; 64 x 256 rows on
   // 262 .. 1017 keys, 32/8 heads of 128, 0.997.
   auto mask = [&](int cur, int key0) __attribute__((always_inline)) {
